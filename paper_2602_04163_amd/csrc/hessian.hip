@@ -407,12 +407,38 @@ __global__ __launch_bounds__(SplitF16::kThreads, 1) void hess_syrk_f16x2_kernel(
   sInv[256 + threadIdx.x] = inv[c0 + threadIdx.x];
   __syncthreads();
   if (p.direct) {
-    auto emit = [&](int row, int col, float v) {
+    // H += tile, in batches of 64 results per lane: all loads of a batch first (entries past the
+    // matrix read H[0] and are not stored), then its stores.  One load, one wait, one store at a
+    // time -- what the compiler must make of a plain `+=`, since it cannot tell the addresses apart
+    // -- left the matrix pipe idle for a quarter of a launch (4096 x 18944: 4.45 -> 3.54 ms).
+    auto at = [&](int row, int col) {
       const int r = r0 + row, c = c0 + col;
-      if (r < d && c < d) H[(long)r * d + c] += scale * (v * sInv[row] * sInv[256 + col]);
+      return (r < d && c < d) ? (long)r * d + c : -1L;
     };
-    if (bi == bj) SplitF16::for_each_diag(acc, emit);
-    else SplitF16::for_each(acc, emit);
+    auto batch = [&](auto visit) {
+      float old[64];
+      int n = 0;
+      visit([&](int row, int col, float) {
+        const long e = at(row, col);
+        old[n++] = H[e < 0 ? 0L : e];
+      });
+      n = 0;
+      visit([&](int row, int col, float v) {
+        const long e = at(row, col);
+        if (e >= 0) H[e] = old[n] + scale * (v * sInv[row] * sInv[256 + col]);
+        ++n;
+      });
+    };
+    if (bi == bj) {
+      batch([&](auto f) { SplitF16::for_each_diag<0, 4>(acc, f); });
+      batch([&](auto f) { SplitF16::for_each_diag<4, 8>(acc, f); });
+      batch([&](auto f) { SplitF16::for_each_diag<8, 9>(acc, f); });
+    } else {
+      batch([&](auto f) { SplitF16::for_each<0, 1>(acc, f); });
+      batch([&](auto f) { SplitF16::for_each<1, 2>(acc, f); });
+      batch([&](auto f) { SplitF16::for_each<2, 3>(acc, f); });
+      batch([&](auto f) { SplitF16::for_each<3, 4>(acc, f); });
+    }
   } else {
     float* out = partial + (long)item * kTileFloats;
     auto emit = [&](int row, int col, float v) {

@@ -231,13 +231,14 @@ struct SplitF16 {
     __syncthreads();
   }
 
-  // f(row_in_tile, col_in_tile, value) over this lane's results of an off-diagonal tile
-  template <typename F>
+  // f(row_in_tile, col_in_tile, value) over this lane's results of an off-diagonal tile (block rows
+  // [I0, I1) of the wavefront's four)
+  template <int I0 = 0, int I1 = 4, typename F>
   __device__ static __forceinline__ void for_each(const Acc& acc, F f) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = I0; i < I1; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -245,12 +246,12 @@ struct SplitF16 {
           f(wm * 128 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), wn * 128 + j * 32 + (lane & 31),
             acc.c[i][j][r]);
   }
-  // ... of a diagonal tile (upper-triangular schedule)
-  template <typename F>
+  // ... of a diagonal tile (upper-triangular schedule, blocks [Q0, Q1) of the wavefront's nine)
+  template <int Q0 = 0, int Q1 = kDiagBlocks, typename F>
   __device__ static __forceinline__ void for_each_diag(const Acc& acc, F f) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int q = 0; q < kDiagBlocks; ++q) {
+    for (int q = Q0; q < Q1; ++q) {
       const int rb = kDiagRow[wave][q], cb = kDiagCol[wave][q];
 #pragma unroll
       for (int r = 0; r < 16; ++r)
