@@ -798,6 +798,36 @@ def test_pack_and_dequant_bit_exact(dev, bits):
     assert np.allclose(Wg, orc.dequant(pg, coef, group), rtol=1e-6, atol=1e-7)
 
 
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("d_out,d_in,group,shift", [
+    (1, 32, 32, 0), (3, 1056, 32, 0), (5, 2080, 4, 0),      # vector stores: one row, columns past a work-group's 1024
+    (4, 1024, 2, 0), (7, 96, 3, 0), (6, 64, 64, 1),         # groups that four columns straddle, W_hat off 16 bytes
+])
+def test_dequant_tile_edges(dev, half, d_out, d_in, group, shift):
+    """Both store widths of the dequant kernel at the edges of its tiles, bit for bit."""
+    print(f"dequant d_out={d_out} d_in={d_in} g={group} shift={shift} half={half}", flush=True)
+    rng = np.random.default_rng(d_in + group)
+    bits = 3
+    code = rng.integers(0, 1 << bits, size=(d_out, d_in)).astype(np.uint8)
+    planes = torch.from_numpy(orc.pack_planes(code, bits).view(np.int32)).to(dev)
+    coef = rng.standard_normal((bits + 1, d_out, d_in // group)).astype(np.float16 if half else np.float32)
+    coef_d = torch.from_numpy(coef).to(dev)
+    buf = torch.full((d_out * d_in + 8,), np.nan, device=dev)
+    lib = bq.load()
+    fn = lib.bpdq_dequant_fp16 if half else lib.bpdq_dequant
+    W = buf[shift:]
+    assert fn(planes.data_ptr(), coef_d.data_ptr(), d_out, d_in, bits, group, W.data_ptr(), bq._stream()) == 0
+    torch.cuda.synchronize()
+    c32 = coef.astype(np.float32)
+    want = np.repeat(c32[0], group, axis=1)
+    for i in range(1, bits + 1):
+        b = ((code >> (i - 1)) & 1).astype(bool)
+        want = np.where(b, (want + np.repeat(c32[i], group, axis=1)).astype(np.float32), want)
+    got = buf.cpu().numpy()
+    assert np.array_equal(got[shift:shift + d_out * d_in].reshape(d_out, d_in), want)
+    assert np.isnan(got[:shift]).all() and np.isnan(got[shift + d_out * d_in:]).all()
+
+
 def test_prepare_many_panels_defining_property(dev):
     """A width whose panel launches have more work-groups than the chip holds at once
     (18944 = 296 panels): checked through the defining property U^T U (H + lambda I) = I on
