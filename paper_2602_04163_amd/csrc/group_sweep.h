@@ -53,10 +53,6 @@ __device__ __forceinline__ double dpp_d(double x) {
   const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
   return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
 }
-// value of lane O of this 16-lane row, in every lane of the row
-template <int O>
-__device__ __forceinline__ float bcast16(float x) { return dpp_f<0x150 + O>(x); }
-
 // Butterfly over the 16 lanes of a row: xor 1, xor 2 (quad permutes), then half-row mirror and
 // row mirror, which act as xor 4 / xor 8 once quads are uniform.  Every lane ends with the same
 // bits (each stage adds the same two operands in both partners).
@@ -154,117 +150,291 @@ __device__ __forceinline__ void load_u_row(const float* __restrict__ p, int lane
 
 enum : int { kStepInit = 0, kStepSweep = 1, kStepUniform = 2 };
 
+// x of lane O of this 16-lane row as the DPP operand of the arithmetic it feeds (bound_ctrl set and no
+// "old" value: the compiler folds the move into a VOP2 instruction that uses it once).
+template <int CTRL>
+__device__ __forceinline__ int dpp_operand(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, true);
+}
+template <int O>
+__device__ __forceinline__ float from_lane(float x) {
+  return __builtin_bit_cast(float, dpp_operand<0x150 + O>(__builtin_bit_cast(int, x)));
+}
+// unsigned minimum with the partner of butterfly stage R (xor 1, xor 2, half mirror, mirror)
+template <int R>
+__device__ __forceinline__ unsigned min_stage(unsigned x) {
+  constexpr int kCtrl[4] = {0xB1, 0x4E, 0x141, 0x140};
+  const unsigned o = (unsigned)dpp_operand<kCtrl[R]>((int)x);
+  return o < x ? o : x;
+}
+template <int R>
+__device__ __forceinline__ float byte_f(unsigned x) {
+  return (float)((x >> (8 * R)) & 0xffu);              // v_cvt_f32_ubyteR
+}
+
+// Empty asm statements with a value as in/out operand fix the place of the instruction that
+// produces it: volatile asm statements keep their order.
+#define BPDQ_PIN(x) asm volatile("" : "+v"(x))
+
+// What a column step leaves for the next one: the broadcast coordinates of its column and its row of
+// the local factor.  The update of a column's own slot (and of the next column's) is on the critical
+// path and done at once; the slots beyond it are updated inside the next step, where their
+// multiply-adds fill the wait states of that step's serial chain.
+template <int K, int G>
+struct Pending {
+  float e, t, o;        // error coordinate; tau and P_0 coordinates (kStepInit)
+  float x[K];           // plane coordinates
+  float u[G / 16];      // row of the local factor
+};
+
+// Far update number F of the previous column: vector F % NV of slot FIRST + F / NV.
+template <int K, int G, int MODE, int FIRST, int F>
+__device__ __forceinline__ void far_update(RowState<K, G>& st, const Pending<K, G>& pd) {
+  constexpr int NV = (MODE == kStepInit) ? K + 2 : (MODE == kStepUniform ? 1 : K + 1);
+  constexpr int m = FIRST + F / NV, v = F % NV;
+  if constexpr (m < G / 16) {
+    if constexpr (MODE == kStepInit && v == 0) { st.tau[m] = fmaf(-pd.t, pd.u[m], st.tau[m]); BPDQ_PIN(st.tau[m]); }
+    else if constexpr (MODE == kStepInit && v == 1) { st.p0[m] = fmaf(-pd.o, pd.u[m], st.p0[m]); BPDQ_PIN(st.p0[m]); }
+    else if constexpr (MODE != kStepInit && v == 0) { st.wg[m] = fmaf(-pd.e, pd.u[m], st.wg[m]); BPDQ_PIN(st.wg[m]); }
+    else {
+      constexpr int i = v - (MODE == kStepInit ? 2 : 1);
+      st.P[i][m] = fmaf(-pd.x[i], pd.u[m], st.P[i][m]);
+      BPDQ_PIN(st.P[i][m]);
+    }
+  }
+}
+template <int K, int G, int MODE, int FIRST, int F0, int F1>
+__device__ __forceinline__ void far_updates(RowState<K, G>& st, const Pending<K, G>& pd) {
+  if constexpr (F0 < F1) {
+    far_update<K, G, MODE, FIRST, F0>(st, pd);
+    far_updates<K, G, MODE, FIRST, F0 + 1, F1>(st, pd);
+  }
+}
+
 // One column of the forward recurrence.
 //   kStepInit:    initial pass (codes known): builds tau, P_0 and the plane solves P_i.
 //   kStepSweep:   bit-plane update of column L (Eq. 7-8), its error coordinate (Eq. 3),
 //                 compensation of the later columns (Eq. 4), and the plane solves.
-//   kStepUniform: the same column update with frozen coefficients and nothing else: the error
-//                 coordinates themselves are kept in st.tau (fixed-grid GPTQ comparator).
-// Row L of the local factor (`u`, `inv` = 1 / U_LL) arrives in registers; the step first issues
-// the LDS reads of row L + 1 and hands them over at its end, so that their latency overlaps this
-// column's arithmetic (one wave per SIMD: nothing else would hide it).
+//   kStepUniform: the same column update with frozen coefficients and nothing else.
+//
+// A step is bound by vector issue (a SIMD holds one or two wavefronts, and every instruction of one
+// takes four cycles), so what counts is how few instructions it has and that the serial chain of the
+// decision never waits:
+//   * Nearest level: lane c of a row holds the level of code c % 2^K (`lv`), so one subtraction and one
+//     multiplication give all distances; K butterfly stages give the smallest, and K more the lowest
+//     code that attains it -- the code that a scan over the levels with a strict `<` keeps.  Distances are
+//     squares, so their bit patterns order like the values (and a NaN sorts above infinity).  2 + 2 K + 2
+//     instructions against 2 + 6 (2^K - 1) for the scan.
+//   * `lc` carries the code as bytes (bit i in byte i: the same order), so a plane bit becomes a float by
+//     one v_cvt_f32_ubyte; the level itself follows from the bits, ((c_0 + b_1 c_1) + b_2 c_2) + ...
+//   * Broadcasts are DPP operands of the arithmetic that needs them.  The factor's row is zero on and left
+//     of its diagonal, so the running right-hand side of a finished column stays as it was, and its
+//     coordinate x = (b + P) / U_ll is taken for all columns at once after the sweep (finish_columns)
+//     instead of by a select per step.
+//   * A DPP operand must be two instructions old, and a select two after its compare: the far updates of
+//     the previous column are dealt to those places.
+// Whole sweep phase against a step with the scan and per-step selects (5 iterations, groups of 128): 3584 x 3584,
+// 2 planes 3.38 -> 2.92 ms; 18944 x 3584, 3 planes 16.1 -> 11.9 ms; 256 x 256 (groups of 64, 3 iterations)
+// 144 -> 128 us.  45 instead of 60 instructions per column at 2 planes.
 template <int K, int G, int L, int MODE>
 __device__ __forceinline__ void column_step(RowState<K, G>& st, const float* __restrict__ sU,
-                                            const float* __restrict__ sInv,
-                                            const float (&lv)[1 << K], int lane16,
-                                            float (&u)[G / 16], float& inv) {
-  constexpr int CPL = G / 16, M = L / 16, O = L % 16;
-  const bool owner = (lane16 == O);
-  constexpr bool kPinState = true;
-  constexpr bool kPrefetch = true;
+                                            const float* __restrict__ sInv, const float (&c)[K + 1], float lv,
+                                            unsigned lc, const float (&bits)[K][G / 16], int lane16,
+                                            Pending<K, G>& pd, float (&u)[G / 16], float& inv) {
+  constexpr int CPL = G / 16, M = L / 16, O = L % 16, MN = (L + 1) / 16;
+  constexpr bool kInit = (MODE == kStepInit), kUni = (MODE == kStepUniform);
+  // far updates of column L - 1: the slots beyond column L's
+  constexpr int NV = kInit ? K + 2 : (kUni ? 1 : K + 1);
+  constexpr int NF = (L == 0) ? 0 : NV * (CPL - M - 1);
   float un[CPL];
   float invn = 0.f;
-  if constexpr (!kPrefetch) {
-    load_u_row<G, M>(sU + SuLayout<G>::row_offset(L), lane16, u);
-    inv = sInv[L];
-  } else if constexpr (L + 1 < G) {
-    load_u_row<G, (L + 1) / 16>(sU + SuLayout<G>::row_offset(L + 1), lane16, un);
+  if constexpr (L + 1 < G) {
+    load_u_row<G, MN>(sU + SuLayout<G>::row_offset(L + 1), lane16, un);
     invn = sInv[L + 1];
-    __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the arithmetic below
+    __builtin_amdgcn_sched_barrier(0);   // the reads of the next row stay ahead of this column's arithmetic
   }
-  float x[K], xb[K];
-  if constexpr (MODE != kStepInit) {
-    const float w = st.wg[M];
-    float diff = w - lv[0];
-    float bd = diff * diff;
-    float bq = lv[0];
-    int bc = 0;
-#pragma unroll
-    for (int c = 1; c < (1 << K); ++c) {
-      diff = w - lv[c];
-      const float dist = diff * diff;
-      const bool lt = dist < bd;      // strict: the lowest code wins ties
-      bd = lt ? dist : bd;
-      bq = lt ? lv[c] : bq;
-      bc = lt ? c : bc;
-    }
-    const float e = (w - bq) * inv;
-    if (owner) st.code[M] = bc;
-    if constexpr (MODE == kStepUniform) {
-      if (owner) st.tau[M] = e;
-    } else {
-#pragma unroll
-      for (int i = 0; i < K; ++i) x[i] = ((float)((bc >> i) & 1) + st.P[i][M]) * inv;
-    }
-    const float eb = bcast16<O>(e);
-#pragma unroll
-    for (int m = M; m < CPL; ++m) st.wg[m] = fmaf(-eb, u[m], st.wg[m]);
-  } else {
-    const float xt = st.tau[M] * inv;
-    const float x0 = st.p0[M] * inv;
-#pragma unroll
-    for (int i = 0; i < K; ++i) x[i] = ((float)((st.code[M] >> i) & 1) + st.P[i][M]) * inv;
-    if (owner) {
-      st.tau[M] = xt;
-      st.p0[M] = x0;
-    }
-    const float tb = bcast16<O>(xt);
-    const float ob = bcast16<O>(x0);
-#pragma unroll
-    for (int m = M; m < CPL; ++m) {
-      st.tau[m] = fmaf(-tb, u[m], st.tau[m]);
-      st.p0[m] = fmaf(-ob, u[m], st.p0[m]);
-    }
-  }
-  if constexpr (MODE != kStepUniform) {
+  float e = 0.f, tb = 0.f, ob = 0.f, x[K];
+  constexpr auto at = [](int f) { return f < NF ? f : NF; };
+  if constexpr (kInit) {
+    float y[K];
 #pragma unroll
     for (int i = 0; i < K; ++i) {
-      if (owner) st.P[i][M] = x[i];
-      xb[i] = bcast16<O>(x[i]);
-#pragma unroll
-      for (int m = M; m < CPL; ++m) st.P[i][m] = fmaf(-xb[i], u[m], st.P[i][m]);
+      y[i] = bits[i][M] + st.P[i][M];
+      BPDQ_PIN(y[i]);
     }
-  }
-  // The updates of far slots are not consumed for many steps; left alone, instruction selection
-  // lets them drift there, together with the factor rows they need (hundreds of live registers).
-  // Empty asm statements with the values as in/out operands pin them to this step.
-  if constexpr (kPinState) {
+    tb = from_lane<O>(st.tau[M]) * inv;
+    BPDQ_PIN(tb);
+    ob = from_lane<O>(st.p0[M]) * inv;
+    BPDQ_PIN(ob);
 #pragma unroll
-    for (int m = M; m < CPL; ++m) {
-      if constexpr (MODE != kStepInit) asm volatile("" : "+v"(st.wg[m]));
-      if constexpr (MODE == kStepInit) asm volatile("" : "+v"(st.tau[m]), "+v"(st.p0[m]));
-      if constexpr (MODE != kStepUniform) {
+    for (int i = 0; i < K; ++i) {
+      x[i] = from_lane<O>(y[i]) * inv;
+      BPDQ_PIN(x[i]);
+    }
+    far_updates<K, G, MODE, M + 1, 0, NF>(st, pd);
+  } else {
+    float d = from_lane<O>(st.wg[M]) - lv;
+    BPDQ_PIN(d);
+    d = d * d;
+    unsigned dist = __builtin_bit_cast(unsigned, d);
+    BPDQ_PIN(dist);
+    far_updates<K, G, MODE, M + 1, 0, at(2)>(st, pd);
+    unsigned least = min_stage<0>(dist);
+    BPDQ_PIN(least);
+    far_updates<K, G, MODE, M + 1, at(2), at(4)>(st, pd);
+    if constexpr (K > 1) { least = min_stage<1>(least); BPDQ_PIN(least); }
+    if constexpr (K > 2) {
+      far_updates<K, G, MODE, M + 1, at(4), at(6)>(st, pd);
+      least = min_stage<2>(least);
+      BPDQ_PIN(least);
+    }
+    if constexpr (K > 3) {
+      far_updates<K, G, MODE, M + 1, at(6), at(8)>(st, pd);
+      least = min_stage<3>(least);
+      BPDQ_PIN(least);
+    }
+    constexpr int f0 = 2 + 2 * (K - 1) + (K == 1 ? 2 : 0);
+    const bool hit = (dist == least);
+    unsigned code = hit ? lc : 0xffffffffu;
+    far_updates<K, G, MODE, M + 1, at(f0), at(f0 + 2)>(st, pd);
+    BPDQ_PIN(code);
+    far_updates<K, G, MODE, M + 1, at(f0 + 2), at(f0 + 4)>(st, pd);
+    code = min_stage<0>(code);
+    BPDQ_PIN(code);
+    if constexpr (K > 1) {
+      far_updates<K, G, MODE, M + 1, at(f0 + 4), at(f0 + 6)>(st, pd);
+      code = min_stage<1>(code);
+      BPDQ_PIN(code);
+    }
+    if constexpr (K > 2) {
+      far_updates<K, G, MODE, M + 1, at(f0 + 6), at(f0 + 8)>(st, pd);
+      code = min_stage<2>(code);
+      BPDQ_PIN(code);
+    }
+    if constexpr (K > 3) {
+      far_updates<K, G, MODE, M + 1, at(f0 + 8), at(f0 + 10)>(st, pd);
+      code = min_stage<3>(code);
+      BPDQ_PIN(code);
+    }
+    constexpr int f1 = f0 + 4 + 2 * (K - 1);
+    float b[K];
+    b[0] = byte_f<0>(code);
+    if constexpr (K > 1) b[1] = byte_f<1>(code);
+    if constexpr (K > 2) b[2] = byte_f<2>(code);
+    if constexpr (K > 3) b[3] = byte_f<3>(code);
+    float q = c[0];
 #pragma unroll
-        for (int i = 0; i < K; ++i) asm volatile("" : "+v"(st.P[i][m]));
+    for (int i = 0; i < K; ++i) {
+      BPDQ_PIN(b[i]);
+      q = fmaf(b[i], c[i + 1], q);          // b is 0 or 1: the sum of the level table, bit for bit
+      BPDQ_PIN(q);
+      if constexpr (!kUni) {
+        x[i] = from_lane<O>(st.P[i][M]) + b[i];
+        BPDQ_PIN(x[i]);
       }
     }
-  }
-  __builtin_amdgcn_sched_barrier(0);     // later steps' reads stay behind this step
-  if constexpr (kPrefetch && L + 1 < G) {
+    e = from_lane<O>(st.wg[M]) - q;
+    BPDQ_PIN(e);
+    st.code[M] = (lane16 == O) ? (int)code : st.code[M];
+    BPDQ_PIN(st.code[M]);
+    e = e * inv;
+    BPDQ_PIN(e);
+    if constexpr (!kUni) {
 #pragma unroll
-    for (int m = (L + 1) / 16; m < CPL; ++m) u[m] = un[m];
+      for (int i = 0; i < K; ++i) {
+        x[i] = x[i] * inv;
+        BPDQ_PIN(x[i]);
+      }
+    }
+    far_updates<K, G, MODE, M + 1, at(f1), NF>(st, pd);
+  }
+  if constexpr (L + 1 < G) {
+    // the slot of column L + 1 at once, the others in the next step
+    if constexpr (kInit) {
+      st.tau[MN] = fmaf(-tb, u[MN], st.tau[MN]);
+      BPDQ_PIN(st.tau[MN]);
+      st.p0[MN] = fmaf(-ob, u[MN], st.p0[MN]);
+      BPDQ_PIN(st.p0[MN]);
+    } else {
+      st.wg[MN] = fmaf(-e, u[MN], st.wg[MN]);
+      BPDQ_PIN(st.wg[MN]);
+    }
+    if constexpr (!kUni) {
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        st.P[i][MN] = fmaf(-x[i], u[MN], st.P[i][MN]);
+        BPDQ_PIN(st.P[i][MN]);
+      }
+    }
+    pd.e = e; pd.t = tb; pd.o = ob;
+    if constexpr (!kUni) {
+#pragma unroll
+      for (int i = 0; i < K; ++i) pd.x[i] = x[i];
+    }
+#pragma unroll
+    for (int m = MN; m < CPL; ++m) {
+      pd.u[m] = u[m];
+      u[m] = un[m];
+    }
     inv = invn;
   }
+  __builtin_amdgcn_sched_barrier(0);     // later steps' reads stay behind this step
 }
 
 template <int K, int G, int MODE, int... Ls>
 __device__ __forceinline__ void run_columns(RowState<K, G>& st, const float* sU, const float* sInv,
-                                            const float (&lv)[1 << K], int lane16,
+                                            const float (&c)[K + 1], int lane16,
                                             std::integer_sequence<int, Ls...>) {
-  float u[G / 16];
+  constexpr int CPL = G / 16;
+  // level and byte-wise code of this lane: code lane % 2^K, summed in the order of level_table.  A
+  // coefficient that is not finite never belongs to the nearest level unless C_0 is not finite
+  // either; it is left out of the sums below, where 0 * inf would be NaN.
+  float lv = c[0], cs[K + 1];
+  unsigned lc = 0u;
+  cs[0] = c[0];
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    const bool set = ((lane16 >> i) & 1) != 0;
+    lv = set ? lv + c[i + 1] : lv;
+    lc |= set ? (1u << (8 * i)) : 0u;
+    cs[i + 1] = __builtin_isfinite(c[i + 1]) ? c[i + 1] : 0.f;
+  }
+  float bits[K][CPL];
+  if constexpr (MODE == kStepInit) {
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+      for (int m = 0; m < CPL; ++m) bits[i][m] = (float)((st.code[m] >> i) & 1);
+  }
+  float u[CPL];
   load_u_row<G, 0>(sU, lane16, u);
   float inv = sInv[0];
-  (column_step<K, G, Ls, MODE>(st, sU, sInv, lv, lane16, u, inv), ...);
+  Pending<K, G> pd;
+  (column_step<K, G, Ls, MODE>(st, sU, sInv, cs, lv, lc, bits, lane16, pd, u, inv), ...);
+  // finished columns: coordinates from the right-hand sides that the sweep left in place
+#pragma unroll
+  for (int m = 0; m < CPL; ++m) {
+    const float iv = sInv[16 * m + lane16];
+    if constexpr (MODE == kStepInit) {
+      st.tau[m] *= iv;
+      st.p0[m] *= iv;
+    } else {
+      const unsigned cb = (unsigned)st.code[m];           // bytes -> bits
+      st.code[m] = (int)((cb | (cb >> 7) | (cb >> 14) | (cb >> 21)) & ((1u << K) - 1u));
+    }
+    if constexpr (MODE == kStepUniform) {
+      float q = cs[0];
+#pragma unroll
+      for (int i = 0; i < K; ++i) q = fmaf((float)((st.code[m] >> i) & 1), cs[i + 1], q);
+      st.tau[m] = (st.wg[m] - q) * iv;
+    } else {
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        const float b = (MODE == kStepInit) ? bits[i][m] : (float)((st.code[m] >> i) & 1);
+        st.P[i][m] = (b + st.P[i][m]) * iv;
+      }
+    }
+  }
 }
 
 // Stage the local factor U[s0:s0+G, s0:s0+G] in LDS (layout above) and 1 / U_ll in sInv.
@@ -650,27 +820,25 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void bpdq_gro
 #pragma unroll
     for (int i = 0; i < K; ++i) st.P[i][m] = 0.f;
   }
-  float lv[1 << K];
-#pragma unroll
-  for (int c = 0; c < (1 << K); ++c) lv[c] = 0.f;
-  using Seq = std::make_integer_sequence<int, G>;
-  run_columns<K, G, kStepInit>(st, sU, sInv, lv, lane16, Seq{});
-
   float c32[K + 1], Ep[CPL];
+#pragma unroll
+  for (int i = 0; i <= K; ++i) c32[i] = 0.f;
+  using Seq = std::make_integer_sequence<int, G>;
+  run_columns<K, G, kStepInit>(st, sU, sInv, c32, lane16, Seq{});
+
   double rs = fit_and_score<K, G>(st, (double)alpha, coef_fp16, c32, Ep);
   store_candidate<K, G>(st, c32, Ep, rs, 0, row, valid, d_out, n_wg, cand_codes, cand_coef,
                         cand_E, cand_score, sScore, lane16);
 
   // ---- refinement iterations (Sec. 3.3)
   for (int it = 1; it <= T; ++it) {
-    level_table<K>(c32, lv);
 #pragma unroll
     for (int m = 0; m < CPL; ++m) {
       st.wg[m] = st.t[m];
 #pragma unroll
       for (int i = 0; i < K; ++i) st.P[i][m] = 0.f;
     }
-    run_columns<K, G, kStepSweep>(st, sU, sInv, lv, lane16, Seq{});
+    run_columns<K, G, kStepSweep>(st, sU, sInv, c32, lane16, Seq{});
     rs = fit_and_score<K, G>(st, (double)alpha, coef_fp16, c32, Ep);
     store_candidate<K, G>(st, c32, Ep, rs, it, row, valid, d_out, n_wg, cand_codes, cand_coef,
                           cand_E, cand_score, sScore, lane16);
@@ -722,11 +890,10 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void uniform_
   hi = row_reduce_f(hi, [](float a, float b) { return fmaxf(a, b); });
   float step = (hi - lo) / (float)((1 << K) - 1);
   if (step == 0.f) step = 1.0f;                 // flat row: every weight takes code 0
-  float c32[K + 1], lv[1 << K], Ep[CPL];
+  float c32[K + 1], Ep[CPL];
   c32[0] = store_precision(lo, coef_fp16);
 #pragma unroll
   for (int i = 0; i < K; ++i) c32[i + 1] = store_precision(step * (float)(1 << i), coef_fp16);
-  level_table<K>(c32, lv);
 #pragma unroll
   for (int m = 0; m < CPL; ++m) {
     st.wg[m] = st.t[m];
@@ -734,7 +901,7 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void uniform_
     st.code[m] = 0;
   }
   using Seq = std::make_integer_sequence<int, G>;
-  run_columns<K, G, kStepUniform>(st, sU, sInv, lv, lane16, Seq{});
+  run_columns<K, G, kStepUniform>(st, sU, sInv, c32, lane16, Seq{});
   double sc = 0.0;
 #pragma unroll
   for (int m = 0; m < CPL; ++m) {

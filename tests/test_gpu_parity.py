@@ -777,6 +777,31 @@ def test_gather_scatter_bit_exact_and_ordered_pass(dev):
     print(f"   objective descending-diagonal order / natural order = {og / o0:.3f}", flush=True)
 
 
+@pytest.mark.parametrize("group", [32, 64, 128, 256])
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+def test_nearest_level_ties_take_the_lowest_code(dev, bits, group):
+    """With U = I nothing propagates, and the fixed grid over [0, 2^k - 1] has the integers as levels: every
+    half-way weight must take the lower code, whatever column it is in, and every other the nearest."""
+    if group == 256 and bits == 4:
+        pytest.skip("4 planes at g = 256 are not built")
+    print(f"ties k={bits} g={group}", flush=True)
+    rng = np.random.default_rng(bits * 100 + group)
+    top = (1 << bits) - 1
+    d_out = 21
+    W = rng.integers(0, 4 * top + 1, size=(d_out, group)).astype(np.float32) / 4      # quarters: exact distances
+    W[:, 0], W[:, -1] = 0.0, float(top)
+    W[1] = np.minimum(np.arange(group) % (top + 1) + 0.5, top)                        # a row of half-way weights
+    W[1, 0], W[1, -1] = 0.0, float(top)
+    U = torch.eye(group, device=dev)
+    p = bq.make_params(bits, group, group, 0, grid=bq.GRID_UNIFORM)
+    out = bq.bpdq_quantize_layer(torch.from_numpy(W).to(dev), U, None, p)
+    code = orc.unpack_planes(out["planes"].cpu().numpy().view(np.uint32), group)
+    want = np.ceil(W - 0.5).astype(np.int64)
+    assert np.array_equal(code, want)
+    assert np.array_equal(out["W_hat"].cpu().numpy(), want.astype(np.float32))
+    assert float(out["grp_err"][0]) == float(((W - want).astype(np.float64) ** 2).sum())
+
+
 # ------------------------------------------------------------------ storage helpers
 @pytest.mark.parametrize("bits", [1, 2, 3, 4])
 def test_pack_and_dequant_bit_exact(dev, bits):
