@@ -693,6 +693,37 @@ def test_gemv_from_stored_format(dev, bits, group, d_out, d_in):
     assert np.all(err <= bound)
 
 
+@pytest.mark.parametrize("bits,group,d_out,d_in,shift", [
+    (1, 32, 1, 32, 0), (2, 64, 17, 2048, 0), (2, 32, 33, 2080, 0),          # one word; all 64 lanes of one word; two words
+    (3, 64, 40, 4096, 0), (3, 96, 40, 2400, 0),                             # two words per lane: full, odd word count
+    (4, 64, 4100, 4160, 0), (2, 128, 4130, 8448, 0), (2, 64, 70, 16512, 1),  # four words, two rows, chunks, unaligned planes
+    (3, 32, 4097, 4224, 0), (1, 256, 8200, 512, 0),                         # one row of three planes; several passes
+    (2, 128, 8230, 8448, 0),                                                # passes times chunks
+])
+def test_gemv_tile_edges(dev, bits, group, d_out, d_in, shift):
+    """Every words-per-lane, groups-per-lane and rows-per-wavefront variant at its edges against Eq. 1 in fp64."""
+    print(f"gemv edges k={bits} g={group} {d_out}x{d_in} shift={shift}", flush=True)
+    g = torch.Generator(device=dev)
+    g.manual_seed(d_in + bits)
+    n = bits * d_out * (d_in // 32)
+    buf = torch.randint(-(1 << 31), 1 << 31, (n + 4,), generator=g, device=dev, dtype=torch.int64).to(torch.int32)
+    planes = buf[shift:shift + n].reshape(bits, d_out, d_in // 32)
+    coef = (torch.randn((bits + 1, d_out, d_in // group), generator=g, device=dev) * 0.02).half()
+    x = torch.randn(d_in, generator=g, device=dev)
+    y = torch.full((d_out + 3,), float("nan"), device=dev)
+    bq.bpdq_gemv(planes, coef, group, x, y[:d_out])
+    bit = torch.arange(32, device=dev, dtype=torch.int32)
+    W = coef[0].double().repeat_interleave(group, 1)
+    A = W.abs()
+    for i in range(bits):
+        b = ((planes[i][:, :, None] >> bit) & 1).reshape(d_out, d_in).double()
+        c = coef[i + 1].double().repeat_interleave(group, 1)
+        W, A = W + b * c, A + b * c.abs()
+    want, bound = W @ x.double(), 1e-5 * (A @ x.double().abs()) + 1e-12
+    assert bool(((y[:d_out].double() - want).abs() <= bound).all())
+    assert bool(torch.isnan(y[d_out:]).all())
+
+
 def test_gemv_of_a_quantized_layer(dev):
     print("gemv of a quantized layer (fp16 storage) + timing", flush=True)
     wl, W, X = _problem("cfg2_qwen7b_attn", 512, 3584, 4096)
