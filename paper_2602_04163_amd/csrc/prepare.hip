@@ -77,6 +77,13 @@ __device__ __forceinline__ double fast_rcp(double x) {
   return r;
 }
 
+// 1 / sqrt(x) in fp64: hardware estimate and one third-order step, an ulp or two
+__device__ __forceinline__ double fast_rsqrt(double x) {
+  const double r = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * r, r, 1.0);
+  return fma(r, e * fma(0.375, e, 0.5), r);
+}
+
 // A 64 x 64 tile of doubles moves between global memory and LDS through registers, 16 elements
 // per thread of 256 (element e = tid + 256 t -> row e / 64, column e % 64).  All 16 loads of a
 // thread are issued before the first is used: a rolled loop would wait for memory 16 times.
@@ -105,105 +112,120 @@ __device__ __forceinline__ void put_tile64(ROW* s, const double (&v)[16]) {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
+// value of lane J of this lane's 16-lane row, in every lane of the row (one v_mov_b64_dpp)
+template <int J>
+__device__ __forceinline__ double row_bcast(double x) {
+  return __builtin_amdgcn_update_dpp(0.0, x, 0x150 + J, 0xF, 0xF, true);
+}
+
+typedef double Inv16[16][16];
+
+// Elimination of column J of a 16 x 16 symmetric block and of its companion W (at first the identity).
+// Lane i % 16 = row i holds the block's row in a[0..15]; all four 16-lane rows hold the same block, and
+// row q of them the columns 4 ks + q of W in w[ks].  With t_i = A_iJ / A_JJ the rows above J lose t_i
+// times row J; only the reciprocal's chain (about six dependent fp64 operations) is serial, the
+// broadcasts of row J do not wait for it.
+template <int J>
+__device__ __forceinline__ void eliminate16(double (&a)[16], double (&w)[4], double& piv_own, int i, bool& bad_any,
+                                            int& bad_col) {
+  double row[J > 0 ? J : 1], wr[4];
+  const double piv_raw = row_bcast<J>(a[J]);
+#pragma unroll
+  for (int e = J - 1; e >= 0; --e) row[e] = row_bcast<J>(a[e]);
+#pragma unroll
+  for (int ks = J / 4; ks < 4; ++ks) wr[ks] = row_bcast<J>(w[ks]);      // columns left of J are still zero in row J
+  const bool bad = !(piv_raw > 0.0);
+  const double piv = bad ? 1.0 : piv_raw;
+  if (bad) { bad_any = true; bad_col = J; }
+  if (i == J) piv_own = piv;
+  const double t = a[J] * fast_rcp(piv);
+#pragma unroll
+  for (int e = J - 1; e >= 0; --e) a[e] = fma(-t, row[e], a[e]);
+  const double tm = (i < J) ? t : 0.0;
+#pragma unroll
+  for (int ks = J / 4; ks < 4; ++ks) w[ks] = fma(-tm, wr[ks], w[ks]);
+  if constexpr (J > 0) eliminate16<J - 1>(a, w, piv_own, i, bad_any, bad_col);
+}
+
+// a[e] *= (value of `s` in lane e of the 16-lane row), e = E .. 0
+template <int E>
+__device__ __forceinline__ void scale_columns16(double (&a)[16], double s) {
+  a[E] *= row_bcast<E>(s);
+  if constexpr (E > 0) scale_columns16<E - 1>(a, s);
+}
+
 // Reversed Cholesky of one 64 x 64 block held in LDS: D = R R^T, R upper, columns taken from the
 // last to the first, in panels of 16 columns.
 //   in : sD, the full symmetric block (both triangles; identity padding where the block is ragged)
-//   out: sD = R (zero below the diagonal), sInvD[j] = 1 / R_jj
-// A panel is factored by ONE wavefront, lane r holding row r of its 16 columns in registers: a
-// column step writes the pivot column to LDS and reads the pivot and the (at most 15) entries it
-// needs back as broadcasts -- LDS serves one wavefront in order, so no barrier is involved -- then
-// updates only the panel's columns left of the pivot.  The other columns of the block receive the
-// panel's rank-16 update afterwards on the fp64 matrix cores (all four wavefronts).  Against a
-// column step that updates the whole block (16 multiply-adds per thread of 256 behind a barrier)
-// the dependent chain per column is a third as long.  Square roots are taken once, at the end.
+//   out: sD = R on and above the diagonal (undefined below it), sRinv[J] = (R_JJ)^-1 of the four
+//        16 x 16 diagonal blocks (zero below the diagonal)
+// The 16 x 16 diagonal block of a panel is eliminated in registers by every wavefront for itself, one
+// 16-lane row of the wavefront holding the block (row broadcasts are single DPP moves), together with its
+// inverse.  The inverse comes out in the operand layout of the fp64 matrix instruction, so the rest of the
+// panel, X = A R_JJ^-T, and the update of the columns to its left, -= X X^T, are matrix products on the
+// upper 16 x 16 tiles.  Per panel: one chain of 16 columns of about 120 cycles each and two barriers.
+// (One wavefront with lane = row of the whole panel, its pivot columns going through LDS, took 430
+// cycles a column, and the inverses a pass of their own: a panel pair 52 -> 40 us at d = 3584.)
 // A non-positive pivot is reported as column p0 + j + 1 (by the work-group with `report`) and
-// replaced by 1.  All 256 threads call this; sCol and sPiv are 64 doubles each.
-template <int JL>
-__device__ __forceinline__ void factor_panel_step(double (&pa)[16], double* sCol, double* sPiv, int c0,
-                                                  int lane, int* info, int p0, bool report) {
-  sCol[lane] = pa[JL];
-  const double piv_raw = sCol[c0 + JL];
-  double cc[JL > 0 ? JL : 1];
-#pragma unroll
-  for (int e = 0; e < JL; ++e) cc[e] = sCol[c0 + e];
-  const bool bad = !(piv_raw > 0.0);
-  const double piv = bad ? 1.0 : piv_raw;
-  const double t = pa[JL] * fast_rcp(piv);
-#pragma unroll
-  for (int e = 0; e < JL; ++e) pa[e] = fma(-t, cc[e], pa[e]);
-  if (lane == 0) {
-    sPiv[c0 + JL] = piv;
-    if (bad && report) atomicCAS(info, 0, p0 + c0 + JL + 1);
-  }
-  if constexpr (JL > 0) factor_panel_step<JL - 1>(pa, sCol, sPiv, c0, lane, info, p0, report);
-}
-
-__device__ __forceinline__ void factor64_blocked(double (*sD)[NB + 1], double* sCol, double* sPiv,
-                                                 double* sInvD, int* info, int p0, bool report) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+// replaced by 1.  All 256 threads call this; it begins and ends with a barrier.
+__device__ __forceinline__ void factor64_blocked(double (*sD)[NB + 1], Inv16* sRinv, int* info, int p0, bool report) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int m = lane & 15, q = lane >> 4;
 #pragma unroll 1
   for (int J = NB / 16 - 1; J >= 0; --J) {
     const int c0 = 16 * J;
     __syncthreads();                        // the block, with every earlier panel's update, is in LDS
-    if (w == 0) {
-      double pa[16];
+    double a[16], wi[4], piv = 1.0, at[4];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) pa[e] = sD[lane][c0 + e];
-      factor_panel_step<15>(pa, sCol, sPiv, c0, lane, info, p0, report);
+    for (int e = 0; e < 16; ++e) a[e] = sD[c0 + m][c0 + e];
+    if (w < J) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) sD[lane][c0 + e] = (lane <= c0 + e) ? pa[e] : 0.0;   // unscaled columns of R
+      for (int ks = 0; ks < 4; ++ks) at[ks] = sD[16 * w + m][c0 + 4 * ks + q];     // A operand of row tile w
+    }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) wi[ks] = (m == 4 * ks + q) ? 1.0 : 0.0;
+    bool bad = false;
+    int bad_col = 0;
+    eliminate16<15>(a, wi, piv, m, bad, bad_col);
+    const double inv_d = fast_rsqrt(piv);   // 1 / R_jj of row j = m
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) wi[ks] *= inv_d;                                // R_JJ^-1 [m][4 ks + q]
+    if (w == 3) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) sRinv[J][m][4 * ks + q] = wi[ks];
+    }
+    if (bad && report && w == 0 && lane == 0) atomicCAS(info, 0, p0 + c0 + bad_col + 1);
+    if (w < J) {                            // X = A R_JJ^-T, row tile w
+      f64x4 x = (f64x4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) x = __builtin_amdgcn_mfma_f64_16x16x4f64(at[ks], wi[ks], x, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sD[16 * w + 4 * r + q][c0 + m] = x[r];
     }
     __syncthreads();
-    // leading block [0, c0) x [0, c0), upper 16 x 16 tiles:  -= Rp diag(1 / pivot) Rp^T
-    const int m = lane & 15, kq = lane >> 4;
+    // (after the barrier: every wavefront has read the diagonal block)
+    if (w == 3 && q == 0) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const double sc = (m <= e) ? a[e] : 0.0;
+        a[e] = sc;
+      }
+      scale_columns16<15>(a, inv_d);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sD[c0 + m][c0 + e] = a[e];
+    }
     int t = 0;
-    for (int tk = 0; tk < J; ++tk)
-      for (int ti = 0; ti <= tk; ++ti, ++t) {
+    for (int tk = J - 1; tk >= 0; --tk)     // the next panel's tiles first
+      for (int ti = tk; ti >= 0; --ti, ++t) {
         if ((t & 3) != w) continue;
         f64x4 acc = (f64x4){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          const int kk = c0 + 4 * ks + kq;
-          const double a = sD[16 * ti + m][kk] * fast_rcp(sPiv[kk]);
-          const double b = sD[16 * tk + m][kk];
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-        }
+        for (int ks = 0; ks < 4; ++ks)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sD[16 * ti + m][c0 + 4 * ks + q], sD[16 * tk + m][c0 + 4 * ks + q],
+                                                     acc, 0, 0, 0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sD[16 * ti + 4 * r + kq][16 * tk + m] -= acc[r];
+        for (int r = 0; r < 4; ++r) sD[16 * ti + 4 * r + q][16 * tk + m] -= acc[r];
       }
-  }
-  __syncthreads();
-  if (tid < NB) sInvD[tid] = 1.0 / sqrt(sPiv[tid]);
-  __syncthreads();
-  for (int e = tid; e < NB * NB; e += 256) {
-    const int i = e / NB, j = e % NB;
-    sD[i][j] = (i <= j) ? sD[i][j] * sInvD[j] : 0.0;          // R[:, j] = column_j / sqrt(pivot_j)
-  }
-  __syncthreads();
-}
-
-
-// Inverses of the four 16 x 16 diagonal blocks of R (upper triangular, sInvD[j] = 1 / R_jj):
-// sRinv[J][i][c] = (R_JJ^-1)[i][c], zero below the diagonal.  Wavefront J takes block J, lane
-// c < 16 column c by back substitution from row 15 up (rows below c are zero, row c is 1 / R_cc).
-// All 256 threads call this; it ends with a barrier.
-typedef double Inv16[16][16];
-__device__ __forceinline__ void invert_diag16(const double (*sR)[NB + 1], const double* sInvD, Inv16* sRinv) {
-  const int lane = threadIdx.x & 63, J = threadIdx.x >> 6;
-  if (lane < 16) {
-    const int c = lane, o = 16 * J;
-    double x[16];
-#pragma unroll
-    for (int i = 15; i >= 0; --i) {
-      double acc = 0.0;
-#pragma unroll
-      for (int m = 15; m > i; --m) acc = fma(sR[o + i][o + m], x[m], acc);   // (x[m] = 0 for m > c) the newest x last:
-                                                                             // only that term waits for the row before
-      const double v = (i == c) ? 1.0 : -acc;
-      x[i] = (i <= c) ? v * sInvD[o + i] : 0.0;
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) sRinv[J][i][c] = x[i];
   }
   __syncthreads();
 }
@@ -309,8 +331,6 @@ __global__ __launch_bounds__(256) void panel_factor_kernel(double* __restrict__ 
                                                            int* __restrict__ pair_flag, int* info) {
   __shared__ double sR[NB][NB + 1];     // R (upper) of the diagonal block
   __shared__ double sA[NB][NB + 1];     // panel tile of this work-group
-  __shared__ double col[2][NB];
-  __shared__ double sInvD[NB];
   __shared__ Inv16 sRinv[NB / 16];
   const int tid = threadIdx.x;
 
@@ -327,7 +347,7 @@ __global__ __launch_bounds__(256) void panel_factor_kernel(double* __restrict__ 
                  [&](int i, int j) { return (long)(r0 + i) * d + p0 + j; }, v);
     put_tile64(sA, v);
   }
-  factor64_blocked(sR, col[0], col[1], sInvD, info, p0, blockIdx.x == 0);
+  factor64_blocked(sR, sRinv, info, p0, blockIdx.x == 0);
   // R of the diagonal block goes to its own buffer: the block itself must stay untouched, because
   // work-groups of this launch that start later still have to read it
   if (blockIdx.x == 0) {
@@ -335,7 +355,6 @@ __global__ __launch_bounds__(256) void panel_factor_kernel(double* __restrict__ 
     if (tid == 0) *pair_flag = 0;
   }
   if (n_above == 0) return;
-  invert_diag16(sR, sInvD, sRinv);
   trsm64_blocked(sA, sA, false, sR, sRinv);
   for (int e = tid; e < NB * NB; e += 256) {
     const int i = e / NB, j = e % NB;
@@ -456,7 +475,7 @@ __device__ __forceinline__ void quad_for_each(const Quad64& q, F f) {
 // launches of the panel chain (each is short and latency-bound).  Work-group 0 writes R11, R22
 // to Rdiag and R12 to R12buf (never into A, whose blocks later-scheduled work-groups still
 // read) and sets the pair flag of b2, so that the inverse step puts R12 in place.
-constexpr size_t kPairLdsBytes = (size_t)(4 * NB * (NB + 1) + 3 * NB + NB * 16) * sizeof(double);
+constexpr size_t kPairLdsBytes = (size_t)(4 * NB * (NB + 1) + NB * 16) * sizeof(double);
 
 __global__ __launch_bounds__(256) void panel_pair_kernel(double* __restrict__ A, int d, int p1,
                                                          int nb2, int n_above,
@@ -471,10 +490,8 @@ __global__ __launch_bounds__(256) void panel_pair_kernel(double* __restrict__ A,
   Row* sR12 = sR + NB;                              // D12 -> R12
   Row* sA1 = sR12 + NB;                             // own rows, columns of b1
   Row* sA2 = sA1 + NB;                              // own rows, columns of b2
-  double (*col)[NB] = reinterpret_cast<double (*)[NB]>(dyn + 4 * NB * (NB + 1));
-  double* sInvD = dyn + 4 * NB * (NB + 1) + 2 * NB;
-  Inv16* sRinv = reinterpret_cast<Inv16*>(dyn + 4 * NB * (NB + 1) + 3 * NB);
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+  Inv16* sRinv = reinterpret_cast<Inv16*>(dyn + 4 * NB * (NB + 1));
+  const int tid = threadIdx.x;
   const int p2 = p1 + NB;
   const int r0 = blockIdx.x * NB;
   const bool first = blockIdx.x == 0;
@@ -497,11 +514,10 @@ __global__ __launch_bounds__(256) void panel_pair_kernel(double* __restrict__ A,
     }
     put_tile64(sR12, v12);
   }
-  factor64_blocked(sR, col[0], col[1], sInvD, info, p2, first);
+  factor64_blocked(sR, sRinv, info, p2, first);
   if (first)
     for (int e = tid; e < NB * NB; e += 256) Rdiag2[e] = sR[e / NB][e % NB];
   // R12 = D12 R22^-T and X2 = A2 R22^-T
-  invert_diag16(sR, sInvD, sRinv);                  // (its barrier: Rdiag2 has been read out of sR)
   trsm64_blocked(sR12, sA2, n_above > 0, sR, sRinv);
   {
     Quad64 q;
@@ -520,7 +536,7 @@ __global__ __launch_bounds__(256) void panel_pair_kernel(double* __restrict__ A,
     const int e = tid + 256 * t;
     sR[e >> 6][e & 63] += d11[t];
   }
-  factor64_blocked(sR, col[0], col[1], sInvD, info, p1, first);
+  factor64_blocked(sR, sRinv, info, p1, first);
   if (first) {
     for (int e = tid; e < NB * NB; e += 256) {
       Rdiag1[e] = sR[e / NB][e % NB];
@@ -532,7 +548,6 @@ __global__ __launch_bounds__(256) void panel_pair_kernel(double* __restrict__ A,
     }
   }
   if (n_above == 0) return;
-  invert_diag16(sR, sInvD, sRinv);
   trsm64_blocked(sA1, sA1, false, sR, sRinv);
   for (int e = tid; e < NB * NB; e += 256) {
     const int i = e / NB, j = e % NB;
