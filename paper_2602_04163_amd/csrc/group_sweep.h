@@ -21,6 +21,7 @@
 //   * the score of an iterate is ||E'||^2.
 // Decisions (8-bit RTN code, nearest level) are taken in fp32 in a fixed operation order.
 #pragma once
+#include <type_traits>
 #include <utility>
 
 #include "mfma_kmajor.h"
@@ -48,11 +49,13 @@ __device__ __forceinline__ float dpp_f(float x) {
 }
 template <int CTRL>
 __device__ __forceinline__ double dpp_d(double x) {
+  // bound_ctrl: without it the compiler writes a zero into each half first
   const long long b = __builtin_bit_cast(long long, x);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffLL), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffLL), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
   return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
 }
+
 // Butterfly over the 16 lanes of a row: xor 1, xor 2 (quad permutes), then half-row mirror and
 // row mirror, which act as xor 4 / xor 8 once quads are uniform.  Every lane ends with the same
 // bits (each stage adds the same two operands in both partners).
@@ -78,7 +81,8 @@ struct RowState {
   static constexpr int CPL = G / 16;
   float t[CPL];       // group-start working weights (frozen for the group)
   float tau[CPL];     // t U_loc^-1
-  float p0[CPL];      // 1 U_loc^-1
+  float p0[CPL];      // 1 U_loc^-1 (the same for every row)
+  float inv[CPL];     // 1 / U_ll of my columns
   float wg[CPL];      // working copy during a sweep
   float P[K][CPL];    // running right-hand sides, then P_i = b_i U_loc^-1
   int code[CPL];      // plane bits of my columns, bit (i-1) = B_i
@@ -86,39 +90,46 @@ struct RowState {
 
 // LDS layout of the local factor.  Row l only ever meets columns j > l, and column j lives in
 // slot j / 16 of lane j % 16, so row l keeps just the S = CPL - l / 16 slots m >= M = l / 16 of
-// every lane: 16 S floats, no padding.  The slots are cut into chunks of 4, then 2, then 1
-// (S = 7 -> 4 + 2 + 1); a chunk of width w that starts at slot M + o holds
+// every lane.  The slots are cut into chunks of 4, then 2, then 1 (three left over are read as a
+// chunk of 4 with a zero: one read instead of two); a chunk of width w that starts at slot M + o holds
 //   sU[row_offset(l) + 16 o + lane * w + e] = U[l][16 (M + o + e) + lane]     (0 where j <= l)
 // so one ds_read_b128 / b64 / b32 of the 16 lanes of a row covers 16 w contiguous floats (no bank
-// conflicts) at an immediate offset, no register is loaded that the step does not use, and the
-// lower part reads as zero (no masks in the inner loop).  36 KB at g = 128, 136 KB at g = 256.
+// conflicts) at an immediate offset, and the lower part reads as zero (no masks in the inner loop).
+// 38 KB at g = 128, 136 KB at g = 256.
+//
+// The image of every group is laid out once per layer in the workspace, by extra work-groups of the
+// launch that copies W (pack_factor), together with 1 / U_ll and P_0 = 1 U_loc^-1, which are the
+// same for all rows: a group launch streams the image into LDS with LDS-DMA while it gathers its
+// target.  Fetching and rearranging U_loc in every work-group had cost 12 k of a launch's 186 k cycles
+// (k = 2, g = 128, 5 iterations) and the P_0 recurrence a quarter of the initial pass; a launch takes
+// 154 k now, 128 k of them in the five iterations.
 template <int G>
 struct SuLayout {
   static constexpr int CPL = G / 16;
-  static constexpr int live(int M) { return CPL - M; }
-  static constexpr int row_offset(int l) {
+  // widest chunk: 4 floats (ds_read_b128); 2 at g = 256, where the wider reads push the
+  // fully unrolled sweep over the register file
+  static constexpr int kMaxVec = (G >= 256) ? 2 : 4;
+  __host__ __device__ static constexpr int live(int M) {          // slots kept per lane, with the pad
+    return CPL - M + ((kMaxVec == 4 && (CPL - M) % 4 == 3) ? 1 : 0);
+  }
+  __host__ __device__ static constexpr int row_offset(int l) {
     int off = 0;
     for (int M = 0; M < l / 16; ++M) off += 256 * live(M);
     return off + 16 * (l % 16) * live(l / 16);
   }
-  static constexpr int floats() { return row_offset(G); }
-  // widest chunk: 4 floats (ds_read_b128); 2 at g = 256, where the wider reads push the
-  // fully unrolled sweep over the register file
-  static constexpr int kMaxVec = (G >= 256) ? 2 : 4;
+  __host__ __device__ static constexpr int floats() { return row_offset(G); }
+  // a group's record in the workspace: image | 1 / U_ll [G] | P_0 [G], whole KB
+  __host__ __device__ static constexpr int record_floats() { return (floats() + 2 * G + 255) / 256 * 256; }
   // width of the chunk that holds live slot o (0-based among the live slots) of a row with S
   // live slots, and the live slot that chunk starts at
-  static constexpr int chunk_width(int S, int o) {
-    const int g0 = o / kMaxVec * kMaxVec, r = S - g0, i = o - g0;
-    if (r >= kMaxVec) return kMaxVec;     // a full chunk
-    return (r >= 2 && i < 2) ? 2 : 1;     // r = 3: 2 + 1;  r = 2: 2;  r = 1: 1
+  __host__ __device__ static constexpr int chunk_width(int S, int o) {
+    const int g0 = o / kMaxVec * kMaxVec, r = S - g0;
+    if (r >= kMaxVec || r == 3) return kMaxVec;     // a full chunk, or three and a pad
+    return r;                                       // 2 or 1
   }
-  static constexpr int chunk_start(int S, int o) {
-    const int g0 = o / kMaxVec * kMaxVec, r = S - g0, i = o - g0;
-    if (r >= kMaxVec) return g0;
-    return (r >= 2 && i < 2) ? g0 : g0 + i;
-  }
-  // float index (relative to the row) of live slot o for lane `lane`
-  static constexpr int slot_index(int S, int o, int lane) {
+  __host__ __device__ static constexpr int chunk_start(int, int o) { return o / kMaxVec * kMaxVec; }
+  // float index (relative to the row) of live slot o for lane `lane`; o = S: the pad after three left over
+  __host__ __device__ static constexpr int slot_index(int S, int o, int lane) {
     const int w = chunk_width(S, o), c0 = chunk_start(S, o);
     return 16 * c0 + lane * w + (o - c0);
   }
@@ -138,7 +149,9 @@ __device__ __forceinline__ void load_u_row(const float* __restrict__ p, int lane
     const int w = Lay::chunk_width(S, o);
     if (w == 4) {
       const vec4 v = *reinterpret_cast<const vec4*>(p + 16 * o + lane16 * 4);
-      u[M + o] = v[0]; u[M + o + 1] = v[1]; u[M + o + 2] = v[2]; u[M + o + 3] = v[3];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (o + e < S) u[M + o + e] = v[e];
     } else if (w == 2) {
       const vec2 v = *reinterpret_cast<const vec2*>(p + 16 * o + lane16 * 2);
       u[M + o] = v[0]; u[M + o + 1] = v[1];
@@ -147,6 +160,11 @@ __device__ __forceinline__ void load_u_row(const float* __restrict__ p, int lane
     }
   }
 }
+
+constexpr int kMaxIters = 63;             // largest refine_iters
+// LDS floats of the staged image, whole KB
+template <int G>
+constexpr int kStageFloats = (SuLayout<G>::floats() + 255) / 256 * 256;
 
 enum : int { kStepInit = 0, kStepSweep = 1, kStepUniform = 2 };
 
@@ -182,7 +200,7 @@ __device__ __forceinline__ float byte_f(unsigned x) {
 // multiply-adds fill the wait states of that step's serial chain.
 template <int K, int G>
 struct Pending {
-  float e, t, o;        // error coordinate; tau and P_0 coordinates (kStepInit)
+  float e, t;           // error coordinate; tau coordinate (kStepInit)
   float x[K];           // plane coordinates
   float u[G / 16];      // row of the local factor
 };
@@ -190,14 +208,13 @@ struct Pending {
 // Far update number F of the previous column: vector F % NV of slot FIRST + F / NV.
 template <int K, int G, int MODE, int FIRST, int F>
 __device__ __forceinline__ void far_update(RowState<K, G>& st, const Pending<K, G>& pd) {
-  constexpr int NV = (MODE == kStepInit) ? K + 2 : (MODE == kStepUniform ? 1 : K + 1);
+  constexpr int NV = (MODE == kStepUniform) ? 1 : K + 1;
   constexpr int m = FIRST + F / NV, v = F % NV;
   if constexpr (m < G / 16) {
     if constexpr (MODE == kStepInit && v == 0) { st.tau[m] = fmaf(-pd.t, pd.u[m], st.tau[m]); BPDQ_PIN(st.tau[m]); }
-    else if constexpr (MODE == kStepInit && v == 1) { st.p0[m] = fmaf(-pd.o, pd.u[m], st.p0[m]); BPDQ_PIN(st.p0[m]); }
     else if constexpr (MODE != kStepInit && v == 0) { st.wg[m] = fmaf(-pd.e, pd.u[m], st.wg[m]); BPDQ_PIN(st.wg[m]); }
     else {
-      constexpr int i = v - (MODE == kStepInit ? 2 : 1);
+      constexpr int i = v - 1;
       st.P[i][m] = fmaf(-pd.x[i], pd.u[m], st.P[i][m]);
       BPDQ_PIN(st.P[i][m]);
     }
@@ -212,7 +229,7 @@ __device__ __forceinline__ void far_updates(RowState<K, G>& st, const Pending<K,
 }
 
 // One column of the forward recurrence.
-//   kStepInit:    initial pass (codes known): builds tau, P_0 and the plane solves P_i.
+//   kStepInit:    initial pass (codes known): builds tau and the plane solves P_i.
 //   kStepSweep:   bit-plane update of column L (Eq. 7-8), its error coordinate (Eq. 3),
 //                 compensation of the later columns (Eq. 4), and the plane solves.
 //   kStepUniform: the same column update with frozen coefficients and nothing else.
@@ -235,25 +252,26 @@ __device__ __forceinline__ void far_updates(RowState<K, G>& st, const Pending<K,
 //     the previous column are dealt to those places.
 // Whole sweep phase against a step with the scan and per-step selects (5 iterations, groups of 128): 3584 x 3584,
 // 2 planes 3.38 -> 2.92 ms; 18944 x 3584, 3 planes 16.1 -> 11.9 ms; 256 x 256 (groups of 64, 3 iterations)
-// 144 -> 128 us.  45 instead of 60 instructions per column at 2 planes.
+// 144 -> 128 us.  42 instead of 60 instructions per column at 2 planes.  (What surrounds the steps has been
+// cut since: 2.57 ms, 10.7 ms and 110 us.)
 template <int K, int G, int L, int MODE>
 __device__ __forceinline__ void column_step(RowState<K, G>& st, const float* __restrict__ sU,
-                                            const float* __restrict__ sInv, const float (&c)[K + 1], float lv,
-                                            unsigned lc, const float (&bits)[K][G / 16], int lane16,
-                                            Pending<K, G>& pd, float (&u)[G / 16], float& inv) {
+                                            const float (&c)[K + 1], float lv, unsigned lc,
+                                            const float (&bits)[K][G / 16], int lane16,
+                                            Pending<K, G>& pd, float (&u)[G / 16]) {
   constexpr int CPL = G / 16, M = L / 16, O = L % 16, MN = (L + 1) / 16;
   constexpr bool kInit = (MODE == kStepInit), kUni = (MODE == kStepUniform);
   // far updates of column L - 1: the slots beyond column L's
-  constexpr int NV = kInit ? K + 2 : (kUni ? 1 : K + 1);
+  constexpr int NV = kUni ? 1 : K + 1;
   constexpr int NF = (L == 0) ? 0 : NV * (CPL - M - 1);
   float un[CPL];
-  float invn = 0.f;
   if constexpr (L + 1 < G) {
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt 0: this column's row, requested a whole step ago (one wait per step)
     load_u_row<G, MN>(sU + SuLayout<G>::row_offset(L + 1), lane16, un);
-    invn = sInv[L + 1];
     __builtin_amdgcn_sched_barrier(0);   // the reads of the next row stay ahead of this column's arithmetic
   }
-  float e = 0.f, tb = 0.f, ob = 0.f, x[K];
+  float e = 0.f, tb = 0.f, x[K];
+  const float inv = from_lane<O>(st.inv[M]);
   constexpr auto at = [](int f) { return f < NF ? f : NF; };
   if constexpr (kInit) {
     float y[K];
@@ -264,8 +282,6 @@ __device__ __forceinline__ void column_step(RowState<K, G>& st, const float* __r
     }
     tb = from_lane<O>(st.tau[M]) * inv;
     BPDQ_PIN(tb);
-    ob = from_lane<O>(st.p0[M]) * inv;
-    BPDQ_PIN(ob);
 #pragma unroll
     for (int i = 0; i < K; ++i) {
       x[i] = from_lane<O>(y[i]) * inv;
@@ -353,8 +369,6 @@ __device__ __forceinline__ void column_step(RowState<K, G>& st, const float* __r
     if constexpr (kInit) {
       st.tau[MN] = fmaf(-tb, u[MN], st.tau[MN]);
       BPDQ_PIN(st.tau[MN]);
-      st.p0[MN] = fmaf(-ob, u[MN], st.p0[MN]);
-      BPDQ_PIN(st.p0[MN]);
     } else {
       st.wg[MN] = fmaf(-e, u[MN], st.wg[MN]);
       BPDQ_PIN(st.wg[MN]);
@@ -366,7 +380,7 @@ __device__ __forceinline__ void column_step(RowState<K, G>& st, const float* __r
         BPDQ_PIN(st.P[i][MN]);
       }
     }
-    pd.e = e; pd.t = tb; pd.o = ob;
+    pd.e = e; pd.t = tb;
     if constexpr (!kUni) {
 #pragma unroll
       for (int i = 0; i < K; ++i) pd.x[i] = x[i];
@@ -376,13 +390,12 @@ __device__ __forceinline__ void column_step(RowState<K, G>& st, const float* __r
       pd.u[m] = u[m];
       u[m] = un[m];
     }
-    inv = invn;
   }
   __builtin_amdgcn_sched_barrier(0);     // later steps' reads stay behind this step
 }
 
 template <int K, int G, int MODE, int... Ls>
-__device__ __forceinline__ void run_columns(RowState<K, G>& st, const float* sU, const float* sInv,
+__device__ __forceinline__ void run_columns(RowState<K, G>& st, const float* sU,
                                             const float (&c)[K + 1], int lane16,
                                             std::integer_sequence<int, Ls...>) {
   constexpr int CPL = G / 16;
@@ -408,19 +421,20 @@ __device__ __forceinline__ void run_columns(RowState<K, G>& st, const float* sU,
   }
   float u[CPL];
   load_u_row<G, 0>(sU, lane16, u);
-  float inv = sInv[0];
   Pending<K, G> pd;
-  (column_step<K, G, Ls, MODE>(st, sU, sInv, cs, lv, lc, bits, lane16, pd, u, inv), ...);
+  (column_step<K, G, Ls, MODE>(st, sU, cs, lv, lc, bits, lane16, pd, u), ...);
   // finished columns: coordinates from the right-hand sides that the sweep left in place
 #pragma unroll
   for (int m = 0; m < CPL; ++m) {
-    const float iv = sInv[16 * m + lane16];
+    const float iv = st.inv[m];
     if constexpr (MODE == kStepInit) {
       st.tau[m] *= iv;
-      st.p0[m] *= iv;
     } else {
       const unsigned cb = (unsigned)st.code[m];           // bytes -> bits
-      st.code[m] = (int)((cb | (cb >> 7) | (cb >> 14) | (cb >> 21)) & ((1u << K) - 1u));
+      unsigned code = cb;
+#pragma unroll
+      for (int i = 1; i < K; ++i) code |= cb >> (7 * i);
+      st.code[m] = (int)(code & ((1u << K) - 1u));
     }
     if constexpr (MODE == kStepUniform) {
       float q = cs[0];
@@ -437,63 +451,117 @@ __device__ __forceinline__ void run_columns(RowState<K, G>& st, const float* sU,
   }
 }
 
-// Stage the local factor U[s0:s0+G, s0:s0+G] in LDS (layout above) and 1 / U_ll in sInv.
-// The G x G block is fetched as float4 with up to 16 loads of a thread in flight at once (a rolled
-// element loop would wait for memory once per element); the part on or below the diagonal of a
-// kept slot is stored as zero.
+// Group records of a layer (SuLayout), by work-groups of 256 threads.  pack_image: the rearranged
+// block, zeros on and below the diagonal of the kept slots.  pack_p0: 1 / U_ll and P_0 by the forward
+// recurrence of column_step, one wavefront, lane j % 64 holding columns j.
 template <int G>
-__device__ __forceinline__ void stage_local_factor(const float* __restrict__ U, int ldu, int s0,
-                                                   float* sU, float* sInv) {
+__device__ __forceinline__ void pack_image(const float* __restrict__ U, int ldu, int s0, float* __restrict__ rec) {
   using Lay = SuLayout<G>;
-  constexpr int CPL = G / 16;
-  if constexpr (G >= 256) {
-    // the g = 256 kernels are at the limit of what the compiler handles in reasonable time:
-    // they keep the plain element loop
-    for (int e = threadIdx.x; e < G * G; e += kSweepThreads) {
-      const int l = e / G, j = e % G;
-      const int M = l >> 4, m = j >> 4;
-      if (m >= M) {
-        const float v = U[(long)(s0 + l) * ldu + s0 + j];
-        const int off = 256 * (M * CPL - M * (M - 1) / 2) + 16 * (l & 15) * Lay::live(M);
-        sU[off + Lay::slot_index(Lay::live(M), m - M, j & 15)] = (j > l) ? v : 0.f;
-        if (j == l) sInv[l] = 1.0f / v;
-      }
-    }
-    return;
-  }
-  constexpr int kPer = G * G / 4 / kSweepThreads;        // float4 loads per thread: 1, 4, 16
-  constexpr int kBatch = kPer < 16 ? kPer : 16;
+  constexpr int kPer = G * G / 256, kBatch = kPer < 16 ? kPer : 16;
   for (int b = 0; b < kPer; b += kBatch) {
-    float4 v[kBatch];
+    float v[kBatch];
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int q = threadIdx.x + (b + u) * kSweepThreads;
-      const int l = q / (G / 4), j4 = (q % (G / 4)) * 4;
-      v[u] = *reinterpret_cast<const float4*>(U + (long)(s0 + l) * ldu + s0 + j4);
+    for (int t = 0; t < kBatch; ++t) {
+      const int e = threadIdx.x + (b + t) * 256;
+      v[t] = U[(long)(s0 + e / G) * ldu + s0 + e % G];
     }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int q = threadIdx.x + (b + u) * kSweepThreads;
-      const int l = q / (G / 4), j4 = (q % (G / 4)) * 4;
-      const int M = l >> 4, m = j4 >> 4;                  // the four columns share one slot
-      if (m >= M) {
-        const int off = 256 * (M * CPL - M * (M - 1) / 2) + 16 * (l & 15) * Lay::live(M);
-        const float e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const int j = j4 + c;
-          sU[off + Lay::slot_index(Lay::live(M), m - M, j & 15)] = (j > l) ? e[c] : 0.f;
-          if (j == l) sInv[l] = 1.0f / e[c];
-        }
-      }
+    for (int t = 0; t < kBatch; ++t) {
+      const int e = threadIdx.x + (b + t) * 256;
+      const int l = e / G, j = e % G, M = l >> 4, m = j >> 4, S = Lay::CPL - M;
+      if (m < M) continue;
+      float* row = rec + Lay::row_offset(l);
+      row[Lay::slot_index(S, m - M, j & 15)] = (j > l) ? v[t] : 0.f;
+      if (m == M && Lay::live(M) > S) row[Lay::slot_index(S, S, j & 15)] = 0.f;
     }
   }
 }
 
-// Storage precision of a coefficient: IEEE half (nearest even) when the layer is stored with
-// 16-bit coefficients (Table 1), so that everything computed from it belongs to the stored value.
-__device__ __forceinline__ float store_precision(float c, int coef_fp16) {
-  return coef_fp16 ? (float)(_Float16)c : c;
+template <int G>
+__device__ __forceinline__ void pack_p0(const float* __restrict__ U, int ldu, int s0, float* __restrict__ rec) {
+  constexpr int NS = (G + 63) / 64, kRows = 32;
+  if (threadIdx.x >= 64) return;
+  const int lane = threadIdx.x;
+  float* out_inv = rec + SuLayout<G>::floats();
+  float p[NS], iv[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int j = lane + 64 * s;
+    iv[s] = 1.0f / U[(long)(s0 + (j < G ? j : 0)) * ldu + s0 + (j < G ? j : 0)];
+    p[s] = 1.0f;
+  }
+#pragma unroll
+  for (int l0 = 0; l0 < G; l0 += kRows) {
+    float u[kRows][NS];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r)
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int j = lane + 64 * s;
+        u[r][s] = U[(long)(s0 + l0 + r) * ldu + s0 + (j < G ? j : 0)];
+      }
+    __builtin_amdgcn_sched_barrier(0);     // all rows of the batch requested before the first is used
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      const int l = l0 + r, sl = l / 64;
+      const float xl = p[sl] * iv[sl];
+      const float x = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, xl), l % 64));
+#pragma unroll
+      for (int s = 0; s < NS; ++s) p[s] = fmaf(-x, (lane + 64 * s > l) ? u[r][s] : 0.f, p[s]);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int j = lane + 64 * s;
+    if (j >= G) continue;
+    out_inv[j] = iv[s];
+    out_inv[G + j] = p[s] * iv[s];
+  }
+}
+
+// Request a group's image into LDS (at byte address 0 of the dynamic LDS), 1 KB per instruction, dealt
+// to the four wavefronts; stage_wait() before the barrier that publishes it.  (Assembly, because the
+// compiler would wait for all of it before the first LDS access; M0 is used for nothing else here.)
+template <int G>
+__device__ __forceinline__ void stage_request(const float* __restrict__ rec, float* sU) {
+  typedef __attribute__((address_space(3))) float lds_float;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int kKb = (SuLayout<G>::floats() + 255) / 256;
+  const unsigned lds0 = (unsigned)(size_t)(lds_float*)sU;
+  for (int c = wave; c < kKb; c += kSweepThreads / 64)
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :
+                 : "s"(lds0 + 1024u * c), "v"(1024u * c + 16u * lane), "s"(rec)
+                 : "memory");
+}
+__device__ __forceinline__ void stage_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+template <int K, int G>
+__device__ __forceinline__ void load_record_rows(RowState<K, G>& st, const float* __restrict__ rec, int lane16) {
+  const float* p = rec + SuLayout<G>::floats();
+#pragma unroll
+  for (int m = 0; m < G / 16; ++m) {
+    st.inv[m] = p[16 * m + lane16];
+    st.p0[m] = p[G + 16 * m + lane16];
+  }
+}
+
+// Storage precision of the coefficients: fp32, or IEEE half (nearest even, from the precision they come in)
+// when the layer is stored with 16-bit coefficients (Table 1), so that everything computed from them
+// belongs to the stored values.  (A branch, uniform over the launch: as a select both would be computed
+// for every fit, and the rounding of a double to half is a long piece of integer code.)
+template <int N, typename T>
+__device__ __forceinline__ void store_precision(const T (&c)[N], int coef_fp16, float (&c32)[N]) {
+  if (coef_fp16) {
+    asm volatile("");
+#pragma unroll
+    for (int a = 0; a < N; ++a) c32[a] = (float)(_Float16)c[a];
+  } else {
+#pragma unroll
+    for (int a = 0; a < N; ++a) c32[a] = (float)c[a];
+  }
 }
 
 // Coefficient fit (Eq. 6) from the solved vectors; returns c (fp32) and the row's ||E'||^2.
@@ -553,8 +621,7 @@ __device__ __forceinline__ double fit_and_score(const RowState<K, G>& st, double
     for (int b = a + 1; b < N; ++b) s -= Gm[a][b] * c[b];
     c[a] = s / Gm[a][a];
   }
-#pragma unroll
-  for (int a = 0; a < N; ++a) c32[a] = store_precision((float)c[a], coef_fp16);
+  store_precision(c, coef_fp16, c32);
   double sc = 0.0;
 #pragma unroll
   for (int m = 0; m < CPL; ++m) {
@@ -675,27 +742,30 @@ __device__ __forceinline__ void pending_update_tile(const float* __restrict__ Ea
   const float* bp = U + (long)(kp0 + kq) * ldu + s0 + 16 * wave * BPW + i;
   const bool active = wave * BPW < NB;          // g = 32: two blocks, wavefronts 2 and 3 idle
   if (active) {
-    // kChunk MFMA steps (4 columns of E* each) per round trip to memory: all their operands are
-    // requested before the first one is used.  Kp % 32 == 0 (g >= 32 divides it).
-    constexpr int kChunk = (BPW <= 2) ? 16 : 8;
-    for (int k = 0; k < Kp; k += 4 * kChunk) {
-      float a[kChunk], bv[kChunk][BPW];
+    // Every MFMA step (4 columns of E*) of a batch is requested before the first is used, so a batch costs
+    // one round trip to memory: 128 columns at once (the whole of a one-group block), then 64, then 32.
+    // Kp % 32 == 0 (g >= 32 divides it).
+    auto batch = [&](auto steps, int k) {
+      constexpr int kSteps = decltype(steps)::value;
+      float a[kSteps], bv[kSteps][BPW];
 #pragma unroll
-      for (int u = 0; u < kChunk; ++u) {
-        // steps past Kp re-read step k (a valid address) and contribute nothing
-        const bool in = k + 4 * u < Kp;
-        const long kk = in ? k + 4 * u : k;
-        const float av = ap[kk * lde];
-        a[u] = in ? av : 0.f;
+      for (int u = 0; u < kSteps; ++u) {
+        a[u] = ap[(long)(k + 4 * u) * lde];
 #pragma unroll
-        for (int b = 0; b < BPW; ++b) bv[u][b] = bp[kk * ldu + 16 * b];
+        for (int b = 0; b < BPW; ++b) bv[u][b] = bp[(long)(k + 4 * u) * ldu + 16 * b];
       }
+      __builtin_amdgcn_sched_barrier(0);   // or the scheduler sinks every load to its product again
 #pragma unroll
-      for (int u = 0; u < kChunk; ++u)
+      for (int u = 0; u < kSteps; ++u)
 #pragma unroll
         for (int b = 0; b < BPW; ++b)
           acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], bv[u][b], acc[b], 0, 0, 0);
-    }
+    };
+    int k = 0;
+    if constexpr (BPW <= 2)
+      for (; k + 128 <= Kp; k += 128) batch(std::integral_constant<int, 32>{}, k);
+    for (; k + 64 <= Kp; k += 64) batch(std::integral_constant<int, 16>{}, k);
+    for (; k < Kp; k += 32) batch(std::integral_constant<int, 8>{}, k);
 #pragma unroll
     for (int b = 0; b < BPW; ++b)
 #pragma unroll
@@ -724,27 +794,35 @@ __device__ __forceinline__ void load_group_target(RowState<K, G>& st, const floa
   }
 }
 
-template <int K, int G>
-struct Candidates {          // per-iterate scratch in the workspace
-  unsigned char* codes;      // [T+1][d_out][G]
-  float* coef;               // [T+1][d_out][K+1]
-  float* E;                  // [T+1][d_out][G]
-  double* score;             // [T+1][n_wg]
-};
+// Per-iterate scratch in the workspace, laid out by lane: codes uint32 [T+1][d_out][16][words], slot m of a
+// lane in bits 4 (m % 8) of word m / 8; coefficients [T+1][d_out][K+1]; E' [T+1][d_out][16][G/16].  One
+// to four wide stores per lane and iterate instead of one per slot and value.
+template <int G>
+constexpr int kCodeWords = (G > 128) ? 2 : 1;
 
 template <int K, int G>
 __device__ __forceinline__ void store_candidate(const RowState<K, G>& st, const float (&c32)[K + 1],
                                                 const float (&Ep)[G / 16], double rowscore, int it,
-                                                int row, bool valid, int d_out, int n_wg,
-                                                unsigned char* codes, float* coef, float* E,
-                                                double* score, double* sScore, int lane16) {
-  constexpr int CPL = G / 16;
+                                                int row, bool valid, int d_out, uint32_t* codes,
+                                                float* coef, float* E, double* sScore, int lane16) {
+  constexpr int CPL = G / 16, NW = kCodeWords<G>;
+  typedef float evec __attribute__((ext_vector_type(CPL < 4 ? 2 : 4)));
+  constexpr int W = CPL < 4 ? 2 : 4;
   if (valid) {
-    const long base = ((long)it * d_out + row) * G;
+    const long base = ((long)it * d_out + row) * 16 + lane16;
 #pragma unroll
-    for (int m = 0; m < CPL; ++m) {
-      codes[base + 16 * m + lane16] = (unsigned char)st.code[m];
-      E[base + 16 * m + lane16] = Ep[m];
+    for (int w = 0; w < NW; ++w) {
+      uint32_t packed = 0u;
+#pragma unroll
+      for (int m = 8 * w; m < CPL && m < 8 * w + 8; ++m) packed |= (uint32_t)st.code[m] << (4 * (m - 8 * w));
+      codes[base * NW + w] = packed;
+    }
+#pragma unroll
+    for (int m = 0; m < CPL; m += W) {
+      evec v;
+#pragma unroll
+      for (int e = 0; e < W; ++e) v[e] = Ep[m + e];
+      *reinterpret_cast<evec*>(E + base * CPL + m) = v;
     }
     if (lane16 <= K) {
       float v = c32[0];
@@ -753,12 +831,17 @@ __device__ __forceinline__ void store_candidate(const RowState<K, G>& st, const 
       coef[((long)it * d_out + row) * (K + 1) + lane16] = v;
     }
   }
+  if (lane16 == 0) sScore[it * kRowsPerWG + (threadIdx.x >> 4)] = valid ? rowscore : 0.0;
+}
+
+// Scores of the work-group's 16 rows, summed in row order, for iterates 0 .. T.  Once per launch: a
+// barrier per iterate would make every wavefront wait for its stores (1.4 k cycles an iterate).
+__device__ __forceinline__ void store_scores(const double* sScore, int T, int n_wg, double* __restrict__ score) {
   __syncthreads();
-  if (lane16 == 0) sScore[threadIdx.x >> 4] = valid ? rowscore : 0.0;
-  __syncthreads();
-  if (threadIdx.x == 0) {
+  const int it = threadIdx.x;
+  if (it <= T) {
     double s = 0.0;
-    for (int q = 0; q < kRowsPerWG; ++q) s += sScore[q];
+    for (int q = 0; q < kRowsPerWG; ++q) s += sScore[it * kRowsPerWG + q];
     score[(long)it * n_wg + blockIdx.x] = s;
   }
 }
@@ -767,8 +850,8 @@ __device__ __forceinline__ void store_candidate(const RowState<K, G>& st, const 
 // iterations; every iterate's (codes, coefficients, E', score) is kept for the selection.
 template <int K, int G>
 __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void bpdq_group_kernel(
-    const float* __restrict__ Wp, int ldw, int d_out, const float* __restrict__ U, int ldu, int s0,
-    int T, float alpha, int coef_fp16, unsigned char* __restrict__ cand_codes,
+    const float* __restrict__ Wp, int ldw, int d_out, const float* __restrict__ U, int ldu,
+    const float* __restrict__ rec, int s0, int T, float alpha, int coef_fp16, uint32_t* __restrict__ cand_codes,
     float* __restrict__ cand_coef,
     float* __restrict__ cand_E, double* __restrict__ cand_score, int n_wg,
     const float* __restrict__ Eall, int lde, int kp0, TailArgs ta) {
@@ -784,18 +867,19 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void bpdq_gro
   constexpr int CPL = G / 16;
   extern __shared__ float lds[];
   float* sU = lds;                            // packed local factor, see SuLayout
-  float* sInv = lds + SuLayout<G>::floats();          // 1 / U_ll
-  double* sScore = reinterpret_cast<double*>(lds + SuLayout<G>::floats() + G);
-  float* sT = lds + SuLayout<G>::floats() + G + 2 * kRowsPerWG;   // pending-update tile
+  float* sT = lds + kStageFloats<G>;          // pending-update tile, then the row scores of every iterate
+  double* sScore = reinterpret_cast<double*>(sT);
   const int tid = threadIdx.x;
   const int lane16 = tid & 15;
-  stage_local_factor<G>(U, ldu, s0, sU, sInv);
+  stage_request<G>(rec, sU);
 
   const int row = blockIdx.x * kRowsPerWG + (tid >> 4);
   const bool valid = row < d_out;
   const int rr = valid ? row : d_out - 1;
   RowState<K, G> st;
+  load_record_rows<K, G>(st, rec, lane16);
   load_group_target<K, G>(st, Wp, ldw, rr, s0, lane16, Eall, lde, U, ldu, kp0, sT);
+  stage_wait();
   __syncthreads();
 
   // ---- bit-plane initialisation (Sec. 3.2, Eq. 5): 8-bit affine RTN, keep the k MSB planes
@@ -816,7 +900,6 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void bpdq_gro
     z = fminf(fmaxf(z, 0.f), 255.f);
     st.code[m] = flat ? 0 : ((int)z >> (8 - K));
     st.tau[m] = st.t[m];
-    st.p0[m] = 1.0f;
 #pragma unroll
     for (int i = 0; i < K; ++i) st.P[i][m] = 0.f;
   }
@@ -824,11 +907,10 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void bpdq_gro
 #pragma unroll
   for (int i = 0; i <= K; ++i) c32[i] = 0.f;
   using Seq = std::make_integer_sequence<int, G>;
-  run_columns<K, G, kStepInit>(st, sU, sInv, c32, lane16, Seq{});
+  run_columns<K, G, kStepInit>(st, sU, c32, lane16, Seq{});
 
   double rs = fit_and_score<K, G>(st, (double)alpha, coef_fp16, c32, Ep);
-  store_candidate<K, G>(st, c32, Ep, rs, 0, row, valid, d_out, n_wg, cand_codes, cand_coef,
-                        cand_E, cand_score, sScore, lane16);
+  store_candidate<K, G>(st, c32, Ep, rs, 0, row, valid, d_out, cand_codes, cand_coef, cand_E, sScore, lane16);
 
   // ---- refinement iterations (Sec. 3.3)
   for (int it = 1; it <= T; ++it) {
@@ -838,11 +920,11 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void bpdq_gro
 #pragma unroll
       for (int i = 0; i < K; ++i) st.P[i][m] = 0.f;
     }
-    run_columns<K, G, kStepSweep>(st, sU, sInv, c32, lane16, Seq{});
+    run_columns<K, G, kStepSweep>(st, sU, c32, lane16, Seq{});
     rs = fit_and_score<K, G>(st, (double)alpha, coef_fp16, c32, Ep);
-    store_candidate<K, G>(st, c32, Ep, rs, it, row, valid, d_out, n_wg, cand_codes, cand_coef,
-                          cand_E, cand_score, sScore, lane16);
+    store_candidate<K, G>(st, c32, Ep, rs, it, row, valid, d_out, cand_codes, cand_coef, cand_E, sScore, lane16);
   }
+  store_scores(sScore, T, n_wg, cand_score);
 }
 
 // Fixed-uniform-grid comparator (App. A, "Fixed Grid"): the same column sweep with the levels
@@ -851,8 +933,8 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void bpdq_gro
 // GPTQ on the asymmetric min/max grid.  The result is stored as iterate 0.
 template <int K, int G>
 __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void uniform_group_kernel(
-    const float* __restrict__ Wp, int ldw, int d_out, const float* __restrict__ U, int ldu, int s0,
-    int coef_fp16, unsigned char* __restrict__ cand_codes, float* __restrict__ cand_coef,
+    const float* __restrict__ Wp, int ldw, int d_out, const float* __restrict__ U, int ldu,
+    const float* __restrict__ rec, int s0, int coef_fp16, uint32_t* __restrict__ cand_codes, float* __restrict__ cand_coef,
     float* __restrict__ cand_E, double* __restrict__ cand_score, int n_wg,
     const float* __restrict__ Eall, int lde, int kp0, TailArgs ta) {
   if constexpr (kTailInSweep<G>) {
@@ -867,18 +949,19 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void uniform_
   constexpr int CPL = G / 16;
   extern __shared__ float lds[];
   float* sU = lds;
-  float* sInv = lds + SuLayout<G>::floats();
-  double* sScore = reinterpret_cast<double*>(lds + SuLayout<G>::floats() + G);
-  float* sT = lds + SuLayout<G>::floats() + G + 2 * kRowsPerWG;
+  float* sT = lds + kStageFloats<G>;
+  double* sScore = reinterpret_cast<double*>(sT);
   const int tid = threadIdx.x;
   const int lane16 = tid & 15;
-  stage_local_factor<G>(U, ldu, s0, sU, sInv);
+  stage_request<G>(rec, sU);
 
   const int row = blockIdx.x * kRowsPerWG + (tid >> 4);
   const bool valid = row < d_out;
   const int rr = valid ? row : d_out - 1;
   RowState<K, G> st;
+  load_record_rows<K, G>(st, rec, lane16);
   load_group_target<K, G>(st, Wp, ldw, rr, s0, lane16, Eall, lde, U, ldu, kp0, sT);
+  stage_wait();
   __syncthreads();
   float lo = st.t[0], hi = st.t[0];
 #pragma unroll
@@ -890,10 +973,11 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void uniform_
   hi = row_reduce_f(hi, [](float a, float b) { return fmaxf(a, b); });
   float step = (hi - lo) / (float)((1 << K) - 1);
   if (step == 0.f) step = 1.0f;                 // flat row: every weight takes code 0
-  float c32[K + 1], Ep[CPL];
-  c32[0] = store_precision(lo, coef_fp16);
+  float grid[K + 1], c32[K + 1], Ep[CPL];
+  grid[0] = lo;
 #pragma unroll
-  for (int i = 0; i < K; ++i) c32[i + 1] = store_precision(step * (float)(1 << i), coef_fp16);
+  for (int i = 0; i < K; ++i) grid[i + 1] = step * (float)(1 << i);
+  store_precision(grid, coef_fp16, c32);
 #pragma unroll
   for (int m = 0; m < CPL; ++m) {
     st.wg[m] = st.t[m];
@@ -901,7 +985,7 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void uniform_
     st.code[m] = 0;
   }
   using Seq = std::make_integer_sequence<int, G>;
-  run_columns<K, G, kStepUniform>(st, sU, sInv, c32, lane16, Seq{});
+  run_columns<K, G, kStepUniform>(st, sU, c32, lane16, Seq{});
   double sc = 0.0;
 #pragma unroll
   for (int m = 0; m < CPL; ++m) {
@@ -909,8 +993,8 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void uniform_
     sc += (double)Ep[m] * (double)Ep[m];
   }
   sc = row_sum_d(sc);
-  store_candidate<K, G>(st, c32, Ep, sc, 0, row, valid, d_out, n_wg, cand_codes, cand_coef,
-                        cand_E, cand_score, sScore, lane16);
+  store_candidate<K, G>(st, c32, Ep, sc, 0, row, valid, d_out, cand_codes, cand_coef, cand_E, sScore, lane16);
+  store_scores(sScore, 0, n_wg, cand_score);
 }
 
 // Selection + commit of one group, 16 rows per work-group (same lane mapping as the sweep).
@@ -922,7 +1006,7 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void uniform_
 // into the K-major error buffer Eblk[(s0 - b0) + j][row] (leading dimension lde).
 template <int K, int G>
 __global__ __launch_bounds__(256) void commit_group_kernel(
-    const unsigned char* __restrict__ cand_codes, const float* __restrict__ cand_coef,
+    const uint32_t* __restrict__ cand_codes, const float* __restrict__ cand_coef,
     const float* __restrict__ cand_E, const double* __restrict__ cand_score, int n_wg, int T,
     SegArgs seg, double* __restrict__ grp_err, int* __restrict__ grp_iter, int d_out, int d_in,
     int s0, int b0,
@@ -965,17 +1049,29 @@ __global__ __launch_bounds__(256) void commit_group_kernel(
   const bool valid = row < d_out;
   const int rr = valid ? row : d_out - 1;
   const int n_grp = d_in / G, gi = s0 / G, n_word = d_in / 32;
-  const long cbase = ((long)it * d_out + rr) * G;
+  const long cbase = ((long)it * d_out + rr) * 16 + lane16;
   float c[K + 1], lv[1 << K];
 #pragma unroll
   for (int i = 0; i <= K; ++i) c[i] = cand_coef[((long)it * d_out + rr) * (K + 1) + i];
   level_table<K>(c, lv);
   int code[CPL];
+  float ev[CPL];
 #pragma unroll
-  for (int m = 0; m < CPL; ++m) {
-    code[m] = cand_codes[cbase + 16 * m + lane16];
-    sE[16 * m + lane16][rloc] = valid ? cand_E[cbase + 16 * m + lane16] : 0.f;
+  for (int w = 0; w < kCodeWords<G>; ++w) {
+    const uint32_t packed = cand_codes[cbase * kCodeWords<G> + w];
+#pragma unroll
+    for (int m = 8 * w; m < CPL && m < 8 * w + 8; ++m) code[m] = (int)((packed >> (4 * (m - 8 * w))) & 15u);
   }
+  typedef float evec __attribute__((ext_vector_type(CPL < 4 ? 2 : 4)));
+  constexpr int EW = CPL < 4 ? 2 : 4;
+#pragma unroll
+  for (int m = 0; m < CPL; m += EW) {
+    const evec v = *reinterpret_cast<const evec*>(cand_E + cbase * CPL + m);
+#pragma unroll
+    for (int e = 0; e < EW; ++e) ev[m + e] = v[e];
+  }
+#pragma unroll
+  for (int m = 0; m < CPL; ++m) sE[16 * m + lane16][rloc] = valid ? ev[m] : 0.f;
   // planes: a wave ballot holds bit (16 q + lane16) for row q of the wave
   const int shift = 16 * ((tid & 63) >> 4);
 #pragma unroll
@@ -1014,7 +1110,8 @@ __global__ __launch_bounds__(256) void commit_group_kernel(
 
 // ------------------------------------------------------------------ host side --------------
 struct QuantLayout {
-  size_t wp_off, eall_off, codes_off, coef_off, e_off, score_off, total;
+  size_t wp_off, eall_off, codes_off, coef_off, e_off, score_off, rec_off, total;
+  int rec_floats;       // floats of a group's record (SuLayout::record_floats)
   int B, lde, n_wg;
 };
 
@@ -1027,10 +1124,13 @@ static inline QuantLayout quant_layout(int d_out, int d_in, const bpdq_params& p
   size_t off = 0;
   L.wp_off = off;    off += bpdq_align_up((size_t)d_out * d_in * sizeof(float), 256);
   L.eall_off = off;  off += bpdq_align_up((size_t)d_in * L.lde * sizeof(float), 256);
-  L.codes_off = off; off += bpdq_align_up((size_t)(T + 1) * d_out * g, 256);
+  L.codes_off = off; off += bpdq_align_up((size_t)(T + 1) * d_out * 16 * (g > 128 ? 2 : 1) * sizeof(uint32_t), 256);
   L.coef_off = off;  off += bpdq_align_up((size_t)(T + 1) * d_out * (K + 1) * sizeof(float), 256);
   L.e_off = off;     off += bpdq_align_up((size_t)(T + 1) * d_out * g * sizeof(float), 256);
   L.score_off = off; off += bpdq_align_up((size_t)(T + 1) * L.n_wg * sizeof(double), 256);
+  L.rec_floats = g == 32 ? SuLayout<32>::record_floats() : g == 64 ? SuLayout<64>::record_floats()
+                 : g == 128 ? SuLayout<128>::record_floats() : SuLayout<256>::record_floats();
+  L.rec_off = off;   off += (size_t)(d_in / g) * L.rec_floats * sizeof(float);
   L.total = off;
   return L;
 }
@@ -1041,7 +1141,9 @@ int launch_tail_update(hipStream_t stream, TailArgs ta, const float* U, int ldu,
 
 template <int G>
 constexpr size_t sweep_lds_bytes() {
-  const size_t a = (size_t)(SuLayout<G>::floats() + G + 2 * kRowsPerWG + PendingTile<G>::kFloats) * sizeof(float);
+  constexpr size_t kTile = PendingTile<G>::kFloats * sizeof(float);
+  constexpr size_t kScores = (size_t)(kMaxIters + 1) * kRowsPerWG * sizeof(double);
+  const size_t a = kStageFloats<G> * sizeof(float) + (kTile > kScores ? kTile : kScores);
   return a < TailGemm::kLdsBytes ? TailGemm::kLdsBytes : a;
 }
 
@@ -1052,8 +1154,9 @@ struct UniformSweepArgs {
   const float* Wp;
   int d_in, d_out;
   const float* U;
+  const float* rec;
   int s0, coef_fp16;
-  unsigned char* c_codes;
+  uint32_t* c_codes;
   float* c_coef;
   float* c_E;
   double* c_score;
@@ -1068,7 +1171,7 @@ static inline int launch_uniform_sweep(const UniformSweepArgs& a) {
   const size_t lds = sweep_lds_bytes<G>();
   BPDQ_HIP_TRY((bpdq_lds_limit<&uniform_group_kernel<K, G>>(lds)));
   hipLaunchKernelGGL((uniform_group_kernel<K, G>), dim3(a.grid), dim3(kSweepThreads), lds, a.stream,
-                     a.Wp, a.d_in, a.d_out, a.U, a.d_in, a.s0, a.coef_fp16, a.c_codes, a.c_coef, a.c_E,
+                     a.Wp, a.d_in, a.d_out, a.U, a.d_in, a.rec, a.s0, a.coef_fp16, a.c_codes, a.c_coef, a.c_E,
                      a.c_score, a.n_wg, a.Eall, a.lde, a.kp0, a.ta);
   BPDQ_LAUNCH_CHECK();
   return 0;
@@ -1085,13 +1188,14 @@ static inline int launch_group(hipStream_t stream, const float* Wp, int d_out, i
                         int s0, int kp0, TailArgs ta, const SegArgs& seg, const bpdq_params& p,
                         const QuantLayout& L, char* base, uint32_t* planes, float* coefs,
                         float* W_hat, double* grp_err, int* grp_iter) {
-  unsigned char* c_codes = reinterpret_cast<unsigned char*>(base + L.codes_off);
+  uint32_t* c_codes = reinterpret_cast<uint32_t*>(base + L.codes_off);
   float* c_coef = reinterpret_cast<float*>(base + L.coef_off);
   float* c_E = reinterpret_cast<float*>(base + L.e_off);
   double* c_score = reinterpret_cast<double*>(base + L.score_off);
   float* Eall = reinterpret_cast<float*>(base + L.eall_off);
   const size_t lds = sweep_lds_bytes<G>();
   const int gi = s0 / G;
+  const float* rec = reinterpret_cast<const float*>(base + L.rec_off) + (long)gi * L.rec_floats;
   const bool uniform = (p.grid == BPDQ_GRID_UNIFORM);
   const int T = uniform ? 0 : p.refine_iters;
   ta.first_wg = L.n_wg;
@@ -1105,7 +1209,7 @@ static inline int launch_group(hipStream_t stream, const float* Wp, int d_out, i
   }
   const int grid = L.n_wg + n_tail;
   if (uniform) {
-    const UniformSweepArgs a{stream, grid, Wp, d_in, d_out, U, s0, p.coef_fp16, c_codes, c_coef, c_E,
+    const UniformSweepArgs a{stream, grid, Wp, d_in, d_out, U, rec, s0, p.coef_fp16, c_codes, c_coef, c_E,
                              c_score, L.n_wg, Eall, L.lde, kp0, ta};
     int rc;
     if constexpr (G >= 256) rc = launch_uniform_sweep_256<K>(a);   // a translation unit of its own
@@ -1114,7 +1218,7 @@ static inline int launch_group(hipStream_t stream, const float* Wp, int d_out, i
   } else {
     BPDQ_HIP_TRY((bpdq_lds_limit<&bpdq_group_kernel<K, G>>(lds)));
     hipLaunchKernelGGL((bpdq_group_kernel<K, G>), dim3(grid), dim3(kSweepThreads), lds, stream,
-                       Wp, d_in, d_out, U, d_in, s0, T, p.alpha, p.coef_fp16, c_codes, c_coef, c_E, c_score,
+                       Wp, d_in, d_out, U, d_in, rec, s0, T, p.alpha, p.coef_fp16, c_codes, c_coef, c_E, c_score,
                        L.n_wg, Eall, L.lde, kp0, ta);
   }
   BPDQ_LAUNCH_CHECK();

@@ -23,11 +23,23 @@ int launch_tail_update(hipStream_t stream, TailArgs ta, const float* U, int ldu,
   return 0;
 }
 
-// working copy of W with dead input channels zeroed
+// working copy of W with dead input channels zeroed; the first 2 n_grp work-groups lay out the group
+// records of the factor instead (SuLayout), beside the copy, which is bound by memory
+template <int G>
 __global__ __launch_bounds__(256) void copy_in_kernel(const float* __restrict__ W, long n, int d_in,
                                                       const unsigned char* __restrict__ dead,
-                                                      float* __restrict__ Wp) {
-  for (long e = ((long)blockIdx.x * 256 + threadIdx.x) * 4; e < n; e += (long)gridDim.x * 1024) {
+                                                      float* __restrict__ Wp, const float* __restrict__ U,
+                                                      float* __restrict__ rec) {
+  const int n_grp = d_in / G;
+  if ((int)blockIdx.x < 2 * n_grp) {
+    const int gi = blockIdx.x >> 1;
+    float* r = rec + (long)gi * SuLayout<G>::record_floats();
+    if (blockIdx.x & 1) pack_image<G>(U, d_in, gi * G, r);
+    else pack_p0<G>(U, d_in, gi * G, r);
+    return;
+  }
+  const long stride = (long)(gridDim.x - 2 * n_grp) * 1024;
+  for (long e = ((long)(blockIdx.x - 2 * n_grp) * 256 + threadIdx.x) * 4; e < n; e += stride) {
     float4 v = *reinterpret_cast<const float4*>(W + e);
     if (dead) {
       const int c = (int)(e % d_in);
@@ -136,7 +148,7 @@ static int check_params(int d_out, int d_in, const bpdq_params* p) {
   if (d_in % p->group || d_in % 32) return 1;
   const int B = p->block > p->group ? p->block : p->group;
   if (p->block < 1 || B % p->group) return 1;
-  if (p->refine_iters < 0 || p->refine_iters > 63) return 1;
+  if (p->refine_iters < 0 || p->refine_iters > kMaxIters) return 1;
   if (!(p->alpha >= 0.f)) return 1;
   if (p->grid != BPDQ_GRID_VARIABLE && p->grid != BPDQ_GRID_UNIFORM) return 1;
   if (p->coef_fp16 != 0 && p->coef_fp16 != 1) return 1;
@@ -186,8 +198,15 @@ static int quantize_rows(const float* W, int d_out, int d_in, const float* U,
   if (!group) return -6;
 
   const long n = (long)d_out * d_in;
-  const int grid = (int)((n / 4 + 255) / 256 < 65536 ? (n / 4 + 255) / 256 : 65536);
-  hipLaunchKernelGGL(copy_in_kernel, dim3(grid), dim3(256), 0, stream, W, n, d_in, dead, Wp);
+  const int grid = (int)((n / 4 + 255) / 256 < 65536 ? (n / 4 + 255) / 256 : 65536) + 2 * (d_in / p->group);
+  float* rec = reinterpret_cast<float*>(base + L.rec_off);
+  auto copy_in = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, stream, W, n, d_in, dead, Wp, U, rec); };
+  switch (p->group) {
+    case 32: copy_in(copy_in_kernel<32>); break;
+    case 64: copy_in(copy_in_kernel<64>); break;
+    case 128: copy_in(copy_in_kernel<128>); break;
+    default: copy_in(copy_in_kernel<256>); break;
+  }
   BPDQ_LAUNCH_CHECK();
 
   // Blocks of B columns, groups of g inside.  W' only ever receives whole-block updates, one
