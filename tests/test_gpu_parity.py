@@ -907,6 +907,28 @@ def test_prepare_many_panels_defining_property(dev):
     assert float(R.abs().max()) < 1e-5
 
 
+@pytest.mark.parametrize("d", [64, 128, 192, 576, 642, 1217, 1216, 1600, 1604])
+def test_prepare_tile64_paths(dev, d):
+    """U of the same fp32 H against a 64-bit factor, at widths around the 64-column blocks and the 512-column
+    outer blocks: one block, odd and even block counts, odd and ragged widths (which leave the LDS-DMA tiles
+    for the register-staged ones in the trailing update, the inversion, or both).  Only the rounding of U to
+    fp32 separates the two sides: 2^-24 relative per entry."""
+    print(f"prepare d_in={d} (64-tile paths)", flush=True)
+    g = torch.Generator(device=dev)
+    g.manual_seed(91 + d)
+    X = torch.randn((2 * d + 64, d), device=dev, generator=g, dtype=torch.float64)
+    X *= torch.logspace(-1.0, 1.0, d, device=dev, dtype=torch.float64)[None, :]
+    H = (X.t().contiguous() @ X).float()
+    U, dead, info = bq.bpdq_prepare(H, 0.01)
+    assert int(info.item()) == 0
+    Hn = H.double().cpu().numpy()
+    Hn = np.triu(Hn) + np.triu(Hn, 1).T
+    Uref, _, _ = orc.prepare(Hn, float(np.float32(0.01)))
+    Un = U.cpu().numpy().astype(np.float64)
+    assert np.count_nonzero(np.tril(Un, -1)) == 0
+    assert np.linalg.norm(Un - Uref) / np.linalg.norm(Uref) < 1e-7
+
+
 @pytest.mark.parametrize("d", [4672, 8256, 1088, 4700])
 def test_prepare_wide_tile_paths_defining_property(dev, d):
     """Widths around the switches to the 128 x 128 tile kernels: the factorisation takes them from
