@@ -82,7 +82,10 @@ static HessPlan plan_hessian(int n_tok, int d_in, int kind) {
     constexpr double kDiagFrac[kNumKinds] = {0.64, 0.64, 0.60};
     const double us_per_tok = kUsPerTok[kind], us_fixed = 8.0, us_per_partial = 0.131;
     const double diag_frac = kDiagFrac[kind];
-    const int s_max = n_tok / 256 < kMaxSlices ? (n_tok / 256 < 1 ? 1 : n_tok / 256) : kMaxSlices;
+    // shortest slice: 64 tokens where the pre-pass has made a stage cheap (a call of 512 tokens on 256
+    // channels is one tile: 2 slices took 13 us, 6 take 10), 256 otherwise
+    const int min_slice = kind == kKindF16x2 ? 64 : 256;
+    const int s_max = n_tok / min_slice < kMaxSlices ? (n_tok / min_slice < 1 ? 1 : n_tok / min_slice) : kMaxSlices;
     // every accumulation chain stays short (see kChainTokens)
     int s_min = bpdq_ceil_div(n_tok, kChainTokens[kind]);
     if (s_min > s_max) s_min = s_max;
@@ -298,18 +301,8 @@ __global__ __launch_bounds__(256) void hess_colmax_kernel(const float* __restric
   }
 }
 
-__global__ __launch_bounds__(256) void hess_scale_kernel(const float* __restrict__ pmax, int n_split,
-                                                         int d_pad, float* __restrict__ mul,
-                                                         float* __restrict__ inv) {
-  // 64 channels per work-group, the partial maxima of a channel dealt to four threads
-  __shared__ float red[4][64];
-  const int c = blockIdx.x * 64 + (threadIdx.x & 63), q = threadIdx.x >> 6;
-  float m = 0.f;
-  for (int s = q; s < n_split; s += 4) m = fmaxf(m, pmax[(long)s * d_pad + c]);
-  red[q][threadIdx.x & 63] = m;
-  __syncthreads();
-  if (q) return;
-  m = fmaxf(fmaxf(red[0][threadIdx.x], red[1][threadIdx.x]), fmaxf(red[2][threadIdx.x], red[3][threadIdx.x]));
+// exponent of the power of two that brings a channel's largest magnitude into [2^13, 2^14)
+__device__ __forceinline__ int channel_exponent(float m) {
   int e = 0;
   if (m > 0.f && m < 3.0e38f) {
     int ex;
@@ -317,12 +310,48 @@ __global__ __launch_bounds__(256) void hess_scale_kernel(const float* __restrict
     e = 14 - ex;                    // m * 2^e in [2^13, 2^14)
     e = e > 100 ? 100 : (e < -100 ? -100 : e);
   }
+  return e;
+}
+
+__global__ __launch_bounds__(256) void hess_scale_kernel(const float* __restrict__ pmax, int n_split,
+                                                         int d_pad, float* __restrict__ mul,
+                                                         float* __restrict__ inv) {
+  // 16 channels per work-group, the partial maxima of a channel dealt to 16 threads
+  __shared__ float red[16][16];
+  const int c = blockIdx.x * 16 + (threadIdx.x & 15), q = threadIdx.x >> 4;
+  float m = 0.f;
+  for (int s = q; s < n_split; s += 16) m = fmaxf(m, pmax[(long)s * d_pad + c]);
+  red[q][threadIdx.x & 15] = m;
+  __syncthreads();
+  if (q) return;
+#pragma unroll
+  for (int w = 1; w < 16; ++w) m = fmaxf(m, red[w][threadIdx.x]);
+  const int e = channel_exponent(m);
   mul[c] = ldexpf(1.0f, e);
   inv[c] = ldexpf(1.0f, -e);
 }
 
 __device__ __forceinline__ unsigned pack_halves(_Float16 a, _Float16 b) {
   return (unsigned)__builtin_bit_cast(unsigned short, a) | ((unsigned)__builtin_bit_cast(unsigned short, b) << 16);
+}
+
+// operand vectors of eight values scaled by s: the high and the low halves, zeros from `count` values on
+__device__ __forceinline__ void split_halves(const float (&x)[8], float s, int count, uint4& hv, uint4& lv) {
+  unsigned hw[4], lw[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    _Float16 h[2], l[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const float xs = (2 * q + e < count) ? x[2 * q + e] * s : 0.f;
+      h[e] = (_Float16)xs;                       // round to nearest even
+      l[e] = (_Float16)(xs - (float)h[e]);       // exact difference, then rounded
+    }
+    hw[q] = pack_halves(h[0], h[1]);
+    lw[q] = pack_halves(l[0], l[1]);
+  }
+  hv = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+  lv = make_uint4(lw[0], lw[1], lw[2], lw[3]);
 }
 
 __global__ __launch_bounds__(256) void hess_split_f16_kernel(const float* __restrict__ X, int n_tok, int d,
@@ -348,24 +377,69 @@ __global__ __launch_bounds__(256) void hess_split_f16_kernel(const float* __rest
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       if (kg + half >= n_kg) break;
-      unsigned hw[4], lw[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        _Float16 h[2], l[2];
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const int i = 8 * half + 2 * q + e;
-          const bool in = live && (8 * kg + i) < n_tok;
-          const float xs = in ? x[i] * s : 0.f;
-          h[e] = (_Float16)xs;                       // round to nearest even
-          l[e] = (_Float16)(xs - (float)h[e]);       // exact difference, then rounded
-        }
-        hw[q] = pack_halves(h[0], h[1]);
-        lw[q] = pack_halves(l[0], l[1]);
-      }
-      planes[(kg + half) * d_pad + ch] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
-      planes[(n_kg + kg + half) * d_pad + ch] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
+      uint4 hv, lv;
+      split_halves(reinterpret_cast<const float(&)[8]>(x[8 * half]), s, live ? n_tok - 8 * (int)(kg + half) : 0, hv, lv);
+      planes[(kg + half) * d_pad + ch] = hv;
+      planes[(n_kg + kg + half) * d_pad + ch] = lv;
     }
+  }
+}
+
+// The whole pre-pass in one launch for calls of at most 4096 tokens: a work-group holds all tokens of 16
+// channels in registers (NI times 8 floats per thread), so X is read once and the maximum, the scale and the
+// split need no second pass and no launches of their own.  Bound by HBM: X read once, the planes written
+// once.  Thread (lane % 16) = channel, the 64 others = k-groups of 8 consecutive tokens, so a thread's
+// eight values are one operand vector.  A row segment is 64 bytes, half a cache line: neighbouring
+// channel blocks run on the same XCD (work-group w runs on XCD w % 8), whose L2 then serves both halves
+// from one fetch.  4096 x 3584: 42 -> 21 us, the call 201 -> 178 us;
+// 512 x 256: 21 -> 4 us, the call 35 -> 22 us.
+constexpr int kFusedChannels = 16;
+constexpr int kFusedThreads = 1024;
+constexpr int kFusedTokens = 4096;
+
+template <int NI>
+__global__ __launch_bounds__(kFusedThreads) void hess_prepass_f16_kernel(const float* __restrict__ X, int n_tok, int d,
+                                                                         long ldx, uint4* __restrict__ planes,
+                                                                         long n_kg, int d_pad,
+                                                                         float* __restrict__ inv) {
+  __shared__ float red[kFusedThreads / 64][kFusedChannels];
+  const int n_blk = d_pad / kFusedChannels;               // a multiple of 16
+  const int blk = (blockIdx.x % kNumXCD) * (n_blk / kNumXCD) + blockIdx.x / kNumXCD;
+  const int c = threadIdx.x & 15, tg = threadIdx.x >> 4;  // 64 token groups
+  const int ch = blk * kFusedChannels + c;
+  const bool live = ch < d;
+  const float* p = X + (live ? ch : d - 1);
+  float x[NI][8];
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int t = 8 * (tg + 64 * i) + e;
+      x[i][e] = p[(long)(t < n_tok ? t : n_tok - 1) * ldx];
+    }
+  __builtin_amdgcn_sched_barrier(0);                      // all loads before the first use
+  float m = 0.f;
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(x[i][e]));      // (tokens past the end repeat the last one)
+  m = fmaxf(m, __shfl_xor(m, 16, 64));
+  m = fmaxf(m, __shfl_xor(m, 32, 64));
+  if ((threadIdx.x & 63) < 16) red[threadIdx.x >> 6][c] = m;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kFusedThreads / 64; ++w) m = fmaxf(m, red[w][c]);
+  const int e2 = live ? channel_exponent(m) : 0;
+  const float s = ldexpf(1.0f, e2);
+  if (threadIdx.x < 16) inv[ch] = ldexpf(1.0f, -e2);
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const long kg = tg + 64 * i;
+    if (kg >= n_kg) break;
+    uint4 hv, lv;
+    split_halves(x[i], s, live ? n_tok - 8 * (int)kg : 0, hv, lv);
+    planes[kg * d_pad + ch] = hv;
+    planes[(n_kg + kg) * d_pad + ch] = lv;
   }
 }
 
@@ -449,13 +523,21 @@ __global__ __launch_bounds__(SplitF16::kThreads, 1) void hess_syrk_f16x2_kernel(
   }
 }
 
-// H[tile] += scale * sum_s partial[s][tile], slices added in index order.  64 work-groups per
-// tile; tiles 0 .. n_off-1 are off-diagonal, the rest diagonal.
+// H[tile] += scale * sum_s partial[s][tile], slices added in index order.  64 work-groups per tile;
+// tiles 0 .. n_off-1 are off-diagonal, the rest diagonal.  SYM (the last launch of a
+// call that symmetrizes): the block's transpose goes to the lower triangle from the same registers, which
+// spares small layers a launch (512 x 256: 4 of 22 us) and large ones a pass over the upper triangle.
+template <bool SYM>
 __global__ __launch_bounds__(256) void hess_reduce_kernel(const float* __restrict__ partial,
                                                           HessPlan p, int d, float scale,
                                                           float* __restrict__ H) {
+  __shared__ float sT[SYM ? 32 : 1][33];
   const int tile = blockIdx.x >> 6;
+  // SYM: one 32 x 32 block; otherwise four whole rows of the tile (1 KB runs: 172 us against 198 for 3584 channels)
   const int e = ((blockIdx.x & 63) * 256 + threadIdx.x) * 4;
+  const int row = SYM ? 32 * ((blockIdx.x & 63) >> 3) + (threadIdx.x >> 3) : e / HessGemm::kTileN;
+  const int col = SYM ? 32 * (blockIdx.x & 7) + (threadIdx.x & 7) * 4 : e % HessGemm::kTileN;
+  const int rb = row / 32, cb = col / 32;
   int bi, bj, S;
   long first, stride;
   if (tile < p.n_off) {
@@ -469,20 +551,43 @@ __global__ __launch_bounds__(256) void hess_reduce_kernel(const float* __restric
     first = (long)p.n_off * p.S_off + bi;
     stride = p.n_diag;
     // blocks of 32 x 32 below the diagonal of a diagonal tile are never computed
-    if ((e % HessGemm::kTileN) / 32 < (e / HessGemm::kTileN) / 32) return;
+    if (cb < rb) return;
   }
-  const int r = bi * HessGemm::kTileM + e / HessGemm::kTileN;
-  const int c = bj * HessGemm::kTileN + e % HessGemm::kTileN;
-  if (r >= d || c >= d) return;
-  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int sp = 0; sp < S; ++sp) {
-    const float4 v = *reinterpret_cast<const float4*>(partial + (first + sp * stride) * kTileFloats + e);
-    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+  const int r = bi * HessGemm::kTileM + row, c = bj * HessGemm::kTileN + col;
+  const bool in = r < d && c < d;                     // d % 4 == 0: the four columns are in or out together
+  float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (in) {
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    const float* src = partial + first * kTileFloats + row * HessGemm::kTileN + col;
+    for (int sp = 0; sp < S; ++sp) {
+      const float4 v = *reinterpret_cast<const float4*>(src + sp * stride * kTileFloats);
+      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    }
+    float4* h = reinterpret_cast<float4*>(H + (long)r * d + c);
+    o = *h;
+    o.x += scale * s.x; o.y += scale * s.y; o.z += scale * s.z; o.w += scale * s.w;
+    // a block on the diagonal: below it the mirror image is what counts
+    const bool mirror_here = SYM && bi == bj && rb == cb;
+    if (!mirror_here) {
+      *h = o;
+    } else {
+      const float e[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (c + q >= r) H[(long)r * d + c + q] = e[q];
+    }
   }
-  float4* h = reinterpret_cast<float4*>(H + (long)r * d + c);
-  float4 o = *h;
-  o.x += scale * s.x; o.y += scale * s.y; o.z += scale * s.z; o.w += scale * s.w;
-  *h = o;
+  if constexpr (SYM) {
+    const int y = threadIdx.x >> 3, x = (threadIdx.x & 7) * 4;
+    sT[y][x] = o.x; sT[y][x + 1] = o.y; sT[y][x + 2] = o.z; sT[y][x + 3] = o.w;
+    __syncthreads();
+    const int tr = bj * HessGemm::kTileN + 32 * cb + y, tc = bi * HessGemm::kTileM + 32 * rb + x;   // row, columns of H
+    if (tr < d) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (tc + q < tr) H[(long)tr * d + tc + q] = sT[x + q][y];
+    }
+  }
 }
 
 // lower triangle <- transpose of the upper triangle, 32 x 32 tiles through LDS
@@ -594,16 +699,28 @@ static int hessian_accumulate(int kind, const float* Xc, int n_tok, int d_in, in
       float* pmax = reinterpret_cast<float*>(base + L.pmax_off);
       float* mul = reinterpret_cast<float*>(base + L.mul_off);
       float* inv = reinterpret_cast<float*>(base + L.inv_off);
-      const int cb = L.d_pad / SplitF16::kTile;
-      hipLaunchKernelGGL(hess_colmax_kernel, dim3(cb, L.n_split), dim3(256), 0, stream, Xpart, n_part,
-                         d_in, (long)ldx, pmax, L.d_pad);
-      BPDQ_LAUNCH_CHECK();
-      hipLaunchKernelGGL(hess_scale_kernel, dim3(L.d_pad / 64), dim3(256), 0, stream, pmax, L.n_split,
-                         L.d_pad, mul, inv);
-      BPDQ_LAUNCH_CHECK();
-      hipLaunchKernelGGL(hess_split_f16_kernel, dim3(cb, (unsigned)bpdq_ceil_div((int)L.n_kg, kSplitKgPerWG)),
-                         dim3(256), 0, stream, Xpart, n_part, d_in, (long)ldx, mul, planes, L.n_kg, L.d_pad);
-      BPDQ_LAUNCH_CHECK();
+      if (n_part <= kFusedTokens) {
+        auto prepass = [&](auto kern) {
+          hipLaunchKernelGGL(kern, dim3(L.d_pad / kFusedChannels), dim3(kFusedThreads), 0, stream, Xpart, n_part, d_in,
+                             (long)ldx, planes, L.n_kg, L.d_pad, inv);
+        };
+        if (L.n_kg <= 64) prepass(hess_prepass_f16_kernel<1>);
+        else if (L.n_kg <= 128) prepass(hess_prepass_f16_kernel<2>);
+        else if (L.n_kg <= 256) prepass(hess_prepass_f16_kernel<4>);
+        else prepass(hess_prepass_f16_kernel<8>);
+        BPDQ_LAUNCH_CHECK();
+      } else {
+        const int cb = L.d_pad / SplitF16::kTile;
+        hipLaunchKernelGGL(hess_colmax_kernel, dim3(cb, L.n_split), dim3(256), 0, stream, Xpart, n_part,
+                           d_in, (long)ldx, pmax, L.d_pad);
+        BPDQ_LAUNCH_CHECK();
+        hipLaunchKernelGGL(hess_scale_kernel, dim3(L.d_pad / 16), dim3(256), 0, stream, pmax, L.n_split,
+                           L.d_pad, mul, inv);
+        BPDQ_LAUNCH_CHECK();
+        hipLaunchKernelGGL(hess_split_f16_kernel, dim3(cb, (unsigned)bpdq_ceil_div((int)L.n_kg, kSplitKgPerWG)),
+                           dim3(256), 0, stream, Xpart, n_part, d_in, (long)ldx, mul, planes, L.n_kg, L.d_pad);
+        BPDQ_LAUNCH_CHECK();
+      }
       if (mark_begin()) return BPDQ_ERR_LAUNCH;
       hipLaunchKernelGGL(hess_syrk_f16x2_kernel, dim3(p.direct ? direct_grid(p.nb) : p.items()),
                          dim3(SplitF16::kThreads),
@@ -613,12 +730,18 @@ static int hessian_accumulate(int kind, const float* Xc, int n_tok, int d_in, in
     BPDQ_LAUNCH_CHECK();
     if (done >= n_tok && ev_end) BPDQ_HIP_TRY(hipEventRecord(static_cast<hipEvent_t>(ev_end), stream));
     if (!p.direct) {
-      hipLaunchKernelGGL(hess_reduce_kernel, dim3((p.n_off + p.n_diag) * 64), dim3(256), 0, stream,
-                         partial, p, d_in, scale, H);
+      const bool sym = symmetrize && done >= n_tok;
+      if (sym)
+        hipLaunchKernelGGL(hess_reduce_kernel<true>, dim3((p.n_off + p.n_diag) * 64), dim3(256), 0, stream,
+                           partial, p, d_in, scale, H);
+      else
+        hipLaunchKernelGGL(hess_reduce_kernel<false>, dim3((p.n_off + p.n_diag) * 64), dim3(256), 0, stream,
+                           partial, p, d_in, scale, H);
       BPDQ_LAUNCH_CHECK();
+      if (sym) return 0;
     }
   }
-  if (symmetrize) {
+  if (symmetrize) {      // nothing accumulated, or the last launch added its tiles straight into H
     const int nt = bpdq_ceil_div(d_in, 32);
     hipLaunchKernelGGL(symmetrize_kernel, dim3(nt, nt), dim3(256), 0, stream, H, d_in);
     BPDQ_LAUNCH_CHECK();

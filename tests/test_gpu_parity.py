@@ -48,6 +48,28 @@ def hess(request):
     return HESSIAN_CALLS[request.param]
 
 
+@pytest.mark.parametrize("n_tok,d_in", [(1, 20), (8, 256), (511, 260), (513, 20), (1024, 516), (1025, 260),
+                                        (2049, 20), (4095, 260), (4096, 516), (4097, 260)])
+def test_hessian_small_call_paths(dev, n_tok, d_in):
+    """Token counts at the edges of the one-launch pre-pass (512, 1024, 2048, 4096 tokens) with strided rows, and
+    the mirror image written by the reduction: symmetric bit for bit, its upper half that of a plain call."""
+    print(f"hessian small call n_tok={n_tok} d_in={d_in}", flush=True)
+    g = torch.Generator().manual_seed(n_tok + d_in)
+    X = torch.randn((n_tok, d_in + 8), generator=g) * torch.exp(2.0 * torch.randn(d_in + 8, generator=g))
+    Xd = X.to(dev)[:, 4:4 + d_in]
+    H0 = torch.randn((d_in, d_in), generator=g).to(dev)
+    Hs, Hp = H0.clone(), H0.clone()
+    bq.bpdq_hessian_accumulate(Xd, Hs, 2.0, True)
+    bq.bpdq_hessian_accumulate(Xd, Hp, 2.0, False)
+    assert torch.equal(Hs, Hs.t())
+    assert torch.equal(Hs.triu(), Hp.triu())
+    x = X[:, 4:4 + d_in].numpy().astype(np.float64)
+    want = np.triu(H0.cpu().numpy().astype(np.float64) + 2.0 * x.T @ x)
+    # halves: 2^-21 of a product; fp32 sums: 2^-24 per addition along a chain, and the rounding of H itself
+    scale = np.sqrt(np.outer((x * x).sum(0), (x * x).sum(0))) * 2.0 + np.abs(H0.cpu().numpy())
+    assert np.all(np.abs(Hs.triu().cpu().numpy() - want) <= 5e-6 * scale)
+
+
 @pytest.mark.parametrize("n_tok,d_in", [(100, 96), (512, 256), (1000, 640), (5000, 776), (37, 4), (16, 260),
                                         (17, 516), (20000, 264)])
 def test_hessian_matches_oracle(dev, hess, n_tok, d_in):
