@@ -105,7 +105,9 @@ def load():
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current stream's handle without the Stream object that torch.cuda.current_stream() builds
+    # (2.8 of the 8.4 us of host time of a bpdq_gemv call)
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _ptr(t):
