@@ -99,12 +99,16 @@ __device__ __forceinline__ double fast_rsqrt(double x) {
 // thread are issued before the first is used: a rolled loop would wait for memory 16 times.
 // ok(i, j): is the element read (else 0);  idx(i, j): its offset from `base`, which must itself
 // be a valid address (masked elements read base[0] and discard it).
+// (Work-groups of 512 threads are two teams of 256 on tiles of their own: team_tid and team_wave.)
+__device__ __forceinline__ int team_tid() { return threadIdx.x & 255; }
+__device__ __forceinline__ int team_wave() { return (threadIdx.x >> 6) & 3; }
+
 template <typename OK, typename IDX>
 __device__ __forceinline__ void fetch_tile64(const double* __restrict__ base, OK ok, IDX idx,
                                              double (&v)[16]) {
 #pragma unroll
   for (int t = 0; t < 16; ++t) {
-    const int e = threadIdx.x + 256 * t;
+    const int e = team_tid() + 256 * t;
     const int i = e >> 6, j = e & 63;
     const bool in = ok(i, j);
     const double x = base[in ? idx(i, j) : 0L];
@@ -115,7 +119,7 @@ template <typename ROW>
 __device__ __forceinline__ void put_tile64(ROW* s, const double (&v)[16]) {
 #pragma unroll
   for (int t = 0; t < 16; ++t) {
-    const int e = threadIdx.x + 256 * t;
+    const int e = team_tid() + 256 * t;
     s[e >> 6][e & 63] = v[t];
   }
 }
@@ -166,7 +170,7 @@ __device__ __forceinline__ void scale_columns16(double (&a)[16], double s) {
 
 // Reversed Cholesky of one 64 x 64 block held in LDS: D = R R^T, R upper, columns taken from the
 // last to the first, in panels of 16 columns.
-//   in : sD, the full symmetric block (both triangles; identity padding where the block is ragged)
+//   in : sD, the upper triangle of the block (identity padding where the block is ragged)
 //   out: sD = R on and above the diagonal (undefined below it), sRinv[J] = (R_JJ)^-1 of the four
 //        16 x 16 diagonal blocks (zero below the diagonal)
 // The 16 x 16 diagonal block of a panel is eliminated in registers by every wavefront for itself, one
@@ -178,16 +182,25 @@ __device__ __forceinline__ void scale_columns16(double (&a)[16], double s) {
 // cycles a column, and the inverses a pass of their own: a panel pair 52 -> 40 us at d = 3584.)
 // A non-positive pivot is reported as column p0 + j + 1 (by the work-group with `report`) and
 // replaced by 1.  All 256 threads call this; it begins and ends with a barrier.
-__device__ __forceinline__ void factor64_blocked(double (*sD)[NB + 1], Inv16* sRinv, int* info, int p0, bool report) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+__device__ __forceinline__ void factor64_blocked(double (*sD)[NB + 1], Inv16* sRinv, int* info, int p0, bool report,
+                                                 bool active = true) {
+  if (!active) {                            // the other team of a 512-thread work-group keeps the barriers company
+#pragma unroll 1
+    for (int n = 0; n < 2 * (NB / 16) + 1; ++n) __syncthreads();
+    return;
+  }
+  const int lane = threadIdx.x & 63, w = team_wave();
   const int m = lane & 15, q = lane >> 4;
+  int off[16];                              // element (m, e) of a diagonal block, from its upper triangle
+#pragma unroll
+  for (int e = 0; e < 16; ++e) off[e] = (m < e) ? m * (NB + 1) + e : e * (NB + 1) + m;
 #pragma unroll 1
   for (int J = NB / 16 - 1; J >= 0; --J) {
     const int c0 = 16 * J;
     __syncthreads();                        // the block, with every earlier panel's update, is in LDS
     double a[16], wi[4], piv = 1.0, at[4];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) a[e] = sD[c0 + m][c0 + e];
+    for (int e = 0; e < 16; ++e) a[e] = (&sD[c0][c0])[off[e]];
     if (w < J) {
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) at[ks] = sD[16 * w + m][c0 + 4 * ks + q];     // A operand of row tile w
@@ -240,91 +253,83 @@ __device__ __forceinline__ void factor64_blocked(double (*sD)[NB + 1], Inv16* sR
   __syncthreads();
 }
 
-// X R^T = A for one or two 64 x 64 tiles at once, in place, by blocks of 16 columns from the
-// right (R upper, sRinv = inverses of its 16 x 16 diagonal blocks), all on the fp64 matrix cores
-// (v_mfma_f64_16x16x4_f64):
+// X R^T = A for a 64 x 64 tile, in place, by blocks of 16 columns from the right (R upper, sRinv =
+// inverses of its 16 x 16 diagonal blocks), all on the fp64 matrix cores (v_mfma_f64_16x16x4_f64):
 //   (1) X_J = A_J R_JJ^-T;
 //   (2) the blocks to its left receive  A_J' -= X_J R[J', J]^T.
-// Wavefront w takes rows 16 w .. 16 w + 15 of both tiles through all four blocks; a row block
-// never meets another one's data, so there is no barrier inside and no dependent substitution
-// chain: against a column-by-column substitution inside each block (one lane per row, 120 LDS
-// broadcasts per block) a solve takes 2 us instead of 7.
-// All 256 threads call this; it ends with a barrier.
-// One block step for TILES tiles at once (their chains of dependent matrix instructions
-// interleave): X_J = A_J R_JJ^-T, then A_J' -= X_J R[J', J]^T for every J' < J.
-template <int J, int TILES>
-__device__ __forceinline__ void trsm_block_step(double (*const (&sX)[2])[NB + 1], const double (*sR)[NB + 1],
-                                                const Inv16* sRinv) {
-  const int lane = threadIdx.x & 63, i0 = 16 * (threadIdx.x >> 6);
+// Wavefront w of the team takes rows 16 w .. 16 w + 15 through all four blocks; a row block never
+// meets another one's data, so there is no barrier inside and no dependent substitution chain (a
+// column-by-column substitution took 7 us a solve instead of 2).  The caller puts a barrier behind it.
+template <int J>
+__device__ __forceinline__ void trsm_block_step(double (*sX)[NB + 1], const double (*sR)[NB + 1], const Inv16* sRinv) {
+  const int lane = threadIdx.x & 63, i0 = 16 * team_wave();
   const int lm = lane & 15, lq = lane >> 4;
-  double a[TILES][4], b[4];
-  f64x4 acc[TILES];
+  double a[4];
+  f64x4 acc = (f64x4){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    b[ks] = sRinv[J][lm][4 * ks + lq];                                             // B[k][n] = Rinv[n][k]
+  for (int ks = 0; ks < 4; ++ks)                                                    // A[m][k] = A_J, B[k][n] = Rinv[n][k]
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sX[i0 + lm][16 * J + 4 * ks + lq], sRinv[J][lm][4 * ks + lq], acc, 0, 0, 0);
 #pragma unroll
-    for (int t = 0; t < TILES; ++t) a[t][ks] = sX[t][i0 + lm][16 * J + 4 * ks + lq];   // A[m][k] = A_J
-  }
-#pragma unroll
-  for (int t = 0; t < TILES; ++t) acc[t] = (f64x4){0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-    for (int t = 0; t < TILES; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t][ks], b[ks], acc[t], 0, 0, 0);
-#pragma unroll
-  for (int t = 0; t < TILES; ++t)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) sX[t][i0 + 4 * r + lq][16 * J + lm] = acc[t][r];   // D[4r + l/16][l%16]
+  for (int r = 0; r < 4; ++r) sX[i0 + 4 * r + lq][16 * J + lm] = acc[r];            // D[4r + l/16][l%16]
   if constexpr (J > 0) {
     // X_J back in operand layout (this wavefront's own rows: LDS serves a wavefront in order)
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-      for (int t = 0; t < TILES; ++t) a[t][ks] = sX[t][i0 + lm][16 * J + 4 * ks + lq];
-    f64x4 upd[J][TILES];
+    for (int ks = 0; ks < 4; ++ks) a[ks] = sX[i0 + lm][16 * J + 4 * ks + lq];
+    f64x4 upd[J];
 #pragma unroll
     for (int Jp = 0; Jp < J; ++Jp) {
-      double br[4];
+      upd[Jp] = (f64x4){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) br[ks] = sR[16 * Jp + lm][16 * J + 4 * ks + lq];   // B[k][n] = R[J'n][Jk]
-#pragma unroll
-      for (int t = 0; t < TILES; ++t) upd[Jp][t] = (f64x4){0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-        for (int t = 0; t < TILES; ++t)
-          upd[Jp][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t][ks], br[ks], upd[Jp][t], 0, 0, 0);
+      for (int ks = 0; ks < 4; ++ks)                                                // B[k][n] = R[J'n][Jk]
+        upd[Jp] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ks], sR[16 * Jp + lm][16 * J + 4 * ks + lq], upd[Jp], 0, 0, 0);
     }
 #pragma unroll
     for (int Jp = 0; Jp < J; ++Jp)
 #pragma unroll
-      for (int t = 0; t < TILES; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sX[t][i0 + 4 * r + lq][16 * Jp + lm] -= upd[Jp][t][r];
-    trsm_block_step<J - 1, TILES>(sX, sR, sRinv);
+      for (int r = 0; r < 4; ++r) sX[i0 + 4 * r + lq][16 * Jp + lm] -= upd[Jp][r];
+    trsm_block_step<J - 1>(sX, sR, sRinv);
   }
 }
 
-__device__ __forceinline__ void trsm64_blocked(double (*sXa)[NB + 1], double (*sXb)[NB + 1], bool two,
-                                               const double (*sR)[NB + 1], const Inv16* sRinv) {
-  double (*const tiles[2])[NB + 1] = {sXa, sXb};
-  if (two) trsm_block_step<NB / 16 - 1, 2>(tiles, sR, sRinv);
-  else trsm_block_step<NB / 16 - 1, 1>(tiles, sR, sRinv);
-  __syncthreads();
+__device__ __forceinline__ void trsm64_blocked(double (*sX)[NB + 1], const double (*sR)[NB + 1], const Inv16* sRinv) {
+  trsm_block_step<NB / 16 - 1>(sX, sR, sRinv);
 }
 
-// The symmetric 64 x 64 block at (p0, p0), both triangles (only the upper triangle of A is valid),
-// identity padding beyond nb: 16 elements per thread in the order of fetch_tile64 / put_tile64.
-__device__ __forceinline__ void fetch_diag_block(const double* __restrict__ A, int d, int p0, int nb,
-                                                 double (&v)[16]) {
+// 64 x 64 tile at (r0, c0) of A, `nr` x `nc` of it inside (identity padding where `diag`, else zeros), 16
+// elements per thread of a team in the order of put_tile: pairs of columns (16-byte loads) where `vec`, which
+// needs a full tile and an even d.  Below the diagonal of A there are zeros or nothing of meaning.
+__device__ __forceinline__ void fetch_tile(const double* __restrict__ A, int d, int r0, int c0, int nr, int nc,
+                                           bool diag, bool vec, double (&v)[16]) {
+  if (vec) {
 #pragma unroll
-  for (int t = 0; t < 16; ++t) {
-    const int e = threadIdx.x + 256 * t;
-    const int i = e >> 6, j = e & 63;
-    const bool in = i < nb && j < nb;
-    const int lo = i < j ? i : j, hi = i < j ? j : i;
-    const double x = A[in ? (long)(p0 + lo) * d + p0 + hi : 0L];
-    v[t] = in ? x : ((i == j) ? 1.0 : 0.0);
+    for (int t = 0; t < 8; ++t) {
+      const int e = team_tid() + 256 * t;
+      const double2 x = *reinterpret_cast<const double2*>(A + (long)(r0 + (e >> 5)) * d + c0 + 2 * (e & 31));
+      v[2 * t] = x.x;
+      v[2 * t + 1] = x.y;
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      const int e = team_tid() + 256 * t;
+      const int i = e >> 6, j = e & 63;
+      const bool in = i < nr && j < nc;
+      const double x = A[in ? (long)(r0 + i) * d + c0 + j : 0L];
+      v[t] = in ? x : ((diag && i == j) ? 1.0 : 0.0);
+    }
+  }
+}
+template <typename ROW>
+__device__ __forceinline__ void put_tile(ROW* s, bool vec, const double (&v)[16]) {
+  if (vec) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int e = team_tid() + 256 * t;
+      s[e >> 5][2 * (e & 31)] = v[2 * t];
+      s[e >> 5][2 * (e & 31) + 1] = v[2 * t + 1];
+    }
+  } else {
+    put_tile64(s, v);
   }
 }
 
@@ -346,8 +351,8 @@ __global__ __launch_bounds__(256) void panel_factor_kernel(double* __restrict__ 
 
   {
     double v[16];
-    fetch_diag_block(A, d, p0, nb, v);
-    put_tile64(sR, v);
+    fetch_tile(A, d, p0, p0, nb, nb, true, false, v);
+    put_tile(sR, false, v);
   }
   // panel tile (coalesced), used after the factorisation
   const int r0 = blockIdx.x * NB;
@@ -365,7 +370,8 @@ __global__ __launch_bounds__(256) void panel_factor_kernel(double* __restrict__ 
     if (tid == 0) *pair_flag = 0;
   }
   if (n_above == 0) return;
-  trsm64_blocked(sA, sA, false, sR, sRinv);
+  trsm64_blocked(sA, sR, sRinv);
+  __syncthreads();
   for (int e = tid; e < NB * NB; e += 256) {
     const int i = e / NB, j = e % NB;
     if (r0 + i < p0 && j < nb) A[(long)(r0 + i) * d + p0 + j] = sA[i][j];
@@ -473,7 +479,7 @@ __device__ __forceinline__ void quad_zero(Quad64& q) {
 template <bool B_T>
 __device__ __forceinline__ void quad_mfma_64(const double (*sa)[NB + 1], const double (*sb)[NB + 1],
                                              Quad64& q) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = team_wave();
   const int m0 = (w >> 1) * 32 + (lane & 15), n0 = (w & 1) * 32 + (lane & 15);
   const int kq = lane >> 4;
 #pragma unroll 4
@@ -495,7 +501,7 @@ __device__ __forceinline__ void quad_mfma_64(const double (*sa)[NB + 1], const d
 // f(row, col, value) over this lane's 16 results, row / col inside the 64 x 64 tile
 template <typename F>
 __device__ __forceinline__ void quad_for_each(const Quad64& q, F f) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = team_wave();
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -512,90 +518,108 @@ __device__ __forceinline__ void quad_for_each(const Quad64& q, F f) {
 //     D22 = R22 R22^T,   R12 = D12 R22^-T,   D11 - R12 R12^T = R11 R11^T
 // and for its own rows [A1 A2] of the two panels
 //     X2 = A2 R22^-T,    X1 = (A1 - X2 R12^T) R11^-T.
-// The two small products run on the fp64 matrix cores.  This halves the number of dependent
-// launches of the panel chain (each is short and latency-bound).  Work-group 0 writes R11, R22
-// to Rdiag and R12 to R12buf (never into A, whose blocks later-scheduled work-groups still
-// read) and sets the pair flag of b2, so that the inverse step puts R12 in place.
+// The solves and products run on the fp64 matrix cores.  This halves the number of dependent launches of
+// the panel chain (each is short and latency-bound).  A work-group is two teams of four wavefronts: the
+// first walks the chain of the diagonal block, the second solves and updates the work-group's rows beside it
+// and stores what is finished, so that of the rows only the last solve comes after the chain (one team that
+// did both in turn took 40.5 us a launch at d = 3584, two take 34.4).  Work-group 0 writes R11, R22 to
+// Rdiag and R12 to R12buf (never into A, whose blocks later-scheduled work-groups still read) and sets the
+// pair flag of b2, so that the inverse step puts R12 in place.
 constexpr size_t kPairLdsBytes = (size_t)(4 * NB * (NB + 1) + NB * 16) * sizeof(double);
+constexpr int kPairThreads = 512;
 
-__global__ __launch_bounds__(256) void panel_pair_kernel(double* __restrict__ A, int d, int p1,
-                                                         int nb2, int n_above,
-                                                         double* __restrict__ Rdiag1,
-                                                         double* __restrict__ Rdiag2,
-                                                         double* __restrict__ R12buf,
-                                                         int* __restrict__ pair_flag1,
-                                                         int* __restrict__ pair_flag2, int* info) {
+__global__ __launch_bounds__(kPairThreads) void panel_pair_kernel(double* __restrict__ A, int d, int p1,
+                                                                  int nb2, int n_above,
+                                                                  double* __restrict__ Rdiag1,
+                                                                  double* __restrict__ Rdiag2,
+                                                                  double* __restrict__ R12buf,
+                                                                  int* __restrict__ pair_flag1,
+                                                                  int* __restrict__ pair_flag2, int* info) {
   extern __shared__ double dyn[];
   typedef double Row[NB + 1];
-  Row* sR = reinterpret_cast<Row*>(dyn);            // R22, then R12 R12^T, then R11
+  Row* sR = reinterpret_cast<Row*>(dyn);            // R22, then R11
   Row* sR12 = sR + NB;                              // D12 -> R12
   Row* sA1 = sR12 + NB;                             // own rows, columns of b1
   Row* sA2 = sA1 + NB;                              // own rows, columns of b2
   Inv16* sRinv = reinterpret_cast<Inv16*>(dyn + 4 * NB * (NB + 1));
-  const int tid = threadIdx.x;
+  const int tid = team_tid();
+  const bool chain = threadIdx.x < 256;             // team of the diagonal block; the other has the rows
   const int p2 = p1 + NB;
   const int r0 = blockIdx.x * NB;
-  const bool first = blockIdx.x == 0;
+  const bool first = blockIdx.x == 0, rows = n_above > 0;
+  const bool vec = nb2 == NB && d % 2 == 0;
 
-  double d11[16];                                   // D11, needed after the first factorisation
-  fetch_diag_block(A, d, p1, NB, d11);
-  {
-    double v22[16], v12[16], v1[16], v2[16];
-    fetch_diag_block(A, d, p2, nb2, v22);           // D22
-    put_tile64(sR, v22);
-    fetch_tile64(A, [&](int, int j) { return j < nb2; },
-                 [&](int i, int j) { return (long)(p1 + i) * d + p2 + j; }, v12);
-    if (n_above > 0) {
-      fetch_tile64(A, [&](int i, int) { return r0 + i < p1; },
-                   [&](int i, int j) { return (long)(r0 + i) * d + p1 + j; }, v1);
-      fetch_tile64(A, [&](int i, int j) { return r0 + i < p1 && j < nb2; },
-                   [&](int i, int j) { return (long)(r0 + i) * d + p2 + j; }, v2);
-      put_tile64(sA1, v1);
-      put_tile64(sA2, v2);
-    }
-    put_tile64(sR12, v12);
+  Quad64 d11;                                       // D11 in the product's layout, needed after the first factorisation
+  quad_zero(d11);
+  if (chain) {
+    double v22[16], v12[16];
+    fetch_tile(A, d, p2, p2, nb2, nb2, true, vec, v22);
+    fetch_tile(A, d, p1, p2, NB, nb2, false, vec, v12);
+    const int lane = threadIdx.x & 63, w = team_wave();
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          d11.c[i][j][r] = A[(long)(p1 + (w >> 1) * 32 + 16 * i + 4 * r + (lane >> 4)) * d + p1 + (w & 1) * 32 + 16 * j +
+                             (lane & 15)];
+    put_tile(sR, vec, v22);
+    put_tile(sR12, vec, v12);
+  } else if (rows) {                                // (the rows above a full panel are all there)
+    double v1[16], v2[16];
+    fetch_tile(A, d, r0, p2, NB, nb2, false, vec, v2);
+    fetch_tile(A, d, r0, p1, NB, NB, false, vec, v1);
+    put_tile(sA2, vec, v2);
+    put_tile(sA1, vec, v1);
   }
-  factor64_blocked(sR, sRinv, info, p2, first);
-  if (first)
-    for (int e = tid; e < NB * NB; e += 256) Rdiag2[e] = sR[e / NB][e % NB];
+  factor64_blocked(sR, sRinv, info, p2, first, chain);
   // R12 = D12 R22^-T and X2 = A2 R22^-T
-  trsm64_blocked(sR12, sA2, n_above > 0, sR, sRinv);
-  {
-    Quad64 q;
-    quad_zero(q);
-    quad_mfma_64<true>(sR12, sR12, q);              // R12 R12^T
-    quad_for_each(q, [&](int r, int c, double v) { sR[r][c] = -v; });     // (R22 is no longer needed)
-    if (n_above > 0) {
-      quad_zero(q);
-      quad_mfma_64<true>(sA2, sR12, q);             // X2 R12^T
-      quad_for_each(q, [&](int r, int c, double v) { sA1[r][c] -= v; });
-    }
+  if (chain) {
+    trsm64_blocked(sR12, sR, sRinv);
+  } else {
+    if (first)
+      for (int e = tid; e < NB * NB; e += 256) Rdiag2[e] = sR[e / NB][e % NB];
+    if (rows) trsm64_blocked(sA2, sR, sRinv);
   }
   __syncthreads();
+  if (chain) {
+    Quad64 q;
+    quad_zero(q);
+    quad_mfma_64<true>(sR12, sR12, q);              // D11 - R12 R12^T  (R22 is no longer needed)
 #pragma unroll
-  for (int t = 0; t < 16; ++t) {                    // sR = D11 - R12 R12^T
-    const int e = tid + 256 * t;
-    sR[e >> 6][e & 63] += d11[t];
-  }
-  factor64_blocked(sR, sRinv, info, p1, first);
-  if (first) {
-    for (int e = tid; e < NB * NB; e += 256) {
-      Rdiag1[e] = sR[e / NB][e % NB];
-      R12buf[e] = sR12[e / NB][e % NB];
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) q.c[i][j] = d11.c[i][j] - q.c[i][j];
+    quad_for_each(q, [&](int r, int c, double v) { sR[r][c] = v; });
+  } else {
+    if (rows) {
+      Quad64 q;
+      quad_zero(q);
+      quad_mfma_64<true>(sA2, sR12, q);             // A1 - X2 R12^T
+      quad_for_each(q, [&](int r, int c, double v) { sA1[r][c] -= v; });
+      for (int e = tid; e < NB * NB; e += 256) {    // X2 is finished
+        const int i = e / NB, j = e % NB;
+        if (j < nb2) A[(long)(r0 + i) * d + p2 + j] = sA2[i][j];
+      }
     }
+    if (first)
+      for (int e = tid; e < NB * NB; e += 256) R12buf[e] = sR12[e / NB][e % NB];
+  }
+  factor64_blocked(sR, sRinv, info, p1, first, chain);
+  if (first && !chain) {
+    for (int e = tid; e < NB * NB; e += 256) Rdiag1[e] = sR[e / NB][e % NB];
     if (tid == 0) {
       *pair_flag1 = 0;
       *pair_flag2 = 1;
     }
   }
-  if (n_above == 0) return;
-  trsm64_blocked(sA1, sA1, false, sR, sRinv);
-  for (int e = tid; e < NB * NB; e += 256) {
+  if (!rows) return;
+  if (chain) trsm64_blocked(sA1, sR, sRinv);
+  __syncthreads();
+  for (int e = threadIdx.x; e < NB * NB; e += kPairThreads) {
     const int i = e / NB, j = e % NB;
-    if (r0 + i < p1) {
-      A[(long)(r0 + i) * d + p1 + j] = sA1[i][j];
-      if (j < nb2) A[(long)(r0 + i) * d + p2 + j] = sA2[i][j];
-    }
+    A[(long)(r0 + i) * d + p1 + j] = sA1[i][j];
   }
 }
 
@@ -1285,7 +1309,7 @@ extern "C" int bpdq_prepare(const float* H, int d_in, float damp, float* U, unsi
       if (p - 1 >= ob0) {                    // a pair of panels
         const int b1 = p - 1, p1 = b1 * NB;
         const int nb2 = (d - p * NB < NB) ? d - p * NB : NB;
-        hipLaunchKernelGGL(panel_pair_kernel, dim3(b1 > 0 ? b1 : 1), dim3(256), kPairLdsBytes, stream,
+        hipLaunchKernelGGL(panel_pair_kernel, dim3(b1 > 0 ? b1 : 1), dim3(kPairThreads), kPairLdsBytes, stream,
                            A, d, p1, nb2, b1, Rdiag + (size_t)b1 * NB * NB,
                            Rdiag + (size_t)p * NB * NB, R12buf + (size_t)p * NB * NB,
                            pair_flag + b1, pair_flag + p, info);
