@@ -702,9 +702,19 @@ __device__ __forceinline__ void tail_role(const TailArgs& ta, const float* __res
   const int r0 = tm * TailGemm::kTileM, c0 = task.c_begin + tn * TailGemm::kTileN;
   float* Wp = ta.Wp;
   const int c_end = task.c_end;
-  // in-place read-modify-write of this lane's 64 results: all loads first (masked elements read
-  // a valid address and are not stored), then the stores
+  // in-place read-modify-write of this lane's 64 results: all loads first, then the stores.  A tile that
+  // lies inside the matrix takes them unguarded (guards become a branch per element); at the edges
+  // masked elements read a valid address and are not stored.
   float old[TailGemm::kAccPerLane];
+  if (r0 + TailGemm::kTileM <= d_out && c0 + TailGemm::kTileN <= c_end) {
+    float* w = Wp + (long)r0 * ldw + c0;
+    int n = 0;
+    TailGemm::for_each(acc, [&](int row, int col, float) { old[n++] = w[(long)row * ldw + col]; });
+    __builtin_amdgcn_sched_barrier(0);
+    n = 0;
+    TailGemm::for_each(acc, [&](int row, int col, float v) { w[(long)row * ldw + col] = old[n++] - v; });
+    return;
+  }
   int n = 0;
   TailGemm::for_each(acc, [&](int row, int col, float) {
     const int r = r0 + row, c = c0 + col;
@@ -1029,7 +1039,16 @@ __global__ __launch_bounds__(256) void commit_group_kernel(
   // xor butterfly over the 64 lanes
   for (int q = tid >> 6; q <= T; q += 4) {
     double s = 0.0;
-    for (int w = wg_lo + (tid & 63); w < wg_hi; w += 64) s += cand_score[(long)q * n_wg + w];
+    // eight scores of a lane in flight, added in the order of the row blocks (one at a time a layer of 18944
+    // rows waited 19 times per iterate; a score past the end adds zero)
+    for (int w = wg_lo + (tid & 63); w < wg_hi; w += 512) {
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = cand_score[(long)q * n_wg + (w + 64 * u < wg_hi ? w + 64 * u : w)];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += (w + 64 * u < wg_hi) ? v[u] : 0.0;
+    }
 #pragma unroll
     for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m, 64);
     if ((tid & 63) == 0) tot[q] = s;
