@@ -63,12 +63,16 @@ constexpr int kMaxSlices = 64;
 // kind 2: pre-split fp16 kernel (about twice the rate of kind 1)
 enum : int { kKindF32 = 0, kKindBf16x3 = 1, kKindF16x2 = 2, kNumKinds = 3 };
 
-static HessPlan plan_hessian(int n_tok, int d_in, int kind) {
+// fine: slices down to 64 tokens (fp16 path), which takes more partial tiles than the 256-token slices that a
+// workspace may have been sized for; see hessian_accumulate.
+static HessPlan plan_hessian(int n_tok, int d_in, int kind, bool fine) {
   // the last plan of each kind, per host thread (the search below costs a fraction of a millisecond,
   // which a stream of short calls would otherwise pay every time)
-  thread_local HessPlan cache[kNumKinds];
-  thread_local int cache_n[kNumKinds] = {-1, -1, -1}, cache_d[kNumKinds] = {-1, -1, -1};
-  if (n_tok == cache_n[kind] && d_in == cache_d[kind]) return cache[kind];
+  constexpr int kSlots = 2 * kNumKinds;
+  thread_local HessPlan cache[kSlots];
+  thread_local int cache_n[kSlots] = {-1, -1, -1, -1, -1, -1}, cache_d[kSlots] = {-1, -1, -1, -1, -1, -1};
+  const int slot = kind + (fine ? kNumKinds : 0);
+  if (n_tok == cache_n[slot] && d_in == cache_d[slot]) return cache[slot];
   HessPlan p;
   p.nb = bpdq_ceil_div(d_in, HessGemm::kTileM);
   p.n_diag = p.nb;
@@ -84,7 +88,7 @@ static HessPlan plan_hessian(int n_tok, int d_in, int kind) {
     const double diag_frac = kDiagFrac[kind];
     // shortest slice: 64 tokens where the pre-pass has made a stage cheap (a call of 512 tokens on 256
     // channels is one tile: 2 slices took 13 us, 6 take 10), 256 otherwise
-    const int min_slice = kind == kKindF16x2 ? 64 : 256;
+    const int min_slice = fine && kind == kKindF16x2 ? 64 : 256;
     const int s_max = n_tok / min_slice < kMaxSlices ? (n_tok / min_slice < 1 ? 1 : n_tok / min_slice) : kMaxSlices;
     // every accumulation chain stays short (see kChainTokens)
     int s_min = bpdq_ceil_div(n_tok, kChainTokens[kind]);
@@ -108,7 +112,7 @@ static HessPlan plan_hessian(int n_tok, int d_in, int kind) {
     }
     p.direct = (p.S_off == 1 && p.S_diag == 1);
   }
-  cache[kind] = p; cache_n[kind] = n_tok; cache_d[kind] = d_in;
+  cache[slot] = p; cache_n[slot] = n_tok; cache_d[slot] = d_in;
   return p;
 }
 
@@ -614,11 +618,11 @@ using namespace bpdq;
 // Tokens of the next launch: the chain length is bounded (kChainTokens).  A launch that adds
 // straight into H (no slices) takes one chain's worth of tokens, a sliced one as many as its
 // slices can cover; successive launches on one stream accumulate in order.
-static int hessian_launch_tokens(int kind, int n_left, int d_in) {
+static int hessian_launch_tokens(int kind, bool fine, int n_left, int d_in) {
   const int chain = kChainTokens[kind];
   const long cover = (long)chain * kMaxSlices;
   int n = n_left > cover ? (int)cover : n_left;
-  if (n > chain && plan_hessian(n, d_in, kind).direct) n = chain;
+  if (n > chain && plan_hessian(n, d_in, kind, fine).direct) n = chain;
   return n;
 }
 
@@ -630,11 +634,11 @@ struct HessWs {
   int d_pad, n_split;
 };
 
-static HessWs hessian_ws_layout(int kind, int n_part, int d_in) {
+static HessWs hessian_ws_layout(int kind, bool fine, int n_part, int d_in) {
   HessWs L{};
   size_t off = 0;
   L.partial_off = off;
-  off += bpdq_align_up(plan_hessian(n_part, d_in, kind).ws_bytes(), 256);
+  off += bpdq_align_up(plan_hessian(n_part, d_in, kind, fine).ws_bytes(), 256);
   if (kind == kKindF16x2) {
     L.d_pad = (int)bpdq_align_up((size_t)d_in, SplitF16::kTile);
     L.n_kg = (long)bpdq_align_up((size_t)n_part, 2 * SplitF16::kStageK) / 8;
@@ -649,8 +653,8 @@ static HessWs hessian_ws_layout(int kind, int n_part, int d_in) {
 }
 
 // the first launch of a call is its largest
-static size_t hessian_ws_bytes(int kind, int n_tok, int d_in) {
-  return hessian_ws_layout(kind, hessian_launch_tokens(kind, n_tok, d_in), d_in).total;
+static size_t hessian_ws_bytes(int kind, bool fine, int n_tok, int d_in) {
+  return hessian_ws_layout(kind, fine, hessian_launch_tokens(kind, fine, n_tok, d_in), d_in).total;
 }
 
 static int hessian_accumulate(int kind, const float* Xc, int n_tok, int d_in, int ldx, float scale,
@@ -663,14 +667,21 @@ static int hessian_accumulate(int kind, const float* Xc, int n_tok, int d_in, in
   if (ldx < d_in || ldx % 4) return -4;
   if (n_tok > 0 && (!Xc || (reinterpret_cast<uintptr_t>(Xc) & 15))) return -1;
   if (!H || (reinterpret_cast<uintptr_t>(H) & 15)) return -6;
-  const size_t need = n_tok > 0 ? hessian_ws_bytes(kind, n_tok, d_in) : 0;
+  // A workspace that holds the coarse plan but not the fine one (sized for another call, say the larger
+  // chunks before a short last one) gets the coarse plan.
+  bool fine = kind == kKindF16x2;
+  size_t need = n_tok > 0 ? hessian_ws_bytes(kind, fine, n_tok, d_in) : 0;
+  if (fine && ws_bytes < need) {
+    fine = false;
+    need = hessian_ws_bytes(kind, fine, n_tok, d_in);
+  }
   if (need > 0 && (!ws || (reinterpret_cast<uintptr_t>(ws) & 255))) return -8;
   if (ws_bytes < need) return -9;
   char* base = static_cast<char*>(ws);
   for (int done = 0; done < n_tok;) {
-    const int n_part = hessian_launch_tokens(kind, n_tok - done, d_in);
-    const HessPlan p = plan_hessian(n_part, d_in, kind);
-    const HessWs L = hessian_ws_layout(kind, n_part, d_in);
+    const int n_part = hessian_launch_tokens(kind, fine, n_tok - done, d_in);
+    const HessPlan p = plan_hessian(n_part, d_in, kind, fine);
+    const HessWs L = hessian_ws_layout(kind, fine, n_part, d_in);
     float* partial = reinterpret_cast<float*>(base + L.partial_off);
     const float* Xpart = Xc + (long)done * ldx;
     const bool first = (done == 0);
@@ -754,7 +765,7 @@ extern "C" size_t bpdq_hessian_workspace_bytes(int n_tok, int d_in) {
   // one workspace serves any of the kernels
   size_t need = 0;
   for (int kind = 0; kind < kNumKinds; ++kind) {
-    const size_t b = hessian_ws_bytes(kind, n_tok, d_in);
+    const size_t b = hessian_ws_bytes(kind, true, n_tok, d_in);
     need = b > need ? b : need;
   }
   return need;

@@ -335,8 +335,8 @@ __device__ __forceinline__ void put_tile(ROW* s, bool vec, const double (&v)[16]
 
 // Panel step of the reversed Cholesky for ONE 64-column panel, one work-group (256 threads) per
 // 64 rows of the panel.
-//   (1) every work-group factors the 64 x 64 diagonal block for itself (factor64);
-//   (2) rows [64 b, 64 b + 64) of the panel above the block: X R^T = A12, one thread per row.
+//   (1) every work-group factors the 64 x 64 diagonal block for itself (factor64_blocked);
+//   (2) rows [64 b, 64 b + 64) of the panel above the block: X R^T = A12 (trsm64_blocked).
 // Work-group 0 also writes R of the diagonal block to Rdiag (NB x NB, row-major, zero below the
 // diagonal, identity-padded), clears the block's pair flag and reports a non-positive pivot.
 // Launch with max(p, 1) work-groups, p = number of 64-row blocks above the diagonal block.

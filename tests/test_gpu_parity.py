@@ -70,6 +70,26 @@ def test_hessian_small_call_paths(dev, n_tok, d_in):
     assert np.all(np.abs(Hs.triu().cpu().numpy() - want) <= 5e-6 * scale)
 
 
+@pytest.mark.parametrize("n_tok,d_in,n_sized", [(256, 512, 300), (400, 1024, 512), (256, 768, 300)])
+def test_hessian_workspace_of_another_call(dev, n_tok, d_in, n_sized):
+    """A short call on a workspace sized for a longer one, where its own finest plan would want more than that:
+    it runs on coarser slices, to the same tolerance; a workspace too small for those is refused."""
+    print(f"hessian n_tok={n_tok} d_in={d_in} on the workspace of {n_sized} tokens", flush=True)
+    have, own = bq.bpdq_hessian_workspace_bytes(n_sized, d_in), bq.bpdq_hessian_workspace_bytes(n_tok, d_in)
+    assert have < own
+    g = torch.Generator().manual_seed(n_tok + d_in)
+    X = torch.randn((n_tok, d_in), generator=g)
+    want = 2.0 * X.double().t() @ X.double()
+    for nbytes in (own, have):
+        H = torch.zeros((d_in, d_in), device=dev)
+        bq.bpdq_hessian_accumulate(X.to(dev), H, 2.0, True, torch.empty(nbytes, dtype=torch.uint8, device=dev))
+        assert _relfro(H.cpu().numpy(), want.numpy()) < 2e-6
+    planes_only = 4 * ((n_tok + 31) // 32 * 32) * ((d_in + 255) // 256 * 256)
+    with pytest.raises(bq.BpdqError):
+        bq.bpdq_hessian_accumulate(X.to(dev), torch.zeros((d_in, d_in), device=dev), 2.0, False,
+                                   torch.empty(planes_only - 256, dtype=torch.uint8, device=dev))
+
+
 @pytest.mark.parametrize("n_tok,d_in", [(100, 96), (512, 256), (1000, 640), (5000, 776), (37, 4), (16, 260),
                                         (17, 516), (20000, 264)])
 def test_hessian_matches_oracle(dev, hess, n_tok, d_in):
