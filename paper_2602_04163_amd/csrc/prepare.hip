@@ -150,7 +150,8 @@ __device__ __forceinline__ void eliminate16(double (&a)[16], double (&w)[4], dou
   for (int ks = J / 4; ks < 4; ++ks) wr[ks] = row_bcast<J>(w[ks]);      // columns left of J are still zero in row J
   const bool bad = !(piv_raw > 0.0);
   const double piv = bad ? 1.0 : piv_raw;
-  if (bad) { bad_any = true; bad_col = J; }
+  if (bad && !bad_any) bad_col = J;         // the first one met: what follows it stands on the replaced pivot
+  bad_any = bad_any || bad;
   if (i == J) piv_own = piv;
   const double t = a[J] * fast_rcp(piv);
 #pragma unroll

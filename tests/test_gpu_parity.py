@@ -90,6 +90,23 @@ def test_hessian_workspace_of_another_call(dev, n_tok, d_in, n_sized):
                                    torch.empty(planes_only - 256, dtype=torch.uint8, device=dev))
 
 
+def test_hessian_with_a_workspace_asks_for_no_size(dev, monkeypatch):
+    """The size query plans all three kernels; a call that brings its workspace does not make it."""
+    print("hessian with a workspace", flush=True)
+    X = torch.randn((300, 64), generator=torch.Generator().manual_seed(3)).to(dev)
+    ws = torch.empty(bq.bpdq_hessian_workspace_bytes(300, 64), dtype=torch.uint8, device=dev)
+    want = bq.bpdq_hessian_accumulate(X, torch.zeros((64, 64), device=dev))
+
+    class NoQuery:
+        def __getattr__(self, name):
+            assert name != "bpdq_hessian_workspace_bytes"
+            return getattr(lib, name)
+
+    lib = bq.load()
+    monkeypatch.setattr(bq, "_lib", NoQuery())
+    assert torch.equal(bq.bpdq_hessian_accumulate(X, torch.zeros((64, 64), device=dev), ws=ws), want)
+
+
 @pytest.mark.parametrize("n_tok,d_in", [(100, 96), (512, 256), (1000, 640), (5000, 776), (37, 4), (16, 260),
                                         (17, 516), (20000, 264)])
 def test_hessian_matches_oracle(dev, hess, n_tok, d_in):
@@ -921,6 +938,21 @@ def test_dequant_tile_edges(dev, half, d_out, d_in, group, shift):
     got = buf.cpu().numpy()
     assert np.array_equal(got[shift:shift + d_out * d_in].reshape(d_out, d_in), want)
     assert np.isnan(got[:shift]).all() and np.isnan(got[shift + d_out * d_in:]).all()
+
+
+@pytest.mark.parametrize("d,bad", [
+    (64, (20, 25)), (64, (0, 15)), (192, (1, 2)),                   # one block; an odd single panel at the left edge
+    (128, (3, 9)), (128, (3, 70)), (256, (17, 30)), (256, (200, 201, 207)),   # first and second block of a pair
+    (130, (70, 75)), (100, (97, 98)), (640, (40, 600)), (65, (64,)),          # ragged last block; two outer blocks
+])
+def test_prepare_info_names_the_first_bad_pivot(dev, d, bad):
+    """The factorisation runs from the last column to the first, so the first pivot that is not positive is the last
+    of the negative entries of a diagonal H, wherever it lies among the panels."""
+    print(f"prepare info d={d} bad={bad}", flush=True)
+    h = torch.full((d,), 101.0)
+    h[list(bad)] = -50.0
+    _, _, info = bq.bpdq_prepare(torch.diag(h).to(dev), 0.0)
+    assert int(info.item()) == max(bad) + 1
 
 
 def test_prepare_many_panels_defining_property(dev):
