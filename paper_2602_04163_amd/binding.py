@@ -146,9 +146,8 @@ def bpdq_hessian_accumulate(Xc, H, scale=2.0, symmetrize=False, ws=None, _entry=
     n_tok, d_in = Xc.shape
     if H.shape != (d_in, d_in):
         raise BpdqError("H: expected d_in x d_in")
-    need = lib.bpdq_hessian_workspace_bytes(n_tok, d_in)
     if ws is None:
-        ws = _workspace(need, H.device)
+        ws = _workspace(lib.bpdq_hessian_workspace_bytes(n_tok, d_in), H.device)
     rc = getattr(lib, _entry)(_ptr(Xc), n_tok, d_in, Xc.stride(0) if n_tok > 1 else d_in,
                               scale, _ptr(H), int(bool(symmetrize)), _ptr(ws), ws.numel(),
                               _stream())

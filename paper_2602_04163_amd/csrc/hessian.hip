@@ -66,8 +66,7 @@ enum : int { kKindF32 = 0, kKindBf16x3 = 1, kKindF16x2 = 2, kNumKinds = 3 };
 // fine: slices down to 64 tokens (fp16 path), which takes more partial tiles than the 256-token slices that a
 // workspace may have been sized for; see hessian_accumulate.
 static HessPlan plan_hessian(int n_tok, int d_in, int kind, bool fine) {
-  // the last plan of each kind, per host thread (the search below costs a fraction of a millisecond,
-  // which a stream of short calls would otherwise pay every time)
+  // the last plan of each kind, per host thread: a stream of equal calls plans once
   constexpr int kSlots = 2 * kNumKinds;
   thread_local HessPlan cache[kSlots];
   thread_local int cache_n[kSlots] = {-1, -1, -1, -1, -1, -1}, cache_d[kSlots] = {-1, -1, -1, -1, -1, -1};
@@ -95,6 +94,16 @@ static HessPlan plan_hessian(int n_tok, int d_in, int kind, bool fine) {
     if (s_min > s_max) s_min = s_max;
     double best = 1e300;
     for (int So = s_min; So <= s_max; ++So) {
+      // More slices only add to the fixed and the partial-tile cost.  Once these and an even spread of the
+      // products over the chip (no makespan is below that; 1e-9 for the rounding of the sums) exceed the best,
+      // no later So can win: the plan of a search to s_max at a fraction of its host time (4096 x 3584, fp16 path:
+      // 309 us -> 1.5; all three kinds through the size query: 430 -> 20).  A program whose calls differ in shape pays
+      // this each time.
+      const int Sd_least = (int)(So * 0.625 + 0.5) - 1 > s_min ? (int)(So * 0.625 + 0.5) - 1 : s_min;
+      const double products = (double)n_tok * us_per_tok * (p.n_off + p.n_diag * diag_frac);
+      const double least = (products + (double)(p.n_off * So + p.n_diag * Sd_least) * us_fixed) / kNumCU +
+                           (So > 1 ? (double)(p.n_off * So + p.n_diag * Sd_least) * us_per_partial : 0.0);
+      if (least * (1.0 - 1e-9) >= best * 0.998) break;
       for (int dd = -1; dd <= 1; ++dd) {
         int Sd = (int)(So * 0.625 + 0.5) + dd;
         if (Sd < s_min) Sd = s_min;

@@ -1,0 +1,96 @@
+"""The slice plan behind the Hessian's workspace size: what the size query returns is what a search over every
+admissible slice count gives, and a call whose shape differs from the last one's does not pay for that search."""
+import ctypes
+import heapq
+import os
+import time
+
+import pytest
+
+from paper_2602_04163_amd import binding
+
+CUS, XCDS, TILE, STAGE, MAX_SLICES = 256, 8, 256, 32, 64
+CHAIN = (16384, 8192, 8192)                       # tokens of one accumulation chain: f32, bf16x3, f16x2
+US_PER_TOK, DIAG_FRAC, US_FIXED, US_PER_PARTIAL = (0.26, 0.14, 0.055), (0.64, 0.64, 0.60), 8.0, 0.131
+
+
+@pytest.fixture(scope="module")
+def lib():
+    if not os.path.exists(binding.LIB_PATH):
+        from paper_2602_04163_amd import build
+        build.build(verbose=False)
+    return binding.load()
+
+
+def _up(x, a):
+    return -(-x // a) * a
+
+
+def _makespan(n_full, c_full, n_short, c_short):
+    """The busiest XCD: the full items round-robin over its compute units, the short ones each to the first free."""
+    per = CUS // XCDS
+    q, r = divmod(-(-n_full // XCDS), per)
+    free = [(q + (i < r)) * c_full for i in range(per)]
+    heapq.heapify(free)
+    for _ in range(-(-n_short // XCDS)):
+        heapq.heapreplace(free, free[0] + c_short)
+    return max(free)
+
+
+def _plan(n, d, kind):
+    """(S_off, S_diag) by a search over every slice count."""
+    nb = -(-d // TILE)
+    n_off, n_diag = nb * (nb - 1) // 2, nb
+    if n_off + n_diag >= 4 * CUS:
+        return 1, 1
+    s_max = min(MAX_SLICES, max(1, n // (64 if kind == 2 else 256)))
+    s_min = min(s_max, -(-n // CHAIN[kind]))
+    best, out = 1e300, (1, 1)
+    for so in range(s_min, s_max + 1):
+        for dd in (-1, 0, 1):
+            sd = min(s_max, max(s_min, int(so * 0.625 + 0.5) + dd))
+            ko, kd = _up(-(-n // so), STAGE), _up(-(-n // sd), STAGE)
+            t = _makespan(n_off * so, ko * US_PER_TOK[kind] + US_FIXED, n_diag * sd,
+                          kd * US_PER_TOK[kind] * DIAG_FRAC[kind] + US_FIXED)
+            if so > 1 or sd > 1:
+                t += float(n_off * so + n_diag * sd) * US_PER_PARTIAL
+            if t < best * 0.998:
+                best, out = t, (so, sd)
+    return out
+
+
+def _bytes(n, d, kind):
+    """Partial tiles, and for the fp16 kernel the split planes, channel maxima and channel factors."""
+    part = min(n, CHAIN[kind] * MAX_SLICES)
+    if part > CHAIN[kind] and _plan(part, d, kind) == (1, 1):
+        part = CHAIN[kind]
+    so, sd = _plan(part, d, kind)
+    nb = -(-d // TILE)
+    total = 0 if (so, sd) == (1, 1) else (nb * (nb - 1) // 2 * so + nb * sd) * TILE * TILE * 4
+    if kind == 2:
+        d_pad = _up(d, TILE)
+        total += 2 * _up(part, 32) // 8 * d_pad * 16 + -(-part // 1024) * d_pad * 4 + 2 * d_pad * 4
+    return total
+
+
+@pytest.mark.parametrize("n,d", [(1, 4), (64, 64), (300, 512), (512, 256), (513, 260), (1024, 1024), (1000, 1536), (2048, 640),
+                                 (4096, 256), (4096, 1024), (4096, 2048), (4096, 3584), (4097, 512), (5000, 1284),
+                                 (12288, 1536), (16384, 3000), (70000, 256), (262144, 3584), (600000, 512), (9000, 18944)])
+def test_workspace_is_that_of_the_full_search(lib, n, d):
+    assert lib.bpdq_hessian_workspace_bytes(n, d) == max(_bytes(n, d, k) for k in range(3))
+
+
+def test_alternating_shapes_do_not_pay_for_the_search(lib):
+    """A calibration stream that alternates between chunk lengths and layer widths misses the plan of the last call
+    every time.  The three plans of a query took 355 us where every slice count was scored, 70 us with the slices at
+    least 256 tokens long; the smallest of many repetitions, so that a busy machine does not count."""
+    shapes = [(4096, 3584), (3000, 3584), (4096, 2048), (4096, 4096), (4096, 8192)]
+    best = [1e9] * len(shapes)
+    query = lib.bpdq_hessian_workspace_bytes
+    args = [(ctypes.c_int(n), ctypes.c_int(d)) for n, d in shapes]
+    for _ in range(50):
+        for i, (n, d) in enumerate(args):
+            t0 = time.perf_counter()
+            query(n, d)
+            best[i] = min(best[i], time.perf_counter() - t0)
+    assert max(best) < 60e-6
