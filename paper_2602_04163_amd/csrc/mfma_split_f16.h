@@ -231,14 +231,13 @@ struct SplitF16 {
     __syncthreads();
   }
 
-  // f(row_in_tile, col_in_tile, value) over this lane's results of an off-diagonal tile (block rows
-  // [I0, I1) of the wavefront's four)
-  template <int I0 = 0, int I1 = 4, typename F>
+  // f(row_in_tile, col_in_tile, value) over this lane's results of an off-diagonal tile
+  template <typename F>
   __device__ static __forceinline__ void for_each(const Acc& acc, F f) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
 #pragma unroll
-    for (int i = I0; i < I1; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -246,16 +245,48 @@ struct SplitF16 {
           f(wm * 128 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), wn * 128 + j * 32 + (lane & 31),
             acc.c[i][j][r]);
   }
-  // ... of a diagonal tile (upper-triangular schedule, blocks [Q0, Q1) of the wavefront's nine)
-  template <int Q0 = 0, int Q1 = kDiagBlocks, typename F>
+  // ... of a diagonal tile (upper-triangular schedule)
+  template <typename F>
   __device__ static __forceinline__ void for_each_diag(const Acc& acc, F f) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int q = Q0; q < Q1; ++q) {
+    for (int q = 0; q < kDiagBlocks; ++q) {
       const int rb = kDiagRow[wave][q], cb = kDiagCol[wave][q];
 #pragma unroll
       for (int r = 0; r < 16; ++r)
         f(32 * rb + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), 32 * cb + (lane & 31), acc.c[q / 4][q % 4][r]);
+    }
+  }
+
+  // The same in batches, f(row, col, value, n) with n counting a batch's results from 0: block rows [I0, I1) of
+  // the wavefront's four, or blocks [Q0, Q1) of its nine.  Blocks of 32 x 32 whose corner in(row, col)
+  // turns down are passed over (n counts on); `wave` is the wavefront's number as a scalar, so that this is a branch.
+  template <int I0, int I1, typename F, typename IN>
+  __device__ static __forceinline__ void for_each_in(const Acc& acc, int wave, IN in, F f) {
+    const int lane = threadIdx.x & 63;
+    const int wm = wave >> 1, wn = wave & 1;
+#pragma unroll
+    for (int i = I0; i < I1; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (!in(wm * 128 + i * 32, wn * 128 + j * 32)) continue;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          f(wm * 128 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), wn * 128 + j * 32 + (lane & 31),
+            acc.c[i][j][r], 64 * (i - I0) + 16 * j + r);
+      }
+  }
+  template <int Q0, int Q1, typename F, typename IN>
+  __device__ static __forceinline__ void for_each_diag_in(const Acc& acc, int wave, IN in, F f) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int q = Q0; q < Q1; ++q) {
+      const int rb = kDiagRow[wave][q], cb = kDiagCol[wave][q];
+      if (!in(32 * rb, 32 * cb)) continue;
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        f(32 * rb + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), 32 * cb + (lane & 31), acc.c[q / 4][q % 4][r],
+          16 * (q - Q0) + r);
     }
   }
 };
