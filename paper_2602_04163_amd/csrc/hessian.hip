@@ -11,6 +11,8 @@
 // per token) into fewer, longer slices S_diag, so that every work-group costs about the same.
 // Slice partials go to the workspace and are summed in a fixed order (no float atomics, so H is
 // bit-reproducible).
+#include <type_traits>
+
 #include "mfma_kmajor.h"
 #include "mfma_split_bf16.h"
 #include "mfma_split_f16.h"
@@ -457,13 +459,15 @@ __global__ __launch_bounds__(kFusedThreads) void hess_prepass_f16_kernel(const f
 }
 
 // The tile product of the fp16 path and its epilogue: every result is brought back to the
-// activations' own units by the two channel factors (powers of two: exact).
+// activations' own units by the two channel factors (powers of two: exact).  DIRECT (p.direct): one slice
+// per tile, added into H; else partial tiles.  (Kernels of their own, so that neither carries the other's code.)
+template <bool DIRECT>
 __global__ __launch_bounds__(SplitF16::kThreads, 1) void hess_syrk_f16x2_kernel(
     const uint4* __restrict__ planes, long n_kg, int d_pad, const float* __restrict__ inv, int n_tok,
     int d, float scale, float* __restrict__ H, float* __restrict__ partial, HessPlan p) {
   const int n_off_items = p.n_off * p.S_off;
   int item = 0, bi, bj, k_begin, k_end;
-  if (p.direct) {
+  if constexpr (DIRECT) {
     if (!direct_tile(blockIdx.x, p.nb, bi, bj)) return;
     k_begin = 0;
     k_end = n_tok;
@@ -493,7 +497,7 @@ __global__ __launch_bounds__(SplitF16::kThreads, 1) void hess_syrk_f16x2_kernel(
   sInv[threadIdx.x] = inv[r0 + threadIdx.x];
   sInv[256 + threadIdx.x] = inv[c0 + threadIdx.x];
   __syncthreads();
-  if (p.direct) {
+  if constexpr (DIRECT) {
     // H += tile, in batches of 64 results per lane: all loads of a batch first, then its stores.  One load,
     // one wait, one store at a time -- what the compiler must make of a plain `+=`, since it cannot tell
     // the addresses apart -- left the matrix pipe idle for a quarter of a launch (4096 x 18944: 4.45 -> 3.54 ms).
@@ -536,7 +540,12 @@ __global__ __launch_bounds__(SplitF16::kThreads, 1) void hess_syrk_f16x2_kernel(
 // tiles 0 .. n_off-1 are off-diagonal, the rest diagonal.  SYM (the last launch of a
 // call that symmetrizes): the block's transpose goes to the lower triangle from the same registers, which
 // spares small layers a launch (512 x 256: 4 of 22 us) and large ones a pass over the upper triangle.
-template <bool SYM>
+// FLIGHT: slices in flight per wavefront.  A layer of few tiles has many slices and too few wavefronts to cover
+// a load and a wait per slice (8192 tokens, 1 tile of 57 slices: the call 53.2 -> 47.4 us with eight in flight; 3 tiles
+// 64.3 -> 58.2, 11 slices 23.5 -> 22.8); from 10 tiles on the wavefronts cover for one another (21 tiles of 10
+// slices: 57.4 us, with eight 58.7).
+constexpr int kReduceFewTiles = 6;
+template <bool SYM, int FLIGHT>
 __global__ __launch_bounds__(256) void hess_reduce_kernel(const float* __restrict__ partial,
                                                           HessPlan p, int d, float scale,
                                                           float* __restrict__ H) {
@@ -568,7 +577,23 @@ __global__ __launch_bounds__(256) void hess_reduce_kernel(const float* __restric
   if (in) {
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
     const float* src = partial + first * kTileFloats + row * HessGemm::kTileN + col;
-    for (int sp = 0; sp < S; ++sp) {
+    // slices in index order, FLIGHT of them on their way at a time
+    int sp = 0;
+    if constexpr (FLIGHT > 1) {
+      auto add = [&](auto count) {
+        constexpr int kN = decltype(count)::value;
+        float4 v[kN];
+#pragma unroll
+        for (int u = 0; u < kN; ++u) v[u] = *reinterpret_cast<const float4*>(src + (sp + u) * stride * kTileFloats);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < kN; ++u) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
+        sp += kN;
+      };
+      while (sp + FLIGHT <= S) add(std::integral_constant<int, FLIGHT>{});
+      while (sp + 2 <= S) add(std::integral_constant<int, 2>{});
+    }
+    for (; sp < S; ++sp) {
       const float4 v = *reinterpret_cast<const float4*>(src + sp * stride * kTileFloats);
       s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
     }
@@ -710,7 +735,8 @@ static int hessian_accumulate(int kind, const float* Xc, int n_tok, int d_in, in
                          SplitSyrk::kLdsBytes, stream, Xpart, n_part, d_in, (long)ldx, scale, H,
                          partial, p);
     } else {
-      BPDQ_HIP_TRY(bpdq_lds_limit<&hess_syrk_f16x2_kernel>(SplitF16::kLdsBytes));
+      BPDQ_HIP_TRY(bpdq_lds_limit<&hess_syrk_f16x2_kernel<true>>(SplitF16::kLdsBytes));
+      BPDQ_HIP_TRY(bpdq_lds_limit<&hess_syrk_f16x2_kernel<false>>(SplitF16::kLdsBytes));
       uint4* planes = reinterpret_cast<uint4*>(base + L.planes_off);
       float* pmax = reinterpret_cast<float*>(base + L.pmax_off);
       float* mul = reinterpret_cast<float*>(base + L.mul_off);
@@ -738,21 +764,22 @@ static int hessian_accumulate(int kind, const float* Xc, int n_tok, int d_in, in
         BPDQ_LAUNCH_CHECK();
       }
       if (mark_begin()) return BPDQ_ERR_LAUNCH;
-      hipLaunchKernelGGL(hess_syrk_f16x2_kernel, dim3(p.direct ? direct_grid(p.nb) : p.items()),
-                         dim3(SplitF16::kThreads),
-                         SplitF16::kLdsBytes, stream, planes, L.n_kg, L.d_pad, inv, n_part, d_in, scale,
-                         H, partial, p);
+      auto tiles = [&](auto kern, int grid) {
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(SplitF16::kThreads), SplitF16::kLdsBytes, stream, planes, L.n_kg,
+                           L.d_pad, inv, n_part, d_in, scale, H, partial, p);
+      };
+      if (p.direct) tiles(hess_syrk_f16x2_kernel<true>, direct_grid(p.nb));
+      else tiles(hess_syrk_f16x2_kernel<false>, p.items());
     }
     BPDQ_LAUNCH_CHECK();
     if (done >= n_tok && ev_end) BPDQ_HIP_TRY(hipEventRecord(static_cast<hipEvent_t>(ev_end), stream));
     if (!p.direct) {
       const bool sym = symmetrize && done >= n_tok;
-      if (sym)
-        hipLaunchKernelGGL(hess_reduce_kernel<true>, dim3((p.n_off + p.n_diag) * 64), dim3(256), 0, stream,
-                           partial, p, d_in, scale, H);
-      else
-        hipLaunchKernelGGL(hess_reduce_kernel<false>, dim3((p.n_off + p.n_diag) * 64), dim3(256), 0, stream,
-                           partial, p, d_in, scale, H);
+      auto reduce = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((p.n_off + p.n_diag) * 64), dim3(256), 0, stream, partial, p, d_in, scale, H);
+      };
+      if (p.n_off + p.n_diag <= kReduceFewTiles) sym ? reduce(hess_reduce_kernel<true, 8>) : reduce(hess_reduce_kernel<false, 8>);
+      else sym ? reduce(hess_reduce_kernel<true, 1>) : reduce(hess_reduce_kernel<false, 1>);
       BPDQ_LAUNCH_CHECK();
       if (sym) return 0;
     }
