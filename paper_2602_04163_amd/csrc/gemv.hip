@@ -75,7 +75,11 @@ __device__ __forceinline__ void gemv_fetch(const uint32_t* __restrict__ planes, 
       wg = wg < nw ? wg : nw - 1;
       const long G = wg / wpg;
 #pragma unroll
-      for (int i = 0; i <= K; ++i) it.c[q][i][g] = coefs[((long)i * d_out + r) * n_grp + G];
+      for (int i = 0; i <= K; ++i) {
+        const _Float16 v = coefs[((long)i * d_out + r) * n_grp + G];
+        // words past the end add nothing, whatever the coefficient: zero times an infinite one is not zero
+        it.c[q][i][g] = (vec || wl + g * (WPL / NG) < n_word) ? v : (_Float16)0.f;
+      }
     }
   }
 }

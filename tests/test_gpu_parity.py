@@ -783,6 +783,22 @@ def test_gemv_tile_edges(dev, bits, group, d_out, d_in, shift):
     assert bool(torch.isnan(y[d_out:]).all())
 
 
+@pytest.mark.parametrize("bits,group,d_in", [(2, 32, 32 * 65), (2, 32, 32 * 129), (2, 64, 32 * 130), (1, 96, 96 * 25),
+                                             (4, 32, 32 * 257), (2, 32, 32 * 64), (2, 128, 32 * 132)])
+def test_gemv_infinite_coefficient(dev, bits, group, d_in):
+    """A coefficient beyond the half range is stored as an infinity and shows as one: the idle lanes and words past a
+    row's end contribute nothing, not zero times it."""
+    print(f"gemv infinite coefficient k={bits} g={group} d_in={d_in}", flush=True)
+    d_out = 5
+    planes = torch.full((bits, d_out, d_in // 32), -1, dtype=torch.int32, device=dev)
+    coef = torch.zeros((bits + 1, d_out, d_in // group), device=dev).half()
+    coef[0] = 0.5
+    coef[0, 2, -1] = float("inf")
+    coef[bits, 4, 0] = float("-inf")
+    y = bq.bpdq_gemv(planes, coef, group, torch.ones(d_in, device=dev))
+    assert y.tolist() == [d_in / 2, d_in / 2, float("inf"), d_in / 2, float("-inf")]
+
+
 def test_gemv_of_a_quantized_layer(dev):
     print("gemv of a quantized layer (fp16 storage) + timing", flush=True)
     wl, W, X = _problem("cfg2_qwen7b_attn", 512, 3584, 4096)
