@@ -758,9 +758,14 @@ def test_gemv_from_stored_format(dev, bits, group, d_out, d_in):
     (4, 64, 4100, 4160, 0), (2, 128, 4130, 8448, 0), (2, 64, 70, 16512, 1),  # four words, two rows, chunks, unaligned planes
     (3, 32, 4097, 4224, 0), (1, 256, 8200, 512, 0),                         # one row of three planes; several passes
     (2, 128, 8230, 8448, 0),                                                # passes times chunks
+    (4, 32, 33, 2112, 0), (3, 96, 50, 3072, 0), (1, 32, 20, 4032, 1),       # two words: group per word, group of three words, unaligned
+    (4, 32, 35, 8192, 0), (3, 32, 4099, 8192, 0), (2, 64, 41, 8192, 0),     # four words: four and two groups to a lane
+    (2, 32, 4100, 8224, 0), (4, 64, 33, 8320, 0), (3, 128, 8195, 12416, 0),  # strided: 257 words, 260 and 388 for the idle lanes
+    (2, 192, 18, 6144, 0), (1, 160, 4100, 20480, 2),                        # strided: groups that no lane holds whole
 ])
 def test_gemv_tile_edges(dev, bits, group, d_out, d_in, shift):
-    """Every words-per-lane, groups-per-lane and rows-per-wavefront variant at its edges against Eq. 1 in fp64."""
+    """Every words-per-lane, groups-per-lane, lane-order and rows-per-wavefront variant at its edges against Eq. 1 in
+    fp64; a second time with the coefficients two bytes off, where they no longer come as one load."""
     print(f"gemv edges k={bits} g={group} {d_out}x{d_in} shift={shift}", flush=True)
     g = torch.Generator(device=dev)
     g.manual_seed(d_in + bits)
@@ -771,6 +776,8 @@ def test_gemv_tile_edges(dev, bits, group, d_out, d_in, shift):
     x = torch.randn(d_in, generator=g, device=dev)
     y = torch.full((d_out + 3,), float("nan"), device=dev)
     bq.bpdq_gemv(planes, coef, group, x, y[:d_out])
+    off = torch.empty(coef.numel() + 1, dtype=torch.float16, device=dev)[1:].view_as(coef).copy_(coef)
+    y2 = bq.bpdq_gemv(planes, off, group, x)
     bit = torch.arange(32, device=dev, dtype=torch.int32)
     W = coef[0].double().repeat_interleave(group, 1)
     A = W.abs()
@@ -779,7 +786,8 @@ def test_gemv_tile_edges(dev, bits, group, d_out, d_in, shift):
         c = coef[i + 1].double().repeat_interleave(group, 1)
         W, A = W + b * c, A + b * c.abs()
     want, bound = W @ x.double(), 1e-5 * (A @ x.double().abs()) + 1e-12
-    assert bool(((y[:d_out].double() - want).abs() <= bound).all())
+    for got in (y[:d_out], y2):
+        assert bool(((got.double() - want).abs() <= bound).all())
     assert bool(torch.isnan(y[d_out:]).all())
 
 
