@@ -23,8 +23,8 @@
 // chunk or row pass, and the x values of the next chunk, are requested before the current one is worked on;
 // without that every chunk waited for memory twice.
 // Measured, back to back in a graph (one word per lane and load, no prefetch -> this): 8192 x 29568 k = 2
-// g = 64 48.6 -> 27.1 us (3.1 TB/s of stored bytes), 8192 x 8192 k = 2 11.3 -> 7.7, 3584 x 18944 k = 3 40.6 -> 15.2, 3584 x 3584 k = 2 7.0 -> 4.2, 5000 x 8224 k = 4
-// g = 32 17.7 -> 16.5, 152064 x 1024 k = 1 24.9 -> 24.4.
+// g = 64 48.6 -> 27.1 us (3.1 TB/s of stored bytes), 8192 x 8192 k = 2 11.3 -> 7.7, 3584 x 18944 k = 3 40.6 -> 15.2,
+// 3584 x 3584 k = 2 7.0 -> 4.2, 5000 x 8224 k = 4 g = 32 17.7 -> 16.5, 152064 x 1024 k = 1 24.9 -> 24.4.
 #include "common.h"
 
 namespace bpdq {

@@ -74,61 +74,48 @@ __device__ __forceinline__ float coef_value(float c) { return c; }
 __device__ __forceinline__ float coef_value(_Float16 c) { return (float)c; }
 
 // Eq. 1 from the packed format, ((C_0 + b_1 C_1) + b_2 C_2) + ... in fp32; CT = float or half.
-// Bound by the store of W_hat.  A thread owns four consecutive columns of kDequantRows rows: eight
-// threads share a plane word, all loads of the rows are in flight before the first value is formed,
-// and a row's four values leave as one 16-byte store.  VEC: the four columns lie in one group and
-// W_hat is 16-byte aligned; otherwise the group is looked up per column and the stores are scalar.
-// Rows are taken from a grid-stride loop, columns from blockIdx.x: no division per element (one
-// 64-bit division and a modulo per element had cost most of the kernel).
+// Bound by the store of W_hat.  A thread owns COLS consecutive columns of ROWS rows: all its loads are in flight
+// before the first value is formed, and with four columns (of one group, W_hat 16-byte aligned) a row's values
+// leave as one 16-byte store.  WIDE: a work-group is 256 threads of one row block; otherwise it is blockDim.x
+// threads wide and blockDim.y row blocks high, so that narrow matrices fill it too (131072 x 32, 2 planes: 23.8 us
+// with one row block per work-group, 15.5 with a thread per element, now 6.7).  Rows come from a grid-stride loop: no
+// division per element (one 64-bit division and a modulo per element had cost most of the kernel).
 // 8192 x 8192, 2 planes, half coefficients: 303 -> 66 us a call
 // (4.3 TB/s; one thread per element with its own division: 0.95 TB/s).
-constexpr int kDequantRows = 4;
-
-template <typename CT, int K, bool VEC>
+template <typename CT, int K, int COLS, int ROWS, bool WIDE>
 __global__ __launch_bounds__(256) void dequant_kernel(const uint32_t* __restrict__ planes,
                                                       const CT* __restrict__ coefs, int d_out,
                                                       int d_in, int group, float* __restrict__ W_hat) {
-  const int c = (blockIdx.x * 256 + threadIdx.x) * 4;
+  const int c = (blockIdx.x * (WIDE ? 256 : blockDim.x) + threadIdx.x) * COLS;
   if (c >= d_in) return;
   const int n_word = d_in / 32, n_grp = d_in / group;
-  const int sh = c & 31;
-  constexpr int NG = VEC ? 1 : 4;
-  int gi[NG];
+  const int sh = c & 31, gi = c / group;
+  const long step = (long)gridDim.y * (WIDE ? 1 : blockDim.y) * ROWS;
+  for (long r0 = (WIDE ? (long)blockIdx.y : (long)blockIdx.y * blockDim.y + threadIdx.y) * ROWS; r0 < d_out; r0 += step) {
+    uint32_t w[ROWS][K];
+    CT cf[ROWS][K + 1];
 #pragma unroll
-  for (int e = 0; e < NG; ++e) gi[e] = (c + e) / group;
-  const long step = (long)gridDim.y * kDequantRows;
-  for (long r0 = (long)blockIdx.y * kDequantRows; r0 < d_out; r0 += step) {
-    uint32_t w[kDequantRows][K];
-    CT cf[kDequantRows][NG][K + 1];
-#pragma unroll
-    for (int q = 0; q < kDequantRows; ++q) {
+    for (int q = 0; q < ROWS; ++q) {
       const long r = (r0 + q < d_out) ? r0 + q : d_out - 1;      // past the end: the last row again, not stored
 #pragma unroll
       for (int i = 0; i < K; ++i) w[q][i] = planes[((long)i * d_out + r) * n_word + (c >> 5)];
 #pragma unroll
-      for (int e = 0; e < NG; ++e)
-#pragma unroll
-        for (int i = 0; i <= K; ++i) cf[q][e][i] = coefs[((long)i * d_out + r) * n_grp + gi[e]];
+      for (int i = 0; i <= K; ++i) cf[q][i] = coefs[((long)i * d_out + r) * n_grp + gi];
     }
 #pragma unroll
-    for (int q = 0; q < kDequantRows; ++q) {
+    for (int q = 0; q < ROWS; ++q) {
       if (r0 + q >= d_out) break;
-      float v[4];
+      float v[COLS];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const CT* ce = cf[q][VEC ? 0 : e];
-        v[e] = coef_value(ce[0]);
+      for (int e = 0; e < COLS; ++e) {
+        v[e] = coef_value(cf[q][0]);
 #pragma unroll
         for (int i = 0; i < K; ++i)
-          if ((w[q][i] >> (sh + e)) & 1u) v[e] = v[e] + coef_value(ce[i + 1]);
+          if ((w[q][i] >> (sh + e)) & 1u) v[e] = v[e] + coef_value(cf[q][i + 1]);
       }
       float* out = W_hat + (r0 + q) * d_in + c;
-      if constexpr (VEC) {
-        *reinterpret_cast<float4*>(out) = make_float4(v[0], v[1], v[2], v[3]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) out[e] = v[e];
-      }
+      if constexpr (COLS == 4) *reinterpret_cast<float4*>(out) = make_float4(v[0], v[1], v[2], v[3]);
+      else *out = v[0];
     }
   }
 }
@@ -370,19 +357,33 @@ static int launch_dequant(const uint32_t* planes, const CT* coefs, int d_out, in
   if (bits < 1 || bits > 4) return -5;
   if (group <= 0 || d_in % group) return -6;
   if (!W_hat) return -7;
-  const int row_blocks = bpdq_ceil_div(d_out, kDequantRows);
-  const dim3 grid(bpdq_ceil_div(d_in, 1024), row_blocks < 65535 ? row_blocks : 65535);
   const bool vec = group % 4 == 0 && (reinterpret_cast<uintptr_t>(W_hat) & 15) == 0;
+  // Several rows per thread once one would already fill the chip (2 planes: 1024 x 1056, 270 k threads of one row, 4.8 us
+  // against 4.3 with four; 256 x 1056 3.2 against 3.5; scalar stores, groups of 2: 256 x 1056 3.3 us with one row and
+  // 4.0 with eight, 4096 x 8192 67 and 53).
+  const int per = vec ? 4 : 1;
+  const bool many = (long)d_out * d_in / per >= (vec ? 1L << 18 : 1L << 20);
+  const int cols = d_in / per, rows = many ? (vec ? 4 : 8) : 1;
+  int width = 256;                                       // threads along the columns: as many as there are, to a power of two
+  while (width / 2 >= cols) width /= 2;
+  const int row_blocks = bpdq_ceil_div(bpdq_ceil_div(d_out, rows), 256 / width);
   auto launch = [&](auto kern) -> int {
-    hipLaunchKernelGGL(kern, grid, dim3(256), 0, stream, planes, coefs, d_out, d_in, group, W_hat);
+    hipLaunchKernelGGL(kern, dim3(bpdq_ceil_div(cols, width), row_blocks < 65535 ? row_blocks : 65535),
+                       dim3(width, 256 / width), 0, stream, planes, coefs, d_out, d_in, group, W_hat);
     BPDQ_LAUNCH_CHECK();
     return 0;
   };
+  auto pick = [&](auto planes_of) -> int {
+    constexpr int K = decltype(planes_of)::value;
+    if (!vec) return many ? launch(dequant_kernel<CT, K, 1, 8, false>) : launch(dequant_kernel<CT, K, 1, 1, false>);
+    if (width < 256) return many ? launch(dequant_kernel<CT, K, 4, 4, false>) : launch(dequant_kernel<CT, K, 4, 1, false>);
+    return many ? launch(dequant_kernel<CT, K, 4, 4, true>) : launch(dequant_kernel<CT, K, 4, 1, true>);
+  };
   switch (bits) {
-    case 1: return vec ? launch(dequant_kernel<CT, 1, true>) : launch(dequant_kernel<CT, 1, false>);
-    case 2: return vec ? launch(dequant_kernel<CT, 2, true>) : launch(dequant_kernel<CT, 2, false>);
-    case 3: return vec ? launch(dequant_kernel<CT, 3, true>) : launch(dequant_kernel<CT, 3, false>);
-    default: return vec ? launch(dequant_kernel<CT, 4, true>) : launch(dequant_kernel<CT, 4, false>);
+    case 1: return pick(std::integral_constant<int, 1>{});
+    case 2: return pick(std::integral_constant<int, 2>{});
+    case 3: return pick(std::integral_constant<int, 3>{});
+    default: return pick(std::integral_constant<int, 4>{});
   }
 }
 

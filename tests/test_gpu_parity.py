@@ -938,6 +938,9 @@ def test_pack_and_dequant_bit_exact(dev, bits):
 @pytest.mark.parametrize("d_out,d_in,group,shift", [
     (1, 32, 32, 0), (3, 1056, 32, 0), (5, 2080, 4, 0),      # vector stores: one row, columns past a work-group's 1024
     (4, 1024, 2, 0), (7, 96, 3, 0), (6, 64, 64, 1),         # groups that four columns straddle, W_hat off 16 bytes
+    (33, 32, 32, 0), (130, 96, 32, 0),                      # several row blocks to a work-group, the last one part full
+    (4099, 256, 64, 0), (1025, 1056, 32, 0),                # several rows per thread: narrow, wide
+    (1027, 1056, 3, 0), (8201, 128, 64, 1),                 # ... with scalar stores
 ])
 def test_dequant_tile_edges(dev, half, d_out, d_in, group, shift):
     """Both store widths of the dequant kernel at the edges of its tiles, bit for bit."""
