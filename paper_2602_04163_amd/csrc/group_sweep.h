@@ -451,64 +451,81 @@ __device__ __forceinline__ void run_columns(RowState<K, G>& st, const float* sU,
   }
 }
 
-// Group records of a layer (SuLayout), by work-groups of 256 threads.  pack_image: the rearranged
-// block, zeros on and below the diagonal of the kept slots.  pack_p0: 1 / U_ll and P_0 by the forward
-// recurrence of column_step, one wavefront, lane j % 64 holding columns j.
+// Group records of a layer (SuLayout), by work-groups of 256 threads, kPackWGs<G> to a group: one per 16 rows of the
+// image (they keep the same slots, so an element's place is a few operations) and one for 1 / U_ll and P_0.
+// Each is one or a few round trips to memory and a short chain.  With the whole image to a work-group, whose places
+// took a loop per element, the launch took 20 us at g = 128: 16 x 256, 1 plane, fixed grid 46.1 us, 40.0 before there
+// were records, 28.9 now; larger layers hide it beside the copy.
 template <int G>
-__device__ __forceinline__ void pack_image(const float* __restrict__ U, int ldu, int s0, float* __restrict__ rec) {
+constexpr int kPackWGs = G / 16 + 1;
+
+// Rows [16 M, 16 M + 16) of the rearranged block, zeros on and below the diagonal of the kept slots.
+template <int G>
+__device__ __forceinline__ void pack_image(const float* __restrict__ U, int ldu, int s0, int M, float* __restrict__ rec) {
   using Lay = SuLayout<G>;
-  constexpr int kPer = G * G / 256, kBatch = kPer < 16 ? kPer : 16;
-  for (int b = 0; b < kPer; b += kBatch) {
-    float v[kBatch];
+  constexpr int kPer = 16 * G / 256;
+  const int S = Lay::CPL - M, live = Lay::live(M), l0 = 16 * M;
+  float* rows = rec + Lay::row_offset(l0);
+  float v[kPer];
 #pragma unroll
-    for (int t = 0; t < kBatch; ++t) {
-      const int e = threadIdx.x + (b + t) * 256;
-      v[t] = U[(long)(s0 + e / G) * ldu + s0 + e % G];
-    }
-    __builtin_amdgcn_sched_barrier(0);
+  for (int t = 0; t < kPer; ++t) {
+    const int e = threadIdx.x + t * 256;
+    v[t] = U[(long)(s0 + l0 + e / G) * ldu + s0 + e % G];
+  }
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int t = 0; t < kBatch; ++t) {
-      const int e = threadIdx.x + (b + t) * 256;
-      const int l = e / G, j = e % G, M = l >> 4, m = j >> 4, S = Lay::CPL - M;
-      if (m < M) continue;
-      float* row = rec + Lay::row_offset(l);
-      row[Lay::slot_index(S, m - M, j & 15)] = (j > l) ? v[t] : 0.f;
-      if (m == M && Lay::live(M) > S) row[Lay::slot_index(S, S, j & 15)] = 0.f;
-    }
+  for (int t = 0; t < kPer; ++t) {
+    const int e = threadIdx.x + t * 256;
+    const int l = e / G, j = e % G, m = j >> 4;         // row l0 + l
+    if (m < M) continue;
+    float* row = rows + 16 * l * live;
+    row[Lay::slot_index(S, m - M, j & 15)] = (j > l0 + l) ? v[t] : 0.f;
+    if (m == M && live > S) row[Lay::slot_index(S, S, j & 15)] = 0.f;
   }
 }
 
+// 1 / U_ll and, where `ones` (a fit follows), P_0 by the forward recurrence of column_step: one wavefront, lane
+// j % 64 holding columns j, the next rows on their way while the present ones are worked on.
 template <int G>
-__device__ __forceinline__ void pack_p0(const float* __restrict__ U, int ldu, int s0, float* __restrict__ rec) {
-  constexpr int NS = (G + 63) / 64, kRows = 32;
+__device__ __forceinline__ void pack_p0(const float* __restrict__ U, int ldu, int s0, bool ones, float* __restrict__ rec) {
+  constexpr int NS = (G + 63) / 64, kRows = (G > 128) ? 16 : 32;
   if (threadIdx.x >= 64) return;
   const int lane = threadIdx.x;
   float* out_inv = rec + SuLayout<G>::floats();
-  float p[NS], iv[NS];
-#pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    const int j = lane + 64 * s;
-    iv[s] = 1.0f / U[(long)(s0 + (j < G ? j : 0)) * ldu + s0 + (j < G ? j : 0)];
-    p[s] = 1.0f;
-  }
-#pragma unroll
-  for (int l0 = 0; l0 < G; l0 += kRows) {
-    float u[kRows][NS];
+  float p[NS], iv[NS], u[2][kRows][NS];
+  auto fetch = [&](int l0, float (&w)[kRows][NS]) {
 #pragma unroll
     for (int r = 0; r < kRows; ++r)
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         const int j = lane + 64 * s;
-        u[r][s] = U[(long)(s0 + l0 + r) * ldu + s0 + (j < G ? j : 0)];
+        w[r][s] = U[(long)(s0 + l0 + r) * ldu + s0 + (j < G ? j : 0)];
       }
-    __builtin_amdgcn_sched_barrier(0);     // all rows of the batch requested before the first is used
+  };
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      const int l = l0 + r, sl = l / 64;
-      const float xl = p[sl] * iv[sl];
-      const float x = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, xl), l % 64));
+  for (int s = 0; s < NS; ++s) {
+    const int j = lane + 64 * s;
+    iv[s] = U[(long)(s0 + (j < G ? j : 0)) * ldu + s0 + (j < G ? j : 0)];
+    p[s] = 1.0f;
+  }
+  if (ones) fetch(0, u[0]);
+  __builtin_amdgcn_sched_barrier(0);       // all on their way before the first is used
 #pragma unroll
-      for (int s = 0; s < NS; ++s) p[s] = fmaf(-x, (lane + 64 * s > l) ? u[r][s] : 0.f, p[s]);
+  for (int s = 0; s < NS; ++s) iv[s] = 1.0f / iv[s];
+  if (ones) {
+#pragma unroll
+    for (int l0 = 0; l0 < G; l0 += kRows) {
+      if (l0 + kRows < G) fetch(l0 + kRows, u[(l0 / kRows + 1) & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) {
+        const int l = l0 + r, sl = l / 64;
+        const float xl = p[sl] * iv[sl];
+        const float x = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, xl), l % 64));
+#pragma unroll
+        for (int s = 0; s < NS; ++s) p[s] = fmaf(-x, (lane + 64 * s > l) ? u[(l0 / kRows) & 1][r][s] : 0.f, p[s]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 #pragma unroll
@@ -516,7 +533,7 @@ __device__ __forceinline__ void pack_p0(const float* __restrict__ U, int ldu, in
     const int j = lane + 64 * s;
     if (j >= G) continue;
     out_inv[j] = iv[s];
-    out_inv[G + j] = p[s] * iv[s];
+    if (ones) out_inv[G + j] = p[s] * iv[s];
   }
 }
 

@@ -23,23 +23,23 @@ int launch_tail_update(hipStream_t stream, TailArgs ta, const float* U, int ldu,
   return 0;
 }
 
-// working copy of W with dead input channels zeroed; the first 2 n_grp work-groups lay out the group
-// records of the factor instead (SuLayout), beside the copy, which is bound by memory
+// working copy of W with dead input channels zeroed; the first kPackWGs n_grp work-groups lay out the group
+// records of the factor instead (SuLayout), beside the copy, which is bound by memory.  ones: a fit follows
 template <int G>
 __global__ __launch_bounds__(256) void copy_in_kernel(const float* __restrict__ W, long n, int d_in,
                                                       const unsigned char* __restrict__ dead,
-                                                      float* __restrict__ Wp, const float* __restrict__ U,
+                                                      float* __restrict__ Wp, const float* __restrict__ U, int ones,
                                                       float* __restrict__ rec) {
-  const int n_grp = d_in / G;
-  if ((int)blockIdx.x < 2 * n_grp) {
-    const int gi = blockIdx.x >> 1;
+  const int n_pack = kPackWGs<G> * (d_in / G);
+  if ((int)blockIdx.x < n_pack) {
+    const int gi = blockIdx.x / kPackWGs<G>, part = blockIdx.x % kPackWGs<G>;
     float* r = rec + (long)gi * SuLayout<G>::record_floats();
-    if (blockIdx.x & 1) pack_image<G>(U, d_in, gi * G, r);
-    else pack_p0<G>(U, d_in, gi * G, r);
+    if (part == 0) pack_p0<G>(U, d_in, gi * G, ones != 0, r);      // the longest first
+    else pack_image<G>(U, d_in, gi * G, part - 1, r);
     return;
   }
-  const long stride = (long)(gridDim.x - 2 * n_grp) * 1024;
-  for (long e = ((long)(blockIdx.x - 2 * n_grp) * 256 + threadIdx.x) * 4; e < n; e += stride) {
+  const long stride = (long)(gridDim.x - n_pack) * 1024;
+  for (long e = ((long)(blockIdx.x - n_pack) * 256 + threadIdx.x) * 4; e < n; e += stride) {
     float4 v = *reinterpret_cast<const float4*>(W + e);
     if (dead) {
       const int c = (int)(e % d_in);
@@ -185,14 +185,18 @@ static int quantize_rows(const float* W, int d_out, int d_in, const float* U,
   if (!group) return -6;
 
   const long n = (long)d_out * d_in;
-  const int grid = (int)((n / 4 + 255) / 256 < 65536 ? (n / 4 + 255) / 256 : 65536) + 2 * (d_in / p->group);
+  const int copy_wgs = (int)((n / 4 + 255) / 256 < 65536 ? (n / 4 + 255) / 256 : 65536);
   float* rec = reinterpret_cast<float*>(base + L.rec_off);
-  auto copy_in = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, stream, W, n, d_in, dead, Wp, U, rec); };
+  const int ones = p->grid != BPDQ_GRID_UNIFORM;
+  auto copy_in = [&](auto kern, int pack_wgs) {
+    hipLaunchKernelGGL(kern, dim3(copy_wgs + pack_wgs * (d_in / p->group)), dim3(256), 0, stream, W, n, d_in, dead, Wp, U,
+                       ones, rec);
+  };
   switch (p->group) {
-    case 32: copy_in(copy_in_kernel<32>); break;
-    case 64: copy_in(copy_in_kernel<64>); break;
-    case 128: copy_in(copy_in_kernel<128>); break;
-    default: copy_in(copy_in_kernel<256>); break;
+    case 32: copy_in(copy_in_kernel<32>, kPackWGs<32>); break;
+    case 64: copy_in(copy_in_kernel<64>, kPackWGs<64>); break;
+    case 128: copy_in(copy_in_kernel<128>, kPackWGs<128>); break;
+    default: copy_in(copy_in_kernel<256>, kPackWGs<256>); break;
   }
   BPDQ_LAUNCH_CHECK();
 
