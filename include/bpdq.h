@@ -50,7 +50,8 @@ typedef struct bpdq_params {
                            ignored, the coefficients returned are (lo, s, 2s, ...).             */
   int   coef_fp16;      /* storage precision of the coefficients (Table 1 counts 16 bits each).
                            0: fp32 throughout.  1: every coefficient is rounded to IEEE half
-                           (nearest even) right after its fit, so the levels of the next bit-plane
+                           (nearest even, in one step from the fp64 fit; a fixed grid's from fp32)
+                           right after its fit, so the levels of the next bit-plane
                            update, What, E*, the scores and the compensation all belong to the
                            values that are stored; `coefs` still holds floats, each exactly a
                            half (bpdq_coefs_to_fp16 is then lossless).  Magnitudes above 65504

@@ -157,7 +157,7 @@ def fit_coefficients(code, T, UL, k, alpha=1e-4):
 def round_coefficients(c, coef_dtype=None, margins=None):
     """Storage precision of the coefficients.  Table 1 counts 16 bits per coefficient; the
     paper does not say when the rounding happens.  Reading taken: with `coef_dtype=np.float16`
-    every fitted coefficient is rounded (fp64 -> fp32 -> fp16, round to nearest even) right
+    every fitted coefficient is rounded (to nearest even, in one step from the fp64 fit) right
     after the fit, so that the levels of the next bit-plane update, What, the propagation
     coordinates E and the score all belong to the values that are stored.  None = no rounding.
     `margins` (rows,), if given, is lowered to the smallest distance of any coefficient of the
@@ -165,7 +165,7 @@ def round_coefficients(c, coef_dtype=None, margins=None):
     coefficient magnitude (instrumentation for the parity tests: the rounding is a decision too)."""
     if coef_dtype is None:
         return c
-    r = np.asarray(c).astype(np.float32).astype(coef_dtype)
+    r = np.asarray(c).astype(coef_dtype)
     if margins is not None:
         c64 = np.asarray(c, dtype=np.float64)
         up = np.nextafter(r, coef_dtype(np.inf)).astype(np.float64)
@@ -317,6 +317,8 @@ def uniform_frozen_group(T, UL, k, decision_dtype=np.float32, coef_dtype=None, m
     s = (hi - lo) / float((1 << k) - 1)
     s = np.where(s == 0.0, 1.0, s)
     c = np.stack([lo] + [s * (1 << i) for i in range(k)], axis=1)
+    if coef_dtype is not None:
+        c = c.astype(np.float32)          # the grid is formed in fp32 before it is stored
     c = round_coefficients(c, coef_dtype, coef_margins)
     code, What, E = bitplane_sweep(T, UL, c, k, decision_dtype, margins)
     return dict(code=code, coef=c, What=What, E=E, it=np.zeros(T.shape[0], dtype=np.int32))

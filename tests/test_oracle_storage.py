@@ -23,6 +23,12 @@ def test_round_coefficients_is_round_to_nearest_even_fp16():
     assert orc.round_coefficients(c, None) is c
 
 
+def test_round_coefficients_rounds_once():
+    # a little above (below) the midpoint of two halves, by less than fp32 resolves: fp32 first would make it a tie
+    c = np.array([[1.0 + 2.0 ** -11 + 2.0 ** -27, 1.0 + 3 * 2.0 ** -11 - 2.0 ** -27]])
+    assert orc.round_coefficients(c, np.float16).tolist() == [[1.0 + 2.0 ** -10, 1.0 + 2.0 ** -10]]
+
+
 def test_stored_fp16_layer_is_self_consistent():
     # with fp16 storage the returned What, E and objective must all belong to the stored values:
     #   coefficients exactly representable; What = Eq. 1 of the stored format (bit for bit in
