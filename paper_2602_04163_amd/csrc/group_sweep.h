@@ -401,7 +401,9 @@ __device__ __forceinline__ void run_columns(RowState<K, G>& st, const float* sU,
   constexpr int CPL = G / 16;
   // level and byte-wise code of this lane: code lane % 2^K, summed in the order of level_table.  A
   // coefficient that is not finite never belongs to the nearest level unless C_0 is not finite
-  // either; it is left out of the sums below, where 0 * inf would be NaN.
+  // either; it is left out of the sums below, where 0 * inf would be NaN.  A level that is not finite never beats
+  // code 0 in a scan with a strict `<`: it takes part as another code 0, so that all distances of a
+  // NaN weight, and of an infinite C_0, are one bit pattern (NaNs of different origin are not).
   float lv = c[0], cs[K + 1];
   unsigned lc = 0u;
   cs[0] = c[0];
@@ -412,6 +414,7 @@ __device__ __forceinline__ void run_columns(RowState<K, G>& st, const float* sU,
     lc |= set ? (1u << (8 * i)) : 0u;
     cs[i + 1] = __builtin_isfinite(c[i + 1]) ? c[i + 1] : 0.f;
   }
+  lv = __builtin_isfinite(lv) ? lv : c[0];
   float bits[K][CPL];
   if constexpr (MODE == kStepInit) {
 #pragma unroll

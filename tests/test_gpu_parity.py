@@ -913,6 +913,91 @@ def test_nearest_level_ties_take_the_lowest_code(dev, bits, group):
     assert float(out["grp_err"][0]) == float(((W - want).astype(np.float64) ** 2).sum())
 
 
+@pytest.mark.parametrize("bits,group", [(1, 64), (2, 32), (2, 128), (3, 256), (4, 64)])
+def test_levels_that_are_not_finite_never_win(dev, bits, group):
+    """The nearest level is the one that a scan from code 0 with a strict `<` keeps: an infinite or NaN distance never
+    replaces code 0, whatever the bit patterns of its NaN.  U = I, fixed grid."""
+    print(f"levels not finite k={bits} g={group}", flush=True)
+    rng = np.random.default_rng(bits + group)
+    U = torch.eye(group, device=dev)
+    W = rng.standard_normal((24, group)).astype(np.float32)
+    W[:, 0], W[:, 1] = -4.0, 4.0                       # the row's grid, so that one weight does not move it
+
+    def run(w, fp16):
+        out = bq.bpdq_quantize_layer(torch.from_numpy(w).to(dev), U, None, bq.make_params(bits, group, group, 0,
+                                                                                      grid=bq.GRID_UNIFORM, coef_fp16=fp16))
+        return orc.unpack_planes(out["planes"].cpu().numpy().view(np.uint32), group), out
+
+    clean, _ = run(W, False)
+    bad = W.copy()
+    bad[3, 7] = np.nan                                 # from here on the row's weights are NaN: code 0
+    bad[5, 9] = np.inf                                 # step infinite, C_0 finite
+    bad[7, 11] = -np.inf                               # C_0 infinite: every level is
+    bad[9] *= 1e6                                      # (beyond the half range below)
+    code, out = run(bad, False)
+    want = clean.copy()
+    want[3, 7:] = 0
+    want[5] = want[7] = 0
+    assert np.array_equal(code, want)
+    assert np.all(out["W_hat"].cpu().numpy()[7] == -np.inf)
+    code, out = run(bad, True)
+    keep = [r for r in range(24) if r not in (3, 5, 7, 9)]
+    assert np.array_equal(code[keep], run(W, True)[0][keep])
+    assert not code[[5, 7, 9]].any() and not code[3, 7:].any()
+    assert np.all(out["W_hat"].cpu().numpy()[[7, 9]] == -np.inf)
+    # with propagation an infinite C_0 meets infinite weights too: NaN distances of different origin
+    U = torch.eye(group, device=dev) + 0.1 * torch.randn((group, group), device=dev).triu(1)
+    for fp16, rows in ((False, [7]), (True, [7, 9])):
+        code, out = run(bad, fp16)
+        assert not code[rows].any() and np.all(out["W_hat"].cpu().numpy()[rows] == -np.inf)
+
+
+def test_levels_beyond_the_half_range(dev):
+    """A plane step above 65504 is stored as an infinity; its levels are never the nearest."""
+    print("levels beyond the half range", flush=True)
+    rng = np.random.default_rng(5)
+    g, d_out = 64, 20
+    W = 5000.0 * rng.integers(0, 29, size=(d_out, g)).astype(np.float32)
+    W[:, 0], W[:, -1] = 0.0, 140000.0                  # lo 0, step 20000: coefficients 0, 20000, 40000, infinite
+    p = bq.make_params(3, g, g, 0, grid=bq.GRID_UNIFORM, coef_fp16=True)
+    out = bq.bpdq_quantize_layer(torch.from_numpy(W).to(dev), torch.eye(g, device=dev), None, p)
+    want = np.minimum(np.ceil(W / 20000.0 - 0.5), 3).astype(np.int64)
+    assert np.array_equal(orc.unpack_planes(out["planes"].cpu().numpy().view(np.uint32), g), want)
+    assert bool(torch.isinf(out["coefs"][3]).all()) and np.array_equal(out["W_hat"].cpu().numpy(), 20000.0 * want)
+    assert float(out["grp_err"][0]) == float(((W - 20000.0 * want).astype(np.float64) ** 2).sum())
+
+
+def test_half_coefficients_are_rounded_once(dev):
+    """The fitted fp64 coefficient goes to a half in one step: values a little off a midpoint of two halves, which
+    rounding to fp32 first would put on it."""
+    print("half rounding", flush=True)
+    g = 32
+    up, down = np.float32(1 + 2.0 ** -11), np.float32(1 + 3 * 2.0 ** -11)      # midpoints of neighbouring halves
+    W = np.full((2, g), 3.0, dtype=np.float32)
+    W[0, :16], W[0, 0] = up, np.nextafter(up, np.float32(2))
+    W[1, :16], W[1, 0] = down, np.nextafter(down, np.float32(0))
+    mean = W[:, :16].astype(np.float64).mean(axis=1)                           # midpoint +- 2^-27
+    p = bq.make_params(1, g, g, 0, alpha=0.0, coef_fp16=True)
+    out = bq.bpdq_quantize_layer(torch.from_numpy(W).to(dev), torch.eye(g, device=dev), None, p)
+    got = out["coefs"][0, :, 0].cpu().numpy()
+    assert got.tolist() == [1 + 2.0 ** -10, 1 + 2.0 ** -10]
+    assert np.array_equal(got, orc.round_coefficients(mean[:, None], np.float16)[:, 0])
+
+
+@pytest.mark.parametrize("bits,group,d_out,d_in", [(2, 32, 40, 128), (2, 128, 33, 256), (1, 64, 20, 192)])
+def test_most_iterations(dev, bits, group, d_out, d_in):
+    """refine_iters = 63: the row scores of all 64 iterates, kept where the pending tile was, and their sums."""
+    print(f"63 iterations k={bits} g={group} {d_out}x{d_in}", flush=True)
+    wl, W, X = _problem("cfg1_tiny", d_out, d_in, 4 * d_in)
+    H = np.zeros((d_in, d_in))
+    orc.hessian_accumulate(X.numpy(), H)
+    Uref, dead, _ = orc.prepare(H, wl.damp)
+    U32 = Uref.astype(np.float32)
+    ref, out = _run_both(dev, wl, W, U32, dead, bits, group, group, 63)
+    assert int(out["grp_iter"].max()) <= 63
+    _teacher_forced(ref, out, W, U32, bits, group, 63, wl.alpha)
+
+
 # ------------------------------------------------------------------ storage helpers
 @pytest.mark.parametrize("bits", [1, 2, 3, 4])
 def test_pack_and_dequant_bit_exact(dev, bits):
