@@ -104,10 +104,16 @@ def load():
     return lib
 
 
+# private to torch; where a torch lacks it the handle comes by way of a Stream object
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
     # the current stream's handle without the Stream object that torch.cuda.current_stream() builds
     # (2.8 of the 8.4 us of host time of a bpdq_gemv call)
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    if _raw_stream is None:
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
 
 
 def _ptr(t):

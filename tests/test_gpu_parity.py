@@ -90,6 +90,17 @@ def test_hessian_workspace_of_another_call(dev, n_tok, d_in, n_sized):
                                    torch.empty(planes_only - 256, dtype=torch.uint8, device=dev))
 
 
+def test_stream_handle_without_the_private_name(dev, monkeypatch):
+    """The current stream's handle comes from a private function of torch where it exists, else by way of a Stream."""
+    print("stream handle", flush=True)
+    for s in (torch.cuda.default_stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(s):
+            fast = bq._stream().value
+            with monkeypatch.context() as m:
+                m.setattr(bq, "_raw_stream", None)
+                assert bq._stream().value == fast == (s.cuda_stream or None)
+
+
 def test_hessian_with_a_workspace_asks_for_no_size(dev, monkeypatch):
     """The size query plans all three kernels; a call that brings its workspace does not make it."""
     print("hessian with a workspace", flush=True)
