@@ -139,27 +139,24 @@ typedef double Inv16[16][16];
 // row q of them the columns 4 ks + q of W in w[ks].  With t_i = A_iJ / A_JJ the rows above J lose t_i
 // times row J; only the reciprocal's chain (about six dependent fp64 operations) is serial, the
 // broadcasts of row J do not wait for it.
+// A pivot that is not positive is replaced by 1; row i keeps its own as it came (raw_own), so that the caller can tell.
 template <int J>
-__device__ __forceinline__ void eliminate16(double (&a)[16], double (&w)[4], double& piv_own, int i, bool& bad_any,
-                                            int& bad_col) {
+__device__ __forceinline__ void eliminate16(double (&a)[16], double (&w)[4], double& raw_own, int i) {
   double row[J > 0 ? J : 1], wr[4];
   const double piv_raw = row_bcast<J>(a[J]);
 #pragma unroll
   for (int e = J - 1; e >= 0; --e) row[e] = row_bcast<J>(a[e]);
 #pragma unroll
   for (int ks = J / 4; ks < 4; ++ks) wr[ks] = row_bcast<J>(w[ks]);      // columns left of J are still zero in row J
-  const bool bad = !(piv_raw > 0.0);
-  const double piv = bad ? 1.0 : piv_raw;
-  if (bad && !bad_any) bad_col = J;         // the first one met: what follows it stands on the replaced pivot
-  bad_any = bad_any || bad;
-  if (i == J) piv_own = piv;
+  const double piv = piv_raw > 0.0 ? piv_raw : 1.0;
+  if (i == J) raw_own = piv_raw;
   const double t = a[J] * fast_rcp(piv);
 #pragma unroll
   for (int e = J - 1; e >= 0; --e) a[e] = fma(-t, row[e], a[e]);
   const double tm = (i < J) ? t : 0.0;
 #pragma unroll
   for (int ks = J / 4; ks < 4; ++ks) w[ks] = fma(-tm, wr[ks], w[ks]);
-  if constexpr (J > 0) eliminate16<J - 1>(a, w, piv_own, i, bad_any, bad_col);
+  if constexpr (J > 0) eliminate16<J - 1>(a, w, raw_own, i);
 }
 
 // a[e] *= (value of `s` in lane e of the 16-lane row), e = E .. 0
@@ -199,7 +196,7 @@ __device__ __forceinline__ void factor64_blocked(double (*sD)[NB + 1], Inv16* sR
   for (int J = NB / 16 - 1; J >= 0; --J) {
     const int c0 = 16 * J;
     __syncthreads();                        // the block, with every earlier panel's update, is in LDS
-    double a[16], wi[4], piv = 1.0, at[4];
+    double a[16], wi[4], raw = 1.0, at[4];
 #pragma unroll
     for (int e = 0; e < 16; ++e) a[e] = (&sD[c0][c0])[off[e]];
     if (w < J) {
@@ -208,17 +205,18 @@ __device__ __forceinline__ void factor64_blocked(double (*sD)[NB + 1], Inv16* sR
     }
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) wi[ks] = (m == 4 * ks + q) ? 1.0 : 0.0;
-    bool bad = false;
-    int bad_col = 0;
-    eliminate16<15>(a, wi, piv, m, bad, bad_col);
-    const double inv_d = fast_rsqrt(piv);   // 1 / R_jj of row j = m
+    eliminate16<15>(a, wi, raw, m);
+    const bool bad = !(raw > 0.0);          // the pivot of row j = m
+    const unsigned bad_rows = (unsigned)__builtin_amdgcn_ballot_w64(bad) & 0xffffu;
+    const double inv_d = fast_rsqrt(bad ? 1.0 : raw);      // 1 / R_jj
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) wi[ks] *= inv_d;                                // R_JJ^-1 [m][4 ks + q]
     if (w == 3) {
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) sRinv[J][m][4 * ks + q] = wi[ks];
     }
-    if (bad && report && w == 0 && lane == 0) atomicCAS(info, 0, p0 + c0 + bad_col + 1);
+    if (bad_rows && report && w == 0 && lane == 0)         // the first one met: the rest stands on replaced pivots
+      atomicCAS(info, 0, p0 + c0 + 32 - __builtin_clz(bad_rows));
     if (w < J) {                            // X = A R_JJ^-T, row tile w
       f64x4 x = (f64x4){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
