@@ -72,13 +72,18 @@ int bpdq_version(void);
  *   ws : split-K partial sums and, for the default entry, the activations re-encoded as halves;
  *        bpdq_hessian_workspace_bytes(n_tok, d_in) bytes serve any of the three entries
  *        (about 4 * n_tok * d_in bytes plus the partial tiles).
+ *        That size is not monotonic in n_tok: a short call on a narrow layer is cut into more slices
+ *        than a longer one.  The default entry also accepts a workspace that does not hold those
+ *        slices but holds coarser ones (sized for a longer call, say); see below.
  * Requirements: d_in % 4 == 0, ldx % 4 == 0, Xc and H 16-byte aligned, ws 256-byte aligned, n_tok >= 0.
  * Returns 0, or a negative code naming the offending argument (-1 Xc, -2 n_tok, -3 d_in,
  * -4 ldx, -6 H, -8 ws, -9 ws_bytes); nothing is launched then.
  *
  * Three kernels compute the same update; each result is bit-reproducible from call to call, they
  * are not bit-identical to one another (they differ by rounding), and each is checked against the
- * fp64 definition to 1e-5 relative Frobenius error.
+ * fp64 definition to 1e-5 relative Frobenius error.  The slices, hence the last bits, follow from
+ * n_tok and d_in alone with any workspace of at least bpdq_hessian_workspace_bytes(n_tok, d_in)
+ * bytes; on a smaller one that is accepted they are the coarser slices, the same in every such call.
  * bpdq_hessian_accumulate (the fastest) runs on the fp16 matrix cores: a streaming pre-pass finds
  *   every channel's largest magnitude in the call, scales the channel by the power of two that
  *   brings it into [2^13, 2^14) and cuts every scaled value into two halves h + l (22 significant
@@ -120,8 +125,9 @@ int bpdq_hessian_accumulate_timed(int kernel, const float* Xc, int n_tok, int d_
  * triangular matrix with positive diagonal such that Ht^-1 = U^T U.
  *   U    : d_in x d_in fp32, full matrix written (strictly lower part = 0); may alias H.
  *   dead : d_in bytes.
- *   info : one device int: 0, or the 1-based index of a column whose pivot was not
- *          positive (Ht not positive definite; U is then undefined).
+ *   info : one device int: 0, or the 1-based index of the first column whose pivot was not
+ *          positive (Ht not positive definite; U is then undefined).  The columns are taken from
+ *          the last to the first.
  * The factorisation runs in fp64 inside ws. */
 size_t bpdq_prepare_workspace_bytes(int d_in);
 int bpdq_prepare(const float* H, int d_in, float damp, float* U, unsigned char* dead,

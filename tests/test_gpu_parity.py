@@ -70,6 +70,21 @@ def test_hessian_small_call_paths(dev, n_tok, d_in):
     assert np.all(np.abs(Hs.triu().cpu().numpy() - want) <= 5e-6 * scale)
 
 
+@pytest.mark.parametrize("n_tok", [100, 300, 4096, 5000])
+def test_hessian_of_activations_that_are_not_finite(dev, n_tok):
+    """An infinity or NaN makes its channel's row and column NaN and touches nothing else, through either pre-pass."""
+    print(f"hessian not finite n_tok={n_tok}", flush=True)
+    X = torch.randn((n_tok, 260), generator=torch.Generator().manual_seed(n_tok)).to(dev)
+    clean = bq.bpdq_hessian_accumulate(X, torch.zeros((260, 260), device=dev), 2.0, True)
+    X[7, 3], X[n_tok - 1, 259], X[11, 100] = float("inf"), -float("inf"), float("nan")
+    H = bq.bpdq_hessian_accumulate(X, torch.zeros((260, 260), device=dev), 2.0, True)
+    bad = torch.zeros(260, dtype=torch.bool, device=dev)
+    bad[[3, 100, 259]] = True
+    nan = bad[:, None] | bad[None, :]
+    assert torch.equal(torch.isnan(H), nan)
+    assert torch.equal(H[~nan], clean[~nan])
+
+
 @pytest.mark.parametrize("n_tok,d_in,n_sized", [(256, 512, 300), (400, 1024, 512), (256, 768, 300)])
 def test_hessian_workspace_of_another_call(dev, n_tok, d_in, n_sized):
     """A short call on a workspace sized for a longer one, where its own finest plan would want more than that:
@@ -80,10 +95,13 @@ def test_hessian_workspace_of_another_call(dev, n_tok, d_in, n_sized):
     g = torch.Generator().manual_seed(n_tok + d_in)
     X = torch.randn((n_tok, d_in), generator=g)
     want = 2.0 * X.double().t() @ X.double()
-    for nbytes in (own, have):
+    results = []
+    for nbytes in (own, own + 4096, have, have):
         H = torch.zeros((d_in, d_in), device=dev)
         bq.bpdq_hessian_accumulate(X.to(dev), H, 2.0, True, torch.empty(nbytes, dtype=torch.uint8, device=dev))
         assert _relfro(H.cpu().numpy(), want.numpy()) < 2e-6
+        results.append(H)
+    assert torch.equal(results[0], results[1]) and torch.equal(results[2], results[3])
     planes_only = 4 * ((n_tok + 31) // 32 * 32) * ((d_in + 255) // 256 * 256)
     with pytest.raises(bq.BpdqError):
         bq.bpdq_hessian_accumulate(X.to(dev), torch.zeros((d_in, d_in), device=dev), 2.0, False,
