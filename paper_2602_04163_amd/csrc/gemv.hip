@@ -18,8 +18,8 @@
 // per look-up forms the address from the nibble and the lane's base; with the add that is 2.4 vector instructions
 // per look-up.
 //
-// What bounds it: these instructions and the LDS reads (7 and 6 us on the 8192 x 29568 layer, whose 83 MB of
-// planes and half-precision coefficients need 16.3 us at 5.1 TB/s).  The plane words and coefficients of the next
+// What bounds it: these instructions and the LDS reads (12 and 8 us on the 8192 x 29568 layer, by their counts,
+// whose 83 MB of planes and half-precision coefficients need 16.3 us at 5.1 TB/s).  The plane words and coefficients of the next
 // chunk or row pass, and the x values of the next chunk, are requested before the current one is worked on;
 // without that every chunk waited for memory twice.
 // Measured, back to back in a graph (one word per lane and load, no prefetch -> this): 8192 x 29568 k = 2

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(1024) void prep_diag_kernel(const float* __restrict
 
 // A (fp64, d x d) <- upper triangle of H with the diagonal fixed and damped, one 64 x 64 block per
 // work-group; blocks below the diagonal are neither written nor ever read.  Bound by HBM (no division per
-// element, half of the stores: 24 -> 13 us at d = 3584, 181 -> 96 us at 8192).
+// element, half of the stores: 24 -> 17 us at d = 3584, 181 -> 72 us at 8192).
 __global__ __launch_bounds__(256) void prep_load_kernel(const float* __restrict__ H, int d,
                                                         const double* __restrict__ scal,
                                                         double* __restrict__ A) {
