@@ -714,6 +714,13 @@ __device__ __forceinline__ void wait_all_vm() {
   __builtin_amdgcn_s_waitcnt(0x0070 | 0x0f00);      // vmcnt 0; expcnt / lgkmcnt at their maxima
 }
 
+// ... and this wavefront's LDS reads have returned: the slot they read is requested anew behind the barrier that
+// follows.  (The compiler moves products over a barrier, and with them the wait for their operands.)
+__device__ __forceinline__ void wait_vm_and_reads() {
+  asm volatile("" ::: "memory");                    // the reads stay above
+  __builtin_amdgcn_s_waitcnt(0x0070);               // vmcnt 0, lgkmcnt 0; expcnt at its maximum
+}
+
 // DMA sources of wavefront w for slice 0 of an operand given by rows: rows [32 w, 32 w + 32) of the
 // tile that starts at row0, 8 rows per request.
 __device__ __forceinline__ void gemm128_row_sources(const double* base, long ld, int row0, int row_limit,
@@ -791,11 +798,11 @@ __device__ __forceinline__ void gemm128_accumulate(const double* const (&src_a)[
   if (n_stage <= 0) return;
   request(0);
   for (int s = 0; s < n_stage; s += 2) {
-    wait_all_vm();                                 // this wavefront's part of slice s has landed
-    __builtin_amdgcn_s_barrier();                  // ... everyone's has, and slice s - 1 is read out
+    wait_vm_and_reads();                           // this wavefront's part of slice s has landed, s - 1 is read out
+    __builtin_amdgcn_s_barrier();                  // ... everyone's has, and is
     asm volatile("" ::: "memory");
     compute(0u, s + 1);
-    wait_all_vm();
+    wait_vm_and_reads();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     compute(kGemmStageBytes, (s + 2 < n_stage) ? s + 2 : -1);
@@ -877,7 +884,9 @@ __device__ __forceinline__ void gemm64_accumulate(const double* const (&src_a)[2
 #pragma unroll
   for (int s = 0; s < kRing64 - 1; ++s) request(s);
   for (int s = 0; s < n_stage; ++s) {
-    __builtin_amdgcn_s_waitcnt(8 | 0x0070 | 0x0f00);   // vmcnt 8: all but the two youngest slices of this wavefront
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(8 | 0x0070);            // vmcnt 8: all but the two youngest slices of this wavefront;
+                                                       // lgkmcnt 0: its reads of slice s - 1, whose slot is next
     __builtin_amdgcn_s_barrier();                      // ... of all, and slice s - 1 is read out
     asm volatile("" ::: "memory");
     const char* st = lds_bytes + (unsigned)(s % kRing64) * kStage64Bytes;

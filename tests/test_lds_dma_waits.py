@@ -1,0 +1,47 @@
+"""The fp64 tile kernels request a slot of LDS by LDS-DMA behind the barrier that ends its reading, so no LDS read may still
+be in flight at a barrier.  The compiler knows nothing of the DMA and moves products, and with them the waits for their
+operands, over a barrier: checked in the assembly that it makes of the source."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2602_04163_amd import build
+
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+KERNELS = ("syrk_trailing128_kernel", "syrk_trailing64_kernel", "tri_inverse_level128_kernel", "tri_inverse_level64_kernel")
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="no hipcc")
+def test_no_lds_read_is_in_flight_at_a_barrier(tmp_path):
+    out = tmp_path / "prepare.s"
+    flags = [f for f in build.FLAGS if f not in ("-shared", "-fPIC")]
+    subprocess.run([HIPCC, *flags, "--cuda-device-only", "-S", os.path.join(build.CSRC, "prepare.hip"), "-o", str(out)],
+                   check=True, capture_output=True)
+    seen, barriers = set(), 0
+    for m in re.finditer(r"^(_ZN4bpdq\w+):[^\n]*\n(.*?)^\.Lfunc_end", out.read_text(), re.S | re.M):
+        name = next((k for k in KERNELS if k in m.group(1)), None)
+        if name is None:
+            continue
+        seen.add(name)
+        ops = [op for op in (line.split(";")[0].strip() for line in m.group(2).split("\n")) if op]
+        label = {op.rstrip(":"): i for i, op in enumerate(ops) if op.startswith(".LBB")}
+        barriers += sum(op.startswith("s_barrier") for op in ops)
+        # from behind every LDS read along every path: its wait must come before a barrier does
+        todo, done = [i + 1 for i, op in enumerate(ops) if op.startswith("ds_read")], set()
+        while todo:
+            i = todo.pop()
+            if i in done or i >= len(ops):
+                continue
+            done.add(i)
+            op = ops[i]
+            if op.startswith("s_waitcnt") and "lgkmcnt(0)" in op:
+                continue
+            assert not op.startswith("s_barrier"), f"{m.group(1)}: an LDS read is in flight at a barrier"
+            if op.startswith(("s_cbranch", "s_branch")):
+                todo.append(label[op.split()[-1]])
+            if not op.startswith(("s_branch", "s_endpgm")):
+                todo.append(i + 1)
+    assert seen == set(KERNELS) and barriers >= 9
