@@ -82,8 +82,8 @@ def test_workspace_is_that_of_the_full_search(lib, n, d):
 
 def test_alternating_shapes_do_not_pay_for_the_search(lib):
     """A calibration stream that alternates between chunk lengths and layer widths misses the plan of the last call
-    every time.  The three plans of a query took 355 us where every slice count was scored, 70 us with the slices at
-    least 256 tokens long; the smallest of many repetitions, so that a busy machine does not count."""
+    every time.  Scoring every slice count, a query of these shapes took 0.4 to 1.9 ms, now 8 to 33 us; the bound is six
+    times that, and the smallest of many repetitions is taken, so that a slow or busy machine does not count."""
     shapes = [(4096, 3584), (3000, 3584), (4096, 2048), (4096, 4096), (4096, 8192)]
     best = [1e9] * len(shapes)
     query = lib.bpdq_hessian_workspace_bytes
@@ -93,4 +93,4 @@ def test_alternating_shapes_do_not_pay_for_the_search(lib):
             t0 = time.perf_counter()
             query(n, d)
             best[i] = min(best[i], time.perf_counter() - t0)
-    assert max(best) < 60e-6
+    assert max(best) < 200e-6
