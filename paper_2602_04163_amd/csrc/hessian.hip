@@ -328,6 +328,9 @@ __device__ __forceinline__ int channel_exponent(float m) {
   return e;
 }
 
+// maximum that keeps a NaN (fmaxf drops it)
+__device__ __forceinline__ float nan_max(float m, float x) { return (x <= m) ? m : x; }
+
 __global__ __launch_bounds__(256) void hess_scale_kernel(const float* __restrict__ pmax, int n_split,
                                                          int d_pad, float* __restrict__ mul,
                                                          float* __restrict__ inv) {
@@ -455,6 +458,112 @@ __global__ __launch_bounds__(kFusedThreads) void hess_prepass_f16_kernel(const f
     split_halves(x[i], s, live ? n_tok - 8 * (int)kg : 0, hv, lv);
     planes[kg * d_pad + ch] = hv;
     planes[(n_kg + kg) * d_pad + ch] = lv;
+  }
+}
+
+// A whole small call in one launch: one TILE x TILE tile of H (16 or 32) to a work-group, WAVES wavefronts that share
+// the tokens.  A lane holds its tokens of both operands in registers (NI of each), so X is read once per tile; every
+// channel is brought to [2^13, 2^14) like above (the range of the two-halves path; a channel with an infinity or a
+// NaN becomes NaN), and the products go through the fp32 matrix cores in chains of at most kSmallChain tokens, whose
+// sums are added in order, the wavefronts' in 64 bits.  The 32 x 32 blocks on the diagonal come whole, as from the tile kernels; `sym` writes
+// the mirror image instead.  Bound by its latency, one round trip to memory and a reduction, while the tiles fit the
+// chip once; beyond that by reading a tile's channels again for every tile, which the 256 x 256 tiles do not.
+// 512 x 256: 14.7 us for three launches (pre-pass, tile product, reduction) -> 5.8; 256 x 1024: 19.6 -> 10.4;
+// 2048 x 256: 19.5 -> 11.7.  Error of H against 64 bits (relative Frobenius, loud channels) 2e-8 .. 7e-8, 5e-8 .. 1.2e-7 before.
+constexpr int kSmallChain = 32;
+
+template <int TILE, int WAVES, int NI>
+__global__ __launch_bounds__(64 * WAVES) void hess_small_kernel(const float* __restrict__ X, int n_tok, int d, long ldx,
+                                                                float scale, float* __restrict__ H, int sym) {
+  constexpr int kPer = 64 / TILE;                          // tokens an instruction takes
+  constexpr int kAcc = TILE * TILE / 64;                   // results of a lane
+  constexpr int kOut = TILE * TILE / (64 * WAVES) > 0 ? TILE * TILE / (64 * WAVES) : 1;      // ... of a thread at the end
+  typedef float acc_t __attribute__((ext_vector_type(kAcc)));
+  __shared__ float red[WAVES][TILE * TILE];
+  __shared__ float top[WAVES][2][TILE];
+  // 32 x 32 block (bi, bj) of the upper triangle, its tile (ti, tj)
+  constexpr int kSub = 32 / TILE;
+  const int blk = blockIdx.x / (kSub * kSub), sub = blockIdx.x % (kSub * kSub);
+  int bj = (int)((sqrtf(8.0f * (float)blk + 1.0f) - 1.0f) * 0.5f);
+  while (bj * (bj + 1) / 2 > blk) --bj;
+  while ((bj + 1) * (bj + 2) / 2 <= blk) ++bj;
+  const int bi = blk - bj * (bj + 1) / 2;
+  const int ti = kSub * bi + sub / kSub, tj = kSub * bj + sub % kSub;
+  const int r0 = TILE * ti, c0 = TILE * tj;
+  if (r0 >= d || c0 >= d || (sym && ti > tj)) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m = lane % TILE, kq = lane / TILE;
+  const bool diag = ti == tj;                              // both operands are the same channels
+  const float* pa = X + (r0 + m < d ? r0 + m : d - 1);
+  const float* pb = X + (c0 + m < d ? c0 + m : d - 1);
+  const int t0 = wave * kPer * NI + kq;
+  float a[NI], b[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int t = t0 + kPer * i;
+    const long off = (long)(t < n_tok ? t : n_tok - 1) * ldx;
+    a[i] = pa[off];
+    b[i] = diag ? a[i] : pb[off];
+  }
+  float old[kOut];
+  bool mine[kOut];
+#pragma unroll
+  for (int q = 0; q < kOut; ++q) {
+    const int e = tid + 64 * WAVES * q, row = r0 + e / TILE, col = c0 + e % TILE;
+    mine[q] = e < TILE * TILE && row < d && col < d && !(sym && row > col);
+    old[q] = H[mine[q] ? (long)row * d + col : 0L];
+  }
+  __builtin_amdgcn_sched_barrier(0);                       // all loads before the first use
+  // largest magnitude of a channel (tokens past the end repeat the last one)
+  float ma = 0.f, mb = 0.f;
+#pragma unroll
+  for (int i = 0; i < NI; ++i) { ma = nan_max(ma, fabsf(a[i])); mb = nan_max(mb, fabsf(b[i])); }
+#pragma unroll
+  for (int x = TILE; x < 64; x *= 2) { ma = nan_max(ma, __shfl_xor(ma, x, 64)); mb = nan_max(mb, __shfl_xor(mb, x, 64)); }
+  if (kq == 0) { top[wave][0][m] = ma; top[wave][1][m] = mb; }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) { ma = nan_max(ma, top[w][0][m]); mb = nan_max(mb, top[w][1][m]); }
+  const int ea = channel_exponent(ma), eb = channel_exponent(mb);
+  const float sa = (ma < INFINITY) ? ldexpf(1.0f, ea) : NAN, sb = (mb < INFINITY) ? ldexpf(1.0f, eb) : NAN;
+  constexpr int kLen = kSmallChain / kPer, kChains = NI > kLen ? NI / kLen : 1;
+  acc_t part[kChains] = {};
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const bool in = t0 + kPer * i < n_tok;
+    const float x = in ? a[i] * sa : 0.f, y = in ? b[i] * sb : 0.f;
+    acc_t& acc = part[i % kChains];
+    if constexpr (TILE == 16) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, acc, 0, 0, 0);
+    else acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, acc, 0, 0, 0);
+  }
+  acc_t acc = part[0];
+#pragma unroll
+  for (int c = 1; c < kChains; ++c) acc += part[c];
+  // D register i of lane l: row 4 (l / TILE) + i % 4 (+ 8 (i / 4) in the 32 x 32 form), column l % TILE
+#pragma unroll
+  for (int i = 0; i < kAcc; ++i) red[wave][(8 * (i / 4) + 4 * kq + i % 4) * TILE + m] = acc[i];
+  __syncthreads();                                         // (the maxima are read out too)
+  if (wave == 0 && kq == 0) { top[0][0][m] = ldexpf(1.0f, -ea); top[0][1][m] = ldexpf(1.0f, -eb); }
+  double v[kOut];
+#pragma unroll
+  for (int q = 0; q < kOut; ++q) {
+    const int e = tid + 64 * WAVES * q;
+    v[q] = 0.0;
+    if (e < TILE * TILE) {
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) v[q] += (double)red[w][e];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kOut; ++q) {
+    if (!mine[q]) continue;
+    const int e = tid + 64 * WAVES * q, row = r0 + e / TILE, col = c0 + e % TILE;
+    // in the activations' units again (powers of two), rounded once
+    const float h = (float)((double)old[q] + (double)scale * (v[q] * (double)top[0][0][e / TILE] * (double)top[0][1][e % TILE]));
+    H[(long)row * d + col] = h;
+    if (sym && row < col) H[(long)col * d + row] = h;
   }
 }
 
@@ -687,6 +796,40 @@ static size_t hessian_ws_bytes(int kind, bool fine, int n_tok, int d_in) {
   return hessian_ws_layout(kind, fine, hessian_launch_tokens(kind, fine, n_tok, d_in), d_in).total;
 }
 
+// Calls that one launch serves best (hess_small_kernel), and its form.  The lines lie where the two ways take the
+// same time or a little before (us, three launches / one): 64 tokens, 512 channels 18.9 / 4.1, 2048 28.6 / 10.8, 3072
+// 26.9 / 19.2, 4096 28.4 / 31.2; 256 tokens, 1024 channels 19.6 / 10.4, 2048 38.8 / 28.0, 3072 37.7 / 62.2; 512 tokens,
+// 512 channels 17.3 / 9.4, 1024 23.6 / 21.7, 1536 27.9 / 34.7; 1024 tokens, 512 channels 20.8 / 17.4, 768 26.2 / 26.8;
+// 2048 tokens, 384 channels 25.5 / 21.8, 512 28.4 / 36.2.  Small layers take 16 x 16 tiles, which occupy more compute
+// units (256 tokens, 256 channels: 4.5 us, 6.4 with 32 x 32), and more wavefronts the more tokens there are.
+enum SmallForm { kNotSmall, k16x4, k16x8, k16x16, k32x4, k32x8 };
+static SmallForm hessian_small_form(int n_tok, int d_in) {
+  if (n_tok <= 64) return d_in <= 512 ? k16x4 : d_in <= 3072 ? k32x4 : kNotSmall;
+  if (n_tok <= 256) return d_in <= 384 ? k16x8 : d_in <= 2048 ? k32x8 : kNotSmall;
+  if (n_tok <= 512) return d_in <= 256 ? k16x16 : d_in <= 512 ? k16x8 : d_in <= 1024 ? k32x8 : kNotSmall;
+  if (n_tok <= 1024) return d_in <= 512 ? k16x16 : kNotSmall;
+  if (n_tok <= 2048) return d_in <= 384 ? k16x16 : kNotSmall;
+  return kNotSmall;
+}
+
+static void launch_hessian_small(SmallForm form, const float* X, int n_tok, int d_in, int ldx, float scale, float* H,
+                                 int symmetrize, hipStream_t stream) {
+  const int nb = bpdq_ceil_div(d_in, 32), blocks = nb * (nb + 1) / 2;
+  auto go = [&](auto kern, int tiles, int waves) {
+    hipLaunchKernelGGL(kern, dim3(tiles), dim3(64 * waves), 0, stream, X, n_tok, d_in, (long)ldx, scale, H, symmetrize);
+  };
+  // NI: the tokens (64, 256, 512, 1024, 2048) over the lanes that share them
+  switch (form) {
+    case k16x4: return go(hess_small_kernel<16, 4, 4>, 4 * blocks, 4);
+    case k16x8: return n_tok <= 256 ? go(hess_small_kernel<16, 8, 8>, 4 * blocks, 8) : go(hess_small_kernel<16, 8, 16>, 4 * blocks, 8);
+    case k16x16:
+      if (n_tok <= 512) return go(hess_small_kernel<16, 16, 8>, 4 * blocks, 16);
+      return n_tok <= 1024 ? go(hess_small_kernel<16, 16, 16>, 4 * blocks, 16) : go(hess_small_kernel<16, 16, 32>, 4 * blocks, 16);
+    case k32x4: return go(hess_small_kernel<32, 4, 8>, blocks, 4);
+    default: return n_tok <= 256 ? go(hess_small_kernel<32, 8, 16>, blocks, 8) : go(hess_small_kernel<32, 8, 32>, blocks, 8);
+  }
+}
+
 static int hessian_accumulate(int kind, const float* Xc, int n_tok, int d_in, int ldx, float scale,
                               float* H, int symmetrize, void* ws, size_t ws_bytes, void* stream_,
                               void* ev_begin = nullptr, void* ev_end = nullptr) {
@@ -707,6 +850,14 @@ static int hessian_accumulate(int kind, const float* Xc, int n_tok, int d_in, in
   }
   if (need > 0 && (!ws || (reinterpret_cast<uintptr_t>(ws) & 255))) return -8;
   if (ws_bytes < need) return -9;
+  const SmallForm small = kind == kKindF16x2 && n_tok > 0 ? hessian_small_form(n_tok, d_in) : kNotSmall;
+  if (small != kNotSmall) {
+    if (ev_begin) BPDQ_HIP_TRY(hipEventRecord(static_cast<hipEvent_t>(ev_begin), stream));
+    launch_hessian_small(small, Xc, n_tok, d_in, ldx, scale, H, symmetrize, stream);
+    BPDQ_LAUNCH_CHECK();
+    if (ev_end) BPDQ_HIP_TRY(hipEventRecord(static_cast<hipEvent_t>(ev_end), stream));
+    return 0;
+  }
   char* base = static_cast<char*>(ws);
   for (int done = 0; done < n_tok;) {
     const int n_part = hessian_launch_tokens(kind, fine, n_tok - done, d_in);

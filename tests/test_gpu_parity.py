@@ -70,6 +70,34 @@ def test_hessian_small_call_paths(dev, n_tok, d_in):
     assert np.all(np.abs(Hs.triu().cpu().numpy() - want) <= 5e-6 * scale)
 
 
+@pytest.mark.parametrize("n_tok,d_in", [(1, 4), (3, 516), (64, 512), (64, 3072), (65, 388), (64, 3076), (256, 384),
+                                        (255, 2044), (257, 260), (256, 2052), (512, 256), (400, 508), (512, 1024),
+                                        (513, 36), (512, 1028), (1024, 512), (1000, 516), (1025, 100), (2048, 384),
+                                        (2047, 388), (2049, 256)])
+def test_hessian_one_launch_calls(dev, n_tok, d_in):
+    """Both sides of the lines between one launch and three, at the edges of the tiles and of the tokens a lane
+    holds: strided rows, channels far apart in magnitude, a scale, a start that is not zero; the blocks of 32 x 32 on
+    the diagonal come whole and nothing below them is touched unless H is symmetrized."""
+    print(f"hessian one launch n_tok={n_tok} d_in={d_in}", flush=True)
+    g = torch.Generator().manual_seed(7 * n_tok + d_in)
+    X = torch.randn((n_tok, d_in + 4), generator=g) * torch.pow(10.0, torch.randint(-15, 16, (d_in + 4,), generator=g).float())
+    Xd = X.to(dev)[:, :d_in]
+    x = Xd.double()
+    h0 = torch.linalg.vector_norm(x, dim=0)
+    H0 = (torch.randn((d_in, d_in), generator=g).to(dev).double() * h0[:, None] * h0[None, :]).float()
+    Hp = bq.bpdq_hessian_accumulate(Xd, H0.clone(), 0.5, False)
+    Hs = bq.bpdq_hessian_accumulate(Xd, H0.clone(), 0.5, True)
+    i = torch.arange(d_in, device=dev) // 32
+    whole = i[:, None] <= i[None, :]
+    want = H0.double() + 0.5 * (x.t().contiguous() @ x)
+    # 2^-21 of a product of halves, 2^-24 for each addition of a chain (at most 8192 tokens between roundings, and
+    # about the square root of that in practice), and the rounding of H itself
+    bound = 5e-6 * (0.5 * h0[:, None] * h0[None, :] + H0.double().abs())
+    assert bool(((Hp.double() - want).abs()[whole] <= bound[whole]).all())
+    assert torch.equal(Hp[~whole], H0[~whole])
+    assert torch.equal(Hs, Hs.t()) and torch.equal(Hs.triu(), Hp.triu())
+
+
 @pytest.mark.parametrize("n_tok", [100, 300, 4096, 5000])
 def test_hessian_of_activations_that_are_not_finite(dev, n_tok):
     """An infinity or NaN makes its channel's row and column NaN and touches nothing else, through either pre-pass."""
