@@ -7,6 +7,11 @@
 // inverse (2/3 d^3 flops) and Ht^-1 is never formed.  Everything runs in fp64 inside the
 // workspace; the result is rounded to fp32 once, on output.
 //
+// Two ways to do it.  From 65 to 6656 columns, where the chain of the panels bounds the time, the factor and its inverse in
+// one sweep over pairs of 64-column panels from the right (prepare_by_pairs): while a pair is factored by a few
+// work-groups, the others of the same launch update what the next pairs need only later and build the rows of the inverse
+// behind it (3584 columns: 1912 -> 1288 us; 8192 would take 11.5 ms instead of 9.8).  Otherwise, and with a workspace
+// of only the size that this needs, the factor first and then the inverse:
 //   factor : right-looking over 64-column panels from the right, two panels per launch: every
 //            panel work-group factors the two diagonal blocks for itself (in LDS, by panels of
 //            16 columns) and solves its 64 rows of R12 R22^T = A12.  The trailing update
@@ -19,6 +24,8 @@
 //            where a level has enough of them, 64 x 64 otherwise).
 // Both tile sizes stream their operands by LDS-DMA; widths that are odd (trailing updates) or not a
 // multiple of 64 (inversion) take 64 x 64 tiles staged through registers.
+#include <type_traits>
+
 #include "common.h"
 
 namespace bpdq {
@@ -53,11 +60,21 @@ __global__ __launch_bounds__(1024) void prep_diag_kernel(const float* __restrict
 // A (fp64, d x d) <- upper triangle of H with the diagonal fixed and damped, one 64 x 64 block per
 // work-group; blocks below the diagonal are neither written nor ever read.  Bound by HBM (no division per
 // element, half of the stores: 24 -> 17 us at d = 3584, 181 -> 72 us at 8192).
-__global__ __launch_bounds__(256) void prep_load_kernel(const float* __restrict__ H, int d,
+// ld > d: A is padded with the identity to ld x ld.  U: zeros below the diagonal blocks go there at once (U may be H: the
+// blocks below the diagonal are not read).
+__global__ __launch_bounds__(256) void prep_load_kernel(const float* H, int d,
                                                         const double* __restrict__ scal,
-                                                        double* __restrict__ A) {
+                                                        double* __restrict__ A, int ld, float* U) {
   const int bi = blockIdx.y, bj = blockIdx.x;
-  if (bj < bi) return;
+  if (bj < bi) {
+    if (!U) return;
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      const int i = bi * NB + (threadIdx.x >> 6) + 4 * t, j = bj * NB + (threadIdx.x & 63);
+      if (i < d && j < d) U[(long)i * d + j] = 0.f;
+    }
+    return;
+  }
   const double lam = scal[0];
   const int j = bj * NB + (threadIdx.x & 63), i0 = bi * NB + (threadIdx.x >> 6);
   float h[16];
@@ -69,10 +86,11 @@ __global__ __launch_bounds__(256) void prep_load_kernel(const float* __restrict_
 #pragma unroll
   for (int t = 0; t < 16; ++t) {
     const int i = i0 + 4 * t;
-    if (i >= d || j >= d) continue;
+    if (i >= ld || j >= ld) continue;
     double v = (j >= i) ? (double)h[t] : 0.0;
     if (i == j) v = (h[t] == 0.f ? 1.0 : v) + lam;
-    A[(long)i * d + j] = v;
+    if (i >= d || j >= d) v = (i == j) ? 1.0 : 0.0;
+    A[(long)i * ld + j] = v;
   }
 }
 
@@ -102,6 +120,7 @@ __device__ __forceinline__ double fast_rsqrt(double x) {
 // (Work-groups of 512 threads are two teams of 256 on tiles of their own: team_tid and team_wave.)
 __device__ __forceinline__ int team_tid() { return threadIdx.x & 255; }
 __device__ __forceinline__ int team_wave() { return (threadIdx.x >> 6) & 3; }
+__device__ __forceinline__ int team_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 8); }
 
 template <typename OK, typename IDX>
 __device__ __forceinline__ void fetch_tile64(const double* __restrict__ base, OK ok, IDX idx,
@@ -140,22 +159,35 @@ typedef double Inv16[16][16];
 // times row J; only the reciprocal's chain (about six dependent fp64 operations) is serial, the
 // broadcasts of row J do not wait for it.
 // A pivot that is not positive is replaced by 1; row i keeps its own as it came (raw_own), so that the caller can tell.
+// The broadcast is an operand of the multiply-add (v_fmac_f64_dpp, which the compiler does not form: a move and a
+// multiply-add each were 30 instructions a column, now about 22; every one takes a wavefront alone about eight cycles).
+// A DPP operand must be two instructions old, and the compiler does not look into assembly: the entry the next
+// column's pivot is read from is followed by the wait, every other one by more than two instructions.
+template <int J, bool WAIT>
+__device__ __forceinline__ void fmac_bcast(double& x, double t) {      // x -= t (x of lane J of the 16-lane row)
+  if constexpr (WAIT)
+    asm volatile("v_fmac_f64_dpp %0, %0, -%1 row_newbcast:%2 row_mask:0xf bank_mask:0xf\n\ts_nop 1" : "+v"(x) : "v"(t), "n"(J));
+  else
+    asm volatile("v_fmac_f64_dpp %0, %0, -%1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(x) : "v"(t), "n"(J));
+}
 template <int J>
 __device__ __forceinline__ void eliminate16(double (&a)[16], double (&w)[4], double& raw_own, int i) {
-  double row[J > 0 ? J : 1], wr[4];
+  if constexpr (J == 15) {                  // the loaded and selected values stand two instructions before their first use
+    asm volatile("s_nop 1"
+                 : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]), "+v"(a[8]),
+                   "+v"(a[9]), "+v"(a[10]), "+v"(a[11]), "+v"(a[12]), "+v"(a[13]), "+v"(a[14]));
+    asm volatile("s_nop 1" : "+v"(a[15]), "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]));
+  }
   const double piv_raw = row_bcast<J>(a[J]);
-#pragma unroll
-  for (int e = J - 1; e >= 0; --e) row[e] = row_bcast<J>(a[e]);
-#pragma unroll
-  for (int ks = J / 4; ks < 4; ++ks) wr[ks] = row_bcast<J>(w[ks]);      // columns left of J are still zero in row J
-  const double piv = piv_raw > 0.0 ? piv_raw : 1.0;
   if (i == J) raw_own = piv_raw;
-  const double t = a[J] * fast_rcp(piv);
-#pragma unroll
-  for (int e = J - 1; e >= 0; --e) a[e] = fma(-t, row[e], a[e]);
+  const double r = fast_rcp(piv_raw);       // the test of the pivot runs beside the reciprocal's chain
+  const double t = a[J] * (piv_raw > 0.0 ? r : 1.0);
   const double tm = (i < J) ? t : 0.0;
+  if constexpr (J > 0) fmac_bcast<J, true>(a[J - 1], t);
 #pragma unroll
-  for (int ks = J / 4; ks < 4; ++ks) w[ks] = fma(-tm, wr[ks], w[ks]);
+  for (int e = J - 2; e >= 0; --e) fmac_bcast<J, false>(a[e], t);
+#pragma unroll
+  for (int ks = J / 4; ks < 4; ++ks) fmac_bcast<J, false>(w[ks], tm);  // columns left of J are still zero in row J
   if constexpr (J > 0) eliminate16<J - 1>(a, w, raw_own, i);
 }
 
@@ -180,14 +212,29 @@ __device__ __forceinline__ void scale_columns16(double (&a)[16], double s) {
 // cycles a column, and the inverses a pass of their own: a panel pair 52 -> 40 us at d = 3584.)
 // A non-positive pivot is reported as column p0 + j + 1 (by the work-group with `report`) and
 // replaced by 1.  All 256 threads call this; it begins and ends with a barrier.
+//
+// `idle`: of a 512-thread work-group one team factors (active), the other keeps the barriers company and does work of
+// its own between them, idle(integral_constant<int, n>), n = 0 .. 7: the odd ones are the short intervals.
+struct NoWork {
+  template <typename N>
+  __device__ __forceinline__ void operator()(N) const {}
+};
+template <typename IDLE = NoWork>
 __device__ __forceinline__ void factor64_blocked(double (*sD)[NB + 1], Inv16* sRinv, int* info, int p0, bool report,
-                                                 bool active = true) {
-  if (!active) {                            // the other team of a 512-thread work-group keeps the barriers company
-#pragma unroll 1
-    for (int n = 0; n < 2 * (NB / 16) + 1; ++n) __syncthreads();
+                                                 bool active = true, IDLE idle = IDLE{}) {
+  if (!active) {
+    auto wait = [&](auto n) {
+      __syncthreads();
+      idle(n);
+    };
+    wait(std::integral_constant<int, 0>{}); wait(std::integral_constant<int, 1>{});
+    wait(std::integral_constant<int, 2>{}); wait(std::integral_constant<int, 3>{});
+    wait(std::integral_constant<int, 4>{}); wait(std::integral_constant<int, 5>{});
+    wait(std::integral_constant<int, 6>{}); wait(std::integral_constant<int, 7>{});
+    __syncthreads();
     return;
   }
-  const int lane = threadIdx.x & 63, w = team_wave();
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(team_wave());
   const int m = lane & 15, q = lane >> 4;
   int off[16];                              // element (m, e) of a diagonal block, from its upper triangle
 #pragma unroll
@@ -218,11 +265,11 @@ __device__ __forceinline__ void factor64_blocked(double (*sD)[NB + 1], Inv16* sR
     if (bad_rows && report && w == 0 && lane == 0)         // the first one met: the rest stands on replaced pivots
       atomicCAS(info, 0, p0 + c0 + 32 - __builtin_clz(bad_rows));
     if (w < J) {                            // X = A R_JJ^-T, row tile w
-      f64x4 x = (f64x4){0.0, 0.0, 0.0, 0.0};
+      f64x4 x[2] = {(f64x4){0.0, 0.0, 0.0, 0.0}, (f64x4){0.0, 0.0, 0.0, 0.0}};
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) x = __builtin_amdgcn_mfma_f64_16x16x4f64(at[ks], wi[ks], x, 0, 0, 0);
+      for (int ks = 0; ks < 4; ++ks) x[ks & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(at[ks], wi[ks], x[ks & 1], 0, 0, 0);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) sD[16 * w + 4 * r + q][c0 + m] = x[r];
+      for (int r = 0; r < 4; ++r) sD[16 * w + 4 * r + q][c0 + m] = x[0][r] + x[1][r];
     }
     __syncthreads();
     // (after the barrier: every wavefront has read the diagonal block)
@@ -236,18 +283,47 @@ __device__ __forceinline__ void factor64_blocked(double (*sD)[NB + 1], Inv16* sR
 #pragma unroll
       for (int e = 0; e < 16; ++e) sD[c0 + m][c0 + e] = a[e];
     }
-    int t = 0;
-    for (int tk = J - 1; tk >= 0; --tk)     // the next panel's tiles first
-      for (int ti = tk; ti >= 0; --ti, ++t) {
-        if ((t & 3) != w) continue;
-        f64x4 acc = (f64x4){0.0, 0.0, 0.0, 0.0};
+    // the tiles to the left, the next panel's first; a wavefront's two are in flight together
+    auto tile_of = [&](int t, int& ti, int& tk) {
+      tk = J - 1;
+      while (tk > 0 && t > tk) { t -= tk + 1; --tk; }
+      ti = tk - t;
+    };
+    const int n_tiles = J * (J + 1) / 2;
+    if (w < n_tiles) {
+      const bool two = w + 4 < n_tiles;
+      int ti[2], tk[2];
+      tile_of(w, ti[0], tk[0]);
+      tile_of(two ? w + 4 : w, ti[1], tk[1]);
+      double xi[2][4], xk[2][4], old[2][4];
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          xi[u][ks] = sD[16 * ti[u] + m][c0 + 4 * ks + q];
+          xk[u][ks] = sD[16 * tk[u] + m][c0 + 4 * ks + q];
+          old[u][ks] = sD[16 * ti[u] + 4 * ks + q][16 * tk[u] + m];
+        }
+      __builtin_amdgcn_sched_barrier(0);
+      f64x4 acc[2][2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) acc[u][h] = (f64x4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+        acc[0][ks & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(xi[0][ks], xk[0][ks], acc[0][ks & 1], 0, 0, 0);
+      if (two)
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sD[16 * ti + m][c0 + 4 * ks + q], sD[16 * tk + m][c0 + 4 * ks + q],
-                                                     acc, 0, 0, 0);
+          acc[1][ks & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(xi[1][ks], xk[1][ks], acc[1][ks & 1], 0, 0, 0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sD[16 * ti + 4 * r + q][16 * tk + m] -= acc[r];
-      }
+      for (int u = 0; u < 2; ++u)
+        if (u == 0 || two) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) sD[16 * ti[u] + 4 * r + q][16 * tk[u] + m] = old[u][r] - (acc[u][0][r] + acc[u][1][r]);
+        }
+    }
   }
   __syncthreads();
 }
@@ -259,39 +335,62 @@ __device__ __forceinline__ void factor64_blocked(double (*sD)[NB + 1], Inv16* sR
 // Wavefront w of the team takes rows 16 w .. 16 w + 15 through all four blocks; a row block never
 // meets another one's data, so there is no barrier inside and no dependent substitution chain (a
 // column-by-column substitution took 7 us a solve instead of 2).  The caller puts a barrier behind it.
+// What is not solved yet stays in registers (acc, the layout of the result), the operands of a step are requested
+// before its first product.
+
+// LDS serves a wavefront in order, so what one lane wrote another lane of it may read without a barrier; but the compiler,
+// which looks at one lane's addresses only, has to be kept from moving the reads over the writes.
+__device__ __forceinline__ void in_wave_order() { asm volatile("" ::: "memory"); }
+
 template <int J>
-__device__ __forceinline__ void trsm_block_step(double (*sX)[NB + 1], const double (*sR)[NB + 1], const Inv16* sRinv) {
+__device__ __forceinline__ void trsm_block_step(f64x4 (&acc)[4], double (*sX)[NB + 1], const double (*sR)[NB + 1], const Inv16* sRinv) {
   const int lane = threadIdx.x & 63, i0 = 16 * team_wave();
   const int lm = lane & 15, lq = lane >> 4;
-  double a[4];
-  f64x4 acc = (f64x4){0.0, 0.0, 0.0, 0.0};
+  double a[4], ri[4], rb[J > 0 ? J : 1][4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    ri[ks] = sRinv[J][lm][4 * ks + lq];
+#pragma unroll
+    for (int Jp = 0; Jp < J; ++Jp) rb[Jp][ks] = sR[16 * Jp + lm][16 * J + 4 * ks + lq];
+  }
+  if constexpr (J < 3) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sX[i0 + 4 * r + lq][16 * J + lm] = acc[J][r];
+  }
+  in_wave_order();
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) a[ks] = sX[i0 + lm][16 * J + 4 * ks + lq];
+  f64x4 x[2] = {(f64x4){0.0, 0.0, 0.0, 0.0}, (f64x4){0.0, 0.0, 0.0, 0.0}};
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks)                                                    // A[m][k] = A_J, B[k][n] = Rinv[n][k]
-    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sX[i0 + lm][16 * J + 4 * ks + lq], sRinv[J][lm][4 * ks + lq], acc, 0, 0, 0);
+    x[ks & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ks], ri[ks], x[ks & 1], 0, 0, 0);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) sX[i0 + 4 * r + lq][16 * J + lm] = acc[r];            // D[4r + l/16][l%16]
+  for (int r = 0; r < 4; ++r) sX[i0 + 4 * r + lq][16 * J + lm] = x[0][r] + x[1][r];  // D[4r + l/16][l%16]
+  in_wave_order();
   if constexpr (J > 0) {
-    // X_J back in operand layout (this wavefront's own rows: LDS serves a wavefront in order)
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) a[ks] = sX[i0 + lm][16 * J + 4 * ks + lq];
-    f64x4 upd[J];
+    for (int ks = 0; ks < 4; ++ks) a[ks] = -sX[i0 + lm][16 * J + 4 * ks + lq];
 #pragma unroll
-    for (int Jp = 0; Jp < J; ++Jp) {
-      upd[Jp] = (f64x4){0.0, 0.0, 0.0, 0.0};
+    for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks)                                                // B[k][n] = R[J'n][Jk]
-        upd[Jp] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ks], sR[16 * Jp + lm][16 * J + 4 * ks + lq], upd[Jp], 0, 0, 0);
-    }
-#pragma unroll
-    for (int Jp = 0; Jp < J; ++Jp)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) sX[i0 + 4 * r + lq][16 * Jp + lm] -= upd[Jp][r];
-    trsm_block_step<J - 1>(sX, sR, sRinv);
+      for (int Jp = J - 1; Jp >= 0; --Jp)                                           // B[k][n] = R[J'n][Jk]
+        acc[Jp] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ks], rb[Jp][ks], acc[Jp], 0, 0, 0);
   }
 }
-
+__device__ __forceinline__ void trsm_load(f64x4 (&acc)[4], const double (*sX)[NB + 1]) {
+  const int lane = threadIdx.x & 63, i0 = 16 * team_wave();
+#pragma unroll
+  for (int Jp = 0; Jp < 3; ++Jp)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[Jp][r] = sX[i0 + 4 * r + (lane >> 4)][16 * Jp + (lane & 15)];
+}
 __device__ __forceinline__ void trsm64_blocked(double (*sX)[NB + 1], const double (*sR)[NB + 1], const Inv16* sRinv) {
-  trsm_block_step<NB / 16 - 1>(sX, sR, sRinv);
+  f64x4 acc[4];
+  trsm_load(acc, sX);
+  trsm_block_step<3>(acc, sX, sR, sRinv);
+  trsm_block_step<2>(acc, sX, sR, sRinv);
+  trsm_block_step<1>(acc, sX, sR, sRinv);
+  trsm_block_step<0>(acc, sX, sR, sRinv);
 }
 
 // 64 x 64 tile at (r0, c0) of A, `nr` x `nc` of it inside (identity padding where `diag`, else zeros), 16
@@ -383,7 +482,7 @@ __global__ __launch_bounds__(256) void panel_factor_kernel(double* __restrict__ 
 // layout in which the second product reads it.  All 256 threads; begins and ends with a barrier.
 // (A thread per column with a dot product per element took 40 us of the launch.)
 __device__ __forceinline__ void invert64(const double (*sR)[NB + 1], double (*sV)[NB + 1]) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = team_wave();
   const int m = lane & 15, q = lane >> 4;
   __syncthreads();
   if (lane < 16) {
@@ -475,14 +574,14 @@ __device__ __forceinline__ void quad_zero(Quad64& q) {
     for (int j = 0; j < 2; ++j) q.c[i][j] = (f64x4){0.0, 0.0, 0.0, 0.0};
 }
 
-template <bool B_T>
+template <bool B_T, int K0 = 0, int K1 = NB>
 __device__ __forceinline__ void quad_mfma_64(const double (*sa)[NB + 1], const double (*sb)[NB + 1],
                                              Quad64& q) {
   const int lane = threadIdx.x & 63, w = team_wave();
   const int m0 = (w >> 1) * 32 + (lane & 15), n0 = (w & 1) * 32 + (lane & 15);
   const int kq = lane >> 4;
 #pragma unroll 4
-  for (int k0 = 0; k0 < NB; k0 += 4) {
+  for (int k0 = K0; k0 < K1; k0 += 4) {
     const int k = k0 + kq;
     double a[2], b[2];
 #pragma unroll
@@ -509,117 +608,6 @@ __device__ __forceinline__ void quad_for_each(const Quad64& q, F f) {
       for (int r = 0; r < 4; ++r)
         f((w >> 1) * 32 + 16 * i + 4 * r + (lane >> 4), (w & 1) * 32 + 16 * j + (lane & 15),
           q.c[i][j][r]);
-}
-
-// Two adjacent 64-column panels -- block b1 (columns p1 ..) and block b2 = b1 + 1 -- in one
-// launch, one work-group per 64 rows above them.  With the diagonal 128 x 128 block
-// [D11 D12; D12^T D22] every work-group computes for itself
-//     D22 = R22 R22^T,   R12 = D12 R22^-T,   D11 - R12 R12^T = R11 R11^T
-// and for its own rows [A1 A2] of the two panels
-//     X2 = A2 R22^-T,    X1 = (A1 - X2 R12^T) R11^-T.
-// The solves and products run on the fp64 matrix cores.  This halves the number of dependent launches of
-// the panel chain (each is short and latency-bound).  A work-group is two teams of four wavefronts: the
-// first walks the chain of the diagonal block, the second solves and updates the work-group's rows beside it
-// and stores what is finished, so that of the rows only the last solve comes after the chain (one team that
-// did both in turn took 40.5 us a launch at d = 3584, two take 34.4).  Work-group 0 writes R11, R22 to
-// Rdiag and R12 to R12buf (never into A, whose blocks later-scheduled work-groups still read) and sets the
-// pair flag of b2, so that the inverse step puts R12 in place.
-constexpr size_t kPairLdsBytes = (size_t)(4 * NB * (NB + 1) + NB * 16) * sizeof(double);
-constexpr int kPairThreads = 512;
-
-__global__ __launch_bounds__(kPairThreads) void panel_pair_kernel(double* __restrict__ A, int d, int p1,
-                                                                  int nb2, int n_above,
-                                                                  double* __restrict__ Rdiag1,
-                                                                  double* __restrict__ Rdiag2,
-                                                                  double* __restrict__ R12buf,
-                                                                  int* __restrict__ pair_flag1,
-                                                                  int* __restrict__ pair_flag2, int* info) {
-  extern __shared__ double dyn[];
-  typedef double Row[NB + 1];
-  Row* sR = reinterpret_cast<Row*>(dyn);            // R22, then R11
-  Row* sR12 = sR + NB;                              // D12 -> R12
-  Row* sA1 = sR12 + NB;                             // own rows, columns of b1
-  Row* sA2 = sA1 + NB;                              // own rows, columns of b2
-  Inv16* sRinv = reinterpret_cast<Inv16*>(dyn + 4 * NB * (NB + 1));
-  const int tid = team_tid();
-  const bool chain = threadIdx.x < 256;             // team of the diagonal block; the other has the rows
-  const int p2 = p1 + NB;
-  const int r0 = blockIdx.x * NB;
-  const bool first = blockIdx.x == 0, rows = n_above > 0;
-  const bool vec = nb2 == NB && d % 2 == 0;
-
-  Quad64 d11;                                       // D11 in the product's layout, needed after the first factorisation
-  quad_zero(d11);
-  if (chain) {
-    double v22[16], v12[16];
-    fetch_tile(A, d, p2, p2, nb2, nb2, true, vec, v22);
-    fetch_tile(A, d, p1, p2, NB, nb2, false, vec, v12);
-    const int lane = threadIdx.x & 63, w = team_wave();
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          d11.c[i][j][r] = A[(long)(p1 + (w >> 1) * 32 + 16 * i + 4 * r + (lane >> 4)) * d + p1 + (w & 1) * 32 + 16 * j +
-                             (lane & 15)];
-    put_tile(sR, vec, v22);
-    put_tile(sR12, vec, v12);
-  } else if (rows) {                                // (the rows above a full panel are all there)
-    double v1[16], v2[16];
-    fetch_tile(A, d, r0, p2, NB, nb2, false, vec, v2);
-    fetch_tile(A, d, r0, p1, NB, NB, false, vec, v1);
-    put_tile(sA2, vec, v2);
-    put_tile(sA1, vec, v1);
-  }
-  factor64_blocked(sR, sRinv, info, p2, first, chain);
-  // R12 = D12 R22^-T and X2 = A2 R22^-T
-  if (chain) {
-    trsm64_blocked(sR12, sR, sRinv);
-  } else {
-    if (first)
-      for (int e = tid; e < NB * NB; e += 256) Rdiag2[e] = sR[e / NB][e % NB];
-    if (rows) trsm64_blocked(sA2, sR, sRinv);
-  }
-  __syncthreads();
-  if (chain) {
-    Quad64 q;
-    quad_zero(q);
-    quad_mfma_64<true>(sR12, sR12, q);              // D11 - R12 R12^T  (R22 is no longer needed)
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) q.c[i][j] = d11.c[i][j] - q.c[i][j];
-    quad_for_each(q, [&](int r, int c, double v) { sR[r][c] = v; });
-  } else {
-    if (rows) {
-      Quad64 q;
-      quad_zero(q);
-      quad_mfma_64<true>(sA2, sR12, q);             // A1 - X2 R12^T
-      quad_for_each(q, [&](int r, int c, double v) { sA1[r][c] -= v; });
-      for (int e = tid; e < NB * NB; e += 256) {    // X2 is finished
-        const int i = e / NB, j = e % NB;
-        if (j < nb2) A[(long)(r0 + i) * d + p2 + j] = sA2[i][j];
-      }
-    }
-    if (first)
-      for (int e = tid; e < NB * NB; e += 256) R12buf[e] = sR12[e / NB][e % NB];
-  }
-  factor64_blocked(sR, sRinv, info, p1, first, chain);
-  if (first && !chain) {
-    for (int e = tid; e < NB * NB; e += 256) Rdiag1[e] = sR[e / NB][e % NB];
-    if (tid == 0) {
-      *pair_flag1 = 0;
-      *pair_flag2 = 1;
-    }
-  }
-  if (!rows) return;
-  if (chain) trsm64_blocked(sA1, sR, sRinv);
-  __syncthreads();
-  for (int e = threadIdx.x; e < NB * NB; e += kPairThreads) {
-    const int i = e / NB, j = e % NB;
-    A[(long)(r0 + i) * d + p1 + j] = sA1[i][j];
-  }
 }
 
 // Trailing update with the panel columns [k0, k0 + Kd):  A[i][j] -= sum_k A[i][k] A[j][k]  on the
@@ -853,16 +841,17 @@ __device__ __forceinline__ void gemm64_col_sources(const double* base, long ld, 
   }
 }
 
-// q += A B over n_stage slices (all 256 threads, kGemm64LdsBytes of dynamic LDS)
+// q += A B over n_stage slices (all 256 threads, kGemm64LdsBytes of dynamic LDS from byte `base` on; the two teams
+// of 512 threads keep step on rings of their own)
 template <bool B_ROWS>
 __device__ __forceinline__ void gemm64_accumulate(const double* const (&src_a)[2], const double* const (&src_b)[2],
-                                                  long step_a, long step_b, int n_stage, Quad64& q) {
+                                                  long step_a, long step_b, int n_stage, Quad64& q, unsigned base = 0u) {
   extern __shared__ __align__(16) double gemm128_lds[];
   typedef __attribute__((address_space(3))) double lds_f64;
   if (n_stage <= 0) return;
   const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const unsigned lds0 = (unsigned)(size_t)(lds_f64*)gemm128_lds + (unsigned)w * 2048u;
+  const int w = __builtin_amdgcn_readfirstlane(team_wave());
+  const unsigned lds0 = (unsigned)(size_t)(lds_f64*)gemm128_lds + base + (unsigned)w * 2048u;
   const int last = n_stage - 1;
   // slices past the last are requested as the last again, into slots nobody reads any more: the number of
   // outstanding requests, which the waits count, is the same in every iteration
@@ -880,7 +869,7 @@ __device__ __forceinline__ void gemm64_accumulate(const double* const (&src_a)[2
   const unsigned b_row = (unsigned)(((w & 1) * 32 + l15) * 128) + sw;
   const unsigned b_col = (unsigned)(kq * 512 + (w & 1) * 256 + l15 * 8);
   const unsigned b_sel[2] = {b_col + (unsigned)((kq & 1) * 128), b_col + (unsigned)(((kq & 1) ^ 1) * 128)};
-  const char* const lds_bytes = reinterpret_cast<const char*>(gemm128_lds);
+  const char* const lds_bytes = reinterpret_cast<const char*>(gemm128_lds) + base;
 #pragma unroll
   for (int s = 0; s < kRing64 - 1; ++s) request(s);
   for (int s = 0; s < n_stage; ++s) {
@@ -910,6 +899,424 @@ __device__ __forceinline__ void gemm64_accumulate(const double* const (&src_a)[2
     }
   }
   wait_all_vm();                                       // nothing may still be writing LDS when the work-group ends
+}
+
+// ---- the factor and its inverse in one sweep over the panel pairs -----------------------------
+// With pairs t = 0, 1, .. from the right (128 columns p_t .. each, L_t = R[0:p_t, p_t ..] above the diagonal block), the
+// inverse grows from the bottom: with V[i, c] = sum_s R[i, s] X[s, c] over the pairs s that are done,
+//     X[p_t, p_t] = R[p_t, p_t]^-1,     X[p_t, c] = -X[p_t, p_t] V[p_t, c],     V[0:p_t, c] += L_t X[p_t, c]   (c >= p_t).
+// The factorisation waits only for its next 128 columns.  So the launch of pair t carries, beside the chain of the
+// diagonal block, which occupies one compute unit per 64 rows above it,
+//     the inverse of pair t - 1's diagonal block, the update of all columns left of pair t by L_{t-1}, and the
+//     update of V by L_{t-2} X[p_{t-2}, :],
+// the short launch behind it, which updates the columns of pair t + 1 by L_t, carries X[p_{t-1}, c].  All of
+// these are products of depth 128 on 64 x 64 tiles.  L_t goes to a ring of three buffers and X[p_t, :] to one of two,
+// and to U at once; V lives in A, in the places that the factorisation has left.
+//
+// A hosted work-group of 512 threads works on two tiles at a time, one per team, in step (they share the barriers of
+// the 64-tile engine).
+constexpr size_t kPairLdsBytes = (size_t)(4 * NB * (NB + 1) + 2 * NB * 16) * sizeof(double);
+constexpr int kPairThreads = 512;
+constexpr int kPairCols = 2 * NB;
+static_assert(2 * kGemm64LdsBytes <= kPairLdsBytes, "two rings");
+
+// tile t of the upper triangle, column by column
+__device__ __forceinline__ void upper_tile(int t, int& i, int& j) {
+  j = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+  while (j * (j + 1) / 2 > t) --j;
+  while ((j + 1) * (j + 2) / 2 <= t) ++j;
+  i = t - j * (j + 1) / 2;
+}
+
+struct Hosted {
+  int inv_p;                      // first column of the pair to invert, -1: none
+  const double *inv_r1, *inv_r2, *inv_r12;
+  double* inv_x;                  // X[inv_p, :], leading dimension ld
+  float* U;                       // d x d
+  int d;
+  const double* Lu;               // trailing update by Lu: tiles (i <= j), j in blocks [0, u1), but for the first u_skip
+  int u1, u_skip;
+  const double *Lv, *Xv;          // V += Lv Xv: rows of blocks [0, bv), columns of blocks [bv, P)
+  int bv, P;
+
+  __host__ __device__ int n_update() const { return u1 * (u1 + 1) / 2 - u_skip; }
+  __host__ __device__ int n_v() const { return bv * (P - bv); }
+  __host__ __device__ int pairs() const { return (n_update() + n_v() + 1) / 2; }
+  __host__ __device__ int items() const { return (inv_p >= 0 ? 1 : 0) + pairs(); }
+
+  __device__ __forceinline__ void invert(int ld) const {
+    extern __shared__ __align__(16) double gemm128_lds[];
+    typedef double Row[NB + 1];
+    const int team = team_id(), tid = team_tid();
+    Row* sR = reinterpret_cast<Row*>(gemm128_lds) + team * NB;
+    Row* sV = reinterpret_cast<Row*>(gemm128_lds) + (2 + team) * NB;
+    double v[16];
+    const double* src = team ? inv_r2 : inv_r1;
+    fetch_tile64(src, [](int, int) { return true; }, [](int i, int j) { return (long)i * NB + j; }, v);
+    put_tile64(sR, v);
+    for (int e = tid; e < NB * NB; e += 256)                    // (the inversion leaves the blocks below the diagonal alone)
+      if ((e >> 6) > (e & 63)) sV[e >> 6][e & 63] = 0.0;
+    if (team == 0) fetch_tile64(inv_r12, [](int, int) { return true; }, [](int i, int j) { return (long)i * NB + j; }, v);
+    invert64(sR, sV);
+    Row* const s0 = reinterpret_cast<Row*>(gemm128_lds);        // R12; X11 in s0 + 2 NB, X22 in s0 + 3 NB
+    if (team == 0) put_tile64(s0, v);
+    __syncthreads();
+    Quad64 q;
+    if (team == 0) {                                            // R12 X22
+      quad_zero(q);
+      quad_mfma_64<false>(s0, s0 + 3 * NB, q);
+      quad_for_each(q, [&](int r, int c, double x) { (s0 + NB)[r][c] = x; });
+    }
+    __syncthreads();
+    auto put = [&](int i, int j, double x) {                    // row i, column j of the pair's block
+      inv_x[(long)i * ld + inv_p + j] = x;
+      if (inv_p + i < d && inv_p + j < d) U[(long)(inv_p + i) * d + inv_p + j] = (float)x;
+    };
+    if (team == 0) {                                            // -X11 (R12 X22)
+      quad_zero(q);
+      quad_mfma_64<false>(s0 + 2 * NB, s0 + NB, q);
+      quad_for_each(q, [&](int r, int c, double x) { put(r, NB + c, -x); });
+    }
+    for (int e = tid; e < NB * NB; e += 256) {
+      const int i = e / NB, j = e % NB;
+      put(team * NB + i, team * NB + j, sV[i][j]);
+      if (team) inv_x[(long)(NB + i) * ld + inv_p + j] = 0.0;   // left of X22: part of the operand X[p, p]
+    }
+  }
+
+  // Tile number t: of the trailing update, then of V.
+  struct Tile {
+    double* C;                      // its place in A
+    const double* a[2];             // sources of slice 0
+    const double* b[2];
+    long step_b;                    // elements from slice to slice of b
+    bool update, store, diag, begun;
+  };
+  __device__ __forceinline__ Tile tile(double* __restrict__ A, int ld, int t, int w, int lane) const {
+    Tile x;
+    const int n_u = n_update(), n_all = n_u + n_v();
+    x.store = t < n_all;
+    if (!x.store) t = n_all - 1;
+    x.update = t < n_u;                                         // (uniform over a team)
+    if (x.update) {
+      int i, j;
+      upper_tile(t + u_skip, i, j);
+      const int row0 = i * NB, col0 = j * NB;
+      x.C = A + (long)row0 * ld + col0;
+      x.diag = row0 == col0;
+      x.begun = true;
+      gemm64_row_sources(Lu, kPairCols, row0, row0 + NB, 0, w, lane, x.a);
+      gemm64_row_sources(Lu, kPairCols, col0, col0 + NB, 0, w, lane, x.b);
+      x.step_b = kGemmK;
+    } else {
+      t -= n_u;
+      const int cols = P - bv, row0 = t / cols * NB, cb = bv + t % cols;
+      x.C = A + (long)row0 * ld + cb * NB;
+      x.diag = false;
+      x.begun = cb >= bv + 2;                                   // the pair's own columns begin here
+      gemm64_row_sources(Lv, kPairCols, row0, row0 + NB, 0, w, lane, x.a);
+      gemm64_col_sources(Xv, ld, 0, cb * NB, w, lane, x.b);
+      x.step_b = (long)kGemmK * ld;
+    }
+    return x;
+  }
+
+  // Tiles first, first + step, ... of this team, the slices of all of them one stream through the ring: the first
+  // slices and the old values of the next tile are on their way while the present one is multiplied.
+  __device__ __forceinline__ void tiles(double* __restrict__ A, int ld, int first, int step, int count) const {
+    extern __shared__ __align__(16) double gemm128_lds[];
+    typedef __attribute__((address_space(3))) double lds_f64;
+    if (count <= 0) return;
+    constexpr int kSlices = kPairCols / kGemmK;                 // of a tile
+    const int team = team_id(), lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(team_wave());
+    const unsigned ring = team * (unsigned)kGemm64LdsBytes;
+    const unsigned lds0 = (unsigned)(size_t)(lds_f64*)gemm128_lds + ring + (unsigned)w * 2048u;
+    auto request = [&](const Tile& x, int s) {
+      const unsigned slot = lds0 + (unsigned)(s % kRing64) * kStage64Bytes;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) dma_1k_f64(x.a[j] + s * kGemmK, slot + j * 1024u);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) dma_1k_f64(x.b[j] + s * x.step_b, slot + kOp64Bytes + j * 1024u);
+    };
+    const int l15 = lane & 15, kq = lane >> 4;
+    const unsigned sw = (unsigned)((((kq >> 1) ^ (l15 >> 1)) << 4) | ((kq & 1) << 3));
+    const unsigned a_row = (unsigned)(((w >> 1) * 32 + l15) * 128) + sw;
+    const unsigned b_row = (unsigned)(((w & 1) * 32 + l15) * 128) + sw;
+    const unsigned b_col = (unsigned)(kq * 512 + (w & 1) * 256 + l15 * 8);
+    const unsigned b_sel[2] = {b_col + (unsigned)((kq & 1) * 128), b_col + (unsigned)(((kq & 1) ^ 1) * 128)};
+    const char* const lds_bytes = reinterpret_cast<const char*>(gemm128_lds) + ring;
+    const int r0 = (w >> 1) * 32 + kq, c0 = (w & 1) * 32 + l15; // this lane's results: rows r0 + 16 i + 4 r, columns c0 + 16 j
+    double old[16];
+    auto load_old = [&](const Tile& x) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) old[8 * i + 4 * j + r] = x.C[(long)(r0 + 16 * i + 4 * r) * ld + c0 + 16 * j];
+    };
+    Tile x = tile(A, ld, first, w, lane), y = x;
+#pragma unroll
+    for (int s = 0; s < kRing64 - 1; ++s) request(x, s);
+    load_old(x);
+    for (int n = 0; n < count; ++n) {
+      // the last tile is followed by itself: requests into slots that nobody reads any more
+      if (n + 1 < count) y = tile(A, ld, first + (n + 1) * step, w, lane);
+      Quad64 q;
+      quad_zero(q);
+#pragma unroll
+      for (int s = 0; s < kSlices; ++s) {
+        asm volatile("" ::: "memory");
+        // lgkmcnt 0: this wavefront's reads of slice s - 1, whose slot is next.  vmcnt: slice s has landed.  Younger than
+        // its four requests are those of two slices (8) and, up to slice 2, which was requested under the tile before,
+        // the 16 stores of that tile and the 16 old values of this one.
+        if (s > 2) __builtin_amdgcn_s_waitcnt(8 | 0x0070);
+        else if (n == 0) __builtin_amdgcn_s_waitcnt(8 | (1 << 14) | 0x0070);      // 24
+        else __builtin_amdgcn_s_waitcnt(8 | (2 << 14) | 0x0070);                  // 40
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        const char* st = lds_bytes + (unsigned)(s % kRing64) * kStage64Bytes;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          double a[2], b[2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            a[i] = *reinterpret_cast<const double*>(st + (a_row ^ (unsigned)(32 * t)) + i * 2048);
+            const unsigned off = x.update ? (b_row ^ (unsigned)(32 * t)) + i * 2048u : b_sel[i] + t * 2048u;
+            b[i] = *reinterpret_cast<const double*>(st + kOp64Bytes + off);
+          }
+          if (t == 0) {                                         // behind the first reads, ahead of the products
+            if (s + kRing64 - 1 < kSlices) request(x, s + kRing64 - 1);
+            else request(y, s + kRing64 - 1 - kSlices);
+          }
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              q.c[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], q.c[i][j], 0, 0, 0);
+        }
+      }
+      if (!x.store) break;                                      // a team's last, when the tiles are odd in number
+      // (every lane stores, below the diagonal what it read: the waits count on 16 stores)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const double v = q.c[i][j][r], o = x.begun ? old[8 * i + 4 * j + r] : 0.0;
+            const int row = r0 + 16 * i + 4 * r, col = c0 + 16 * j;
+            double z = x.update ? o - v : o + v;
+            if (x.diag && col < row) z = o;
+            x.C[(long)row * ld + col] = z;
+          }
+      x = y;
+      if (n + 1 < count) load_old(x);
+    }
+    wait_all_vm();                                              // nothing may still be writing LDS when the work-group ends
+  }
+
+  __device__ __forceinline__ void run(double* __restrict__ A, int ld, int wg, int n_wg) const {
+    if (inv_p >= 0) {                                           // the longest item: a work-group of its own
+      if (wg == 0) {
+        invert(ld);
+        if (n_wg > 1) return;
+        __syncthreads();
+      } else {
+        --wg;
+        --n_wg;
+      }
+    }
+    if (wg < pairs()) tiles(A, ld, 2 * wg + team_id(), 2 * n_wg, (pairs() - wg + n_wg - 1) / n_wg);
+  }
+};
+
+__global__ __launch_bounds__(kPairThreads) void hosted_kernel(double* __restrict__ A, int ld, Hosted host) {
+  host.run(A, ld, blockIdx.x, gridDim.x);
+}
+
+// The short launch between two pairs, one 64 x 64 tile per work-group of 256 threads: first the tiles (i <= j), j in blocks
+// [u0, u0 + 2), of the update by Lu (n_u of them), then X[xp, c] = -X[xp, xp] V[xp, c] for the column blocks c from xc0 on
+// (n_x tiles), then tiles of the update by the L before Lu, from the left, that the launch before left out.
+__global__ __launch_bounds__(256, 2) void pair_link_kernel(double* __restrict__ A, int ld, const double* __restrict__ Lu,
+                                                           int u0, int n_u, double* __restrict__ X, int xp, int xc0,
+                                                           int n_x, const double* __restrict__ Lold,
+                                                           float* __restrict__ U, int d) {
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(team_wave());
+  Quad64 q;
+  quad_zero(q);
+  const double* src_a[2];
+  const double* src_b[2];
+  const bool old_update = (int)blockIdx.x >= n_u + n_x;
+  if ((int)blockIdx.x < n_u || old_update) {
+    int j = (int)blockIdx.x <= u0 ? u0 : u0 + 1, i = (int)blockIdx.x <= u0 ? blockIdx.x : blockIdx.x - (u0 + 1);
+    if (old_update) {
+      upper_tile(blockIdx.x - n_u - n_x, i, j);
+      Lu = Lold;
+    }
+    double* const C = A + (long)i * NB * ld + j * NB;
+    double old[16];
+    int n = 0;
+    quad_for_each(q, [&](int r, int c, double) { old[n++] = C[(long)r * ld + c]; });
+    __builtin_amdgcn_sched_barrier(0);
+    gemm64_row_sources(Lu, kPairCols, i * NB, i * NB + NB, 0, w, lane, src_a);
+    gemm64_row_sources(Lu, kPairCols, j * NB, j * NB + NB, 0, w, lane, src_b);
+    gemm64_accumulate<true>(src_a, src_b, kGemmK, kGemmK, kPairCols / kGemmK, q);
+    n = 0;
+    quad_for_each(q, [&](int r, int c, double v) {
+      if (i < j || c >= r) C[(long)r * ld + c] = old[n] - v;
+      ++n;
+    });
+    return;
+  }
+  const int t = blockIdx.x - n_u, half = t & 1, c0 = (xc0 + (t >> 1)) * NB, r0 = half * NB;
+  gemm64_row_sources(X, ld, r0, r0 + NB, xp + r0, w, lane, src_a);          // (left of X22 there are zeros)
+  gemm64_col_sources(A, ld, xp + r0, c0, w, lane, src_b);
+  gemm64_accumulate<false>(src_a, src_b, kGemmK, (long)kGemmK * ld, (kPairCols - r0) / kGemmK, q);
+  quad_for_each(q, [&](int r, int c, double v) {
+    X[(long)(r0 + r) * ld + c0 + c] = -v;
+    if (xp + r0 + r < d && c0 + c < d) U[(long)(xp + r0 + r) * d + c0 + c] = (float)-v;
+  });
+}
+
+// Two adjacent 64-column panels -- block b1 (columns p1 ..) and block b2 = b1 + 1 -- in one
+// launch, one work-group per 64 rows above them.  With the diagonal 128 x 128 block
+// [D11 D12; D12^T D22] every work-group computes for itself
+//     D22 = R22 R22^T,   R12 = D12 R22^-T,   D11 - R12 R12^T = R11 R11^T
+// and for its own rows [A1 A2] of the two panels
+//     X2 = A2 R22^-T,    X1 = (A1 - X2 R12^T) R11^-T.
+// The solves and products run on the fp64 matrix cores.  This halves the number of dependent launches of
+// the panel chain (each is short and latency-bound).  A work-group is two teams of four wavefronts.  The first
+// walks the chain of the diagonal block; the second solves the work-group's rows beside it and updates them in the
+// intervals between the barriers of the second factorisation, whose matrix cores are nearly idle, in pieces that end
+// before the chain reaches the next barrier.  So R22 and its inverses stay where they are while R11 is factored in
+// the place of A1, which waits in registers.  Work-group 0 writes R11, R22 to
+// Rdiag and R12 to R12buf (never into A, whose blocks later-scheduled work-groups still read) and sets the
+// pair flag of b2, so that the inverse step puts R12 in place.
+// The rows' results go to L (leading dimension ldl; row r, column j of the pair at L[r ldl + j]).  Work-groups from
+// `panel_wgs` on carry other tiles of the update (Hosted).
+__global__ __launch_bounds__(kPairThreads) void panel_pair_kernel(double* __restrict__ A, int d, int p1,
+                                                                  int nb2, int n_above, double* __restrict__ L, int ldl,
+                                                                  int panel_wgs, Hosted host,
+                                                                  double* __restrict__ Rdiag1,
+                                                                  double* __restrict__ Rdiag2,
+                                                                  double* __restrict__ R12buf,
+                                                                  int* __restrict__ pair_flag1,
+                                                                  int* __restrict__ pair_flag2, int* info) {
+  if ((int)blockIdx.x >= panel_wgs) {
+    host.run(A, d, blockIdx.x - panel_wgs, gridDim.x - panel_wgs);
+    return;
+  }
+  extern __shared__ __align__(16) double gemm128_lds[];
+  double* const dyn = gemm128_lds;
+  typedef double Row[NB + 1];
+  Row* sR22 = reinterpret_cast<Row*>(dyn);          // R22, then A1 - X2 R12^T -> X1
+  Row* sR12 = sR22 + NB;                            // D12 -> R12
+  Row* sR11 = sR12 + NB;                            // D11 - R12 R12^T -> R11
+  Row* sA2 = sR11 + NB;                             // own rows, columns of b2
+  Inv16* sInv22 = reinterpret_cast<Inv16*>(dyn + 4 * NB * (NB + 1));
+  Inv16* sInv11 = sInv22 + NB / 16;
+  const int tid = team_tid();
+  const bool chain = threadIdx.x < 256;             // team of the diagonal block; the other has the rows
+  const int p2 = p1 + NB;
+  const int r0 = blockIdx.x * NB;
+  const bool first = blockIdx.x == 0, rows = n_above > 0;
+  const bool vec = nb2 == NB && d % 2 == 0;
+
+  // D11 (chain) or A1 (rows) in the product's layout, needed after the first factorisation
+  Quad64 base;
+  quad_zero(base);
+  auto fetch_quad = [&](int row0) {
+    const int lane = threadIdx.x & 63, w = team_wave();
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          base.c[i][j][r] = A[(long)(row0 + (w >> 1) * 32 + 16 * i + 4 * r + (lane >> 4)) * d + p1 + (w & 1) * 32 + 16 * j +
+                              (lane & 15)];
+  };
+  if (chain) {
+    double v22[16], v12[16];
+    fetch_tile(A, d, p2, p2, nb2, nb2, true, vec, v22);
+    fetch_tile(A, d, p1, p2, NB, nb2, false, vec, v12);
+    fetch_quad(p1);
+    put_tile(sR22, vec, v22);
+    put_tile(sR12, vec, v12);
+  } else if (rows) {                                // (the rows above a full panel are all there)
+    double v2[16];
+    fetch_tile(A, d, r0, p2, NB, nb2, false, vec, v2);
+    fetch_quad(r0);
+    put_tile(sA2, vec, v2);
+  }
+  factor64_blocked(sR22, sInv22, info, p2, first, chain);
+  f64x4 acc[4];
+  Quad64 q;
+  quad_zero(q);
+  if (chain) {
+    trsm64_blocked(sR12, sR22, sInv22);             // R12 = D12 R22^-T
+  } else if (rows) {                                // X2 = A2 R22^-T
+    trsm_load(acc, sA2);
+    trsm_block_step<3>(acc, sA2, sR22, sInv22);
+    trsm_block_step<2>(acc, sA2, sR22, sInv22);
+  }
+  __syncthreads();
+  if (chain) {
+    quad_mfma_64<true>(sR12, sR12, q);              // D11 - R12 R12^T
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) q.c[i][j] = base.c[i][j] - q.c[i][j];
+    quad_for_each(q, [&](int r, int c, double v) { sR11[r][c] = v; });
+  } else if (rows) {
+    trsm_block_step<1>(acc, sA2, sR22, sInv22);
+    trsm_block_step<0>(acc, sA2, sR22, sInv22);
+  }
+  factor64_blocked(sR11, sInv11, info, p1, first, chain, [&](auto step) {
+    constexpr int S = decltype(step)::value;
+    if constexpr (S == 1) {
+      if (first)
+        for (int e = tid; e < NB * NB; e += 256) {
+          Rdiag2[e] = sR22[e / NB][e % NB];
+          R12buf[e] = sR12[e / NB][e % NB];
+        }
+    }
+    if (!rows) return;
+    if constexpr (S == 0) {                         // X2 is finished
+      for (int e = tid; e < NB * NB; e += 256) {
+        const int i = e / NB, j = e % NB;
+        if (j < nb2) L[(long)(r0 + i) * ldl + NB + j] = sA2[i][j];
+      }
+    }
+    // A1 - X2 R12^T, in the place of R22
+    if constexpr (S == 2) quad_mfma_64<true, 0, 20>(sA2, sR12, q);
+    if constexpr (S == 4) quad_mfma_64<true, 20, 40>(sA2, sR12, q);
+    if constexpr (S == 6) {
+      quad_mfma_64<true, 40, NB>(sA2, sR12, q);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) q.c[i][j] = base.c[i][j] - q.c[i][j];
+      quad_for_each(q, [&](int r, int c, double v) { sR22[r][c] = v; });
+    }
+  });
+  if (first && !chain) {
+    for (int e = tid; e < NB * NB; e += 256) Rdiag1[e] = sR11[e / NB][e % NB];
+    if (tid == 0) {
+      *pair_flag1 = 0;
+      *pair_flag2 = 1;
+    }
+  }
+  if (!rows) return;
+  if (chain) trsm64_blocked(sR22, sR11, sInv11);
+  __syncthreads();
+  for (int e = threadIdx.x; e < NB * NB; e += kPairThreads) {
+    const int i = e / NB, j = e % NB;
+    L[(long)(r0 + i) * ldl + j] = sR22[i][j];
+  }
 }
 
 // The trailing update on this engine.  Tile order: the hardware deals work-groups to the 8 dies in
@@ -1228,6 +1635,33 @@ struct PrepLayout {
   int P, ldt;
 };
 
+// The sweep over panel pairs: A padded to whole pairs, a ring of three L_t, a ring of two X[p_t, :].
+struct SweepLayout {
+  size_t a_off, l_off, x_off, rdiag_off, r12_off, flag_off, scal_off, total;
+  int n_pair, ld;
+};
+static SweepLayout sweep_layout(int d) {
+  SweepLayout L;
+  L.n_pair = bpdq_ceil_div(d, kPairCols);
+  L.ld = L.n_pair * kPairCols;
+  size_t off = 0;
+  L.a_off = off;     off += (size_t)L.ld * L.ld * sizeof(double);
+  L.l_off = off;     off += (size_t)3 * L.ld * kPairCols * sizeof(double);
+  L.x_off = off;     off += (size_t)2 * L.ld * kPairCols * sizeof(double);
+  L.rdiag_off = off; off += (size_t)2 * L.n_pair * NB * NB * sizeof(double);
+  L.r12_off = off;   off += (size_t)2 * L.n_pair * NB * NB * sizeof(double);
+  L.flag_off = off;  off += bpdq_align_up((size_t)2 * L.n_pair * sizeof(int), 256);
+  L.scal_off = off;  off += 256;
+  L.total = off;
+  return L;
+}
+// One panel has nothing to pair or to hide (d <= 64: 46 us by pairs, 24 to 27 by panels).  From there on the pairs are
+// quicker or even (192: 92 us against 89, 384: 139 against 164, 3584: 1288 against 1830, 6016: 4412 against 4919, 6500:
+// 5620 against 6638) until a pass over A per 128 columns costs more than the chain that it hides (7168: 7415 against 6987,
+// 8192: 11547 against 9750).  The line lies where multiples of 64, for which the panels have the faster inversion, cross.
+constexpr int kSweepMin = NB + 1, kSweepMax = 6656;
+static bool sweep_pays(int d) { return d >= kSweepMin && d <= kSweepMax; }
+
 static PrepLayout prep_layout(int d) {
   PrepLayout L;
   L.P = bpdq_ceil_div(d, NB);
@@ -1271,9 +1705,94 @@ static int launch_trailing(hipStream_t st, double* A, int d, int k0, int depth, 
 
 using namespace bpdq;
 
+static int prepare_by_pairs(const float* H, int d, float damp, float* U, unsigned char* dead, int* info, char* base,
+                            hipStream_t stream) {
+  const SweepLayout L = sweep_layout(d);
+  const int ld = L.ld, P = 2 * L.n_pair, n = L.n_pair;
+  double* A = reinterpret_cast<double*>(base + L.a_off);
+  double* ring = reinterpret_cast<double*>(base + L.l_off);
+  double* X = reinterpret_cast<double*>(base + L.x_off);
+  double* Rdiag = reinterpret_cast<double*>(base + L.rdiag_off);
+  double* R12 = reinterpret_cast<double*>(base + L.r12_off);
+  double* scal = reinterpret_cast<double*>(base + L.scal_off);
+  int* flag = reinterpret_cast<int*>(base + L.flag_off);
+  BPDQ_HIP_TRY(bpdq_lds_limit<&panel_pair_kernel>(kPairLdsBytes));
+  BPDQ_HIP_TRY(bpdq_lds_limit<&hosted_kernel>(kPairLdsBytes));
+  BPDQ_HIP_TRY(bpdq_lds_limit<&pair_link_kernel>(kGemm64LdsBytes));
+  hipLaunchKernelGGL(prep_diag_kernel, dim3(1), dim3(1024), 0, stream, H, d, damp, dead, scal, info);
+  BPDQ_LAUNCH_CHECK();
+  hipLaunchKernelGGL(prep_load_kernel, dim3(P, P), dim3(256), 0, stream, H, d, scal, A, ld, U);
+  BPDQ_LAUNCH_CHECK();
+  auto first_block = [&](int t) { return 2 * (n - 1 - t); };
+  auto l_slot = [&](int t) { return ring + (size_t)(t % 3) * ld * kPairCols; };
+  auto x_slot = [&](int t) { return X + (size_t)(t % 2) * ld * kPairCols; };
+  // beside the pair t: the inverse of pair t - 1, the update of the columns left of t by L_{t-1}, V by X[p_{t-2}, :]
+  auto beside = [&](int t) {
+    Hosted h{};
+    h.inv_p = -1;
+    h.P = P;
+    h.U = U;
+    h.d = d;
+    if (t >= 1) {
+      const int b = first_block(t - 1);
+      h.inv_p = b * NB;
+      h.inv_r1 = Rdiag + (size_t)b * NB * NB;
+      h.inv_r2 = Rdiag + (size_t)(b + 1) * NB * NB;
+      h.inv_r12 = R12 + (size_t)(b + 1) * NB * NB;
+      h.inv_x = x_slot(t - 1);
+      h.Lu = l_slot(t - 1);
+      h.u1 = t < n ? first_block(t) : 0;
+    }
+    if (t >= 2) {
+      h.Lv = l_slot(t - 2);
+      h.Xv = x_slot(t - 2);
+      h.bv = first_block(t - 2);
+    }
+    return h;
+  };
+  // one work-group to a compute unit
+  auto hosted_wgs = [&](const Hosted& h, int taken) {
+    const int left = 256 - taken > 64 ? 256 - taken : 64;
+    return h.items() < left ? h.items() : left;
+  };
+  // Tiles of the update to leave to the link launch: it has one tile on most compute units and takes a second at 3 us,
+  // a round of tiles beside the pair, once there are more than two, takes 10.
+  auto left_over = [&](const Hosted& h, int taken) {
+    const int w = (256 - taken > 64 ? 256 - taken : 64) - (h.inv_p >= 0 ? 1 : 0);
+    const int rounds = bpdq_ceil_div(h.pairs(), w), over = 2 * (h.pairs() - (rounds - 1) * w);
+    const int may = h.u1 > 2 ? (h.u1 - 2) * (h.u1 - 1) / 2 : 0;       // not of the columns that the link updates
+    return rounds > 2 && over <= 256 && over <= may ? over : 0;
+  };
+  // behind the pair t: the columns of pair t + 1 by L_t, X[p_{t-1}, :] right of its own columns, what was left over
+  auto link = [&](int t, int n_old) -> int {
+    const int u0 = t + 1 < n ? first_block(t + 1) : 0, n_u = t + 1 < n ? 2 * u0 + 3 : 0;
+    const int xb = t >= 1 ? first_block(t - 1) : P, n_x = t >= 1 ? 2 * (P - xb - 2) : 0;
+    if (n_u + n_x + n_old == 0) return 0;
+    hipLaunchKernelGGL(pair_link_kernel, dim3(n_u + n_x + n_old), dim3(256), kGemm64LdsBytes, stream, A, ld, l_slot(t), u0,
+                       n_u, t >= 1 ? x_slot(t - 1) : X, xb * NB, xb + 2, n_x, t >= 1 ? l_slot(t - 1) : ring, U, d);
+    BPDQ_LAUNCH_CHECK();
+    return 0;
+  };
+  for (int t = 0; t < n; ++t) {
+    const int b = first_block(t), panel = b > 0 ? b : 1;
+    Hosted h = beside(t);
+    h.u_skip = left_over(h, panel);
+    hipLaunchKernelGGL(panel_pair_kernel, dim3(panel + hosted_wgs(h, panel)), dim3(kPairThreads), kPairLdsBytes, stream, A, ld,
+                       b * NB, NB, b, l_slot(t), kPairCols, panel, h, Rdiag + (size_t)b * NB * NB,
+                       Rdiag + (size_t)(b + 1) * NB * NB, R12 + (size_t)(b + 1) * NB * NB, flag + b, flag + b + 1, info);
+    BPDQ_LAUNCH_CHECK();
+    BPDQ_TRY(link(t, h.u_skip));
+  }
+  const Hosted h = beside(n);
+  hipLaunchKernelGGL(hosted_kernel, dim3(hosted_wgs(h, 0)), dim3(kPairThreads), kPairLdsBytes, stream, A, ld, h);
+  BPDQ_LAUNCH_CHECK();
+  return link(n, 0);
+}
+
 extern "C" size_t bpdq_prepare_workspace_bytes(int d_in) {
   if (d_in <= 0) return 0;
-  return prep_layout(d_in).total;
+  const size_t a = prep_layout(d_in).total, b = sweep_pays(d_in) ? sweep_layout(d_in).total : 0;
+  return a > b ? a : b;
 }
 
 extern "C" int bpdq_prepare(const float* H, int d_in, float damp, float* U, unsigned char* dead,
@@ -1288,6 +1807,8 @@ extern "C" int bpdq_prepare(const float* H, int d_in, float damp, float* U, unsi
   const PrepLayout L = prep_layout(d_in);
   if (ws_bytes < L.total) return -8;
   char* base = static_cast<char*>(ws);
+  if (sweep_pays(d_in) && ws_bytes >= sweep_layout(d_in).total)
+    return prepare_by_pairs(H, d_in, damp, U, dead, info, base, stream);
   double* A = reinterpret_cast<double*>(base + L.a_off);
   double* tmp = reinterpret_cast<double*>(base + L.tmp_off);
   double* Rdiag = reinterpret_cast<double*>(base + L.rdiag_off);
@@ -1305,7 +1826,7 @@ extern "C" int bpdq_prepare(const float* H, int d_in, float damp, float* U, unsi
 
   hipLaunchKernelGGL(prep_diag_kernel, dim3(1), dim3(1024), 0, stream, H, d, damp, dead, scal, info);
   BPDQ_LAUNCH_CHECK();
-  hipLaunchKernelGGL(prep_load_kernel, dim3(P, P), dim3(256), 0, stream, H, d, scal, A);
+  hipLaunchKernelGGL(prep_load_kernel, dim3(P, P), dim3(256), 0, stream, H, d, scal, A, d, static_cast<float*>(nullptr));
   BPDQ_LAUNCH_CHECK();
 
   // outer panels of kOuter blocks, from the right; inside one, 64-column panels from the right
@@ -1319,7 +1840,7 @@ extern "C" int bpdq_prepare(const float* H, int d_in, float damp, float* U, unsi
         const int b1 = p - 1, p1 = b1 * NB;
         const int nb2 = (d - p * NB < NB) ? d - p * NB : NB;
         hipLaunchKernelGGL(panel_pair_kernel, dim3(b1 > 0 ? b1 : 1), dim3(kPairThreads), kPairLdsBytes, stream,
-                           A, d, p1, nb2, b1, Rdiag + (size_t)b1 * NB * NB,
+                           A, d, p1, nb2, b1, A + p1, d, b1 > 0 ? b1 : 1, Hosted{}, Rdiag + (size_t)b1 * NB * NB,
                            Rdiag + (size_t)p * NB * NB, R12buf + (size_t)p * NB * NB,
                            pair_flag + b1, pair_flag + p, info);
         first_blk = b1;

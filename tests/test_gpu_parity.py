@@ -1169,6 +1169,70 @@ def test_prepare_tile64_paths(dev, d):
     assert np.linalg.norm(Un - Uref) / np.linalg.norm(Uref) < 1e-7
 
 
+@pytest.mark.parametrize("d", [65, 127, 128, 129, 191, 256, 257, 383, 385, 640, 1001])
+def test_prepare_by_pairs_is_prepare_by_panels(dev, d):
+    """Widths around the 128-column pairs, and 65, the smallest that is done by pairs.  With a workspace that is too small
+    for the padded matrix of the pairs, the panels of 64 columns do the same, odd and ragged widths included.  Both are
+    64-bit computations of the same U, whose rounding to fp32 may fall either way in a few entries (d 2^-53 times the
+    condition, 1e4 here, against 2^-24); the workspaces hold NaN, H is overwritten, and the same pivot is reported."""
+    print(f"prepare d_in={d} (pairs and panels)", flush=True)
+    g = torch.Generator(device=dev)
+    g.manual_seed(57 + d)
+    X = torch.randn((2 * d + 64, d), device=dev, generator=g, dtype=torch.float64)
+    X *= torch.logspace(-1.0, 1.0, d, device=dev, dtype=torch.float64)[None, :]
+    X[:, d // 3] = 0.0
+    H = (X.t().contiguous() @ X).float()
+    bad = H.clone()
+    bad[d // 2, d // 2] = -1.0
+    lib, blocks = bq.load(), -(-d // 64)
+    align = lambda n: -(-n // 256) * 256
+    panels = (align(8 * d * d) + align(8 * d * 64 * ((blocks + 1) // 2)) + 2 * align(8 * blocks * 64 * 64)
+              + align(4 * blocks) + 256)
+    full = lib.bpdq_prepare_workspace_bytes(d)
+    assert panels < full
+    got = []
+    for size in (full, full - 256, panels):
+        for h in (H, bad):
+            U, dead = h.clone(), torch.full((d,), 7, dtype=torch.uint8, device=dev)
+            info = torch.full((1,), -7, dtype=torch.int32, device=dev)
+            ws = torch.full((size // 8,), float("nan"), dtype=torch.float64, device=dev)
+            assert lib.bpdq_prepare(U.data_ptr(), d, 0.01, U.data_ptr(), dead.data_ptr(), info.data_ptr(), ws.data_ptr(),
+                                    size, bq._stream()) == 0
+            got.append((U.cpu().numpy(), dead.cpu().numpy(), int(info.item())))
+    assert lib.bpdq_prepare(H.data_ptr(), d, 0.01, U.data_ptr(), None, info.data_ptr(), ws.data_ptr(), panels - 256,
+                            bq._stream()) == -8
+    Hn = np.triu(H.double().cpu().numpy())
+    Uref, _, _ = orc.prepare(Hn + np.triu(Hn, 1).T, float(np.float32(0.01)))
+    for i in (0, 2, 4):
+        U, dead, info = got[i]
+        assert info == 0 and got[i + 1][2] == got[1][2] > 0
+        assert dead[d // 3] == 1 and dead.sum() == 1 and np.array_equal(dead, got[i + 1][1])
+        assert np.count_nonzero(np.tril(U, -1)) == 0
+        assert np.linalg.norm(U - Uref) / np.linalg.norm(Uref) < 1e-7
+        assert np.linalg.norm(U - got[4][0]) / np.linalg.norm(Uref) < 1e-9
+
+
+@pytest.mark.parametrize("d", [6656, 6657, 6700])
+def test_prepare_at_the_widest_pairs(dev, d):
+    """The widest matrix that is done by pairs and the narrowest that are not: U on sampled columns through
+    U^T U (H + lambda I) = I."""
+    print(f"prepare d_in={d} (pairs to panels)", flush=True)
+    g = torch.Generator(device=dev)
+    g.manual_seed(d)
+    X = torch.randn((2 * d, d), device=dev, generator=g)
+    H = (X.t().contiguous() @ X).triu()
+    H += H.triu(1).t()
+    U, dead, info = bq.bpdq_prepare(H, 0.01)
+    assert int(info.item()) == 0 and int(dead.sum().item()) == 0
+    assert float(torch.tril(U, diagonal=-1).abs().max()) == 0.0
+    idx = torch.cat([torch.arange(0, d, 97, device=dev), torch.arange(d - 140, d, device=dev)])
+    Ht = H.double()
+    Ht.diagonal().add_(0.01 * float(H.diagonal().mean()))
+    R = U.double().T @ (U.double() @ Ht[:, idx])
+    R[idx, torch.arange(len(idx), device=dev)] -= 1.0
+    assert float(R.abs().max()) < 1e-5
+
+
 @pytest.mark.parametrize("d", [4672, 8256, 1088, 4700])
 def test_prepare_wide_tile_paths_defining_property(dev, d):
     """Widths around the switches to the 128 x 128 tile kernels: the factorisation takes them from

@@ -11,7 +11,8 @@ import pytest
 from paper_2602_04163_amd import build
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-KERNELS = ("syrk_trailing128_kernel", "syrk_trailing64_kernel", "tri_inverse_level128_kernel", "tri_inverse_level64_kernel")
+KERNELS = ("syrk_trailing128_kernel", "syrk_trailing64_kernel", "tri_inverse_level128_kernel", "tri_inverse_level64_kernel",
+           "pair_link_kernel", "hosted_kernel")
 
 
 @pytest.mark.skipif(shutil.which(HIPCC) is None, reason="no hipcc")
