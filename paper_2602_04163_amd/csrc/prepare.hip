@@ -7,11 +7,10 @@
 // inverse (2/3 d^3 flops) and Ht^-1 is never formed.  Everything runs in fp64 inside the
 // workspace; the result is rounded to fp32 once, on output.
 //
-// Two ways to do it.  From 65 to 6656 columns, where the chain of the panels bounds the time, the factor and its inverse in
-// one sweep over pairs of 64-column panels from the right (prepare_by_pairs): while a pair is factored by a few
-// work-groups, the others of the same launch update what the next pairs need only later and build the rows of the inverse
-// behind it (3584 columns: 1912 -> 1288 us; 8192 would take 11.5 ms instead of 9.8).  Otherwise, and with a workspace
-// of only the size that this needs, the factor first and then the inverse:
+// Two ways to do it.  From 65 to 12288 columns the factor and its inverse in one sweep over pairs of 64-column panels from
+// the right (prepare_by_pairs): while a pair is factored by a few work-groups, the others of the same launch update what
+// the next pairs need only later and build the rows of the inverse behind it (3584 columns: 1912 -> 1270 us; 8192: 9950
+// -> 8160).  Otherwise, and with a workspace of only the size that this needs, the factor first and then the inverse:
 //   factor : right-looking over 64-column panels from the right, two panels per launch: every
 //            panel work-group factors the two diagonal blocks for itself (in LDS, by panels of
 //            16 columns) and solves its 64 rows of R12 R22^T = A12.  The trailing update
@@ -698,6 +697,10 @@ struct Acc128 {
 __device__ __forceinline__ void dma_1k_f64(const double* gptr, unsigned lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_addr), "v"(gptr) : "memory");
 }
+// ... from base (uniform) + off bytes (per lane)
+__device__ __forceinline__ void dma_1k(const char* base, unsigned off, unsigned lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(off), "s"(base) : "memory");
+}
 __device__ __forceinline__ void wait_all_vm() {
   __builtin_amdgcn_s_waitcnt(0x0070 | 0x0f00);      // vmcnt 0; expcnt / lgkmcnt at their maxima
 }
@@ -907,26 +910,23 @@ __device__ __forceinline__ void gemm64_accumulate(const double* const (&src_a)[2
 //     X[p_t, p_t] = R[p_t, p_t]^-1,     X[p_t, c] = -X[p_t, p_t] V[p_t, c],     V[0:p_t, c] += L_t X[p_t, c]   (c >= p_t).
 // The factorisation waits only for its next 128 columns.  So the launch of pair t carries, beside the chain of the
 // diagonal block, which occupies one compute unit per 64 rows above it,
-//     the inverse of pair t - 1's diagonal block, the update of all columns left of pair t by L_{t-1}, and the
-//     update of V by L_{t-2} X[p_{t-2}, :],
+//     the inverse of pair t - 1's diagonal block, updates of the columns left of pair t by the L up to L_{t-1}, and
+//     updates of V by the L X up to L_{t-2} X[p_{t-2}, :],
 // the short launch behind it, which updates the columns of pair t + 1 by L_t, carries X[p_{t-1}, c].  All of
-// these are products of depth 128 on 64 x 64 tiles.  L_t goes to a ring of three buffers and X[p_t, :] to one of two,
-// and to U at once; V lives in A, in the places that the factorisation has left.
+// these are products of depth 128 on 64 x 64 tiles; a tile may wait for several pairs and take their products in one
+// visit (Hosted::plan).  L_t and X[p_t, :] go to rings, X to U at once; V lives in A, in the places that the
+// factorisation has left.
 //
 // A hosted work-group of 512 threads works on two tiles at a time, one per team, in step (they share the barriers of
-// the 64-tile engine).
+// the 64-tile engine).  A launch with nothing else (8192 columns, half of the pairs done) runs at 44 TFLOP/s with one pair
+// a visit, 46 with two, 55 with eight; without any loads or LDS reads it would reach 61.  It ran at 41, 41 and 50 before
+// the operands were read ahead over the barriers, the requests went behind the products and the old values of a tile had
+// their registers to themselves (a copy of them in the loop waits for memory); that all operands came from one place in
+// L2 made no difference.
 constexpr size_t kPairLdsBytes = (size_t)(4 * NB * (NB + 1) + 2 * NB * 16) * sizeof(double);
 constexpr int kPairThreads = 512;
 constexpr int kPairCols = 2 * NB;
 static_assert(2 * kGemm64LdsBytes <= kPairLdsBytes, "two rings");
-
-// tile t of the upper triangle, column by column
-__device__ __forceinline__ void upper_tile(int t, int& i, int& j) {
-  j = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
-  while (j * (j + 1) / 2 > t) --j;
-  while ((j + 1) * (j + 2) / 2 <= t) ++j;
-  i = t - j * (j + 1) / 2;
-}
 
 struct Hosted {
   int inv_p;                      // first column of the pair to invert, -1: none
@@ -934,15 +934,84 @@ struct Hosted {
   double* inv_x;                  // X[inv_p, :], leading dimension ld
   float* U;                       // d x d
   int d;
-  const double* Lu;               // trailing update by Lu: tiles (i <= j), j in blocks [0, u1), but for the first u_skip
-  int u1, u_skip;
-  const double *Lv, *Xv;          // V += Lv Xv: rows of blocks [0, bv), columns of blocks [bv, P)
-  int bv, P;
+  const double *L, *X;            // rings: pair s in slot s % (every + 2)
+  int t, n, every;                // beside pair t of n
+  // Update of A: tiles (i <= j) of the column pairs whose turn it is, u_far of them, from the left, every 2 `every`
+  // blocks from u_b on, then of pair t + 1; n_u tiles, but for the first u_skip.  By the pairs [lo, t).
+  int u_b, u_far, n_u_far, n_u, u_skip, u_lo, u_lo_next;
+  // V: row pairs likewise, then pair t - 1; all columns of the pairs before t - 1.  By the pairs [lo, t - 1).
+  int v_b, v_far, n_v, v_lo, v_lo_next;
+  int n_early, head;              // work-groups that start with the panel's, and the rounds that are theirs alone
 
-  __host__ __device__ int n_update() const { return u1 * (u1 + 1) / 2 - u_skip; }
-  __host__ __device__ int n_v() const { return bv * (P - bv); }
-  __host__ __device__ int pairs() const { return (n_update() + n_v() + 1) / 2; }
-  __host__ __device__ int items() const { return (inv_p >= 0 ? 1 : 0) + pairs(); }
+  __host__ __device__ int first_block(int s) const { return 2 * (n - 1 - s); }
+  __host__ __device__ int far_tiles(int m) const { return m * (2 * u_b + 3) + 2 * every * m * (m - 1); }
+  __host__ __device__ int n_tiles() const { return n_u - u_skip + n_v; }
+  __host__ __device__ int pairs() const { return (n_tiles() + 1) / 2; }
+
+  // Where the tiles of launch t come from: pair c of the columns is due at t = c - 1, its last time, and before that
+  // whenever (t + c) is a multiple of `every`, and takes what has come since its last time; pair r of the rows of V
+  // is due at t = r + 1 and whenever (t + r) is such a multiple.
+  __host__ void plan() {
+    const int far = n - 1 - (n - 1 + t) % every;                // the leftmost pair whose turn it is
+    const int back_u = (2 * t + 1) % every, back_v = (2 * t - 1) % every;
+    if (t >= 1 && t < n) {
+      u_b = first_block(far);
+      u_far = far >= t + 2 ? (far - (t + 2)) / every + 1 : 0;
+      n_u_far = far_tiles(u_far);
+      n_u = n_u_far + (t + 1 < n ? 2 * first_block(t + 1) + 3 : 0);
+      u_lo = t > every ? t - every : 0;
+      u_lo_next = back_u && t > back_u ? t - back_u : u_lo;
+    }
+    if (t >= 2) {
+      v_b = first_block(far);
+      v_far = far >= t ? (far - t) / every + 1 : 0;
+      n_v = 2 * (2 * (t - 1)) * (v_far + 1);
+      v_lo = t - 1 > every ? t - 1 - every : 0;
+      v_lo_next = back_v && t - 1 > back_v ? t - 1 - back_v : v_lo;
+    }
+  }
+
+  // Tile number x (of the update, then of V): its block and the pairs [lo, hi] whose contributions it takes.
+  struct Place {
+    int i, j, lo, hi;
+    bool update, begun;
+  };
+  __device__ __forceinline__ Place place(int x) const {
+    Place p;
+    p.update = x < n_u - u_skip;                                // (uniform over a team)
+    if (p.update) {
+      x += u_skip;
+      int b;
+      if (x < n_u_far) {
+        const float f = (float)(2 * u_b + 3 - 2 * every);
+        int m = (int)((sqrtf(f * f + (float)(8 * every) * (float)x) - f) / (float)(4 * every));
+        while (far_tiles(m) > x) --m;
+        while (far_tiles(m + 1) <= x) ++m;
+        x -= far_tiles(m);
+        b = u_b + 2 * every * m;
+        p.lo = u_lo;
+      } else {
+        x -= n_u_far;
+        b = first_block(t + 1);
+        p.lo = u_lo_next;
+      }
+      p.i = x <= b ? x : x - (b + 1);
+      p.j = x <= b ? b : b + 1;
+      p.hi = t - 1;
+      p.begun = true;
+    } else {
+      x -= n_u - u_skip;
+      const int cols = 2 * (t - 1), row = x / cols, m = row >> 1;
+      p.i = (m < v_far ? v_b + 2 * every * m : first_block(t - 1)) + (row & 1);
+      p.j = first_block(t - 2) + x % cols;
+      p.lo = m < v_far ? v_lo : v_lo_next;
+      const int from = n - 1 - (p.j >> 1);                      // V begins with the pair of these columns
+      p.begun = from < p.lo;
+      if (!p.begun) p.lo = from;
+      p.hi = t - 2;
+    }
+    return p;
+  }
 
   __device__ __forceinline__ void invert(int ld) const {
     extern __shared__ __align__(16) double gemm128_lds[];
@@ -984,60 +1053,78 @@ struct Hosted {
     }
   }
 
-  // Tile number t: of the trailing update, then of V.
+  // (Pointers are the same for all lanes, whose 32-bit offsets stay: a request takes no vector arithmetic.)
   struct Tile {
-    double* C;                      // its place in A
-    const double* a[2];             // sources of slice 0
-    const double* b[2];
-    long step_b;                    // elements from slice to slice of b
+    char* C;                        // its place in A
+    const char *a, *b;              // sources of slice 0, but for the slot of the rings
+    long step_b;                    // bytes from slice to slice of b
+    unsigned of_b[2];               // (the lane's)
+    int from, lo, hi;               // pairs [lo, hi]; those before lo are multiplied to keep step, and dropped
     bool update, store, diag, begun;
   };
-  __device__ __forceinline__ Tile tile(double* __restrict__ A, int ld, int t, int w, int lane) const {
+  __device__ __forceinline__ Tile tile(double* __restrict__ A, int ld, int number) const {
     Tile x;
-    const int n_u = n_update(), n_all = n_u + n_v();
-    x.store = t < n_all;
-    if (!x.store) t = n_all - 1;
-    x.update = t < n_u;                                         // (uniform over a team)
-    if (x.update) {
-      int i, j;
-      upper_tile(t + u_skip, i, j);
-      const int row0 = i * NB, col0 = j * NB;
-      x.C = A + (long)row0 * ld + col0;
-      x.diag = row0 == col0;
-      x.begun = true;
-      gemm64_row_sources(Lu, kPairCols, row0, row0 + NB, 0, w, lane, x.a);
-      gemm64_row_sources(Lu, kPairCols, col0, col0 + NB, 0, w, lane, x.b);
-      x.step_b = kGemmK;
-    } else {
-      t -= n_u;
-      const int cols = P - bv, row0 = t / cols * NB, cb = bv + t % cols;
-      x.C = A + (long)row0 * ld + cb * NB;
-      x.diag = false;
-      x.begun = cb >= bv + 2;                                   // the pair's own columns begin here
-      gemm64_row_sources(Lv, kPairCols, row0, row0 + NB, 0, w, lane, x.a);
-      gemm64_col_sources(Xv, ld, 0, cb * NB, w, lane, x.b);
-      x.step_b = (long)kGemmK * ld;
+    const int n_all = n_tiles();
+    x.store = number < n_all;
+    const Place p = place(x.store ? number : n_all - 1);
+    const int other = number ^ 1;                               // of the other team
+    int len = p.hi - p.lo + 1;
+    if (other < n_all) {
+      const Place o = place(other);
+      if (o.hi - o.lo + 1 > len) len = o.hi - o.lo + 1;
     }
+    x.from = __builtin_amdgcn_readfirstlane(p.hi - len + 1);
+    x.lo = __builtin_amdgcn_readfirstlane(p.lo);
+    x.hi = p.hi;
+    x.update = p.update;
+    x.begun = p.begun;
+    const int row0 = __builtin_amdgcn_readfirstlane(p.i) * NB, col0 = __builtin_amdgcn_readfirstlane(p.j) * NB;
+    x.C = reinterpret_cast<char*>(A + (long)row0 * ld + col0);
+    x.diag = row0 == col0;
+    x.a = reinterpret_cast<const char*>(L + (long)row0 * kPairCols);
+    x.b = reinterpret_cast<const char*>(x.update ? L + (long)col0 * kPairCols : X + col0);
+    x.step_b = (x.update ? 1 : ld) * (long)(kGemmK * sizeof(double));
     return x;
   }
+  __device__ __forceinline__ long slot(int s, int ld) const { return (long)(s % (every + 2)) * ld * kPairCols; }
 
-  // Tiles first, first + step, ... of this team, the slices of all of them one stream through the ring: the first
-  // slices and the old values of the next tile are on their way while the present one is multiplied.
-  __device__ __forceinline__ void tiles(double* __restrict__ A, int ld, int first, int step, int count) const {
+  // This team's tiles, the slices of all of them one stream through the ring: the first slices and the old values of
+  // the next tile are on their way while the present one is multiplied.
+  __device__ __forceinline__ void tiles(double* __restrict__ A, int ld, int wg, int n_wg) const {
+    const int n = pairs(), alone = n_early * head, early = wg < n_early && wg < n ? min(head, (n - wg + n_early - 1) / n_early) : 0;
+    const int count = early + (alone + wg < n ? (n - alone - wg + n_wg - 1) / n_wg : 0);
+    auto number = [&](int k) {
+      return 2 * (k < early ? wg + k * n_early : alone + wg + (k - early) * n_wg) + team_id();
+    };
     extern __shared__ __align__(16) double gemm128_lds[];
     typedef __attribute__((address_space(3))) double lds_f64;
     if (count <= 0) return;
-    constexpr int kSlices = kPairCols / kGemmK;                 // of a tile
+    constexpr int kSlices = kPairCols / kGemmK;                 // of a tile and a pair
     const int team = team_id(), lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(team_wave());
     const unsigned ring = team * (unsigned)kGemm64LdsBytes;
     const unsigned lds0 = (unsigned)(size_t)(lds_f64*)gemm128_lds + ring + (unsigned)w * 2048u;
-    auto request = [&](const Tile& x, int s) {
-      const unsigned slot = lds0 + (unsigned)(s % kRing64) * kStage64Bytes;
+    unsigned of_rows[2], of_cols[2];                            // this lane's bytes, as in gemm64_{row,col}_sources
 #pragma unroll
-      for (int j = 0; j < 2; ++j) dma_1k_f64(x.a[j] + s * kGemmK, slot + j * 1024u);
+    for (int j = 0; j < 2; ++j) {
+      const int r = 16 * w + 8 * j + (lane >> 3), k = 4 * w + 2 * j + (lane >> 5);
+      of_rows[j] = (unsigned)(r * kPairCols + 2 * ((lane & 7) ^ ((r >> 1) & 7))) * 8u;
+      of_cols[j] = (unsigned)(k * ld + 2 * ((lane & 31) ^ ((lane >> 5) << 3))) * 8u;
+    }
+    auto request = [&](const Tile& x, long off, int s) {
+      const unsigned at = lds0 + (unsigned)(s % kRing64) * kStage64Bytes;
+      const char* const a = x.a + off + s * (long)(kGemmK * sizeof(double));
+      const char* const b = x.b + off + s * x.step_b;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) dma_1k_f64(x.b[j] + s * x.step_b, slot + kOp64Bytes + j * 1024u);
+      for (int j = 0; j < 2; ++j) dma_1k(a, of_rows[j], at + j * 1024u);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) dma_1k(b, x.of_b[j], at + kOp64Bytes + j * 1024u);
+    };
+    auto tile_at = [&](int k) {
+      Tile x = tile(A, ld, number(k));
+#pragma unroll
+      for (int j = 0; j < 2; ++j) x.of_b[j] = x.update ? of_rows[j] : of_cols[j];
+      return x;
     };
     const int l15 = lane & 15, kq = lane >> 4;
     const unsigned sw = (unsigned)((((kq >> 1) ^ (l15 >> 1)) << 4) | ((kq & 1) << 3));
@@ -1048,87 +1135,130 @@ struct Hosted {
     const char* const lds_bytes = reinterpret_cast<const char*>(gemm128_lds) + ring;
     const int r0 = (w >> 1) * 32 + kq, c0 = (w & 1) * 32 + l15; // this lane's results: rows r0 + 16 i + 4 r, columns c0 + 16 j
     double old[16];
+    const unsigned of_result = (unsigned)(r0 * ld + c0) * 8u;
+    const long row4 = 4l * ld * (long)sizeof(double);
+    auto result = [&](const Tile& x, int i, int j, int r) {
+      return reinterpret_cast<double*>(x.C + (4 * i + r) * row4 + of_result) + 16 * j;
+    };
     auto load_old = [&](const Tile& x) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) old[8 * i + 4 * j + r] = x.C[(long)(r0 + 16 * i + 4 * r) * ld + c0 + 16 * j];
+          for (int r = 0; r < 4; ++r) old[8 * i + 4 * j + r] = *result(x, i, j, r);
     };
-    Tile x = tile(A, ld, first, w, lane), y = x;
+    auto slot_of = [&](const Tile& x, int pair) { return slot(pair > x.lo ? pair : x.lo, ld) * (long)sizeof(double); };
+    Tile x = tile_at(0), y = x;
+    int pair = x.from, left = count;                            // tiles left, this one included
+    long off = slot_of(x, pair);
 #pragma unroll
-    for (int s = 0; s < kRing64 - 1; ++s) request(x, s);
+    for (int s = 0; s < kRing64 - 1; ++s) request(x, off, s);
     load_old(x);
-    for (int n = 0; n < count; ++n) {
-      // the last tile is followed by itself: requests into slots that nobody reads any more
-      if (n + 1 < count) y = tile(A, ld, first + (n + 1) * step, w, lane);
-      Quad64 q;
-      quad_zero(q);
+    // The operands of the next four products are read while the present four are multiplied, so the barrier of slice
+    // s + 1 lies in the middle of slice s, with products before and behind it that need nothing.
+    // vmcnt there: slice s + 1 has landed.  Younger than its four requests are those of slice s + 2 (4) and, in the
+    // first two slices of a tile, its 16 old values and the 16 stores of the tile before.
+    int begin = 20;
+    Quad64 q;
+    double a[2][2], b[2][2];
+    auto slice = [&](int s) { return lds_bytes + (unsigned)(s % kRing64) * kStage64Bytes; };
+    auto read = [&](const char* st, int t, bool update) {
 #pragma unroll
-      for (int s = 0; s < kSlices; ++s) {
-        asm volatile("" ::: "memory");
-        // lgkmcnt 0: this wavefront's reads of slice s - 1, whose slot is next.  vmcnt: slice s has landed.  Younger than
-        // its four requests are those of two slices (8) and, up to slice 2, which was requested under the tile before,
-        // the 16 stores of that tile and the 16 old values of this one.
-        if (s > 2) __builtin_amdgcn_s_waitcnt(8 | 0x0070);
-        else if (n == 0) __builtin_amdgcn_s_waitcnt(8 | (1 << 14) | 0x0070);      // 24
-        else __builtin_amdgcn_s_waitcnt(8 | (2 << 14) | 0x0070);                  // 40
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        const char* st = lds_bytes + (unsigned)(s % kRing64) * kStage64Bytes;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          double a[2], b[2];
-#pragma unroll
-          for (int i = 0; i < 2; ++i) {
-            a[i] = *reinterpret_cast<const double*>(st + (a_row ^ (unsigned)(32 * t)) + i * 2048);
-            const unsigned off = x.update ? (b_row ^ (unsigned)(32 * t)) + i * 2048u : b_sel[i] + t * 2048u;
-            b[i] = *reinterpret_cast<const double*>(st + kOp64Bytes + off);
-          }
-          if (t == 0) {                                         // behind the first reads, ahead of the products
-            if (s + kRing64 - 1 < kSlices) request(x, s + kRing64 - 1);
-            else request(y, s + kRing64 - 1 - kSlices);
-          }
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-              q.c[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], q.c[i][j], 0, 0, 0);
-        }
+      for (int i = 0; i < 2; ++i) {
+        a[t & 1][i] = *reinterpret_cast<const double*>(st + (a_row ^ (unsigned)(32 * t)) + i * 2048);
+        const unsigned at = update ? (b_row ^ (unsigned)(32 * t)) + i * 2048u : b_sel[i] + t * 2048u;
+        b[t & 1][i] = *reinterpret_cast<const double*>(st + kOp64Bytes + at);
       }
-      if (!x.store) break;                                      // a team's last, when the tiles are odd in number
-      // (every lane stores, below the diagonal what it read: the waits count on 16 stores)
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto multiply = [&](int t) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
+          q.c[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t & 1][i], b[t & 1][j], q.c[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(8 | (1 << 14) | 0x0070);         // 24: slice 0 of the first tile
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    read(slice(0), 0, x.update);
+    for (;;) {                                                  // tiles
+      quad_zero(q);
+      for (;;) {                                                // pairs (a loop of its own: the old values stay in place)
+        // what comes next: the tile's next pair, or the next tile.  The last is followed by itself: requests into slots
+        // that nobody reads any more
+        const bool ends = pair == x.hi;
+        int next = pair + 1;
+        if (ends) {
+          if (left > 1) y = tile_at(count - left + 1);
+          next = y.from;
+        }
+        const long next_off = slot_of(y, next);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const double v = q.c[i][j][r], o = x.begun ? old[8 * i + 4 * j + r] : 0.0;
-            const int row = r0 + 16 * i + 4 * r, col = c0 + 16 * j;
-            double z = x.update ? o - v : o + v;
-            if (x.diag && col < row) z = o;
-            x.C[(long)row * ld + col] = z;
-          }
+        for (int s = 0; s < kSlices; ++s) {
+          read(slice(s), 1, x.update);
+          multiply(0);
+          read(slice(s), 2, x.update);
+          multiply(1);
+          asm volatile("" ::: "memory");
+          __builtin_amdgcn_s_waitcnt(0xC07F);                     // lgkmcnt 0: on every path
+          if (s > 1 || begin == 4) __builtin_amdgcn_s_waitcnt(4 | 0x0070);
+          else if (begin == 20) __builtin_amdgcn_s_waitcnt(4 | (1 << 14) | 0x0070);
+          else __builtin_amdgcn_s_waitcnt(4 | (2 << 14) | 0x0070);                  // 36
+          __builtin_amdgcn_s_barrier();                           // slice s - 1 is read out, by all
+          asm volatile("" ::: "memory");
+          read(slice(s), 3, x.update);
+          multiply(2);
+          if (s + kRing64 - 1 < kSlices) request(x, off, s + kRing64 - 1);
+          else request(y, next_off, s + kRing64 - 1 - kSlices);
+          read(slice(s + 1), 0, s + 1 < kSlices ? x.update : y.update);
+          multiply(3);
+        }
+        off = next_off;
+        const bool dropped = pair < x.lo;
+        pair = next;
+        if (ends) break;
+        if (dropped) quad_zero(q);
+        begin = 4;
+      }
+      if (!x.store) break;                                      // a team's last, when the tiles are odd in number
+      // (every lane stores, below the diagonal what it read: the waits count on 16 stores)
+      const double sign = x.update ? -1.0 : 1.0;
+      auto store = [&](auto value) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) *result(x, i, j, r) = value(i, j, r, old[8 * i + 4 * j + r]);
+      };
+      if (x.diag)
+        store([&](int i, int j, int r, double o) { return c0 + 16 * j < r0 + 16 * i + 4 * r ? o : o - q.c[i][j][r]; });
+      else if (x.begun)
+        store([&](int i, int j, int r, double o) { return fma(sign, q.c[i][j][r], o); });
+      else
+        store([&](int i, int j, int r, double) { return q.c[i][j][r]; });
+      if (--left == 0) break;
       x = y;
-      if (n + 1 < count) load_old(x);
+      load_old(x);
+      begin = 36;
     }
     wait_all_vm();                                              // nothing may still be writing LDS when the work-group ends
   }
 
   __device__ __forceinline__ void run(double* __restrict__ A, int ld, int wg, int n_wg) const {
-    if (inv_p >= 0) {                                           // the longest item: a work-group of its own
+    if (inv_p >= 0) {                                           // it counts as a work-group that starts late
       if (wg == 0) {
         invert(ld);
-        if (n_wg > 1) return;
         __syncthreads();
-      } else {
-        --wg;
-        --n_wg;
+        wg = n_wg;
       }
+      --wg;
     }
-    if (wg < pairs()) tiles(A, ld, 2 * wg + team_id(), 2 * n_wg, (pairs() - wg + n_wg - 1) / n_wg);
+    tiles(A, ld, wg, n_wg);
   }
 };
 
@@ -1138,32 +1268,39 @@ __global__ __launch_bounds__(kPairThreads) void hosted_kernel(double* __restrict
 
 // The short launch between two pairs, one 64 x 64 tile per work-group of 256 threads: first the tiles (i <= j), j in blocks
 // [u0, u0 + 2), of the update by Lu (n_u of them), then X[xp, c] = -X[xp, xp] V[xp, c] for the column blocks c from xc0 on
-// (n_x tiles), then tiles of the update by the L before Lu, from the left, that the launch before left out.
+// (n_x tiles), then the first tiles of `left`, which the launch before left out.
 __global__ __launch_bounds__(256, 2) void pair_link_kernel(double* __restrict__ A, int ld, const double* __restrict__ Lu,
                                                            int u0, int n_u, double* __restrict__ X, int xp, int xc0,
-                                                           int n_x, const double* __restrict__ Lold,
-                                                           float* __restrict__ U, int d) {
+                                                           int n_x, Hosted left, float* __restrict__ U, int d) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(team_wave());
   Quad64 q;
   quad_zero(q);
   const double* src_a[2];
   const double* src_b[2];
-  const bool old_update = (int)blockIdx.x >= n_u + n_x;
-  if ((int)blockIdx.x < n_u || old_update) {
+  const bool left_out = (int)blockIdx.x >= n_u + n_x;
+  if ((int)blockIdx.x < n_u || left_out) {
     int j = (int)blockIdx.x <= u0 ? u0 : u0 + 1, i = (int)blockIdx.x <= u0 ? blockIdx.x : blockIdx.x - (u0 + 1);
-    if (old_update) {
-      upper_tile(blockIdx.x - n_u - n_x, i, j);
-      Lu = Lold;
+    int lo = 0, hi = 0;
+    if (left_out) {
+      const Hosted::Place p = left.place(blockIdx.x - n_u - n_x);
+      i = p.i;
+      j = p.j;
+      lo = p.lo;
+      hi = p.hi;
     }
     double* const C = A + (long)i * NB * ld + j * NB;
     double old[16];
     int n = 0;
     quad_for_each(q, [&](int r, int c, double) { old[n++] = C[(long)r * ld + c]; });
     __builtin_amdgcn_sched_barrier(0);
-    gemm64_row_sources(Lu, kPairCols, i * NB, i * NB + NB, 0, w, lane, src_a);
-    gemm64_row_sources(Lu, kPairCols, j * NB, j * NB + NB, 0, w, lane, src_b);
-    gemm64_accumulate<true>(src_a, src_b, kGemmK, kGemmK, kPairCols / kGemmK, q);
+    for (int s = lo; s <= hi; ++s) {
+      if (left_out) Lu = left.L + left.slot(s, ld);
+      if (s > lo) __syncthreads();
+      gemm64_row_sources(Lu, kPairCols, i * NB, i * NB + NB, 0, w, lane, src_a);
+      gemm64_row_sources(Lu, kPairCols, j * NB, j * NB + NB, 0, w, lane, src_b);
+      gemm64_accumulate<true>(src_a, src_b, kGemmK, kGemmK, kPairCols / kGemmK, q);
+    }
     n = 0;
     quad_for_each(q, [&](int r, int c, double v) {
       if (i < j || c >= r) C[(long)r * ld + c] = old[n] - v;
@@ -1192,7 +1329,7 @@ __global__ __launch_bounds__(256, 2) void pair_link_kernel(double* __restrict__ 
 // walks the chain of the diagonal block; the second solves the work-group's rows beside it and updates them in the
 // intervals between the barriers of the second factorisation, whose matrix cores are nearly idle, in pieces that end
 // before the chain reaches the next barrier.  So R22 and its inverses stay where they are while R11 is factored in
-// the place of A1, which waits in registers.  Work-group 0 writes R11, R22 to
+// the place of A1, which waits in registers (56 rows of work-groups: 33 -> 24 us).  Work-group 0 writes R11, R22 to
 // Rdiag and R12 to R12buf (never into A, whose blocks later-scheduled work-groups still read) and sets the
 // pair flag of b2, so that the inverse step puts R12 in place.
 // The rows' results go to L (leading dimension ldl; row r, column j of the pair at L[r ldl + j]).  Work-groups from
@@ -1635,19 +1772,26 @@ struct PrepLayout {
   int P, ldt;
 };
 
-// The sweep over panel pairs: A padded to whole pairs, a ring of three L_t, a ring of two X[p_t, :].
+// How many pairs a tile of the update or of V waits for: its old values are read and written once for all of them, but
+// the rounds of tiles are coarser.  Up to 4608 columns the chain has to be filled evenly (3584: 1270 us with one pair,
+// 1300 with two, 1389 with three; 4608: 2101, 2119, 2147), beyond the products take the time (6000: 3893, 3787, 3848;
+// 8192: 8904, 8256, 8142; 10240: 17.2 ms, 15.3, 14.8).
+constexpr int kOnePairMax = 4608, kThreePairsMin = 8192;
+// The sweep over panel pairs: A padded to whole pairs, rings of L_t and of X[p_t, :].
 struct SweepLayout {
   size_t a_off, l_off, x_off, rdiag_off, r12_off, flag_off, scal_off, total;
-  int n_pair, ld;
+  int n_pair, ld, every, slots;
 };
 static SweepLayout sweep_layout(int d) {
   SweepLayout L;
   L.n_pair = bpdq_ceil_div(d, kPairCols);
   L.ld = L.n_pair * kPairCols;
+  L.every = d <= kOnePairMax ? 1 : d < kThreePairsMin ? 2 : 3;
+  L.slots = L.every + 2;
   size_t off = 0;
   L.a_off = off;     off += (size_t)L.ld * L.ld * sizeof(double);
-  L.l_off = off;     off += (size_t)3 * L.ld * kPairCols * sizeof(double);
-  L.x_off = off;     off += (size_t)2 * L.ld * kPairCols * sizeof(double);
+  L.l_off = off;     off += (size_t)L.slots * L.ld * kPairCols * sizeof(double);
+  L.x_off = off;     off += (size_t)L.slots * L.ld * kPairCols * sizeof(double);
   L.rdiag_off = off; off += (size_t)2 * L.n_pair * NB * NB * sizeof(double);
   L.r12_off = off;   off += (size_t)2 * L.n_pair * NB * NB * sizeof(double);
   L.flag_off = off;  off += bpdq_align_up((size_t)2 * L.n_pair * sizeof(int), 256);
@@ -1656,10 +1800,10 @@ static SweepLayout sweep_layout(int d) {
   return L;
 }
 // One panel has nothing to pair or to hide (d <= 64: 46 us by pairs, 24 to 27 by panels).  From there on the pairs are
-// quicker or even (192: 92 us against 89, 384: 139 against 164, 3584: 1288 against 1830, 6016: 4412 against 4919, 6500:
-// 5620 against 6638) until a pass over A per 128 columns costs more than the chain that it hides (7168: 7415 against 6987,
-// 8192: 11547 against 9750).  The line lies where multiples of 64, for which the panels have the faster inversion, cross.
-constexpr int kSweepMin = NB + 1, kSweepMax = 6656;
+// quicker or even (192: 92 us against 89, 384: 139 against 164, 3584: 1270 against 1830, 6016: 3800 against 4919, 8192:
+// 8161 against 9760, 12288: 24.4 ms against 25.4) until a tile's traffic costs more than the chain that it hides (14336:
+// 37.7 ms against 37.8, 16384: 54.8 against 53.4).  Widths off 64 gain more (8191: 8.3 ms against 12.9).
+constexpr int kSweepMin = NB + 1, kSweepMax = 12288;
 static bool sweep_pays(int d) { return d >= kSweepMin && d <= kSweepMax; }
 
 static PrepLayout prep_layout(int d) {
@@ -1724,15 +1868,18 @@ static int prepare_by_pairs(const float* H, int d, float damp, float* U, unsigne
   hipLaunchKernelGGL(prep_load_kernel, dim3(P, P), dim3(256), 0, stream, H, d, scal, A, ld, U);
   BPDQ_LAUNCH_CHECK();
   auto first_block = [&](int t) { return 2 * (n - 1 - t); };
-  auto l_slot = [&](int t) { return ring + (size_t)(t % 3) * ld * kPairCols; };
-  auto x_slot = [&](int t) { return X + (size_t)(t % 2) * ld * kPairCols; };
-  // beside the pair t: the inverse of pair t - 1, the update of the columns left of t by L_{t-1}, V by X[p_{t-2}, :]
+  auto l_slot = [&](int t) { return ring + (size_t)(t % L.slots) * ld * kPairCols; };
+  auto x_slot = [&](int t) { return X + (size_t)(t % L.slots) * ld * kPairCols; };
   auto beside = [&](int t) {
     Hosted h{};
     h.inv_p = -1;
-    h.P = P;
     h.U = U;
     h.d = d;
+    h.L = ring;
+    h.X = X;
+    h.t = t;
+    h.n = n;
+    h.every = L.every;
     if (t >= 1) {
       const int b = first_block(t - 1);
       h.inv_p = b * NB;
@@ -1740,53 +1887,54 @@ static int prepare_by_pairs(const float* H, int d, float damp, float* U, unsigne
       h.inv_r2 = Rdiag + (size_t)(b + 1) * NB * NB;
       h.inv_r12 = R12 + (size_t)(b + 1) * NB * NB;
       h.inv_x = x_slot(t - 1);
-      h.Lu = l_slot(t - 1);
-      h.u1 = t < n ? first_block(t) : 0;
     }
-    if (t >= 2) {
-      h.Lv = l_slot(t - 2);
-      h.Xv = x_slot(t - 2);
-      h.bv = first_block(t - 2);
-    }
+    h.plan();
     return h;
   };
-  // one work-group to a compute unit
-  auto hosted_wgs = [&](const Hosted& h, int taken) {
-    const int left = 256 - taken > 64 ? 256 - taken : 64;
-    return h.items() < left ? h.items() : left;
-  };
+  // One work-group to a compute unit.  Those on the compute units that the panel's work-groups leave have `head` rounds
+  // of tiles to themselves, the time of the chain; what is left then is for all.
+  constexpr int kCus = 256;
+  const int kHead = L.every == 1 ? 3 : 1;
   // Tiles of the update to leave to the link launch: it has one tile on most compute units and takes a second at 3 us,
   // a round of tiles beside the pair, once there are more than two, takes 10.
-  auto left_over = [&](const Hosted& h, int taken) {
-    const int w = (256 - taken > 64 ? 256 - taken : 64) - (h.inv_p >= 0 ? 1 : 0);
-    const int rounds = bpdq_ceil_div(h.pairs(), w), over = 2 * (h.pairs() - (rounds - 1) * w);
-    const int may = h.u1 > 2 ? (h.u1 - 2) * (h.u1 - 1) / 2 : 0;       // not of the columns that the link updates
-    return rounds > 2 && over <= 256 && over <= may ? over : 0;
+  auto spread = [&](Hosted& h, int taken) -> int {              // returns the work-groups
+    h.head = kHead;
+    h.n_early = (kCus - taken > 64 ? kCus - taken : 64) - (h.inv_p >= 0 ? 1 : 0);
+    const int alone = h.n_early * h.head, n_pairs = h.pairs();
+    const bool late = n_pairs > alone;
+    const int rounds = bpdq_ceil_div(late ? n_pairs - alone : n_pairs, late ? kCus : h.n_early);
+    const int over = 2 * ((late ? n_pairs - alone : n_pairs) - (rounds - 1) * (late ? kCus : h.n_early));
+    if (rounds + (late ? h.head : 0) > 2 && over <= 256 && over <= h.n_u_far) h.u_skip = over;   // (not the link's columns)
+    if (h.pairs() > alone) return kCus;
+    return (h.inv_p >= 0 ? 1 : 0) + (h.pairs() < h.n_early ? h.pairs() : h.n_early);
   };
   // behind the pair t: the columns of pair t + 1 by L_t, X[p_{t-1}, :] right of its own columns, what was left over
-  auto link = [&](int t, int n_old) -> int {
+  auto link = [&](int t, Hosted h) -> int {
+    const int n_left = h.u_skip;
+    h.u_skip = 0;
     const int u0 = t + 1 < n ? first_block(t + 1) : 0, n_u = t + 1 < n ? 2 * u0 + 3 : 0;
     const int xb = t >= 1 ? first_block(t - 1) : P, n_x = t >= 1 ? 2 * (P - xb - 2) : 0;
-    if (n_u + n_x + n_old == 0) return 0;
-    hipLaunchKernelGGL(pair_link_kernel, dim3(n_u + n_x + n_old), dim3(256), kGemm64LdsBytes, stream, A, ld, l_slot(t), u0,
-                       n_u, t >= 1 ? x_slot(t - 1) : X, xb * NB, xb + 2, n_x, t >= 1 ? l_slot(t - 1) : ring, U, d);
+    if (n_u + n_x + n_left == 0) return 0;
+    hipLaunchKernelGGL(pair_link_kernel, dim3(n_u + n_x + n_left), dim3(256), kGemm64LdsBytes, stream, A, ld, l_slot(t), u0,
+                       n_u, t >= 1 ? x_slot(t - 1) : X, xb * NB, xb + 2, n_x, h, U, d);
     BPDQ_LAUNCH_CHECK();
     return 0;
   };
   for (int t = 0; t < n; ++t) {
     const int b = first_block(t), panel = b > 0 ? b : 1;
     Hosted h = beside(t);
-    h.u_skip = left_over(h, panel);
-    hipLaunchKernelGGL(panel_pair_kernel, dim3(panel + hosted_wgs(h, panel)), dim3(kPairThreads), kPairLdsBytes, stream, A, ld,
+    const int hosted = spread(h, panel);
+    hipLaunchKernelGGL(panel_pair_kernel, dim3(panel + hosted), dim3(kPairThreads), kPairLdsBytes, stream, A, ld,
                        b * NB, NB, b, l_slot(t), kPairCols, panel, h, Rdiag + (size_t)b * NB * NB,
                        Rdiag + (size_t)(b + 1) * NB * NB, R12 + (size_t)(b + 1) * NB * NB, flag + b, flag + b + 1, info);
     BPDQ_LAUNCH_CHECK();
-    BPDQ_TRY(link(t, h.u_skip));
+    BPDQ_TRY(link(t, h));
   }
-  const Hosted h = beside(n);
-  hipLaunchKernelGGL(hosted_kernel, dim3(hosted_wgs(h, 0)), dim3(kPairThreads), kPairLdsBytes, stream, A, ld, h);
+  Hosted h = beside(n);
+  const int hosted = spread(h, 0);
+  hipLaunchKernelGGL(hosted_kernel, dim3(hosted), dim3(kPairThreads), kPairLdsBytes, stream, A, ld, h);
   BPDQ_LAUNCH_CHECK();
-  return link(n, 0);
+  return link(n, h);
 }
 
 extern "C" size_t bpdq_prepare_workspace_bytes(int d_in) {

@@ -1212,9 +1212,10 @@ def test_prepare_by_pairs_is_prepare_by_panels(dev, d):
         assert np.linalg.norm(U - got[4][0]) / np.linalg.norm(Uref) < 1e-9
 
 
-@pytest.mark.parametrize("d", [6656, 6657, 6700])
-def test_prepare_at_the_widest_pairs(dev, d):
-    """The widest matrix that is done by pairs and the narrowest that are not: U on sampled columns through
+@pytest.mark.parametrize("d", [4608, 4609, 8191, 8192, 12288, 12289, 12416])
+def test_prepare_where_the_pairs_change(dev, d):
+    """The widths where a tile begins to wait for two pairs and for three, the widest matrix that is done by pairs and the
+    narrowest that are not, one ragged and one with an odd number of pairs: U on sampled columns through
     U^T U (H + lambda I) = I."""
     print(f"prepare d_in={d} (pairs to panels)", flush=True)
     g = torch.Generator(device=dev)
