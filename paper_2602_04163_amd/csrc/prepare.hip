@@ -9,8 +9,8 @@
 //
 // Two ways to do it.  From 65 to 12288 columns the factor and its inverse in one sweep over pairs of 64-column panels from
 // the right (prepare_by_pairs): while a pair is factored by a few work-groups, the others of the same launch update what
-// the next pairs need only later and build the rows of the inverse behind it (3584 columns: 1912 -> 1270 us; 8192: 9950
-// -> 8160).  Otherwise, and with a workspace of only the size that this needs, the factor first and then the inverse:
+// the next pairs need only later and build the rows of the inverse behind it (3584 columns: 1912 -> 1224 us; 8192: 9950
+// -> 8074).  Otherwise, and with a workspace of only the size that this needs, the factor first and then the inverse:
 //   factor : right-looking over 64-column panels from the right, two panels per launch: every
 //            panel work-group factors the two diagonal blocks for itself (in LDS, by panels of
 //            16 columns) and solves its 64 rows of R12 R22^T = A12.  The trailing update
@@ -1266,56 +1266,110 @@ __global__ __launch_bounds__(kPairThreads) void hosted_kernel(double* __restrict
   host.run(A, ld, blockIdx.x, gridDim.x);
 }
 
-// The short launch between two pairs, one 64 x 64 tile per work-group of 256 threads: first the tiles (i <= j), j in blocks
-// [u0, u0 + 2), of the update by Lu (n_u of them), then X[xp, c] = -X[xp, xp] V[xp, c] for the column blocks c from xc0 on
-// (n_x tiles), then the first tiles of `left`, which the launch before left out.
+// q += A B like gemm64_accumulate for the upper or lower half of a tile: 32 rows of A (src_a: 8 rows a wavefront),
+// wavefront w has the 16 columns from 16 w on, rows 16 i + 4 r + lane / 16 in q[i][r].
+__device__ __forceinline__ const double* gemm32_row_source(const double* base, long ld, int row0, int k_begin, int w, int lane) {
+  const int r = 8 * w + (lane >> 3);
+  return base + (long)(row0 + r) * ld + k_begin + 2 * ((lane & 7) ^ ((r >> 1) & 7));
+}
+template <bool B_ROWS>
+__device__ __forceinline__ void gemm32_accumulate(const double* src_a, const double* const (&src_b)[2], long step_a,
+                                                  long step_b, int n_stage, f64x4 (&q)[2]) {
+  extern __shared__ __align__(16) double gemm128_lds[];
+  typedef __attribute__((address_space(3))) double lds_f64;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(team_wave());
+  const unsigned lds0 = (unsigned)(size_t)(lds_f64*)gemm128_lds + (unsigned)w * 1024u;
+  const int last = n_stage - 1;
+  auto request = [&](int s) {                          // (slices past the last like there)
+    const unsigned slot = lds0 + (unsigned)(s % kRing64) * kStage64Bytes;
+    const int sc = s < last ? s : last;
+    dma_1k_f64(src_a + sc * step_a, slot);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) dma_1k_f64(src_b[j] + sc * step_b, slot + kOp64Bytes + (unsigned)w * 1024u + j * 1024u);
+  };
+  const int l15 = lane & 15, kq = lane >> 4;
+  const unsigned sw = (unsigned)((((kq >> 1) ^ (l15 >> 1)) << 4) | ((kq & 1) << 3));
+  const unsigned a_row = (unsigned)(l15 * 128) + sw, b_row = (unsigned)((16 * w + l15) * 128) + sw;
+  const unsigned b_col = (unsigned)(kq * 512 + (w ^ (kq & 1)) * 128 + l15 * 8);
+  const char* const lds_bytes = reinterpret_cast<const char*>(gemm128_lds);
+#pragma unroll
+  for (int s = 0; s < kRing64 - 1; ++s) request(s);
+  for (int s = 0; s < n_stage; ++s) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(6 | 0x0070);            // vmcnt 6: all but the two youngest slices; lgkmcnt 0
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const char* st = lds_bytes + (unsigned)(s % kRing64) * kStage64Bytes;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const double b = *reinterpret_cast<const double*>(st + kOp64Bytes + (B_ROWS ? b_row ^ (unsigned)(32 * t) : b_col + t * 2048u));
+      double a[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) a[i] = *reinterpret_cast<const double*>(st + (a_row ^ (unsigned)(32 * t)) + i * 2048);
+      if (t == 0) request(s + kRing64 - 1);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) q[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b, q[i], 0, 0, 0);
+    }
+  }
+  wait_all_vm();                                       // nothing may still be writing LDS when the work-group ends
+}
+
+// The short launch between two pairs, half of a 64 x 64 tile per work-group of 256 threads: first the tiles (i <= j), j in
+// blocks [u0, u0 + 2), of the update by Lu (n_u of them), then X[xp, c] = -X[xp, xp] V[xp, c] for the column blocks c from
+// xc0 on (n_x tiles), then the first tiles of `left`, which the launch before left out.  Its length is that of a tile's
+// products, 512 matrix instructions of 64 cycles on four matrix cores, and a round trip to memory: whole tiles, which
+// leave half of the compute units idle at 3584 columns, took 8.3 us (1270 us for the whole of it, 1224 with halves).
 __global__ __launch_bounds__(256, 2) void pair_link_kernel(double* __restrict__ A, int ld, const double* __restrict__ Lu,
                                                            int u0, int n_u, double* __restrict__ X, int xp, int xc0,
                                                            int n_x, Hosted left, float* __restrict__ U, int d) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(team_wave());
-  Quad64 q;
-  quad_zero(q);
-  const double* src_a[2];
+  const int number = blockIdx.x >> 1, half = (blockIdx.x & 1) * (NB / 2);
+  f64x4 q[2] = {(f64x4){0.0, 0.0, 0.0, 0.0}, (f64x4){0.0, 0.0, 0.0, 0.0}};
+  const int row_of = half + (lane >> 4), col_of = 16 * w + (lane & 15);     // results: rows row_of + 16 i + 4 r of the tile
   const double* src_b[2];
-  const bool left_out = (int)blockIdx.x >= n_u + n_x;
-  if ((int)blockIdx.x < n_u || left_out) {
-    int j = (int)blockIdx.x <= u0 ? u0 : u0 + 1, i = (int)blockIdx.x <= u0 ? blockIdx.x : blockIdx.x - (u0 + 1);
+  const bool left_out = number >= n_u + n_x;
+  if (number < n_u || left_out) {
+    int j = number <= u0 ? u0 : u0 + 1, i = number <= u0 ? number : number - (u0 + 1);
     int lo = 0, hi = 0;
     if (left_out) {
-      const Hosted::Place p = left.place(blockIdx.x - n_u - n_x);
+      const Hosted::Place p = left.place(number - n_u - n_x);
       i = p.i;
       j = p.j;
       lo = p.lo;
       hi = p.hi;
     }
     double* const C = A + (long)i * NB * ld + j * NB;
-    double old[16];
-    int n = 0;
-    quad_for_each(q, [&](int r, int c, double) { old[n++] = C[(long)r * ld + c]; });
+    double old[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) old[e] = C[(long)(row_of + 4 * e) * ld + col_of];
     __builtin_amdgcn_sched_barrier(0);
     for (int s = lo; s <= hi; ++s) {
       if (left_out) Lu = left.L + left.slot(s, ld);
       if (s > lo) __syncthreads();
-      gemm64_row_sources(Lu, kPairCols, i * NB, i * NB + NB, 0, w, lane, src_a);
       gemm64_row_sources(Lu, kPairCols, j * NB, j * NB + NB, 0, w, lane, src_b);
-      gemm64_accumulate<true>(src_a, src_b, kGemmK, kGemmK, kPairCols / kGemmK, q);
+      gemm32_accumulate<true>(gemm32_row_source(Lu, kPairCols, i * NB + half, 0, w, lane), src_b, kGemmK, kGemmK,
+                              kPairCols / kGemmK, q);
     }
-    n = 0;
-    quad_for_each(q, [&](int r, int c, double v) {
-      if (i < j || c >= r) C[(long)r * ld + c] = old[n] - v;
-      ++n;
-    });
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int r = row_of + 4 * e;
+      if (i < j || col_of >= r) C[(long)r * ld + col_of] = old[e] - q[e >> 2][e & 3];
+    }
     return;
   }
-  const int t = blockIdx.x - n_u, half = t & 1, c0 = (xc0 + (t >> 1)) * NB, r0 = half * NB;
-  gemm64_row_sources(X, ld, r0, r0 + NB, xp + r0, w, lane, src_a);          // (left of X22 there are zeros)
-  gemm64_col_sources(A, ld, xp + r0, c0, w, lane, src_b);
-  gemm64_accumulate<false>(src_a, src_b, kGemmK, (long)kGemmK * ld, (kPairCols - r0) / kGemmK, q);
-  quad_for_each(q, [&](int r, int c, double v) {
-    X[(long)(r0 + r) * ld + c0 + c] = -v;
-    if (xp + r0 + r < d && c0 + c < d) U[(long)(xp + r0 + r) * d + c0 + c] = (float)-v;
-  });
+  const int t = number - n_u, r0 = (t & 1) * NB, c0 = (xc0 + (t >> 1)) * NB;
+  gemm64_col_sources(A, ld, xp + r0, c0, w, lane, src_b);                   // (left of X22 there are zeros)
+  gemm32_accumulate<false>(gemm32_row_source(X, ld, r0 + half, xp + r0, w, lane), src_b, kGemmK, (long)kGemmK * ld,
+                           (kPairCols - r0) / kGemmK, q);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int r = r0 + row_of + 4 * e, c = c0 + col_of;
+    const double v = -q[e >> 2][e & 3];
+    X[(long)r * ld + c] = v;
+    if (xp + r < d && c < d) U[(long)(xp + r) * d + c] = (float)v;
+  }
 }
 
 // Two adjacent 64-column panels -- block b1 (columns p1 ..) and block b2 = b1 + 1 -- in one
@@ -1915,7 +1969,7 @@ static int prepare_by_pairs(const float* H, int d, float damp, float* U, unsigne
     const int u0 = t + 1 < n ? first_block(t + 1) : 0, n_u = t + 1 < n ? 2 * u0 + 3 : 0;
     const int xb = t >= 1 ? first_block(t - 1) : P, n_x = t >= 1 ? 2 * (P - xb - 2) : 0;
     if (n_u + n_x + n_left == 0) return 0;
-    hipLaunchKernelGGL(pair_link_kernel, dim3(n_u + n_x + n_left), dim3(256), kGemm64LdsBytes, stream, A, ld, l_slot(t), u0,
+    hipLaunchKernelGGL(pair_link_kernel, dim3(2 * (n_u + n_x + n_left)), dim3(256), kGemm64LdsBytes, stream, A, ld, l_slot(t), u0,
                        n_u, t >= 1 ? x_slot(t - 1) : X, xb * NB, xb + 2, n_x, h, U, d);
     BPDQ_LAUNCH_CHECK();
     return 0;
