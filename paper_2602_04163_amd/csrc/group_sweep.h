@@ -542,7 +542,8 @@ __device__ __forceinline__ void pack_p0(const float* __restrict__ U, int ldu, in
 
 // Request a group's image into LDS (at byte address 0 of the dynamic LDS), 1 KB per instruction, dealt
 // to the four wavefronts; stage_wait() before the barrier that publishes it.  (Assembly, because the
-// compiler would wait for all of it before the first LDS access; M0 is used for nothing else here.)
+// compiler would wait for all of it before the first LDS access; M0 is used for nothing else here, and has
+// to be one wait state old when the load reads it, which the compiler does not see to in assembly: the s_nop.)
 template <int G>
 __device__ __forceinline__ void stage_request(const float* __restrict__ rec, float* sU) {
   typedef __attribute__((address_space(3))) float lds_float;
@@ -551,7 +552,7 @@ __device__ __forceinline__ void stage_request(const float* __restrict__ rec, flo
   constexpr int kKb = (SuLayout<G>::floats() + 255) / 256;
   const unsigned lds0 = (unsigned)(size_t)(lds_float*)sU;
   for (int c = wave; c < kKb; c += kSweepThreads / 64)
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
                  : "s"(lds0 + 1024u * c), "v"(1024u * c + 16u * lane), "s"(rec)
                  : "memory");

@@ -66,9 +66,10 @@ struct SplitF16 {
 
   // One LDS-DMA load: 64 lanes x 16 bytes from `base + voff` (per lane) to the 1 KB of LDS that
   // starts at byte address lds_addr (wave-uniform, handed over in M0; the kernel uses M0 for
-  // nothing else).  Counts as one outstanding vector-memory operation of the wavefront.
+  // nothing else).  Counts as one outstanding vector-memory operation of the wavefront.  M0 has to be
+  // one wait state old when the load reads it, and the compiler does not look into assembly: the s_nop.
   __device__ static __forceinline__ void dma_1k(const uint4* base, unsigned voff, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
                  : "s"(lds_addr), "v"(voff), "s"(base)
                  : "memory");

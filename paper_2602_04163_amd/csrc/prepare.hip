@@ -693,13 +693,14 @@ struct Acc128 {
 };
 
 // 64 lanes x 16 bytes from gptr (per lane) to the 1 KB of LDS at byte address lds_addr (uniform,
-// passed in M0, which these kernels use for nothing else).  One outstanding vector-memory operation.
+// passed in M0, which these kernels use for nothing else).  One outstanding vector-memory operation.  M0 has to be one
+// wait state old when the load reads it, and the compiler does not look into assembly: the s_nop.
 __device__ __forceinline__ void dma_1k_f64(const double* gptr, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_addr), "v"(gptr) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_addr), "v"(gptr) : "memory");
 }
 // ... from base (uniform) + off bytes (per lane)
 __device__ __forceinline__ void dma_1k(const char* base, unsigned off, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(off), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(off), "s"(base) : "memory");
 }
 __device__ __forceinline__ void wait_all_vm() {
   __builtin_amdgcn_s_waitcnt(0x0070 | 0x0f00);      // vmcnt 0; expcnt / lgkmcnt at their maxima
