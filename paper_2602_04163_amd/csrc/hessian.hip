@@ -796,19 +796,28 @@ static size_t hessian_ws_bytes(int kind, bool fine, int n_tok, int d_in) {
   return hessian_ws_layout(kind, fine, hessian_launch_tokens(kind, fine, n_tok, d_in), d_in).total;
 }
 
-// Calls that one launch serves best (hess_small_kernel), and its form.  The lines lie where the two ways take the
-// same time or a little before (us, three launches / one): 64 tokens, 512 channels 18.9 / 4.1, 2048 28.6 / 10.8, 3072
-// 26.9 / 19.2, 4096 28.4 / 31.2; 256 tokens, 1024 channels 19.6 / 10.4, 2048 38.8 / 28.0, 3072 37.7 / 62.2; 512 tokens,
-// 512 channels 17.3 / 9.4, 1024 23.6 / 21.7, 1536 27.9 / 34.7; 1024 tokens, 512 channels 20.8 / 17.4, 768 26.2 / 26.8;
-// 2048 tokens, 384 channels 25.5 / 21.8, 512 28.4 / 36.2.  Small layers take 16 x 16 tiles, which occupy more compute
-// units (256 tokens, 256 channels: 4.5 us, 6.4 with 32 x 32), and more wavefronts the more tokens there are.
+// Calls that one launch serves best (hess_small_kernel), and its form.  Measured on activations that no call has read
+// before (us, three launches / one; on the same ones again the one launch gains up to a third):
+//   64 tokens: 512 channels 18.6 / 4.3, 1024 20.2 / 7.1, 2048 28.7 / 13.3, 3072 26.6 / 23.3.
+//   65 tokens: 384 channels 41.7 / 6.4, 1024 21.7 / 13.0, 1536 23.8 / 21.7, 1728 47.4 / 24.4, beyond which the
+//     256 x 256 tiles are quicker if the channels fill them or barely start another (1792 25.2 / 29.1, 1820 27.7 / 30.6,
+//     2048 30.3 / 34.2; at 160 tokens 33.8 / 34.5, at 192 35.7 / 34.7) and slower if not (1856 31.3 / 29.7, 2044 48.9 / 36.2).
+//   257 tokens: 512 channels 16.4 / 11.1, 704 17.9 / 15.4, 768 18.1 / 27.6: up to 704 every 32 x 32 tile has a compute
+//     unit to itself (253 tiles).  512 tokens: 704 19.7 / 16.0, 768 20.3 / 28.6, 1024 24.2 / 36.0.
+//   513 tokens: 512 channels 18.7 / 18.3 (1024 tokens: 21.1 / 18.6).
+//   1025 tokens: 320 channels 21.1 / 16.9 (220 tiles), 352 21.1 / 26.0, 384 21.3 / 31.1; 2048: 320 25.3 / 17.4, 384 26.0 / 32.1.
+// Small layers take 16 x 16 tiles, which occupy more compute units (256 tokens, 256 channels: 4.5 us, 6.4 with 32 x 32),
+// and more wavefronts the more tokens there are.
 enum SmallForm { kNotSmall, k16x4, k16x8, k16x16, k32x4, k32x8 };
 static SmallForm hessian_small_form(int n_tok, int d_in) {
   if (n_tok <= 64) return d_in <= 512 ? k16x4 : d_in <= 3072 ? k32x4 : kNotSmall;
-  if (n_tok <= 256) return d_in <= 384 ? k16x8 : d_in <= 2048 ? k32x8 : kNotSmall;
-  if (n_tok <= 512) return d_in <= 256 ? k16x16 : d_in <= 512 ? k16x8 : d_in <= 1024 ? k32x8 : kNotSmall;
+  if (n_tok <= 256) {
+    if (d_in <= 384) return k16x8;
+    return d_in <= 1728 || (d_in <= 2048 && (n_tok >= 192 || d_in % 256 >= 64)) ? k32x8 : kNotSmall;
+  }
+  if (n_tok <= 512) return d_in <= 256 ? k16x16 : d_in <= 512 ? k16x8 : d_in <= 704 ? k32x8 : kNotSmall;
   if (n_tok <= 1024) return d_in <= 512 ? k16x16 : kNotSmall;
-  if (n_tok <= 2048) return d_in <= 384 ? k16x16 : kNotSmall;
+  if (n_tok <= 2048) return d_in <= 320 ? k16x16 : kNotSmall;
   return kNotSmall;
 }
 

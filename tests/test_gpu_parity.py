@@ -73,7 +73,9 @@ def test_hessian_small_call_paths(dev, n_tok, d_in):
 @pytest.mark.parametrize("n_tok,d_in", [(1, 4), (3, 516), (64, 512), (64, 3072), (65, 388), (64, 3076), (256, 384),
                                         (255, 2044), (257, 260), (256, 2052), (512, 256), (400, 508), (512, 1024),
                                         (513, 36), (512, 1028), (1024, 512), (1000, 516), (1025, 100), (2048, 384),
-                                        (2047, 388), (2049, 256)])
+                                        (2047, 388), (2049, 256), (65, 1728), (70, 1732), (191, 1792), (192, 1792),
+                                        (65, 1852), (65, 1856), (257, 704), (512, 704), (512, 708), (1025, 320),
+                                        (2048, 320), (2048, 324)])
 def test_hessian_one_launch_calls(dev, n_tok, d_in):
     """Both sides of the lines between one launch and three, at the edges of the tiles and of the tokens a lane
     holds: strided rows, channels far apart in magnitude, a scale, a start that is not zero; the blocks of 32 x 32 on
@@ -96,6 +98,28 @@ def test_hessian_one_launch_calls(dev, n_tok, d_in):
     assert bool(((Hp.double() - want).abs()[whole] <= bound[whole]).all())
     assert torch.equal(Hp[~whole], H0[~whole])
     assert torch.equal(Hs, Hs.t()) and torch.equal(Hs.triu(), Hp.triu())
+
+
+def _hessian_takes_one_launch(X):
+    """Whether the call leaves its workspace alone, as the one launch does (the three write their planes into it)."""
+    d_in = X.shape[1]
+    ws = torch.full((bq.bpdq_hessian_workspace_bytes(*X.shape),), 0xA5, dtype=torch.uint8, device=X.device)
+    bq.bpdq_hessian_accumulate(X, torch.zeros((d_in, d_in), device=X.device), 2.0, True, ws)
+    return bool((ws == 0xA5).all())
+
+
+@pytest.mark.parametrize("n_tok,d_in,one", [(64, 3072, True), (65, 1728, True), (65, 2044, True), (192, 2048, True),
+                                            (257, 704, True), (512, 704, True), (513, 512, True), (1025, 320, True),
+                                            (2048, 320, True), (64, 3076, False), (65, 1792, False), (128, 1820, False),
+                                            (160, 2048, False), (257, 768, False), (400, 1024, False), (512, 708, False),
+                                            (512, 1024, False), (1025, 352, False), (2048, 384, False), (2049, 256, False)])
+def test_hessian_one_launch_only_where_it_is_quicker(dev, n_tok, d_in, one):
+    """Calls whose tiles fill the chip more than once, or whose channels fill 256 x 256 tiles, keep to the three
+    launches: on activations not read before one launch took up to half as long again (512 x 1024: 36 us against 24)."""
+    print(f"hessian one launch or three n_tok={n_tok} d_in={d_in}", flush=True)
+    X = torch.randn((n_tok, d_in), generator=torch.Generator().manual_seed(n_tok)).to(dev)
+    took = _hessian_takes_one_launch(X)
+    assert took == one
 
 
 @pytest.mark.parametrize("n_tok", [100, 300, 4096, 5000])
