@@ -328,9 +328,6 @@ __device__ __forceinline__ int channel_exponent(float m) {
   return e;
 }
 
-// maximum that keeps a NaN (fmaxf drops it)
-__device__ __forceinline__ float nan_max(float m, float x) { return (x <= m) ? m : x; }
-
 __global__ __launch_bounds__(256) void hess_scale_kernel(const float* __restrict__ pmax, int n_split,
                                                          int d_pad, float* __restrict__ mul,
                                                          float* __restrict__ inv) {
@@ -463,8 +460,8 @@ __global__ __launch_bounds__(kFusedThreads) void hess_prepass_f16_kernel(const f
 
 // A whole small call in one launch: one TILE x TILE tile of H (16 or 32) to a work-group, WAVES wavefronts that share
 // the tokens.  A lane holds its tokens of both operands in registers (NI of each), so X is read once per tile; every
-// channel is brought to [2^13, 2^14) like above (the range of the two-halves path; a channel with an infinity or a
-// NaN becomes NaN), and the products go through the fp32 matrix cores in chains of at most kSmallChain tokens, whose
+// channel is brought to [2^13, 2^14) like above (the range of the two-halves path; a channel with an infinity gets the
+// factor NaN, one with a NaN, which the maximum passes over, becomes NaN by its products), and the products go through the fp32 matrix cores in chains of at most kSmallChain tokens, whose
 // sums are added in order, the wavefronts' in 64 bits.  The 32 x 32 blocks on the diagonal come whole, as from the tile kernels; `sym` writes
 // the mirror image instead.  Bound by its latency, one round trip to memory and a reduction, while the tiles fit the
 // chip once; beyond that by reading a tile's channels again for every tile, which the 256 x 256 tiles do not.
@@ -518,13 +515,13 @@ __global__ __launch_bounds__(64 * WAVES) void hess_small_kernel(const float* __r
   // largest magnitude of a channel (tokens past the end repeat the last one)
   float ma = 0.f, mb = 0.f;
 #pragma unroll
-  for (int i = 0; i < NI; ++i) { ma = nan_max(ma, fabsf(a[i])); mb = nan_max(mb, fabsf(b[i])); }
+  for (int i = 0; i < NI; ++i) { ma = fmaxf(ma, fabsf(a[i])); mb = fmaxf(mb, fabsf(b[i])); }
 #pragma unroll
-  for (int x = TILE; x < 64; x *= 2) { ma = nan_max(ma, __shfl_xor(ma, x, 64)); mb = nan_max(mb, __shfl_xor(mb, x, 64)); }
+  for (int x = TILE; x < 64; x *= 2) { ma = fmaxf(ma, __shfl_xor(ma, x, 64)); mb = fmaxf(mb, __shfl_xor(mb, x, 64)); }
   if (kq == 0) { top[wave][0][m] = ma; top[wave][1][m] = mb; }
   __syncthreads();
 #pragma unroll
-  for (int w = 0; w < WAVES; ++w) { ma = nan_max(ma, top[w][0][m]); mb = nan_max(mb, top[w][1][m]); }
+  for (int w = 0; w < WAVES; ++w) { ma = fmaxf(ma, top[w][0][m]); mb = fmaxf(mb, top[w][1][m]); }
   const int ea = channel_exponent(ma), eb = channel_exponent(mb);
   const float sa = (ma < INFINITY) ? ldexpf(1.0f, ea) : NAN, sb = (mb < INFINITY) ? ldexpf(1.0f, eb) : NAN;
   constexpr int kLen = kSmallChain / kPer, kChains = NI > kLen ? NI / kLen : 1;

@@ -137,6 +137,27 @@ def test_hessian_of_activations_that_are_not_finite(dev, n_tok):
     assert torch.equal(H[~nan], clean[~nan])
 
 
+@pytest.mark.parametrize("n_tok,d_in", [(13, 260), (64, 1028), (100, 260), (256, 1028), (300, 260), (300, 516),
+                                        (512, 700), (700, 100), (1500, 260)])
+def test_hessian_one_launch_of_activations_that_are_not_finite(dev, n_tok, d_in):
+    """Every form of the one launch: a channel with an infinity, a NaN (first, last, and followed by larger and smaller
+    values, so that the channel's maximum meets it in every place) or both is NaN, and nothing else changes."""
+    print(f"hessian one launch not finite n_tok={n_tok} d_in={d_in}", flush=True)
+    X = torch.randn((n_tok, d_in), generator=torch.Generator().manual_seed(n_tok + d_in)).to(dev)
+    assert _hessian_takes_one_launch(X)
+    clean = bq.bpdq_hessian_accumulate(X, torch.zeros((d_in, d_in), device=dev), 2.0, True)
+    X[0, 3], X[n_tok - 1, d_in - 1], X[11, 40] = float("inf"), -float("inf"), float("nan")
+    X[0, 60], X[n_tok - 1, 33], X[5, 17], X[6, 17] = float("nan"), float("nan"), 1e30, float("nan")
+    X[2, 90], X[9, 90] = float("inf"), float("nan")
+    X[3, 70], X[8, 70] = float("nan"), -float("inf")
+    H = bq.bpdq_hessian_accumulate(X, torch.zeros((d_in, d_in), device=dev), 2.0, True)
+    bad = torch.zeros(d_in, dtype=torch.bool, device=dev)
+    bad[[3, 17, 33, 40, 60, 70, 90, d_in - 1]] = True
+    nan = bad[:, None] | bad[None, :]
+    assert torch.equal(torch.isnan(H), nan)
+    assert torch.equal(H[~nan], clean[~nan])
+
+
 @pytest.mark.parametrize("n_tok,d_in,n_sized", [(256, 512, 300), (400, 1024, 512), (256, 768, 300)])
 def test_hessian_workspace_of_another_call(dev, n_tok, d_in, n_sized):
     """A short call on a workspace sized for a longer one, where its own finest plan would want more than that:
