@@ -122,16 +122,17 @@ def test_hessian_one_launch_only_where_it_is_quicker(dev, n_tok, d_in, one):
     assert took == one
 
 
-@pytest.mark.parametrize("n_tok", [100, 300, 4096, 5000])
-def test_hessian_of_activations_that_are_not_finite(dev, n_tok):
+@pytest.mark.parametrize("n_tok,d_in", [(100, 2052), (300, 772), (1100, 516), (4096, 260), (5000, 260)])
+def test_hessian_of_activations_that_are_not_finite(dev, n_tok, d_in):
     """An infinity or NaN makes its channel's row and column NaN and touches nothing else, through either pre-pass."""
-    print(f"hessian not finite n_tok={n_tok}", flush=True)
-    X = torch.randn((n_tok, 260), generator=torch.Generator().manual_seed(n_tok)).to(dev)
-    clean = bq.bpdq_hessian_accumulate(X, torch.zeros((260, 260), device=dev), 2.0, True)
-    X[7, 3], X[n_tok - 1, 259], X[11, 100] = float("inf"), -float("inf"), float("nan")
-    H = bq.bpdq_hessian_accumulate(X, torch.zeros((260, 260), device=dev), 2.0, True)
-    bad = torch.zeros(260, dtype=torch.bool, device=dev)
-    bad[[3, 100, 259]] = True
+    print(f"hessian not finite n_tok={n_tok} d_in={d_in}", flush=True)
+    X = torch.randn((n_tok, d_in), generator=torch.Generator().manual_seed(n_tok)).to(dev)
+    assert not _hessian_takes_one_launch(X)
+    clean = bq.bpdq_hessian_accumulate(X, torch.zeros((d_in, d_in), device=dev), 2.0, True)
+    X[7, 3], X[n_tok - 1, d_in - 1], X[11, 100] = float("inf"), -float("inf"), float("nan")
+    H = bq.bpdq_hessian_accumulate(X, torch.zeros((d_in, d_in), device=dev), 2.0, True)
+    bad = torch.zeros(d_in, dtype=torch.bool, device=dev)
+    bad[[3, 100, d_in - 1]] = True
     nan = bad[:, None] | bad[None, :]
     assert torch.equal(torch.isnan(H), nan)
     assert torch.equal(H[~nan], clean[~nan])
@@ -158,10 +159,14 @@ def test_hessian_one_launch_of_activations_that_are_not_finite(dev, n_tok, d_in)
     assert torch.equal(H[~nan], clean[~nan])
 
 
-@pytest.mark.parametrize("n_tok,d_in,n_sized", [(256, 512, 300), (400, 1024, 512), (256, 768, 300)])
-def test_hessian_workspace_of_another_call(dev, n_tok, d_in, n_sized):
+@pytest.mark.parametrize("n_tok,d_in,n_sized,one", [(256, 512, 300, True), (256, 768, 300, True), (400, 1024, 512, False),
+                                                    (300, 1280, 344, False), (512, 1536, 556, False),
+                                                    (1024, 768, 1136, False), (2100, 324, 2401, False)])
+def test_hessian_workspace_of_another_call(dev, n_tok, d_in, n_sized, one):
     """A short call on a workspace sized for a longer one, where its own finest plan would want more than that:
-    it runs on coarser slices, to the same tolerance; a workspace too small for those is refused."""
+    it runs on coarser slices, to the same tolerance, and their sums are rounded in other places, so that the bits
+    tell which plan ran; a workspace too small for those is refused.  A call that takes one launch writes into neither
+    workspace, but asks for the same sizes."""
     print(f"hessian n_tok={n_tok} d_in={d_in} on the workspace of {n_sized} tokens", flush=True)
     have, own = bq.bpdq_hessian_workspace_bytes(n_sized, d_in), bq.bpdq_hessian_workspace_bytes(n_tok, d_in)
     assert have < own
@@ -175,6 +180,7 @@ def test_hessian_workspace_of_another_call(dev, n_tok, d_in, n_sized):
         assert _relfro(H.cpu().numpy(), want.numpy()) < 2e-6
         results.append(H)
     assert torch.equal(results[0], results[1]) and torch.equal(results[2], results[3])
+    assert _hessian_takes_one_launch(X.to(dev)) == one and torch.equal(results[0], results[2]) == one
     planes_only = 4 * ((n_tok + 31) // 32 * 32) * ((d_in + 255) // 256 * 256)
     with pytest.raises(bq.BpdqError):
         bq.bpdq_hessian_accumulate(X.to(dev), torch.zeros((d_in, d_in), device=dev), 2.0, False,
