@@ -1387,10 +1387,10 @@ __global__ __launch_bounds__(256, 2) void pair_link_kernel(double* __restrict__ 
 // the place of A1, which waits in registers (56 rows of work-groups: 33 -> 24 us).  Work-group 0 writes R11, R22 to
 // Rdiag and R12 to R12buf (never into A, whose blocks later-scheduled work-groups still read) and sets the
 // pair flag of b2, so that the inverse step puts R12 in place.
-// The rows' results go to L (leading dimension ldl; row r, column j of the pair at L[r ldl + j]).  Work-groups from
-// `panel_wgs` on carry other tiles of the update (Hosted).
-__global__ __launch_bounds__(kPairThreads) void panel_pair_kernel(double* __restrict__ A, int d, int p1,
-                                                                  int nb2, int n_above, double* __restrict__ L, int ldl,
+// The rows' results go to L (leading dimension ldl; row r, column j of the pair at L[r ldl + j]), which may be their own
+// place in A.  Work-groups from `panel_wgs` on carry other tiles of the update (Hosted).
+__global__ __launch_bounds__(kPairThreads) void panel_pair_kernel(double* A, int d, int p1, int nb2, int n_above,
+                                                                  double* L, int ldl,
                                                                   int panel_wgs, Hosted host,
                                                                   double* __restrict__ Rdiag1,
                                                                   double* __restrict__ Rdiag2,
