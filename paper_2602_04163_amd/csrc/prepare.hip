@@ -1828,10 +1828,11 @@ struct PrepLayout {
 };
 
 // How many pairs a tile of the update or of V waits for: its old values are read and written once for all of them, but
-// the rounds of tiles are coarser.  Up to 4608 columns the chain has to be filled evenly (3584: 1270 us with one pair,
-// 1300 with two, 1389 with three; 4608: 2101, 2119, 2147), beyond the products take the time (6000: 3893, 3787, 3848;
-// 8192: 8904, 8256, 8142; 10240: 17.2 ms, 15.3, 14.8).
-constexpr int kOnePairMax = 4608, kThreePairsMin = 8192;
+// the rounds of tiles are coarser.  By the padded width: up to 4608 columns the chain has to be filled evenly (4608: 2106 us with one pair, 2113
+// with two, 2138 with three; 5120: 2672, 2641, 2645), beyond the products take the time (6016: 3888, 3766, 3787; 6272:
+// 4168 with two, 4166 with three; 6400: 4393, 4383; 6656: 5022 with one, 4832, 4802; 8192: 8905, 8208, 8077, 8362 with
+// four; 12288: 28.7 ms, 25.2, 24.1, 24.3).
+constexpr int kOnePairMax = 4608, kThreePairsMin = 6400;
 // The sweep over panel pairs: A padded to whole pairs, rings of L_t and of X[p_t, :].
 struct SweepLayout {
   size_t a_off, l_off, x_off, rdiag_off, r12_off, flag_off, scal_off, total;
@@ -1841,7 +1842,7 @@ static SweepLayout sweep_layout(int d) {
   SweepLayout L;
   L.n_pair = bpdq_ceil_div(d, kPairCols);
   L.ld = L.n_pair * kPairCols;
-  L.every = d <= kOnePairMax ? 1 : d < kThreePairsMin ? 2 : 3;
+  L.every = L.ld <= kOnePairMax ? 1 : L.ld < kThreePairsMin ? 2 : 3;
   L.slots = L.every + 2;
   size_t off = 0;
   L.a_off = off;     off += (size_t)L.ld * L.ld * sizeof(double);

@@ -1263,7 +1263,7 @@ def test_prepare_by_pairs_is_prepare_by_panels(dev, d):
         assert np.linalg.norm(U - got[4][0]) / np.linalg.norm(Uref) < 1e-9
 
 
-@pytest.mark.parametrize("d", [4608, 4609, 8191, 8192, 12288, 12289, 12416])
+@pytest.mark.parametrize("d", [4608, 4609, 6272, 6273, 6400, 8191, 8192, 12288, 12289, 12416])
 def test_prepare_where_the_pairs_change(dev, d):
     """The widths where a tile begins to wait for two pairs and for three, the widest matrix that is done by pairs and the
     narrowest that are not, one ragged and one with an odd number of pairs: U on sampled columns through
