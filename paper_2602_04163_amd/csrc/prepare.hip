@@ -9,8 +9,8 @@
 //
 // Two ways to do it.  From 65 to 12288 columns the factor and its inverse in one sweep over pairs of 64-column panels from
 // the right (prepare_by_pairs): while a pair is factored by a few work-groups, the others of the same launch update what
-// the next pairs need only later and build the rows of the inverse behind it (3584 columns: 1912 -> 1224 us; 8192: 9950
-// -> 8074).  Otherwise, and with a workspace of only the size that this needs, the factor first and then the inverse:
+// the next pairs need only later and build the rows of the inverse behind it (3584 columns: 1939 -> 1245 us; 8192: 9996
+// -> 8095).  Otherwise, and with a workspace of only the size that this needs, the factor first and then the inverse:
 //   factor : right-looking over 64-column panels from the right, two panels per launch: every
 //            panel work-group factors the two diagonal blocks for itself (in LDS, by panels of
 //            16 columns) and solves its 64 rows of R12 R22^T = A12.  The trailing update
@@ -813,12 +813,12 @@ __device__ __forceinline__ void acc128_for_each_in_row(int i, F f) {
 }
 
 // ---- the same on 64 x 64 tiles ---------------------------------------------------------------
-// For launches with too few 128-tiles to fill the chip: the layers up to 4096 columns, the updates inside
-// an outer block, the lower levels of the inversion tree.  256 threads own 64 x 64 results, wavefront w the
+// For launches with too few 128-tiles to fill the chip: the updates inside an outer block, the K = 512 updates of
+// the last 4096 columns, the lower levels of the inversion tree.  256 threads own 64 x 64 results, wavefront w the
 // 32 x 32 quadrant (w / 2, w % 2) as 2 x 2 tiles.  Such launches are short and their work-groups few, so
 // what bounds them is memory latency: a ring of four slices of 16 (64 KB of LDS, two work-groups per CU)
-// keeps three in flight, against one 64-deep chunk staged through registers.  At d = 3584
-// the trailing updates take 550 us instead of 675 and the inversion products 430 instead of 670.
+// keeps three in flight, against one 64-deep chunk staged through registers (by panels at d = 3584 the trailing
+// updates took 550 us instead of 675 and the inversion products 430 instead of 670).
 // Same images as above; a [k][n] slice has 512-byte rows, two per request.
 constexpr int kRing64 = 4;
 constexpr unsigned kOp64Bytes = NB * kGemmK * sizeof(double);
@@ -845,17 +845,16 @@ __device__ __forceinline__ void gemm64_col_sources(const double* base, long ld, 
   }
 }
 
-// q += A B over n_stage slices (all 256 threads, kGemm64LdsBytes of dynamic LDS from byte `base` on; the two teams
-// of 512 threads keep step on rings of their own)
+// q += A B over n_stage slices (all 256 threads, kGemm64LdsBytes of dynamic LDS)
 template <bool B_ROWS>
 __device__ __forceinline__ void gemm64_accumulate(const double* const (&src_a)[2], const double* const (&src_b)[2],
-                                                  long step_a, long step_b, int n_stage, Quad64& q, unsigned base = 0u) {
+                                                  long step_a, long step_b, int n_stage, Quad64& q) {
   extern __shared__ __align__(16) double gemm128_lds[];
   typedef __attribute__((address_space(3))) double lds_f64;
   if (n_stage <= 0) return;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(team_wave());
-  const unsigned lds0 = (unsigned)(size_t)(lds_f64*)gemm128_lds + base + (unsigned)w * 2048u;
+  const unsigned lds0 = (unsigned)(size_t)(lds_f64*)gemm128_lds + (unsigned)w * 2048u;
   const int last = n_stage - 1;
   // slices past the last are requested as the last again, into slots nobody reads any more: the number of
   // outstanding requests, which the waits count, is the same in every iteration
@@ -873,7 +872,7 @@ __device__ __forceinline__ void gemm64_accumulate(const double* const (&src_a)[2
   const unsigned b_row = (unsigned)(((w & 1) * 32 + l15) * 128) + sw;
   const unsigned b_col = (unsigned)(kq * 512 + (w & 1) * 256 + l15 * 8);
   const unsigned b_sel[2] = {b_col + (unsigned)((kq & 1) * 128), b_col + (unsigned)(((kq & 1) ^ 1) * 128)};
-  const char* const lds_bytes = reinterpret_cast<const char*>(gemm128_lds) + base;
+  const char* const lds_bytes = reinterpret_cast<const char*>(gemm128_lds);
 #pragma unroll
   for (int s = 0; s < kRing64 - 1; ++s) request(s);
   for (int s = 0; s < n_stage; ++s) {
@@ -918,8 +917,8 @@ __device__ __forceinline__ void gemm64_accumulate(const double* const (&src_a)[2
 // visit (Hosted::plan).  L_t and X[p_t, :] go to rings, X to U at once; V lives in A, in the places that the
 // factorisation has left.
 //
-// A hosted work-group of 512 threads works on two tiles at a time, one per team, in step (they share the barriers of
-// the 64-tile engine).  A launch with nothing else (8192 columns, half of the pairs done) runs at 44 TFLOP/s with one pair
+// A hosted work-group of 512 threads works on two tiles at a time, one per team, in step (rings of their own, barriers
+// in common; images and slices of the 64-tile engine).  A launch with nothing else (8192 columns, half of the pairs done) runs at 44 TFLOP/s with one pair
 // a visit, 46 with two, 55 with eight; without any loads or LDS reads it would reach 61.  It ran at 41, 41 and 50 before
 // the operands were read ahead over the barriers, the requests went behind the products and the old values of a tile had
 // their registers to themselves (a copy of them in the loop waits for memory); that all operands came from one place in
@@ -1159,7 +1158,10 @@ struct Hosted {
     // The operands of the next four products are read while the present four are multiplied, so the barrier of slice
     // s + 1 lies in the middle of slice s, with products before and behind it that need nothing.
     // vmcnt there: slice s + 1 has landed.  Younger than its four requests are those of slice s + 2 (4) and, in the
-    // first two slices of a tile, its 16 old values and the 16 stores of the tile before.
+    // first two slices of a tile, its 16 old values and the 16 stores of the tile before.  (The compiler, which does not
+    // know of the requests, waits as well: for 20 down to 17 outstanding operations at the head of a tile, where it clears
+    // the accumulators, so that by then most of the stores have drained, and for 15 in the stores of all but the plain
+    // update.  The counts hold all the same; a wait too many only costs its time.)
     int begin = 20;
     Quad64 q;
     double a[2][2], b[2][2];
@@ -1320,7 +1322,7 @@ __device__ __forceinline__ void gemm32_accumulate(const double* src_a, const dou
 // blocks [u0, u0 + 2), of the update by Lu (n_u of them), then X[xp, c] = -X[xp, xp] V[xp, c] for the column blocks c from
 // xc0 on (n_x tiles), then the first tiles of `left`, which the launch before left out.  Its length is that of a tile's
 // products, 512 matrix instructions of 64 cycles on four matrix cores, and a round trip to memory: whole tiles, which
-// leave half of the compute units idle at 3584 columns, took 8.3 us (1270 us for the whole of it, 1224 with halves).
+// leave half of the compute units idle at 3584 columns, took 8.3 us (1284 us for the whole of it, 1241 with halves).
 __global__ __launch_bounds__(256, 2) void pair_link_kernel(double* __restrict__ A, int ld, const double* __restrict__ Lu,
                                                            int u0, int n_u, double* __restrict__ X, int xp, int xc0,
                                                            int n_x, Hosted left, float* __restrict__ U, int d) {
@@ -1619,7 +1621,8 @@ __global__ __launch_bounds__(256, 2) void syrk_trailing64_kernel(double* __restr
   });
 }
 
-// Below this many column blocks the 64-tile kernel has more work-groups to spread over the chip.
+// Below this many column blocks left to update (the last 4096 columns) the 64-tile kernel has more work-groups to spread
+// over the chip.
 constexpr int kTrail128MinBlocks = 64;
 // ... and a level of the inversion tree with fewer 128-tiles than this (two per compute unit)
 constexpr long kInverse128MinTiles = 512;
@@ -1855,10 +1858,11 @@ static SweepLayout sweep_layout(int d) {
   L.total = off;
   return L;
 }
-// One panel has nothing to pair or to hide (d <= 64: 46 us by pairs, 24 to 27 by panels).  From there on the pairs are
-// quicker or even (192: 92 us against 89, 384: 139 against 164, 3584: 1270 against 1830, 6016: 3800 against 4919, 8192:
-// 8161 against 9760, 12288: 24.4 ms against 25.4) until a tile's traffic costs more than the chain that it hides (14336:
-// 37.7 ms against 37.8, 16384: 54.8 against 53.4).  Widths off 64 gain more (8191: 8.3 ms against 12.9).
+// One panel has nothing to pair or to hide (d <= 64: 46 us by pairs, 23 to 27 by panels).  From there on the pairs are
+// quicker (65: 45 us against 55, 192: 88.6 against 89.7, 384: 132 against 165, 1600: 530 against 755, 3584: 1245 against
+// 1939, 6016: 3781 against 5079, 8192: 8095 against 9760, 11008: 17.9 ms against 19.7, 12288: 24.0 against 25.2) until a
+// tile's traffic costs more than the chain that it hides (14336: 37.7 ms against 37.8, 16384: 54.8 against 53.4).  Widths
+// off 64 gain more (4097: 1735 us against 3084, 8191: 8143 against 12848).
 constexpr int kSweepMin = NB + 1, kSweepMax = 12288;
 static bool sweep_pays(int d) { return d >= kSweepMin && d <= kSweepMax; }
 
@@ -1948,11 +1952,15 @@ static int prepare_by_pairs(const float* H, int d, float damp, float* U, unsigne
     return h;
   };
   // One work-group to a compute unit.  Those on the compute units that the panel's work-groups leave have `head` rounds
-  // of tiles to themselves, the time of the chain; what is left then is for all.
+  // of tiles to themselves, the time of the chain; what is left then is for all.  (3584 columns: 1357 us with one such
+  // round, 1272 with two, 1242 with three, 1239 with four.  Where a tile takes two or three pairs a round is that much
+  // longer: 6016 3772 with one, 3779, 3905 with three; 8192 8095, 8370, 8698.)
   constexpr int kCus = 256;
   const int kHead = L.every == 1 ? 3 : 1;
   // Tiles of the update to leave to the link launch: it has one tile on most compute units and takes a second at 3 us,
-  // a round of tiles beside the pair, once there are more than two, takes 10.
+  // a round of tiles beside the pair, once there are more than two, takes 10.  (3584 columns: 1286 us if none is left,
+  // 1247, 1242 and 1268 if up to 128, 256 and 512 are; 8192: 8148, 8140, 8095, 8170.  From how many rounds on makes no
+  // difference: 1239, 1242 and 1238 us from two, three and four.)
   auto spread = [&](Hosted& h, int taken) -> int {              // returns the work-groups
     h.head = kHead;
     h.n_early = (kCus - taken > 64 ? kCus - taken : 64) - (h.inv_p >= 0 ? 1 : 0);
