@@ -74,7 +74,9 @@ int bpdq_version(void);
  *        (about 4 * n_tok * d_in bytes plus the partial tiles).
  *        That size is not monotonic in n_tok: a short call on a narrow layer is cut into more slices
  *        than a longer one.  The default entry also accepts a workspace that does not hold those
- *        slices but holds coarser ones (sized for a longer call, say); see below.
+ *        slices but holds coarser ones (sized for a longer call, say); see below.  Its small calls
+ *        (below) leave ws untouched, but ask for the same sizes, so that a program need not know
+ *        which calls are small.
  * Requirements: d_in % 4 == 0, ldx % 4 == 0, Xc and H 16-byte aligned, ws 256-byte aligned, n_tok >= 0.
  * Returns 0, or a negative code naming the offending argument (-1 Xc, -2 n_tok, -3 d_in,
  * -4 ldx, -6 H, -8 ws, -9 ws_bytes); nothing is launched then.
@@ -90,7 +92,11 @@ int bpdq_version(void);
  *   bits); a product is the sum of the three half products of weight >= 2^-11, accumulated in fp32,
  *   and the result is scaled back exactly.  The error of a product is below 2^-21 of it -- above
  *   the 2^-24 of an fp32 product, far below the rounding of the fp32 accumulation over thousands of
- *   tokens.  Assumes finite X (an infinity or NaN yields NaN in its row and column).
+ *   tokens.  Small calls (up to 64 tokens on 3072 channels, 256 on 2048, 512 on 704, 1024 on 512, 2048
+ *   on 320, less some that the above does sooner) are one launch on the fp32 matrix cores instead: fp32
+ *   products (2^-24) of the channels scaled in the same way, in chains of at most 32 tokens.  Which of
+ *   the two follows from n_tok and d_in alone.
+ *   Assumes finite X (an infinity or NaN yields NaN in its row and column).
  * bpdq_hessian_accumulate_bf16x3 runs on the bf16 matrix cores without a pre-pass: every value is
  *   cut exactly into three bf16 pieces inside the kernel and a product is the sum of the six piece
  *   products of weight >= 2^-16 (error below 2^-24 of a product).  About 1.5 times slower.
@@ -110,7 +116,8 @@ int bpdq_hessian_accumulate_f32(const float* Xc, int n_tok, int d_in, int ldx, f
  * as void*, created by the caller with timing enabled, or NULL) are recorded on `stream`
  * immediately before the first and immediately after the last launch of the tile-product kernel
  * (a call of at most 524288 tokens on a layer of fewer than 1024 tiles is one launch: then the two
- * events bracket that kernel alone, without the pre-pass before it and the reduction after it).
+ * events bracket that kernel alone, without the pre-pass before it and the reduction after it; of a
+ * small call of the default entry they bracket its one launch, which is all of it).
  * Return codes as above with every argument number one higher (-1: unknown kernel). */
 #define BPDQ_HESSIAN_F16X2 0
 #define BPDQ_HESSIAN_BF16X3 1
@@ -128,7 +135,9 @@ int bpdq_hessian_accumulate_timed(int kernel, const float* Xc, int n_tok, int d_
  *   info : one device int: 0, or the 1-based index of the first column whose pivot was not
  *          positive (Ht not positive definite; U is then undefined).  The columns are taken from
  *          the last to the first.
- * The factorisation runs in fp64 inside ws. */
+ * The factorisation runs in fp64 inside ws.  From 65 to 12288 columns a workspace of
+ * 12 d_in^2 bytes and a little (what other widths ask for) is accepted too where the size asked for is
+ * larger: the same U to the rounding of fp64, up to 1.6 times slower. */
 size_t bpdq_prepare_workspace_bytes(int d_in);
 int bpdq_prepare(const float* H, int d_in, float damp, float* U, unsigned char* dead,
                  int* info, void* ws, size_t ws_bytes, void* stream);

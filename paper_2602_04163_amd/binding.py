@@ -144,7 +144,7 @@ def bpdq_hessian_workspace_bytes(n_tok: int, d_in: int) -> int:
 
 def bpdq_hessian_accumulate(Xc, H, scale=2.0, symmetrize=False, ws=None, _entry="bpdq_hessian_accumulate"):
     """H += scale * Xc^T Xc (upper triangle; mirrored when symmetrize), on the fp16 matrix cores
-    with two fp16 halves per channel-scaled value."""
+    with two fp16 halves per channel-scaled value; small calls in one launch on the fp32 matrix cores."""
     lib = load()
     _dev(H, torch.float32, "H")
     if not (Xc.is_cuda and Xc.dtype == torch.float32 and Xc.dim() == 2 and Xc.stride(1) == 1):

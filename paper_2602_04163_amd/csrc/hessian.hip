@@ -4,7 +4,8 @@
 // tile product: fp32 MFMAs (bpdq_hessian_accumulate_f32), bf16 MFMAs on three exact bf16 pieces
 // of every value (bpdq_hessian_accumulate_bf16x3; mfma_split_bf16.h), or fp16 MFMAs on two fp16
 // halves of every value, split and laid out in operand order by a streaming pre-pass
-// (bpdq_hessian_accumulate; mfma_split_f16.h).  Only the upper triangle
+// (bpdq_hessian_accumulate; mfma_split_f16.h; its small calls are one launch of their own,
+// hess_small_kernel, which has none of what follows).  Only the upper triangle
 // of 256 x 256 tiles is computed, and of a diagonal tile only the 32 x 32 blocks on or above the diagonal.
 // The token axis is cut into deterministic slices so that the work-groups fill the 256 compute
 // units in whole rounds: off-diagonal tiles into S_off slices, diagonal tiles (5/8 of the work
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(256) void hess_split_f16_kernel(const float* __rest
 // eight values are one operand vector.  A row segment is 64 bytes, half a cache line: neighbouring
 // channel blocks run on the same XCD (work-group w runs on XCD w % 8), whose L2 then serves both halves
 // from one fetch.  4096 x 3584: 42 -> 21 us, the call 201 -> 178 us;
-// 512 x 256: 21 -> 4 us, the call 35 -> 15 us with the shorter slices and the mirror image of the reduction.
+// 512 x 256, when it took this way: 21 -> 4 us, the call 35 -> 15 us with shorter slices and the reduction's mirror image.
 constexpr int kFusedChannels = 16;
 constexpr int kFusedThreads = 1024;
 constexpr int kFusedTokens = 4096;
@@ -465,8 +466,9 @@ __global__ __launch_bounds__(kFusedThreads) void hess_prepass_f16_kernel(const f
 // sums are added in order, the wavefronts' in 64 bits.  The 32 x 32 blocks on the diagonal come whole, as from the tile kernels; `sym` writes
 // the mirror image instead.  Bound by its latency, one round trip to memory and a reduction, while the tiles fit the
 // chip once; beyond that by reading a tile's channels again for every tile, which the 256 x 256 tiles do not.
-// 512 x 256: 14.7 us for three launches (pre-pass, tile product, reduction) -> 5.8; 256 x 1024: 19.6 -> 10.4;
-// 2048 x 256: 19.5 -> 11.7.  Error of H against 64 bits (relative Frobenius, loud channels) 2e-8 .. 7e-8, 5e-8 .. 1.2e-7 before.
+// Three launches (pre-pass, tile product, reduction) -> one, on activations not read before, and on the same ones again:
+// 512 x 256 14.8 -> 6.8 us, 13.8 -> 5.4; 256 x 1024 19.9 -> 13.2, 19.5 -> 10.9; 2048 x 256 20.7 -> 17.0, 19.0 -> 11.4.
+// Error of H against 64 bits (relative Frobenius, loud channels) 2e-8 .. 7e-8, 5e-8 .. 1.2e-7 before.
 constexpr int kSmallChain = 32;
 
 template <int TILE, int WAVES, int NI>
@@ -645,7 +647,7 @@ __global__ __launch_bounds__(SplitF16::kThreads, 1) void hess_syrk_f16x2_kernel(
 // H[tile] += scale * sum_s partial[s][tile], slices added in index order.  64 work-groups per tile;
 // tiles 0 .. n_off-1 are off-diagonal, the rest diagonal.  SYM (the last launch of a
 // call that symmetrizes): the block's transpose goes to the lower triangle from the same registers, which
-// spares small layers a launch (512 x 256: 4 of 22 us) and large ones a pass over the upper triangle.
+// spares small layers a launch (4 of 22 us at 512 x 256, when it took this way) and large ones a pass over the upper triangle.
 // FLIGHT: slices in flight per wavefront.  A layer of few tiles has many slices and too few wavefronts to cover
 // a load and a wait per slice (8192 tokens, 1 tile of 57 slices: the call 53.2 -> 47.4 us with eight in flight; 3 tiles
 // 64.3 -> 58.2, 11 slices 23.5 -> 22.8); from 10 tiles on the wavefronts cover for one another (21 tiles of 10
