@@ -11,9 +11,10 @@
 // What is computed.  For a row with group-start working weights t and bit rows b_i, all the
 // quantities the method needs are right-solves with U_loc:
 //     tau = t U_loc^-1,   P_0 = 1 U_loc^-1,   P_i = b_i U_loc^-1.
-// They are produced by the same forward recurrence as the error propagation of Eq. 3-4
-// (x_l = v_l / U_ll;  v_{l+1:} -= x_l U_{l,l+1:}), so the bit-plane update of a column, its
-// error coordinate and the k plane solves advance together, one column per step.  Then
+// The same forward recurrence as the error propagation of Eq. 3-4 gives them
+// (x_l = v_l / U_ll;  v_{l+1:} -= x_l U_{l,l+1:}).  The sweep is that recurrence on the working weights alone, one
+// column per step (column_step); the plane solves need the finished codes and no decision needs them, so they
+// follow it by blocks of 16 columns (solve_planes).  Then
 //   * the fit of Eq. 6 is the (k+1) x (k+1) system G c = r with G_ab = P_a.P_b, r_a = P_a.tau
 //     (since U_loc^-T B_r = [P_0 .. P_k]^T), accumulated and solved in fp64;
 //   * the corrected propagation coordinates of Eq. 9 are E' = tau - sum_a c_a P_a
@@ -76,6 +77,8 @@ __device__ __forceinline__ double row_sum_d(double v) {
 }
 
 // ------------------------------------------------------------------ per-row state ----------
+typedef float f4 __attribute__((ext_vector_type(4)));
+
 template <int K, int G>
 struct RowState {
   static constexpr int CPL = G / 16;
@@ -83,8 +86,8 @@ struct RowState {
   float tau[CPL];     // t U_loc^-1
   float p0[CPL];      // 1 U_loc^-1 (the same for every row)
   float inv[CPL];     // 1 / U_ll of my columns
-  float wg[CPL];      // working copy during a sweep
-  float P[K][CPL];    // running right-hand sides, then P_i = b_i U_loc^-1
+  float wg[CPL];      // working copy during a sweep; a finished column keeps the weight that it was decided on
+  f4 P[CPL];          // component i: running right-hand side of plane i, then P_i = b_i U_loc^-1 (solve_planes)
   int code[CPL];      // plane bits of my columns, bit (i-1) = B_i
 };
 
@@ -92,7 +95,7 @@ struct RowState {
 // slot j / 16 of lane j % 16, so row l keeps just the S = CPL - l / 16 slots m >= M = l / 16 of
 // every lane.  The slots are cut into chunks of 4, then 2, then 1 (three left over are read as a
 // chunk of 4 with a zero: one read instead of two); a chunk of width w that starts at slot M + o holds
-//   sU[row_offset(l) + 16 o + lane * w + e] = U[l][16 (M + o + e) + lane]     (0 where j <= l)
+//   sU[row_offset(l) + 16 o + lane * w + e] = -U[l][16 (M + o + e) + lane]    (0 where j <= l)
 // so one ds_read_b128 / b64 / b32 of the 16 lanes of a row covers 16 w contiguous floats (no bank
 // conflicts) at an immediate offset, and the lower part reads as zero (no masks in the inner loop).
 // 38 KB at g = 128, 136 KB at g = 256.
@@ -120,6 +123,8 @@ struct SuLayout {
   __host__ __device__ static constexpr int floats() { return row_offset(G); }
   // a group's record in the workspace: image | 1 / U_ll [G] | P_0 [G], whole KB
   __host__ __device__ static constexpr int record_floats() { return (floats() + 2 * G + 255) / 256 * 256; }
+  // reads of a row that keeps the slots m >= M
+  __host__ __device__ static constexpr int chunks(int M) { return (CPL - M + kMaxVec - 1) / kMaxVec; }
   // width of the chunk that holds live slot o (0-based among the live slots) of a row with S
   // live slots, and the live slot that chunk starts at
   __host__ __device__ static constexpr int chunk_width(int S, int o) {
@@ -135,8 +140,8 @@ struct SuLayout {
   }
 };
 
-// the live slots [M, CPL) of one row for this lane; p = sU + row_offset(l)
-template <int G, int M>
+// the slots [FROM, CPL) of one row that keeps [M, CPL) for this lane; p = sU + row_offset(l)
+template <int G, int M, int FROM = M>
 __device__ __forceinline__ void load_u_row(const float* __restrict__ p, int lane16,
                                            float (&u)[G / 16]) {
   using Lay = SuLayout<G>;
@@ -145,9 +150,14 @@ __device__ __forceinline__ void load_u_row(const float* __restrict__ p, int lane
   typedef float vec2 __attribute__((ext_vector_type(2)));
 #pragma unroll
   for (int o = 0; o < S; ++o) {
-    if (Lay::chunk_start(S, o) != o) continue;
+    if (Lay::chunk_start(S, o) != o || o + Lay::chunk_width(S, o) <= FROM - M) continue;
     const int w = Lay::chunk_width(S, o);
-    if (w == 4) {
+    if (w == 4 && o + 2 <= FROM - M) {             // the upper half of a chunk
+      const vec2 v = *reinterpret_cast<const vec2*>(p + 16 * o + lane16 * 4 + 2);
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+        if (o + 2 + e < S) u[M + o + 2 + e] = v[e];
+    } else if (w == 4) {
       const vec4 v = *reinterpret_cast<const vec4*>(p + 16 * o + lane16 * 4);
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -166,8 +176,6 @@ constexpr int kMaxIters = 63;             // largest refine_iters
 template <int G>
 constexpr int kStageFloats = (SuLayout<G>::floats() + 255) / 256 * 256;
 
-enum : int { kStepInit = 0, kStepSweep = 1, kStepUniform = 2 };
-
 // x of lane O of this 16-lane row as the DPP operand of the arithmetic it feeds (bound_ctrl set and no
 // "old" value: the compiler folds the move into a VOP2 instruction that uses it once).
 template <int CTRL>
@@ -185,273 +193,421 @@ __device__ __forceinline__ unsigned min_stage(unsigned x) {
   const unsigned o = (unsigned)dpp_operand<kCtrl[R]>((int)x);
   return o < x ? o : x;
 }
-template <int R>
-__device__ __forceinline__ float byte_f(unsigned x) {
-  return (float)((x >> (8 * R)) & 0xffu);              // v_cvt_f32_ubyteR
+// A signed distance as an unsigned number that orders by magnitude, then positive before negative
+__device__ __forceinline__ unsigned distance_key(float d) {
+  const unsigned x = __builtin_bit_cast(unsigned, d);
+  return __builtin_amdgcn_alignbit(x, x, 31);
 }
 
 // Empty asm statements with a value as in/out operand fix the place of the instruction that
 // produces it: volatile asm statements keep their order.
 #define BPDQ_PIN(x) asm volatile("" : "+v"(x))
 
-// What a column step leaves for the next one: the broadcast coordinates of its column and its row of
-// the local factor.  The update of a column's own slot (and of the next column's) is on the critical
-// path and done at once; the slots beyond it are updated inside the next step, where their
-// multiply-adds fill the wait states of that step's serial chain.
-template <int K, int G>
-struct Pending {
-  float e, t;           // error coordinate; tau coordinate (kStepInit)
-  float x[K];           // plane coordinates
-  float u[G / 16];      // row of the local factor
+// Rows of the local factor on their way from LDS: a step lasts 55 cycles, less than a read of LDS takes, so rows are requested
+// kAhead steps before the one that uses them (at g = 256, where a step is longer and a row takes twice the registers, one).
+// A ring of kAhead + 2 rows: the update of the next column's slot is on the critical path and done at once; the slots beyond it
+// are updated inside the next step, where their multiply-adds fill the wait states of that step's serial chain.
+template <int G>
+constexpr int kAhead = G > 128 ? 1 : 3;
+template <int G>
+struct RowRing {
+  float e;                              // broadcast error coordinate of the column before
+  float u[kAhead<G> + 2][G / 16];
 };
-
-// Far update number F of the previous column: vector F % NV of slot FIRST + F / NV.
-template <int K, int G, int MODE, int FIRST, int F>
-__device__ __forceinline__ void far_update(RowState<K, G>& st, const Pending<K, G>& pd) {
-  constexpr int NV = (MODE == kStepUniform) ? 1 : K + 1;
-  constexpr int m = FIRST + F / NV, v = F % NV;
-  if constexpr (m < G / 16) {
-    if constexpr (MODE == kStepInit && v == 0) { st.tau[m] = fmaf(-pd.t, pd.u[m], st.tau[m]); BPDQ_PIN(st.tau[m]); }
-    else if constexpr (MODE != kStepInit && v == 0) { st.wg[m] = fmaf(-pd.e, pd.u[m], st.wg[m]); BPDQ_PIN(st.wg[m]); }
-    else {
-      constexpr int i = v - 1;
-      st.P[i][m] = fmaf(-pd.x[i], pd.u[m], st.P[i][m]);
-      BPDQ_PIN(st.P[i][m]);
-    }
-  }
+template <int G, int L>
+__device__ __forceinline__ void request_row(RowRing<G>& ring, const float* __restrict__ sU, int lane16) {
+  if constexpr (L + 1 < G) load_u_row<G, L / 16>(sU + SuLayout<G>::row_offset(L), lane16, ring.u[L % (kAhead<G> + 2)]);
 }
-template <int K, int G, int MODE, int FIRST, int F0, int F1>
-__device__ __forceinline__ void far_updates(RowState<K, G>& st, const Pending<K, G>& pd) {
+// LDS reads in flight behind row L once row L + kAhead is requested
+template <int G>
+constexpr int reads_behind(int L) {
+  int n = 0;
+  for (int r = L + 1; r <= L + kAhead<G> && r + 1 < G; ++r) n += SuLayout<G>::chunks(r / 16);
+  return n;
+}
+template <int K, int G, int L, int FIRST, int F0, int F1>
+__device__ __forceinline__ void far_updates(RowState<K, G>& st, const RowRing<G>& ring) {
   if constexpr (F0 < F1) {
-    far_update<K, G, MODE, FIRST, F0>(st, pd);
-    far_updates<K, G, MODE, FIRST, F0 + 1, F1>(st, pd);
+    st.wg[FIRST + F0] = fmaf(ring.e, ring.u[L % (kAhead<G> + 2)][FIRST + F0], st.wg[FIRST + F0]);
+    BPDQ_PIN(st.wg[FIRST + F0]);
+    far_updates<K, G, L, FIRST, F0 + 1, F1>(st, ring);
   }
 }
 
-// One column of the forward recurrence.
-//   kStepInit:    initial pass (codes known): builds tau and the plane solves P_i.
-//   kStepSweep:   bit-plane update of column L (Eq. 7-8), its error coordinate (Eq. 3),
-//                 compensation of the later columns (Eq. 4), and the plane solves.
-//   kStepUniform: the same column update with frozen coefficients and nothing else.
+// One column of the sweep: nearest level (Eq. 7-8), error coordinate (Eq. 3), compensation of the later
+// columns of the group (Eq. 4).
 //
 // A step is bound by vector issue (a SIMD holds one or two wavefronts, and every instruction of one
 // takes four cycles), so what counts is how few instructions it has and that the serial chain of the
 // decision never waits:
-//   * Nearest level: lane c of a row holds the level of code c % 2^K (`lv`), so one subtraction and one
-//     multiplication give all distances; K butterfly stages give the smallest, and K more the lowest
-//     code that attains it -- the code that a scan over the levels with a strict `<` keeps.  Distances are
-//     squares, so their bit patterns order like the values (and a NaN sorts above infinity).  2 + 2 K + 2
-//     instructions against 2 + 6 (2^K - 1) for the scan.
-//   * `lc` carries the code as bytes (bit i in byte i: the same order), so a plane bit becomes a float by
-//     one v_cvt_f32_ubyte; the level itself follows from the bits, ((c_0 + b_1 c_1) + b_2 c_2) + ...
-//   * Broadcasts are DPP operands of the arithmetic that needs them.  The factor's row is zero on and left
-//     of its diagonal, so the running right-hand side of a finished column stays as it was, and its
-//     coordinate x = (b + P) / U_ll is taken for all columns at once after the sweep (finish_columns)
-//     instead of by a select per step.
-//   * A DPP operand must be two instructions old, and a select two after its compare: the far updates of
-//     the previous column are dealt to those places.
-// Whole sweep phase against a step with the scan and per-step selects (5 iterations, groups of 128): 3584 x 3584,
-// 2 planes 3.38 -> 2.92 ms; 18944 x 3584, 3 planes 16.1 -> 11.9 ms; 256 x 256 (groups of 64, 3 iterations)
-// 144 -> 128 us.  42 instead of 60 instructions per column at 2 planes.  (What surrounds the steps has been
-// cut since: 2.57 ms, 10.7 ms and 110 us.)
-template <int K, int G, int L, int MODE>
-__device__ __forceinline__ void column_step(RowState<K, G>& st, const float* __restrict__ sU,
-                                            const float (&c)[K + 1], float lv, unsigned lc,
-                                            const float (&bits)[K][G / 16], int lane16,
-                                            Pending<K, G>& pd, float (&u)[G / 16]) {
+//   * Lane c of a row holds the level of code c % 2^K (`lv`), so one subtraction gives all distances.  What the
+//     later columns need is the signed distance to the nearest level and not its code: distances are turned into keys that
+//     order by magnitude and keep the sign (distance_key), K butterfly stages give the smallest.  The codes are found after
+//     the sweep, for 16 columns at a time, from the weights that it leaves in place (the factor's row is zero on and
+//     left of its diagonal), and the plane solves, which no decision of the sweep needs, follow it (solve_planes).
+//   * Two levels at the same distance on either side of the weight: the key takes the lower level, a scan over the codes
+//     with a strict `<` the lower code.  That is the same level where levels ascend with their codes; elsewhere
+//     sweep() looks for such ties.
+//   * Broadcasts are DPP operands of the arithmetic that needs them.
+//   * A DPP operand must be two instructions old: the far updates of the previous column are dealt to those places.
+// 14 instructions per column at 2 planes, 73 cycles in a launch of one wavefront per SIMD (their serial chain alone takes 52); with
+// the code found by a second butterfly in the step and the solves advancing with it, 42 instructions and 176 cycles.
+// Sweep and solves together, a group of 128 columns, 2 planes: 22.5 k -> 18.6 k cycles; whole layers, the same bits:
+// 3584 x 3584, 2 planes, 5 iterations 2531 -> 2212 us; 18944 x 3584, 3 planes 10.4 -> 8.96 ms; 256 x 256 (groups of 64, 3
+// iterations) 113.5 -> 90.3 us.
+template <int K, int G, int L>
+__device__ __forceinline__ void column_step(RowState<K, G>& st, const float* __restrict__ sU, float lv, int lane16,
+                                            RowRing<G>& ring) {
   constexpr int CPL = G / 16, M = L / 16, O = L % 16, MN = (L + 1) / 16;
-  constexpr bool kInit = (MODE == kStepInit), kUni = (MODE == kStepUniform);
   // far updates of column L - 1: the slots beyond column L's
-  constexpr int NV = kUni ? 1 : K + 1;
-  constexpr int NF = (L == 0) ? 0 : NV * (CPL - M - 1);
-  float un[CPL];
-  if constexpr (L + 1 < G) {
-    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt 0: this column's row, requested a whole step ago (one wait per step)
-    load_u_row<G, MN>(sU + SuLayout<G>::row_offset(L + 1), lane16, un);
-    __builtin_amdgcn_sched_barrier(0);   // the reads of the next row stay ahead of this column's arithmetic
-  }
-  float e = 0.f, tb = 0.f, x[K];
-  const float inv = from_lane<O>(st.inv[M]);
+  constexpr int NF = (L == 0) ? 0 : CPL - M - 1;
+  request_row<G, L + kAhead<G>>(ring, sU, lane16);
+  __builtin_amdgcn_s_waitcnt(0xc07f | (reads_behind<G>(L) << 8));        // lgkmcnt: this column's row is here
+  __builtin_amdgcn_sched_barrier(0);     // the requests stay ahead of this column's arithmetic
   constexpr auto at = [](int f) { return f < NF ? f : NF; };
-  if constexpr (kInit) {
-    float y[K];
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      y[i] = bits[i][M] + st.P[i][M];
-      BPDQ_PIN(y[i]);
-    }
-    tb = from_lane<O>(st.tau[M]) * inv;
-    BPDQ_PIN(tb);
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      x[i] = from_lane<O>(y[i]) * inv;
-      BPDQ_PIN(x[i]);
-    }
-    far_updates<K, G, MODE, M + 1, 0, NF>(st, pd);
-  } else {
-    float d = from_lane<O>(st.wg[M]) - lv;
-    BPDQ_PIN(d);
-    d = d * d;
-    unsigned dist = __builtin_bit_cast(unsigned, d);
-    BPDQ_PIN(dist);
-    far_updates<K, G, MODE, M + 1, 0, at(2)>(st, pd);
-    unsigned least = min_stage<0>(dist);
-    BPDQ_PIN(least);
-    far_updates<K, G, MODE, M + 1, at(2), at(4)>(st, pd);
-    if constexpr (K > 1) { least = min_stage<1>(least); BPDQ_PIN(least); }
-    if constexpr (K > 2) {
-      far_updates<K, G, MODE, M + 1, at(4), at(6)>(st, pd);
-      least = min_stage<2>(least);
-      BPDQ_PIN(least);
-    }
-    if constexpr (K > 3) {
-      far_updates<K, G, MODE, M + 1, at(6), at(8)>(st, pd);
-      least = min_stage<3>(least);
-      BPDQ_PIN(least);
-    }
-    constexpr int f0 = 2 + 2 * (K - 1) + (K == 1 ? 2 : 0);
-    const bool hit = (dist == least);
-    unsigned code = hit ? lc : 0xffffffffu;
-    far_updates<K, G, MODE, M + 1, at(f0), at(f0 + 2)>(st, pd);
-    BPDQ_PIN(code);
-    far_updates<K, G, MODE, M + 1, at(f0 + 2), at(f0 + 4)>(st, pd);
-    code = min_stage<0>(code);
-    BPDQ_PIN(code);
-    if constexpr (K > 1) {
-      far_updates<K, G, MODE, M + 1, at(f0 + 4), at(f0 + 6)>(st, pd);
-      code = min_stage<1>(code);
-      BPDQ_PIN(code);
-    }
-    if constexpr (K > 2) {
-      far_updates<K, G, MODE, M + 1, at(f0 + 6), at(f0 + 8)>(st, pd);
-      code = min_stage<2>(code);
-      BPDQ_PIN(code);
-    }
-    if constexpr (K > 3) {
-      far_updates<K, G, MODE, M + 1, at(f0 + 8), at(f0 + 10)>(st, pd);
-      code = min_stage<3>(code);
-      BPDQ_PIN(code);
-    }
-    constexpr int f1 = f0 + 4 + 2 * (K - 1);
-    float b[K];
-    b[0] = byte_f<0>(code);
-    if constexpr (K > 1) b[1] = byte_f<1>(code);
-    if constexpr (K > 2) b[2] = byte_f<2>(code);
-    if constexpr (K > 3) b[3] = byte_f<3>(code);
-    float q = c[0];
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      BPDQ_PIN(b[i]);
-      q = fmaf(b[i], c[i + 1], q);          // b is 0 or 1: the sum of the level table, bit for bit
-      BPDQ_PIN(q);
-      if constexpr (!kUni) {
-        x[i] = from_lane<O>(st.P[i][M]) + b[i];
-        BPDQ_PIN(x[i]);
-      }
-    }
-    e = from_lane<O>(st.wg[M]) - q;
-    BPDQ_PIN(e);
-    st.code[M] = (lane16 == O) ? (int)code : st.code[M];
-    BPDQ_PIN(st.code[M]);
-    e = e * inv;
-    BPDQ_PIN(e);
-    if constexpr (!kUni) {
-#pragma unroll
-      for (int i = 0; i < K; ++i) {
-        x[i] = x[i] * inv;
-        BPDQ_PIN(x[i]);
-      }
-    }
-    far_updates<K, G, MODE, M + 1, at(f1), NF>(st, pd);
+  // The two ends of the chain are strings: between two values that a pin fixes the compiler would put wait states.
+  // wg[M] has to be two instructions old for its broadcast, which the compiler does not look after in a string: a read
+  // and a wait lie in between, or two waits.
+  unsigned key;
+  if constexpr (L + kAhead<G> + 1 >= G) asm volatile("s_nop 0");
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("v_sub_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf\n\t"
+               "v_alignbit_b32 %0, %0, %0, 31" : "=&v"(key) : "v"(st.wg[M]), "v"(lv), "n"(O));      // distance_key
+  far_updates<K, G, L - 1, M + 1, 0, at(2)>(st, ring);
+  key = min_stage<0>(key);
+  if constexpr (K > 1) {
+    BPDQ_PIN(key);
+    far_updates<K, G, L - 1, M + 1, at(2), at(4)>(st, ring);
+    key = min_stage<1>(key);
   }
-  if constexpr (L + 1 < G) {
-    // the slot of column L + 1 at once, the others in the next step
-    if constexpr (kInit) {
-      st.tau[MN] = fmaf(-tb, u[MN], st.tau[MN]);
-      BPDQ_PIN(st.tau[MN]);
-    } else {
-      st.wg[MN] = fmaf(-e, u[MN], st.wg[MN]);
-      BPDQ_PIN(st.wg[MN]);
-    }
-    if constexpr (!kUni) {
-#pragma unroll
-      for (int i = 0; i < K; ++i) {
-        st.P[i][MN] = fmaf(-x[i], u[MN], st.P[i][MN]);
-        BPDQ_PIN(st.P[i][MN]);
-      }
-    }
-    pd.e = e; pd.t = tb;
-    if constexpr (!kUni) {
-#pragma unroll
-      for (int i = 0; i < K; ++i) pd.x[i] = x[i];
-    }
-#pragma unroll
-    for (int m = MN; m < CPL; ++m) {
-      pd.u[m] = u[m];
-      u[m] = un[m];
-    }
+  if constexpr (K > 2) {
+    BPDQ_PIN(key);
+    far_updates<K, G, L - 1, M + 1, at(4), at(6)>(st, ring);
+    key = min_stage<2>(key);
   }
+  if constexpr (K > 3) {
+    BPDQ_PIN(key);
+    far_updates<K, G, L - 1, M + 1, at(6), at(8)>(st, ring);
+    key = min_stage<3>(key);
+  }
+  far_updates<K, G, L - 1, M + 1, at(2 * K), NF>(st, ring);
+  // back to the distance, its error coordinate, and the slot of column L + 1 at once; the others in the next step
+  float e;
+  asm volatile("v_alignbit_b32 %0, %2, %2, 1\n\t"
+               "v_mul_f32_dpp %0, %3, %0 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+               "v_fmac_f32 %1, %0, %4"
+               : "=&v"(e), "+v"(st.wg[MN]) : "v"(key), "v"(st.inv[M]), "v"(ring.u[L % (kAhead<G> + 2)][MN]), "n"(O));
+  ring.e = e;
   __builtin_amdgcn_sched_barrier(0);     // later steps' reads stay behind this step
 }
-
-template <int K, int G, int MODE, int... Ls>
-__device__ __forceinline__ void run_columns(RowState<K, G>& st, const float* sU,
-                                            const float (&c)[K + 1], int lane16,
+template <int K, int G, int... Ls>
+__device__ __forceinline__ void run_columns(RowState<K, G>& st, const float* sU, float lv, int lane16,
                                             std::integer_sequence<int, Ls...>) {
-  constexpr int CPL = G / 16;
-  // level and byte-wise code of this lane: code lane % 2^K, summed in the order of level_table.  A
-  // coefficient that is not finite never belongs to the nearest level unless C_0 is not finite
-  // either; it is left out of the sums below, where 0 * inf would be NaN.  A level that is not finite never beats
-  // code 0 in a scan with a strict `<`: it takes part as another code 0, so that all distances of a
-  // NaN weight, and of an infinite C_0, are one bit pattern (NaNs of different origin are not).
-  float lv = c[0], cs[K + 1];
-  unsigned lc = 0u;
-  cs[0] = c[0];
-#pragma unroll
-  for (int i = 0; i < K; ++i) {
-    const bool set = ((lane16 >> i) & 1) != 0;
-    lv = set ? lv + c[i + 1] : lv;
-    lc |= set ? (1u << (8 * i)) : 0u;
-    cs[i + 1] = __builtin_isfinite(c[i + 1]) ? c[i + 1] : 0.f;
+  RowRing<G> ring;
+  request_row<G, 0>(ring, sU, lane16);
+  if constexpr (kAhead<G> > 1) {
+    request_row<G, 1>(ring, sU, lane16);
+    request_row<G, 2>(ring, sU, lane16);
   }
-  lv = __builtin_isfinite(lv) ? lv : c[0];
-  float bits[K][CPL];
-  if constexpr (MODE == kStepInit) {
+  __builtin_amdgcn_sched_barrier(0);
+  (column_step<K, G, Ls>(st, sU, lv, lane16, ring), ...);
+}
+
+// v(code) = ((c0 + b1 c1) + b2 c2) + ...  in fp32 (Eq. 7)
+template <int K>
+__device__ __forceinline__ void level_table(const float (&c)[K + 1], float (&lv)[1 << K]) {
+#pragma unroll
+  for (int code = 0; code < (1 << K); ++code) {
+    float v = c[0];
 #pragma unroll
     for (int i = 0; i < K; ++i)
-#pragma unroll
-      for (int m = 0; m < CPL; ++m) bits[i][m] = (float)((st.code[m] >> i) & 1);
+      if ((code >> i) & 1) v = v + c[i + 1];
+    lv[code] = v;
   }
-  float u[CPL];
-  load_u_row<G, 0>(sU, lane16, u);
-  Pending<K, G> pd;
-  (column_step<K, G, Ls, MODE>(st, sU, cs, lv, lc, bits, lane16, pd, u), ...);
-  // finished columns: coordinates from the right-hand sides that the sweep left in place
+}
+// The levels a sweep decides on.  A level that is not finite never beats code 0 in a scan with a strict `<`: it takes part
+// as another code 0, so that all distances of a NaN weight, and of an infinite C_0, are one bit pattern
+// (NaNs of different origin are not).
+template <int K>
+__device__ __forceinline__ void sweep_levels(const float (&c)[K + 1], float (&lv)[1 << K]) {
+  level_table<K>(c, lv);
+#pragma unroll
+  for (int q = 1; q < (1 << K); ++q) lv[q] = __builtin_isfinite(lv[q]) ? lv[q] : c[0];
+}
+
+// Nearest level of w by squared distance, the lowest code of several: the definition of a decision.
+template <int K>
+__device__ __forceinline__ float scan_levels(float w, const float (&lv)[1 << K], int& code) {
+  float d0 = w - lv[0], best = d0 * d0;
+  code = 0;
+#pragma unroll
+  for (int q = 1; q < (1 << K); ++q) {
+    const float d = w - lv[q], s = d * d;
+    const bool lt = s < best;
+    best = lt ? s : best;
+    d0 = lt ? d : d0;
+    code = lt ? q : code;
+  }
+  return d0;
+}
+
+// The sweep by that definition, column by column, in a loop: for the rare wavefront whose sweep by keys met a tie that
+// the definition decides the other way (a few times the duration of the unrolled sweep).
+template <int K, int G, int M = 0>
+__device__ __forceinline__ void sweep_by_scan(RowState<K, G>& st, const float* __restrict__ sU, const float (&lv)[1 << K],
+                                              int lane16) {
+  using Lay = SuLayout<G>;
+  constexpr int CPL = G / 16;
+  BPDQ_PIN(lane16);           // opaque, as in solve_block
+#pragma unroll 1
+  for (int o = 0; o < 16; ++o) {
+    int code;
+    const float e = scan_levels<K>(__shfl(st.wg[M], o, 16), lv, code) * __shfl(st.inv[M], o, 16);
+    st.code[M] = (lane16 == o) ? code : st.code[M];
+    const float* row = sU + Lay::row_offset(16 * M) + 16 * o * Lay::live(M);
+#pragma unroll
+    for (int m = M; m < CPL; ++m) st.wg[m] = fmaf(e, row[Lay::slot_index(CPL - M, m - M, lane16)], st.wg[m]);
+  }
+  if constexpr (M + 1 < CPL) sweep_by_scan<K, G, M + 1>(st, sU, lv, lane16);
+}
+
+// One sweep over the group's columns with coefficients c: leaves the codes, and in wg the weights they were decided on.
+template <int K, int G>
+__device__ __forceinline__ void sweep(RowState<K, G>& st, const float* __restrict__ sU, const float (&c)[K + 1], int lane16) {
+  constexpr int CPL = G / 16;
+  float lv = c[0];
+#pragma unroll
+  for (int i = 0; i < K; ++i) lv = ((lane16 >> i) & 1) ? lv + c[i + 1] : lv;
+  lv = __builtin_isfinite(lv) ? lv : c[0];
+#pragma unroll
+  for (int m = 0; m < CPL; ++m) st.wg[m] = st.t[m];
+  run_columns<K, G>(st, sU, lv, lane16, std::make_integer_sequence<int, G - 1>{});     // the last column has none behind it
+
+  // The codes, by the smallest magnitude; its order is that of the squares unless those leave the range of fp32.  Where levels
+  // descend somewhere (ties, see column_step), lie so close that squares of distances between them underflow, or so
+  // far out that they overflow, each decision is compared with the definition.  So it is where a weight is not finite:
+  // the zeros left of the factor's diagonal make NaNs of the columns that were finished before it.
+  float lvl[1 << K], sum = 0.f;
+  sweep_levels<K>(c, lvl);
+  bool odd = false;
+#pragma unroll
+  for (int q = 1; q < (1 << K); ++q) {
+    const float gap = lvl[q] - lvl[q - 1];
+    odd |= !(gap >= 0x1p-60f || gap == 0.f);
+  }
+#pragma unroll
+  for (int m = 0; m < CPL; ++m) sum += fabsf(st.wg[m]);
+  odd |= !(sum + fabsf(lvl[0]) + fabsf(lvl[(1 << K) - 1]) < 0x1p60f);
+  if (!__any(odd)) {
+#pragma unroll
+    for (int m = 0; m < CPL; ++m) {
+      const float w = st.wg[m];
+      float best = fabsf(w - lvl[0]);
+      int code = 0;
+#pragma unroll
+      for (int q = 1; q < (1 << K); ++q) {
+        const float d = fabsf(w - lvl[q]);
+        code = d < best ? q : code;
+        best = d < best ? d : best;
+      }
+      st.code[m] = code;
+    }
+    return;
+  }
+  bool other = false;
 #pragma unroll
   for (int m = 0; m < CPL; ++m) {
-    const float iv = st.inv[m];
-    if constexpr (MODE == kStepInit) {
-      st.tau[m] *= iv;
-    } else {
-      const unsigned cb = (unsigned)st.code[m];           // bytes -> bits
-      unsigned code = cb;
+    const float d0 = scan_levels<K>(st.wg[m], lvl, st.code[m]);
+    unsigned key = distance_key(st.wg[m] - lvl[0]);
 #pragma unroll
-      for (int i = 1; i < K; ++i) code |= cb >> (7 * i);
-      st.code[m] = (int)(code & ((1u << K) - 1u));
+    for (int q = 1; q < (1 << K); ++q) {
+      const unsigned k = distance_key(st.wg[m] - lvl[q]);
+      key = k < key ? k : key;
     }
-    if constexpr (MODE == kStepUniform) {
-      float q = cs[0];
+    other |= key != distance_key(d0) || st.wg[m] != st.wg[m];
+  }
+  if (__any(other)) {
 #pragma unroll
-      for (int i = 0; i < K; ++i) q = fmaf((float)((st.code[m] >> i) & 1), cs[i + 1], q);
-      st.tau[m] = (st.wg[m] - q) * iv;
+    for (int m = 0; m < CPL; ++m) st.wg[m] = st.t[m];
+    sweep_by_scan<K, G>(st, sU, lvl, lane16);
+  }
+}
+
+// Right-solves with U_loc of rows that are known: slots [0, NP) of st.P run from the plane bits, and, where NT, slot NP from
+// what st.P holds there (the target).  The forward recurrence x_l = v_l / U_ll, v_j -= x_l U_lj with its products in
+// ascending l, every one a fused multiply-add in fp32, so where a product is formed does not change a bit:
+//   * inside a block of 16 columns, and from a block to the next, on the vector units, x_l as a DPP operand;
+//   * from a block to all later ones on the matrix cores: v_mfma_f32_16x16x4_f32 gives the same bits as a chain of four
+//     fused multiply-adds in ascending k.  Row a = 4 q + i of its A operand is slot i of row q of the wavefront, so register i
+//     of lane (q, c) of the result is that slot's right-hand side of column c, which is where the recurrence wants it.  A
+//     block's coordinates reach that operand layout through LDS.
+// The matrix cores take fp32 products through the vector units' multipliers: nothing of the wavefront issues beside
+// one, and one costs 31 cycles in a run of them on different tiles (40 alone, 52 behind one of the same tile), so a block's
+// products come as one run, tiles innermost.  Four slots wide they do the work of 16 broadcast multiply-adds of 5 cycles
+// a slot; at 2 planes half of that is used: 124 cycles a tile against 166.
+constexpr int kSolveFloats = 256;             // LDS of a wavefront: [column of the block][row][slot]
+template <int G, int M>
+__device__ __forceinline__ void load_block_rows(const float* __restrict__ sU, int lane16, float (&own)[16], float (&next)[16]) {
+  using Lay = SuLayout<G>;
+  typedef float vec2 __attribute__((ext_vector_type(2)));
+  constexpr int S = G / 16 - M, w = Lay::chunk_width(S, 0);
+#pragma unroll
+  for (int o = 0; o < 16; ++o) {
+    const float* p = sU + Lay::row_offset(16 * M + o);
+    if constexpr (S > 1) {
+      const vec2 v = *reinterpret_cast<const vec2*>(p + w * lane16);
+      own[o] = v[0];
+      next[o] = v[1];
     } else {
-#pragma unroll
-      for (int i = 0; i < K; ++i) {
-        const float b = (MODE == kStepInit) ? bits[i][m] : (float)((st.code[m] >> i) & 1);
-        st.P[i][m] = (b + st.P[i][m]) * iv;
-      }
+      own[o] = p[lane16];
     }
   }
+}
+// The multiply-add with a broadcast operand, v += z(lane O of the row) * u, is not formed by the compiler (a move and a
+// multiply-add instead): assembly.  z must have been written two instructions before, which the compiler does not look after
+// there: a string holds what writes z, or begins with the wait; and several columns, because the compiler puts a wait
+// state between two strings that share a register.
+#define BPDQ_FMAC(v, z, u, o) "v_fmac_f32_dpp %[v" #v "], %[z" #z "], %[u" #u "] row_newbcast:%[o]+" #o " row_mask:0xf bank_mask:0xf\n\t"
+#define BPDQ_Z(i) "v_add_f32 %[z" #i "], %[b" #i "], %[v" #i "]\n\t"
+#define BPDQ_S(i) "v_mul_f32 %[z" #i "], %[z" #i "], %[w]\n\t"
+#define BPDQ_STEP1(e) BPDQ_Z(0) BPDQ_S(0) "s_nop 1\n\t" BPDQ_FMAC(0, 0, e, e)
+#define BPDQ_STEP2(e) BPDQ_Z(0) BPDQ_Z(1) BPDQ_S(0) BPDQ_S(1) "s_nop 0\n\t" BPDQ_FMAC(0, 0, e, e) BPDQ_FMAC(1, 1, e, e)
+#define BPDQ_STEP3(e) BPDQ_Z(0) BPDQ_Z(1) BPDQ_Z(2) BPDQ_S(0) BPDQ_S(1) BPDQ_S(2) BPDQ_FMAC(0, 0, e, e) BPDQ_FMAC(1, 1, e, e) \
+  BPDQ_FMAC(2, 2, e, e)
+#define BPDQ_STEP4(e) BPDQ_Z(0) BPDQ_Z(1) BPDQ_Z(2) BPDQ_Z(3) BPDQ_S(0) BPDQ_S(1) BPDQ_S(2) BPDQ_S(3) BPDQ_FMAC(0, 0, e, e) \
+  BPDQ_FMAC(1, 1, e, e) BPDQ_FMAC(2, 2, e, e) BPDQ_FMAC(3, 3, e, e)
+#define BPDQ_FIVE(S) S(0) S(1) S(2) S(3) S(4)
+#define BPDQ_U5 [u0] "v"(u[O]), [u1] "v"(u[O + 1]), [u2] "v"(u[O + 2]), [u3] "v"(u[O + 3]), [u4] "v"(u[O + 4]), [w] "v"(inv), [o] "n"(O)
+// columns O .. O + 4 of a block: z = (b + v) / U_ll where the column is, then the rest of the block
+template <int N, int O>
+__device__ __forceinline__ void solve_five(float (&v)[4], const float (&b)[4], float inv, const float (&u)[16]) {
+  float z0, z1, z2, z3;
+  if constexpr (N == 1)
+    asm volatile(BPDQ_FIVE(BPDQ_STEP1) : [v0] "+v"(v[0]), [z0] "=&v"(z0) : [b0] "v"(b[0]), BPDQ_U5);
+  else if constexpr (N == 2)
+    asm volatile(BPDQ_FIVE(BPDQ_STEP2) : [v0] "+v"(v[0]), [v1] "+v"(v[1]), [z0] "=&v"(z0), [z1] "=&v"(z1)
+                 : [b0] "v"(b[0]), [b1] "v"(b[1]), BPDQ_U5);
+  else if constexpr (N == 3)
+    asm volatile(BPDQ_FIVE(BPDQ_STEP3)
+                 : [v0] "+v"(v[0]), [v1] "+v"(v[1]), [v2] "+v"(v[2]), [z0] "=&v"(z0), [z1] "=&v"(z1), [z2] "=&v"(z2)
+                 : [b0] "v"(b[0]), [b1] "v"(b[1]), [b2] "v"(b[2]), BPDQ_U5);
+  else
+    asm volatile(BPDQ_FIVE(BPDQ_STEP4)
+                 : [v0] "+v"(v[0]), [v1] "+v"(v[1]), [v2] "+v"(v[2]), [v3] "+v"(v[3]), [z0] "=&v"(z0), [z1] "=&v"(z1),
+                   [z2] "=&v"(z2), [z3] "=&v"(z3)
+                 : [b0] "v"(b[0]), [b1] "v"(b[1]), [b2] "v"(b[2]), [b3] "v"(b[3]), BPDQ_U5);
+}
+#define BPDQ_NEXT1(e) BPDQ_FMAC(0, 0, e, e) "s_nop 0\n\t"
+#define BPDQ_NEXT2(e) BPDQ_FMAC(0, 0, e, e) BPDQ_FMAC(1, 1, e, e)
+#define BPDQ_NEXT3(e) BPDQ_NEXT2(e) BPDQ_FMAC(2, 2, e, e)
+#define BPDQ_NEXT4(e) BPDQ_NEXT3(e) BPDQ_FMAC(3, 3, e, e)
+#define BPDQ_EIGHT(S) "s_nop 1\n\t" S(0) S(1) S(2) S(3) S(4) S(5) S(6) S(7)
+#define BPDQ_U8 [u0] "v"(u[O]), [u1] "v"(u[O + 1]), [u2] "v"(u[O + 2]), [u3] "v"(u[O + 3]), [u4] "v"(u[O + 4]), \
+  [u5] "v"(u[O + 5]), [u6] "v"(u[O + 6]), [u7] "v"(u[O + 7]), [o] "n"(O)
+// columns O .. O + 7 of a finished block to the next block
+template <int N, int O>
+__device__ __forceinline__ void solve_next(float (&v)[4], const float (&z)[4], const float (&u)[16]) {
+  if constexpr (N == 1)
+    asm volatile(BPDQ_EIGHT(BPDQ_NEXT1) : [v0] "+v"(v[0]) : [z0] "v"(z[0]), BPDQ_U8);
+  else if constexpr (N == 2)
+    asm volatile(BPDQ_EIGHT(BPDQ_NEXT2) : [v0] "+v"(v[0]), [v1] "+v"(v[1]) : [z0] "v"(z[0]), [z1] "v"(z[1]), BPDQ_U8);
+  else if constexpr (N == 3)
+    asm volatile(BPDQ_EIGHT(BPDQ_NEXT3) : [v0] "+v"(v[0]), [v1] "+v"(v[1]), [v2] "+v"(v[2])
+                 : [z0] "v"(z[0]), [z1] "v"(z[1]), [z2] "v"(z[2]), BPDQ_U8);
+  else
+    asm volatile(BPDQ_EIGHT(BPDQ_NEXT4) : [v0] "+v"(v[0]), [v1] "+v"(v[1]), [v2] "+v"(v[2]), [v3] "+v"(v[3])
+                 : [z0] "v"(z[0]), [z1] "v"(z[1]), [z2] "v"(z[2]), [z3] "v"(z[3]), BPDQ_U8);
+}
+template <int NP, int NT, int K, int G, int M>
+__device__ __forceinline__ void solve_block(RowState<K, G>& st, const float* __restrict__ sU, float* sX, int lane,
+                                            float (&v)[4], float (&own)[16], float (&next)[16]) {
+  using Lay = SuLayout<G>;
+  constexpr int CPL = G / 16, N = NP + NT;
+  int lane16 = lane & 15, q = lane >> 4;
+  if constexpr (G > 128) {      // opaque again: registers are short
+    BPDQ_PIN(lane16);
+    BPDQ_PIN(q);
+  }
+  float b[4], z[4];
+#pragma unroll
+  for (int i = 0; i < N; ++i) b[i] = (i < NP) ? (float)((st.code[M] >> i) & 1) : -0.f;    // -0 + v is v, its sign too
+  solve_five<N, 0>(v, b, st.inv[M], own);
+  solve_five<N, 5>(v, b, st.inv[M], own);
+  solve_five<N, 10>(v, b, st.inv[M], own);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    z[i] = (b[i] + v[i]) * st.inv[M];
+    st.P[M][i] = z[i];
+  }
+  if constexpr (M + 1 < CPL) {
+    constexpr bool kFar = M + 2 < CPL, kAll = G <= 128;
+    float nown[16], nnext[16], a[4], f[kAll ? 4 : 2][CPL], w[4];
+    auto request = [&](int kk) {                                   // the factor's rows 4 kk .. 4 kk + 3 of the block
+      load_u_row<G, M, M + 2>(sU + Lay::row_offset(16 * M) + 16 * (4 * kk + q) * Lay::live(M), lane16, f[kAll ? kk : kk & 1]);
+    };
+    if constexpr (kFar) {
+      *reinterpret_cast<f4*>(sX + 16 * lane16 + 4 * q) = st.P[M];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // one wavefront's LDS accesses keep their order
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        a[kk] = sX[64 * kk + lane];
+        if (kAll || kk == 0) request(kk);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) w[i] = st.P[M + 1][i];
+    solve_next<N, 0>(w, z, next);
+    solve_next<N, 8>(w, z, next);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kAll || !kFar) load_block_rows<G, M + 1>(sU, lane16, nown, nnext);
+    if constexpr (kFar) {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        if constexpr (!kAll) {
+          if (kk < 3) request(kk + 1);
+          else load_block_rows<G, M + 1>(sU, lane16, nown, nnext);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int n = M + 2; n < CPL; ++n)
+          st.P[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], f[kAll ? kk : kk & 1][n], st.P[n], 0, 0, 0);
+      }
+      // The strings of the next block may be given registers of slots that nobody reads: eleven wait states behind a
+      // product that writes them.  (The vector units are not free sooner.)
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_nop 10");
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    solve_block<NP, NT, K, G, M + 1>(st, sU, sX, lane, w, nown, nnext);
+  }
+}
+template <int NP, int NT, int K, int G>
+__device__ __forceinline__ void solve_planes(RowState<K, G>& st, const float* __restrict__ sU, float* sX) {
+  int lane = threadIdx.x & 63;
+  BPDQ_PIN(lane);               // opaque, or the addresses that follow from it stay in registers over all sweeps
+#pragma unroll
+  for (int m = 0; m < G / 16; ++m)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (NT == 0 || i != NP) st.P[m][i] = 0.f;
+  float own[16], next[16], v[4];
+  load_block_rows<G, 0>(sU, lane & 15, own, next);
+#pragma unroll
+  for (int i = 0; i < NP + NT; ++i) v[i] = st.P[0][i];
+  solve_block<NP, NT, K, G, 0>(st, sU, sX, lane, v, own, next);
+}
+// tau = t U_loc^-1 and the planes of the first codes: in one pass where a slot is left for tau
+template <int K, int G>
+__device__ __forceinline__ void solve_target(RowState<K, G>& st, const float* __restrict__ sU, float* sX) {
+  constexpr int kSlot = K < 4 ? K : 0;
+#pragma unroll
+  for (int m = 0; m < G / 16; ++m) st.P[m][kSlot] = st.t[m];
+  solve_planes<kSlot, 1, K, G>(st, sU, sX);
+#pragma unroll
+  for (int m = 0; m < G / 16; ++m) st.tau[m] = st.P[m][kSlot];
+  if constexpr (K == 4) solve_planes<K, 0, K, G>(st, sU, sX);
 }
 
 // Group records of a layer (SuLayout), by work-groups of 256 threads, kPackWGs<G> to a group: one per 16 rows of the
@@ -482,7 +638,7 @@ __device__ __forceinline__ void pack_image(const float* __restrict__ U, int ldu,
     const int l = e / G, j = e % G, m = j >> 4;         // row l0 + l
     if (m < M) continue;
     float* row = rows + 16 * l * live;
-    row[Lay::slot_index(S, m - M, j & 15)] = (j > l0 + l) ? v[t] : 0.f;
+    row[Lay::slot_index(S, m - M, j & 15)] = (j > l0 + l) ? -v[t] : 0.f;
     if (m == M && live > S) row[Lay::slot_index(S, S, j & 15)] = 0.f;
   }
 }
@@ -598,8 +754,8 @@ __device__ __forceinline__ double fit_and_score(const RowState<K, G>& st, double
       double s = 0.0;
 #pragma unroll
       for (int m = 0; m < CPL; ++m) {
-        const float va = (a == 0) ? st.p0[m] : st.P[a - 1 < 0 ? 0 : a - 1][m];
-        const float vb = (b == 0) ? st.p0[m] : st.P[b - 1 < 0 ? 0 : b - 1][m];
+        const float va = (a == 0) ? st.p0[m] : st.P[m][a - 1 < 0 ? 0 : a - 1];
+        const float vb = (b == 0) ? st.p0[m] : st.P[m][b - 1 < 0 ? 0 : b - 1];
         s += (double)va * (double)vb;
       }
       Gm[a][b] = row_sum_d(s);
@@ -607,7 +763,7 @@ __device__ __forceinline__ double fit_and_score(const RowState<K, G>& st, double
     double s = 0.0;
 #pragma unroll
     for (int m = 0; m < CPL; ++m) {
-      const float va = (a == 0) ? st.p0[m] : st.P[a - 1 < 0 ? 0 : a - 1][m];
+      const float va = (a == 0) ? st.p0[m] : st.P[m][a - 1 < 0 ? 0 : a - 1];
       s += (double)va * (double)st.tau[m];
     }
     r[a] = row_sum_d(s);
@@ -648,24 +804,11 @@ __device__ __forceinline__ double fit_and_score(const RowState<K, G>& st, double
   for (int m = 0; m < CPL; ++m) {
     float e = fmaf(-c32[0], st.p0[m], st.tau[m]);
 #pragma unroll
-    for (int i = 0; i < K; ++i) e = fmaf(-c32[i + 1], st.P[i][m], e);
+    for (int i = 0; i < K; ++i) e = fmaf(-c32[i + 1], st.P[m][i], e);
     Ep[m] = e;
     sc += (double)e * (double)e;
   }
   return row_sum_d(sc);
-}
-
-// v(code) = ((c0 + b1 c1) + b2 c2) + ...  in fp32 (Eq. 7)
-template <int K>
-__device__ __forceinline__ void level_table(const float (&c)[K + 1], float (&lv)[1 << K]) {
-#pragma unroll
-  for (int code = 0; code < (1 << K); ++code) {
-    float v = c[0];
-#pragma unroll
-    for (int i = 0; i < K; ++i)
-      if ((code >> i) & 1) v = v + c[i + 1];
-    lv[code] = v;
-  }
 }
 
 // ------------------------------------------------------------------ pending updates --------
@@ -758,11 +901,14 @@ struct PendingTile {
   static constexpr int kStride = G + 4;
   static constexpr int kFloats = kRowsPerWG * kStride;
 };
+// LDS behind the image: the pending tile, later the row scores of every iterate
+template <int G>
+constexpr int kScratchFloats = PendingTile<G>::kFloats > 2 * (kMaxIters + 1) * kRowsPerWG ? PendingTile<G>::kFloats
+                                                                                 : 2 * (kMaxIters + 1) * kRowsPerWG;
 template <int G>
 __device__ __forceinline__ void pending_update_tile(const float* __restrict__ Eall, int lde,
                                                     const float* __restrict__ U, int ldu, int kp0,
                                                     int Kp, int row0, int s0, float* sT) {
-  typedef float f4 __attribute__((ext_vector_type(4)));
   constexpr int NB = G / 16, BPW = (NB + 3) / 4;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int i = lane & 15, kq = lane >> 4;
@@ -858,7 +1004,10 @@ __device__ __forceinline__ void store_candidate(const RowState<K, G>& st, const 
     if (lane16 <= K) {
       float v = c32[0];
 #pragma unroll
-      for (int i = 1; i <= K; ++i) v = (lane16 == i) ? c32[i] : v;
+      for (int i = 1; i <= K; ++i) {
+        v = (lane16 == i) ? c32[i] : v;
+        BPDQ_PIN(v);        // or c32 goes through scratch memory, and its load waits for the stores above
+      }
       coef[((long)it * d_out + row) * (K + 1) + lane16] = v;
     }
   }
@@ -902,6 +1051,7 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void bpdq_gro
   double* sScore = reinterpret_cast<double*>(sT);
   const int tid = threadIdx.x;
   const int lane16 = tid & 15;
+  float* sX = sT + kScratchFloats<G> + (tid >> 6) * kSolveFloats;     // this wavefront's, see solve_planes
   stage_request<G>(rec, sU);
 
   const int row = blockIdx.x * kRowsPerWG + (tid >> 4);
@@ -930,28 +1080,17 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void bpdq_gro
     float z = rintf(q);                       // round half to even
     z = fminf(fmaxf(z, 0.f), 255.f);
     st.code[m] = flat ? 0 : ((int)z >> (8 - K));
-    st.tau[m] = st.t[m];
-#pragma unroll
-    for (int i = 0; i < K; ++i) st.P[i][m] = 0.f;
   }
   float c32[K + 1], Ep[CPL];
-#pragma unroll
-  for (int i = 0; i <= K; ++i) c32[i] = 0.f;
-  using Seq = std::make_integer_sequence<int, G>;
-  run_columns<K, G, kStepInit>(st, sU, c32, lane16, Seq{});
+  solve_target<K, G>(st, sU, sX);
 
   double rs = fit_and_score<K, G>(st, (double)alpha, coef_fp16, c32, Ep);
   store_candidate<K, G>(st, c32, Ep, rs, 0, row, valid, d_out, cand_codes, cand_coef, cand_E, sScore, lane16);
 
   // ---- refinement iterations (Sec. 3.3)
   for (int it = 1; it <= T; ++it) {
-#pragma unroll
-    for (int m = 0; m < CPL; ++m) {
-      st.wg[m] = st.t[m];
-#pragma unroll
-      for (int i = 0; i < K; ++i) st.P[i][m] = 0.f;
-    }
-    run_columns<K, G, kStepSweep>(st, sU, c32, lane16, Seq{});
+    sweep<K, G>(st, sU, c32, lane16);
+    solve_planes<K, 0, K, G>(st, sU, sX);
     rs = fit_and_score<K, G>(st, (double)alpha, coef_fp16, c32, Ep);
     store_candidate<K, G>(st, c32, Ep, rs, it, row, valid, d_out, cand_codes, cand_coef, cand_E, sScore, lane16);
   }
@@ -1009,18 +1148,16 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void uniform_
 #pragma unroll
   for (int i = 0; i < K; ++i) grid[i + 1] = step * (float)(1 << i);
   store_precision(grid, coef_fp16, c32);
-#pragma unroll
-  for (int m = 0; m < CPL; ++m) {
-    st.wg[m] = st.t[m];
-    st.tau[m] = 0.f;
-    st.code[m] = 0;
-  }
-  using Seq = std::make_integer_sequence<int, G>;
-  run_columns<K, G, kStepUniform>(st, sU, c32, lane16, Seq{});
+  sweep<K, G>(st, sU, c32, lane16);
+  float lvl[1 << K];
+  sweep_levels<K>(c32, lvl);
   double sc = 0.0;
 #pragma unroll
   for (int m = 0; m < CPL; ++m) {
-    Ep[m] = st.tau[m];
+    float q = lvl[0];
+#pragma unroll
+    for (int c = 1; c < (1 << K); ++c) q = (st.code[m] == c) ? lvl[c] : q;
+    Ep[m] = (st.wg[m] - q) * st.inv[m];
     sc += (double)Ep[m] * (double)Ep[m];
   }
   sc = row_sum_d(sc);
@@ -1181,9 +1318,7 @@ int launch_tail_update(hipStream_t stream, TailArgs ta, const float* U, int ldu,
 
 template <int G>
 constexpr size_t sweep_lds_bytes() {
-  constexpr size_t kTile = PendingTile<G>::kFloats * sizeof(float);
-  constexpr size_t kScores = (size_t)(kMaxIters + 1) * kRowsPerWG * sizeof(double);
-  const size_t a = kStageFloats<G> * sizeof(float) + (kTile > kScores ? kTile : kScores);
+  const size_t a = (kStageFloats<G> + kScratchFloats<G> + 4 * kSolveFloats) * sizeof(float);
   return a < TailGemm::kLdsBytes ? TailGemm::kLdsBytes : a;
 }
 

@@ -1021,6 +1021,54 @@ def test_nearest_level_ties_take_the_lowest_code(dev, bits, group):
     assert float(out["grp_err"][0]) == float(((W - want).astype(np.float64) ** 2).sum())
 
 
+@pytest.mark.parametrize("group", [32, 64, 128, 256])
+def test_ties_between_descending_levels(dev, group):
+    """Code 1 fitted above code 2, and a weight half-way between the two (114 between 115.75 and 112.25): the lower code
+    wins, not the lower level.  U = I and no ridge: every number of the first refinement is exact."""
+    print(f"descending tie g={group}", flush=True)
+    t = np.repeat([0, 114, 142, 255, 202, 17, 118], np.array([10, 1, 1, 1, 3, 2, 14]) * (group // 32)).astype(np.float32)
+    W = np.tile(t, (19, 1))
+    W[7] = np.roll(t, 5)
+    W[11] = np.linspace(-1, 1, group)
+    ref = orc.quantize_layer(W.astype(np.float64), np.eye(group), None, 2, group, group, 1, alpha=0.0)
+    assert ref["grp_iter"][0] == 1 and np.all(ref["code"][0][t == 114] == 1)
+    out = bq.bpdq_quantize_layer(torch.from_numpy(W).to(dev), torch.eye(group, device=dev), None,
+                                 bq.make_params(2, group, group, 1, 0.0))
+    assert int(out["grp_iter"][0]) == 1
+    assert np.array_equal(orc.unpack_planes(out["planes"].cpu().numpy().view(np.uint32), group), ref["code"])
+
+
+@pytest.mark.parametrize("bits,group", [(1, 64), (2, 128), (3, 32), (3, 256), (4, 128)])
+@pytest.mark.parametrize("exponent", [-70, -64, 0, 64])
+def test_sweep_is_its_definition_where_squares_leave_fp32(dev, bits, group, exponent):
+    """A decision is the smallest squared distance in fp32, the lowest code of several, also where the squares are
+    denormal, zero or infinite and more and more levels tie.  Fixed grid, one group; the sweep column by column in
+    fp32: e = (w - level) (1 / U_ll), and a fused multiply-add (a product of two fp32 is exact in 64 bits) per later column."""
+    print(f"sweep by definition k={bits} g={group} 2^{exponent}", flush=True)
+    rng = np.random.default_rng(100 * bits + group)
+    f = np.float32
+    W = np.ldexp(rng.standard_normal((37, group)).astype(f), exponent)
+    U = (np.eye(group) * (1 + 0.2 * rng.random(group)) + np.triu(rng.standard_normal((group, group)), 1) * 0.3 / group ** 0.5).astype(f)
+    lo, hi = W.min(1), W.max(1)
+    step = (hi - lo) / f((1 << bits) - 1)
+    levels = np.empty((37, 1 << bits), f)
+    for c in range(1 << bits):
+        levels[:, c] = lo
+        for i in range(bits):
+            if c >> i & 1:
+                levels[:, c] += step * f(1 << i)
+    w, want, inv = W.copy(), np.empty((37, group), np.int64), f(1) / U.diagonal()
+    with np.errstate(over="ignore", under="ignore"):
+        for j in range(group):
+            d = w[:, j:j + 1] - levels
+            want[:, j] = np.argmin(d * d, 1)
+            e = d[np.arange(37), want[:, j]] * inv[j]
+            w[:, j + 1:] = (w[:, j + 1:].astype(np.float64) - e[:, None].astype(np.float64) * U[j, j + 1:]).astype(f)
+    out = bq.bpdq_quantize_layer(torch.from_numpy(W).to(dev), torch.from_numpy(U).to(dev), None,
+                                 bq.make_params(bits, group, group, 0, grid=bq.GRID_UNIFORM))
+    assert np.array_equal(orc.unpack_planes(out["planes"].cpu().numpy().view(np.uint32), group), want)
+
+
 @pytest.mark.parametrize("bits,group", [(1, 64), (2, 32), (2, 128), (3, 256), (4, 64)])
 def test_levels_that_are_not_finite_never_win(dev, bits, group):
     """The nearest level is the one that a scan from code 0 with a strict `<` keeps: an infinite or NaN distance never

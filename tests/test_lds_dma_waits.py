@@ -99,6 +99,37 @@ def test_a_broadcast_operand_is_two_instructions_old(assembly):
     assert seen >= 100
 
 
+@pytest.mark.parametrize("source", ["group_sweep_k1.hip", "group_sweep_k2.hip", "group_sweep_k3.hip", "group_sweep_k4.hip",
+                                    "group_sweep_k3_g256.hip"])
+def test_the_sweeps_strings_read_registers_that_are_old_enough(source, assembly):
+    """A broadcast operand two wait states after the vector instruction that wrote it, and what a matrix product wrote eleven
+    after it: the compiler counts neither where an assembly string reads.  (Copies between the register files count too.)"""
+    strings = r"v_(fmac_f32_dpp|sub_f32_dpp|mul_f32_dpp|add_f32|mul_f32|fmac_f32|alignbit_b32)$"
+    broadcasts = matrix = 0
+    for name, ops in assembly(source):
+        if "group_kernel" not in name or "commit" in name:
+            continue
+        ops = plain(ops)
+        for i, op in enumerate(ops):
+            word = op.split()[0]
+            matrix += word.startswith("v_mfma")
+            if not re.match(strings, word):
+                continue
+            regs = [int(r) for r in re.findall(r"\bv(\d+)\b", op)]
+            broadcast = regs[1] if word.endswith("_dpp") else None
+            broadcasts += broadcast is not None
+            states = 0
+            for p in reversed(ops[max(0, i - 12):i]):
+                if states >= 11:
+                    break
+                w = re.match(r"v_\w+ v(?:(\d+)\b|\[(\d+):(\d+)\])", p)
+                wrote = () if not w else {int(w[1])} if w[1] else set(range(int(w[2]), int(w[3]) + 1))
+                assert not (states < 2 and broadcast in wrote), f"{name}: {p} .. {op}"
+                assert not (p.startswith("v_mfma") and wrote & set(regs)), f"{name}: {p} .. {op}"
+                states += 1 + (int(p.split()[1], 0) if p.startswith("s_nop") else 0)
+    assert broadcasts >= 1000 and matrix >= (0 if source.startswith("group_sweep_k1") else 100)
+
+
 def test_no_lds_read_is_in_flight_at_a_barrier(assembly):
     """Where a request may still follow, no LDS read may be in flight at a barrier.  The compiler knows nothing of the DMA and
     moves products, and with them the waits for their operands, over a barrier."""
