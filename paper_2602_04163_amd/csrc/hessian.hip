@@ -273,47 +273,75 @@ __global__ __launch_bounds__(SplitSyrk::kThreads) void hess_syrk_bf16x3_kernel(
 }
 
 // ---- pre-pass of the fp16 path ---------------------------------------------------------------
-// (1) per-channel largest magnitude of the call's tokens, as partial maxima over token ranges;
-// (2) per channel the power of two that brings that maximum into [2^13, 2^14) (so every half is
-//     far from the ends of the fp16 range whatever the activations' units), and its inverse;
+// (1) per-channel largest magnitude, as partial maxima over token ranges; of a large call, of every kSampleStep-th token;
+// (2) per channel the power of two that brings that maximum into [2^13, 2^14), that of a sample into [2^7, 2^8) (so every
+//     half is far from the ends of the fp16 range whatever the activations' units), and its inverse;
 // (3) the split itself: X -> planes[piece][token / 8][channel] (see mfma_split_f16.h), zeros for
 //     the tokens up to the next multiple of 32 and the channels up to the next multiple of 256.
+// A power of two changes nothing in the halves of a value, their products and sums: a sample has to be right only to
+// a factor of 256, which it is unless the channel has an outlier that it missed.  (A low half is denormal, and
+// keeps 2^-32 of the sample's largest, where the value is 2^10 times smaller than that.)  The split looks for values beyond the
+// range, and (1) to (3) then follow with all tokens for the blocks of 256 channels that have one; for the others these
+// launches end at once.
+// Bound by HBM: X is read once and the planes are written, 262144 x 3584 in 1.5 ms against 2.07 with a pass for the maxima
+// of all tokens in front.
+// How a block is marked: its first channel's mul becomes NaN (by the split; nothing reads the planes before
+// the block is done again), then its first channel's inv negative (by the scale of the second turn, which
+// sets mul); the tile product takes magnitudes of inv.
+constexpr int kSampleStep = 64;
+// Values (tokens times channels) from which on the scales come from a sample.  us, all tokens / a sample / a sample that missed
+// an outlier in three blocks of 256 channels / in all of them, at their last tokens: 262144 x 3584 9415 / 8894 / 9280 / 11335;
+// 131072 x 1024 (four blocks) 607 / 532 / 719 / 863; 8192 x 256, below the line, 48 / 43 / 73 (one block): there the three
+// launches that follow up cost more than the pass they may spare.
+constexpr long kSampleValues = 1L << 27;
 constexpr int kColmaxRows = 1024;      // tokens per partial maximum
 constexpr int kSplitKgPerWG = 16;      // k-groups (8 tokens each) per work-group of the split
+constexpr float kHalfMax = 65504.0f;
+enum : int { kAllTokens = 0, kSampled = 1, kMarked = 2 };       // all blocks; the same by a sample; marked blocks
 
+template <int TURN>
 __global__ __launch_bounds__(256) void hess_colmax_kernel(const float* __restrict__ X, int n_tok, int d,
-                                                          long ldx, float* __restrict__ pmax, int d_pad) {
+                                                          long ldx, const float* __restrict__ mul, float* __restrict__ pmax,
+                                                          int n_split, int d_pad) {
+  constexpr int kStep = TURN == kSampled ? kSampleStep : 1, kFlight = TURN == kSampled ? 4 : 8;
   __shared__ float4 red[4][64];
+  if constexpr (TURN == kMarked) {
+    const float first = mul[blockIdx.x * 256];
+    if (first == first) return;
+  }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int c = blockIdx.x * 256 + lane * 4;
-  const int t0 = blockIdx.y * kColmaxRows;
-  const int t1 = min(n_tok, t0 + kColmaxRows);
-  float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (c < d) {                                    // d % 4 == 0: the float4 is inside the row
-    const float* p = X + c;
-    for (int t = t0 + wave; t < t1; t += 32) {    // 8 rows of this wavefront in flight
-      float4 v[8];
+  for (int sp = blockIdx.y; sp < n_split; sp += gridDim.y) {
+    const int t0 = sp * kColmaxRows;
+    const int t1 = min(n_tok, t0 + kColmaxRows);
+    float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (c < d) {                                    // d % 4 == 0: the float4 is inside the row
+      const float* p = X + c;
+      for (int t = t0 + wave * kStep; t < t1; t += 4 * kFlight * kStep) {    // kFlight rows of this wavefront in flight
+        float4 v[kFlight];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int tt = min(t + 4 * u, t1 - 1);    // past the end: the last row again
-        v[u] = *reinterpret_cast<const float4*>(p + (long)tt * ldx);
-      }
+        for (int u = 0; u < kFlight; ++u) {
+          const int tt = min(t + 4 * u * kStep, t1 - 1);    // past the end: the last row again
+          v[u] = *reinterpret_cast<const float4*>(p + (long)tt * ldx);
+        }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        m.x = fmaxf(m.x, fabsf(v[u].x)); m.y = fmaxf(m.y, fabsf(v[u].y));
-        m.z = fmaxf(m.z, fabsf(v[u].z)); m.w = fmaxf(m.w, fabsf(v[u].w));
+        for (int u = 0; u < kFlight; ++u) {
+          m.x = fmaxf(m.x, fabsf(v[u].x)); m.y = fmaxf(m.y, fabsf(v[u].y));
+          m.z = fmaxf(m.z, fabsf(v[u].z)); m.w = fmaxf(m.w, fabsf(v[u].w));
+        }
       }
     }
-  }
-  red[wave][lane] = m;
-  __syncthreads();
-  if (wave == 0) {
+    red[wave][lane] = m;
+    __syncthreads();
+    if (wave == 0) {
 #pragma unroll
-    for (int w = 1; w < 4; ++w) {
-      const float4 o = red[w][lane];
-      m.x = fmaxf(m.x, o.x); m.y = fmaxf(m.y, o.y); m.z = fmaxf(m.z, o.z); m.w = fmaxf(m.w, o.w);
+      for (int w = 1; w < 4; ++w) {
+        const float4 o = red[w][lane];
+        m.x = fmaxf(m.x, o.x); m.y = fmaxf(m.y, o.y); m.z = fmaxf(m.z, o.z); m.w = fmaxf(m.w, o.w);
+      }
+      *reinterpret_cast<float4*>(pmax + (long)sp * d_pad + c) = m;     // c < d_pad always
     }
-    *reinterpret_cast<float4*>(pmax + (long)blockIdx.y * d_pad + c) = m;     // c < d_pad always
+    __syncthreads();                                // (the next range writes red again)
   }
 }
 
@@ -329,22 +357,35 @@ __device__ __forceinline__ int channel_exponent(float m) {
   return e;
 }
 
+template <int TURN>
 __global__ __launch_bounds__(256) void hess_scale_kernel(const float* __restrict__ pmax, int n_split,
                                                          int d_pad, float* __restrict__ mul,
                                                          float* __restrict__ inv) {
-  // 16 channels per work-group, the partial maxima of a channel dealt to 16 threads
+  // 16 channels per work-group, the partial maxima of a channel dealt to 16 threads; marked blocks, a work-group
+  // per block of 256: all of it has seen the mark before it is taken away
+  constexpr bool kSecond = TURN == kMarked;
   __shared__ float red[16][16];
-  const int c = blockIdx.x * 16 + (threadIdx.x & 15), q = threadIdx.x >> 4;
-  float m = 0.f;
-  for (int s = q; s < n_split; s += 16) m = fmaxf(m, pmax[(long)s * d_pad + c]);
-  red[q][threadIdx.x & 15] = m;
-  __syncthreads();
-  if (q) return;
+  if constexpr (kSecond) {
+    const float first = mul[blockIdx.x * 256];
+    __syncthreads();
+    if (first == first) return;
+  }
+  for (int u = 0; u < (kSecond ? 16 : 1); ++u) {
+    const int c = (kSecond ? blockIdx.x * 256 + 16 * u : blockIdx.x * 16) + (threadIdx.x & 15), q = threadIdx.x >> 4;
+    float m = 0.f;
+    for (int s = q; s < n_split; s += 16) m = fmaxf(m, pmax[(long)s * d_pad + c]);
+    red[q][threadIdx.x & 15] = m;
+    __syncthreads();
+    if (q == 0) {
 #pragma unroll
-  for (int w = 1; w < 16; ++w) m = fmaxf(m, red[w][threadIdx.x]);
-  const int e = channel_exponent(m);
-  mul[c] = ldexpf(1.0f, e);
-  inv[c] = ldexpf(1.0f, -e);
+      for (int w = 1; w < 16; ++w) m = fmaxf(m, red[w][threadIdx.x]);
+      // a sample of zeros says nothing: the largest factor, under which anything that counts is out of range
+      const int e = TURN != kSampled ? channel_exponent(m) : m == 0.f ? 100 : max(channel_exponent(m) - 6, -100);
+      mul[c] = ldexpf(1.0f, e);
+      inv[c] = (kSecond && u == 0 && threadIdx.x == 0) ? -ldexpf(1.0f, -e) : ldexpf(1.0f, -e);
+    }
+    __syncthreads();
+  }
 }
 
 __device__ __forceinline__ unsigned pack_halves(_Float16 a, _Float16 b) {
@@ -370,35 +411,51 @@ __device__ __forceinline__ void split_halves(const float (&x)[8], float s, int c
   lv = make_uint4(lw[0], lw[1], lw[2], lw[3]);
 }
 
+template <int TURN>
 __global__ __launch_bounds__(256) void hess_split_f16_kernel(const float* __restrict__ X, int n_tok, int d,
-                                                             long ldx, const float* __restrict__ mul,
+                                                             long ldx, float* mul, const float* __restrict__ inv,
                                                              uint4* __restrict__ planes, long n_kg,
                                                              int d_pad) {
+  if constexpr (TURN == kMarked)
+    if (inv[blockIdx.x * 256] > 0.f) return;
+  if constexpr (TURN == kSampled) {       // marked already: the block is done again anyway
+    const float first = __hip_atomic_load(mul + blockIdx.x * 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (first != first) return;
+  }
   const int ch = blockIdx.x * 256 + threadIdx.x;
   const bool live = ch < d;
   const int chc = live ? ch : d - 1;
   const float s = mul[chc];
   const float* p = X + chc;
-  const long kg0 = (long)blockIdx.y * kSplitKgPerWG;
   const int t_last = n_tok - 1;
-  for (int g = 0; g < kSplitKgPerWG; g += 2) {
-    const long kg = kg0 + g;
-    if (kg >= n_kg) break;
-    float x[16];
+  bool beyond = false;
+  for (long kg0 = (long)blockIdx.y * kSplitKgPerWG; kg0 < n_kg; kg0 += (long)gridDim.y * kSplitKgPerWG) {
+    for (int g = 0; g < kSplitKgPerWG; g += 2) {
+      const long kg = kg0 + g;
+      if (kg >= n_kg) break;
+      float x[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const long t = 8 * kg + i;
-      x[i] = p[(t < t_last ? t : (long)t_last) * ldx];
-    }
+      for (int i = 0; i < 16; ++i) {
+        const long t = 8 * kg + i;
+        x[i] = p[(t < t_last ? t : (long)t_last) * ldx];
+      }
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      if (kg + half >= n_kg) break;
-      uint4 hv, lv;
-      split_halves(reinterpret_cast<const float(&)[8]>(x[8 * half]), s, live ? n_tok - 8 * (int)(kg + half) : 0, hv, lv);
-      planes[(kg + half) * d_pad + ch] = hv;
-      planes[(n_kg + kg + half) * d_pad + ch] = lv;
+      for (int half = 0; half < 2; ++half) {
+        if (kg + half >= n_kg) break;
+        uint4 hv, lv;
+        split_halves(reinterpret_cast<const float(&)[8]>(x[8 * half]), s, live ? n_tok - 8 * (int)(kg + half) : 0, hv, lv);
+        planes[(kg + half) * d_pad + ch] = hv;
+        planes[(n_kg + kg + half) * d_pad + ch] = lv;
+      }
+      if constexpr (TURN == kSampled) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) beyond |= !(fabsf(x[i] * s) <= kHalfMax);    // NaN too (tokens past the end repeat the last)
+      }
     }
   }
+  if constexpr (TURN == kSampled)
+    if (__any(beyond) && (threadIdx.x & 63) == 0)
+      __hip_atomic_store(mul + blockIdx.x * 256, NAN, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The whole pre-pass in one launch for calls of at most 4096 tokens: a work-group holds all tokens of 16
@@ -602,8 +659,8 @@ __global__ __launch_bounds__(SplitF16::kThreads, 1) void hess_syrk_f16x2_kernel(
   // the LDS ring is free now: the channel factors of this tile's rows and columns
   extern __shared__ uint4 smem_f16[];
   float* sInv = reinterpret_cast<float*>(smem_f16);
-  sInv[threadIdx.x] = inv[r0 + threadIdx.x];
-  sInv[256 + threadIdx.x] = inv[c0 + threadIdx.x];
+  sInv[threadIdx.x] = fabsf(inv[r0 + threadIdx.x]);          // (the sign marks a block that was split twice)
+  sInv[256 + threadIdx.x] = fabsf(inv[c0 + threadIdx.x]);
   __syncthreads();
   if constexpr (DIRECT) {
     // H += tile, in batches of 64 results per lane: all loads of a batch first, then its stores.  One load,
@@ -912,15 +969,36 @@ static int hessian_accumulate(int kind, const float* Xc, int n_tok, int d_in, in
         BPDQ_LAUNCH_CHECK();
       } else {
         const int cb = L.d_pad / SplitF16::kTile;
-        hipLaunchKernelGGL(hess_colmax_kernel, dim3(cb, L.n_split), dim3(256), 0, stream, Xpart, n_part,
-                           d_in, (long)ldx, pmax, L.d_pad);
-        BPDQ_LAUNCH_CHECK();
-        hipLaunchKernelGGL(hess_scale_kernel, dim3(L.d_pad / 16), dim3(256), 0, stream, pmax, L.n_split,
-                           L.d_pad, mul, inv);
-        BPDQ_LAUNCH_CHECK();
-        hipLaunchKernelGGL(hess_split_f16_kernel, dim3(cb, (unsigned)bpdq_ceil_div((int)L.n_kg, kSplitKgPerWG)),
-                           dim3(256), 0, stream, Xpart, n_part, d_in, (long)ldx, mul, planes, L.n_kg, L.d_pad);
-        BPDQ_LAUNCH_CHECK();
+        const int kgs = bpdq_ceil_div((int)L.n_kg, kSplitKgPerWG);
+        auto colmax = [&](auto kern, int grid_y) {
+          hipLaunchKernelGGL(kern, dim3(cb, grid_y), dim3(256), 0, stream, Xpart, n_part, d_in, (long)ldx, mul, pmax,
+                             L.n_split, L.d_pad);
+        };
+        auto scale_of = [&](auto kern, int grid) {
+          hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, stream, pmax, L.n_split, L.d_pad, mul, inv);
+        };
+        auto split = [&](auto kern, int grid_y) {
+          hipLaunchKernelGGL(kern, dim3(cb, grid_y), dim3(256), 0, stream, Xpart, n_part, d_in, (long)ldx, mul, inv, planes,
+                             L.n_kg, L.d_pad);
+        };
+        auto turn = [&](auto which, int colmax_y, int scale_wgs, int split_y) -> int {
+          constexpr int kTurn = decltype(which)::value;
+          colmax(hess_colmax_kernel<kTurn>, colmax_y);
+          BPDQ_LAUNCH_CHECK();
+          scale_of(hess_scale_kernel<kTurn>, scale_wgs);
+          BPDQ_LAUNCH_CHECK();
+          split(hess_split_f16_kernel<kTurn>, split_y);
+          BPDQ_LAUNCH_CHECK();
+          return 0;
+        };
+        if ((long)n_part * d_in < kSampleValues) {
+          if (turn(std::integral_constant<int, kAllTokens>{}, L.n_split, L.d_pad / 16, kgs)) return BPDQ_ERR_LAUNCH;
+        } else {
+          if (turn(std::integral_constant<int, kSampled>{}, L.n_split, L.d_pad / 16, kgs)) return BPDQ_ERR_LAUNCH;
+          const int rounds = cb < 512 ? 2048 / cb + 1 : 4;          // small grids where they end at once
+          if (turn(std::integral_constant<int, kMarked>{}, L.n_split < rounds ? L.n_split : rounds, cb, kgs < rounds ? kgs : rounds))
+            return BPDQ_ERR_LAUNCH;
+        }
       }
       if (mark_begin()) return BPDQ_ERR_LAUNCH;
       auto tiles = [&](auto kern, int grid) {

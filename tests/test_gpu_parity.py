@@ -368,6 +368,52 @@ def test_hessian_f16_path_channel_scaling(dev):
 
 
 # ------------------------------------------------------------------ step 2: prepare
+@pytest.mark.parametrize("n_tok,d_in", [(131077, 1024), (44740, 3000)])
+@pytest.mark.parametrize("kind", ["plain", "missed", "not_finite"])
+def test_hessian_scales_from_a_sample(dev, n_tok, d_in, kind):
+    """Calls of 2^27 values and more take a channel's scale from every 64th token.  A channel whose sample is all zeros, or
+    small against an outlier that it missed (first, middle, last token), is split again with all tokens; so is one
+    with an infinity or a NaN, whose row and column of H alone are not finite."""
+    print(f"sampled scales {n_tok}x{d_in} {kind}", flush=True)
+    assert n_tok * d_in >= 1 << 27
+    g = torch.Generator(device=dev)
+    g.manual_seed(n_tok)
+    X = torch.randn((n_tok, d_in), generator=g, device=dev)
+    X *= torch.exp(2 * torch.randn(d_in, generator=g, device=dev))
+    X[:, 17] = 0.0
+    X[:, 33] *= 1e-30
+    X[:, 34] *= 1e15 / X[:, 34].abs().max()                   # (its H entry, below 2 n_tok 1e30, is in fp32's range)
+    if kind != "plain":
+        X[::64, 300] = 0.0                                   # the whole sample
+        X[1, 301], X[n_tok // 2 | 1, 302] = 3e4 * X[1, 301], 1e6
+        X[n_tok - 1 if (n_tok - 1) % 64 else n_tok - 2, 999] = -1e5
+    bad = [] if kind != "not_finite" else [40, 600]
+    if bad:
+        X[5, 40], X[70001 % n_tok | 1, 600] = float("inf"), float("nan")
+    H = torch.zeros((d_in, d_in), device=dev)
+    bq.bpdq_hessian_accumulate(X, H, 2.0, True)
+    good = [c for c in range(d_in) if c not in bad]
+    ref = torch.zeros((len(good), len(good)), dtype=torch.float64, device=dev)
+    for a in range(0, n_tok, 16384):
+        x = X[a:a + 16384, good].double()
+        ref.addmm_(x.t().contiguous(), x, alpha=2.0)
+    got = H[good][:, good].double()
+    for c in bad:
+        assert not torch.isfinite(H[c, c])
+    root = ref.diagonal().sqrt().clamp_min(1e-300)
+    scaled, want = got / root[:, None] / root[None, :], ref / root[:, None] / root[None, :]
+    tiny = root < 1e-18                                       # squares below fp32's range
+    scaled[tiny], want[tiny] = 0.0, 0.0
+    scaled[:, tiny], want[:, tiny] = 0.0, 0.0
+    assert torch.isfinite(scaled).all()
+    assert float((scaled - want).abs().max()) < 2e-5           # the bar of every entry
+    assert float((scaled - want).norm() / want.norm()) < H_TOL
+    assert torch.equal(H[good][:, good], H[good][:, good].t())
+    again = torch.zeros_like(H)
+    bq.bpdq_hessian_accumulate(X, again, 2.0, True)
+    assert torch.equal(torch.nan_to_num(H), torch.nan_to_num(again))
+
+
 @pytest.mark.parametrize("d_in,sigma", [(96, 1.0), (200, 1.0), (640, 1.5), (1288, 1.0)])
 def test_prepare_matches_oracle(dev, d_in, sigma):
     print(f"prepare d_in={d_in}", flush=True)
