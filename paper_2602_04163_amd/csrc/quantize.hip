@@ -120,6 +120,78 @@ __global__ __launch_bounds__(256) void dequant_kernel(const uint32_t* __restrict
   }
 }
 
+// The same for large matrices whose groups hold whole plane words: a work-group stages the words and coefficients of a
+// tile of kTileRows x kTileCols in LDS and forms the tile from there.  Stores alone reach 7.0 TB/s on this card
+// (8192 x 8192: 38.5 us), the loads alone took 19 us and the two together 57: a thread that forms four columns of a row loads
+// K words and K + 1 coefficients that its seven neighbours load too, 20 small requests for every 16 values, and they
+// queue with the stores.  Staged, a row's words come as 256 consecutive bytes per plane, 4 K loads per thread and tile.
+// 8192 x 8192, 2 planes, half coefficients: 62 -> 46 us (16 x 1024 tiles 49, 8 x 4096 46, 32 x 1024 50; a second
+// tile's loads ahead of the stores gains nothing).
+constexpr int kTileRows = 16, kTileCols = 2048;
+template <int K>
+constexpr int kTileCoefs = K < 4 ? 4 : 8;           // floats a (row, group) takes in LDS
+
+template <typename CT, int K>
+__global__ __launch_bounds__(256) void dequant_tile_kernel(const uint32_t* __restrict__ planes, const CT* __restrict__ coefs,
+                                                           int d_out, int d_in, int group, float* __restrict__ W_hat) {
+  constexpr int kWords = kTileCols / 32, CP = kTileCoefs<K>, kLoads = K * kTileRows * kWords / 256;
+  extern __shared__ uint32_t sW[];                                      // [plane][row][word]
+  float* sC = reinterpret_cast<float*>(sW + K * kTileRows * kWords);    // [row][group of the tile][CP]
+  const int n_word = d_in / 32, n_grp = d_in / group, tid = threadIdx.x;
+  const int c0 = blockIdx.x * kTileCols, w0 = c0 / 32, g0 = c0 / group;
+  const int c1 = c0 + kTileCols < d_in ? c0 + kTileCols : d_in;
+  const int last_word = (c1 - 1) / 32, n_c = (c1 - 1) / group - g0 + 1, n_coef = kTileRows * n_c * (K + 1);
+  const int row_tiles = (d_out + kTileRows - 1) / kTileRows;
+  for (int t = blockIdx.y; t < row_tiles; t += gridDim.y) {
+    const int r0 = t * kTileRows;
+    auto row = [&](int r) { return (long)(r0 + r < d_out ? r0 + r : d_out - 1); };      // past the end: the last row, not stored
+    uint32_t w[kLoads];
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+      const int e = tid + 256 * u, x = e % kWords, r = e / kWords % kTileRows, i = e / kWords / kTileRows;
+      w[u] = planes[((long)i * d_out + row(r)) * n_word + (w0 + x <= last_word ? w0 + x : w0)];
+    }
+    for (int e0 = tid; e0 < n_coef; e0 += 1024) {
+      CT c[4];
+      int to[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int e = e0 + 256 * u < n_coef ? e0 + 256 * u : e0;
+        const int g = e % n_c, rr = e / n_c, r = rr % kTileRows, i = rr / kTileRows;
+        c[u] = coefs[((long)i * d_out + row(r)) * n_grp + g0 + g];
+        to[u] = (r * n_c + g) * CP + i;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) sC[to[u]] = coef_value(c[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) sW[tid + 256 * u] = w[u];
+    __syncthreads();
+    for (int q = 0; q < kTileRows && r0 + q < d_out; ++q) {
+#pragma unroll
+      for (int u = 0; u < kTileCols / 1024; ++u) {
+        const int x = 4 * tid + 1024 * u, c = c0 + x;
+        if (c >= d_in) break;
+        const float* f = sC + (q * n_c + c / group - g0) * CP;
+        const float4 f0 = *reinterpret_cast<const float4*>(f);
+        const float cf[5] = {f0.x, f0.y, f0.z, f0.w, K < 4 ? 0.f : f[K < 4 ? 0 : 4]};
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = cf[0];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+          const uint32_t word = sW[(i * kTileRows + q) * kWords + x / 32] >> (x & 31);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if ((word >> e) & 1u) v[e] = v[e] + cf[i + 1];
+        }
+        *reinterpret_cast<float4*>(W_hat + (long)(r0 + q) * d_in + c) = make_float4(v[0], v[1], v[2], v[3]);
+      }
+    }
+    __syncthreads();                                                    // (the next tile's words go to the same place)
+  }
+}
+
 __global__ __launch_bounds__(256) void coefs_to_fp16_kernel(const float* __restrict__ coefs, long n,
                                                             _Float16* __restrict__ out) {
   for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < n; e += (long)gridDim.x * 256)
@@ -377,8 +449,26 @@ static int launch_dequant(const uint32_t* planes, const CT* coefs, int d_out, in
     BPDQ_LAUNCH_CHECK();
     return 0;
   };
+  // Tiles through LDS where there are four for every compute unit and their columns are in use: one tile of 1024 or more, or
+  // seven eighths of several.  us, a thread's own loads / tiles, half coefficients: 8192 x 8192 61.3 / 48.2 at 2 planes and groups
+  // of 128, 82.5 / 64.5 at 4 and 64; 8192 x 3584 24.6 / 21.1 and 34.1 / 27.6; 16384 x 1280 22.7 / 17.4; 70000 x 1024 68.6 / 57.8.
+  // On the other side of the line: 4096 x 4096, 512 tiles, 14.9 / 13.8, but 3000 x 6016, 564, 18.6 / 20.4 at 3 planes and groups of 32
+  // (staging is a round trip to memory that only other work-groups hide, and units with three tiles wait for those with two);
+  // 9300 x 3072, the second of two tiles half full, 22.1 / 22.8; 8192 x 2304, an eighth full, 16.8 / 19.1.
+  const int col_tiles = bpdq_ceil_div(d_in, kTileCols);
+  const bool tiles = vec && group % 32 == 0 && d_in >= 1024 && (col_tiles == 1 || 8L * d_in >= 7L * col_tiles * kTileCols) &&
+                     (long)bpdq_ceil_div(d_out, kTileRows) * col_tiles >= 1024;
   auto pick = [&](auto planes_of) -> int {
     constexpr int K = decltype(planes_of)::value;
+    if (tiles) {
+      const int groups = (d_in < kTileCols ? d_in : kTileCols) / group + 2;
+      const size_t lds = (size_t)(K * kTileRows * kTileCols / 32 + kTileRows * groups * kTileCoefs<K>) * 4;
+      const int row_tiles = bpdq_ceil_div(d_out, kTileRows);
+      hipLaunchKernelGGL((dequant_tile_kernel<CT, K>), dim3(col_tiles, row_tiles < 65535 ? row_tiles : 65535),
+                         dim3(256), lds, stream, planes, coefs, d_out, d_in, group, W_hat);
+      BPDQ_LAUNCH_CHECK();
+      return 0;
+    }
     if (!vec) return many ? launch(dequant_kernel<CT, K, 1, 8, false>) : launch(dequant_kernel<CT, K, 1, 1, false>);
     if (width < 256) return many ? launch(dequant_kernel<CT, K, 4, 4, false>) : launch(dequant_kernel<CT, K, 4, 1, false>);
     return many ? launch(dequant_kernel<CT, K, 4, 4, true>) : launch(dequant_kernel<CT, K, 4, 1, true>);

@@ -1228,6 +1228,8 @@ def test_pack_and_dequant_bit_exact(dev, bits):
     (33, 32, 32, 0), (130, 96, 32, 0),                      # several row blocks to a work-group, the last one part full
     (4099, 256, 64, 0), (1025, 1056, 32, 0),                # several rows per thread: narrow, wide
     (1027, 1056, 3, 0), (8201, 128, 64, 1),                 # ... with scalar stores
+    (16369, 1024, 32, 0), (16387, 1056, 96, 0),             # tiles through LDS: one column tile, rows past the last tile's
+    (8177, 3584, 256, 0), (4097, 7456, 32, 0),              # ... several, the last one part full
 ])
 def test_dequant_tile_edges(dev, half, d_out, d_in, group, shift):
     """Both store widths of the dequant kernel at the edges of its tiles, bit for bit."""
