@@ -1165,62 +1165,89 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void uniform_
   store_scores(sScore, 0, n_wg, cand_score);
 }
 
-// Selection + commit of one group, 16 rows per work-group (same lane mapping as the sweep).
+// Selection + commit of one group, 32 rows (two row blocks of the sweep, with its lane mapping) per work-group.
 // Every work-group first sums the row-block scores of each iterate over its own layer (segment)
 // in one fixed order and takes the earliest minimum (Sec. 3.3: keep the iterate with the smallest
-// ||E_group||_F^2), so all work-groups of a layer agree bit for bit; the first work-group of a
+// ||E_group||_F^2), so all work-groups of a layer agree bit for bit; the first row block of a
 // segment publishes grp_iter / grp_err (arrays of n_grp entries per segment).  Then the kept
 // iterate is written out: packed planes (wave ballots), coefficients, What, and E* transposed
 // into the K-major error buffer Eblk[(s0 - b0) + j][row] (leading dimension lde).
+// Bound by the dependent trips to memory (scores, then the kept iterate) on small layers, by traffic on large ones:
+// 32 rows write whole lines of 128 bytes of Eblk and read the scores half as often as 16 rows do, eight wavefronts take one
+// iterate each up to T = 7, and What goes out by 16 bytes a lane.  A launch at T = 5, 16 rows and 4-byte stores / this:
+// 18944 rows, 3 planes 15.9 / 13.3 us (31 MB), 3584 rows, 2 planes 5.5 / 5.3.
+constexpr int kCommitBlocks = 2, kCommitRows = kCommitBlocks * kRowsPerWG, kCommitThreads = 16 * kCommitRows;
 template <int K, int G>
-__global__ __launch_bounds__(256) void commit_group_kernel(
+__global__ __launch_bounds__(kCommitThreads) void commit_group_kernel(
     const uint32_t* __restrict__ cand_codes, const float* __restrict__ cand_coef,
     const float* __restrict__ cand_E, const double* __restrict__ cand_score, int n_wg, int T,
     SegArgs seg, double* __restrict__ grp_err, int* __restrict__ grp_iter, int d_out, int d_in,
     int s0, int b0,
     uint32_t* __restrict__ planes, float* __restrict__ coefs, float* __restrict__ W_hat,
     float* __restrict__ Eblk, int lde) {
-  constexpr int CPL = G / 16;
+  constexpr int CPL = G / 16, kFlight = 8;
   __shared__ double tot[64];
-  __shared__ float sE[G][17];
+  __shared__ float sE[G][kCommitRows + 1];
+  __shared__ __attribute__((aligned(4))) unsigned char sCode[kCommitRows][G + 4];
+  __shared__ float sLevel[kCommitRows][(1 << K) + 1];
   const int tid = threadIdx.x, lane16 = tid & 15;
-  // my segment (work-groups past the last row belong to the last one; they write nothing)
-  int wg_lo = 0, wg_hi = seg.wg_end[0], si = 0;
+  int it = 0, si_done = -1;
+#pragma unroll 1
+  for (int h = 0; h < kCommitBlocks; ++h) {
+    // the segment of this row block (blocks past the last row belong to the last one; they write nothing)
+    const int blk = blockIdx.x * kCommitBlocks + h;
+    int wg_lo = 0, wg_hi = seg.wg_end[0], si = 0;
 #pragma unroll
-  for (int q = 1; q < kMaxSegments; ++q)
-    if (q < seg.n_seg && (int)blockIdx.x >= seg.wg_end[q - 1]) {
-      wg_lo = seg.wg_end[q - 1];
-      wg_hi = seg.wg_end[q];
-      si = q;
+    for (int q = 1; q < kMaxSegments; ++q)
+      if (q < seg.n_seg && blk >= seg.wg_end[q - 1]) {
+        wg_lo = seg.wg_end[q - 1];
+        wg_hi = seg.wg_end[q];
+        si = q;
+      }
+    if (si == si_done) break;                            // uniform: the block before has it
+    if (h > 0) __syncthreads();                          // tot has been read
+    // iterate q is summed by wavefront q % 8: strided partial sums per lane, then a fixed
+    // xor butterfly over the 64 lanes
+    for (int q = tid >> 6; q <= T; q += kCommitThreads / 64) {
+      double s = 0.0;
+      // kFlight scores of a lane in flight, added in the order of the row blocks (one at a time a layer of 18944
+      // rows waited 19 times per iterate; a score past the end adds zero)
+      for (int w = wg_lo + (tid & 63); w < wg_hi; w += 64 * kFlight) {
+        double v[kFlight];
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) v[u] = cand_score[(long)q * n_wg + (w + 64 * u < wg_hi ? w + 64 * u : w)];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) s += (w + 64 * u < wg_hi) ? v[u] : 0.0;
+      }
+#pragma unroll
+      for (int m = 32; m > 8; m >>= 1) s += __shfl_xor(s, m, 64);
+      // within 16 lanes by rotations: of values that repeat every 16, 8, 4 and 2 lanes by then, those 8, 4, 2 and 1
+      // lanes away are the butterfly's pairs (and a sum of two has no order)
+      s += dpp_d<0x128>(s);
+      s += dpp_d<0x124>(s);
+      s += dpp_d<0x122>(s);
+      s += dpp_d<0x121>(s);
+      if ((tid & 63) == 0) tot[q] = s;
     }
-  // iterate q is summed by wavefront q % 4: strided partial sums per lane, then a fixed
-  // xor butterfly over the 64 lanes
-  for (int q = tid >> 6; q <= T; q += 4) {
-    double s = 0.0;
-    // eight scores of a lane in flight, added in the order of the row blocks (one at a time a layer of 18944
-    // rows waited 19 times per iterate; a score past the end adds zero)
-    for (int w = wg_lo + (tid & 63); w < wg_hi; w += 512) {
-      double v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = cand_score[(long)q * n_wg + (w + 64 * u < wg_hi ? w + 64 * u : w)];
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) s += (w + 64 * u < wg_hi) ? v[u] : 0.0;
+    __syncthreads();
+    int kept = 0;
+    double best = tot[0];
+#pragma unroll 4
+    for (int q = 1; q <= T; ++q) {
+      const double v = tot[q];
+      kept = v < best ? q : kept;
+      best = v < best ? v : best;
     }
-#pragma unroll
-    for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m, 64);
-    if ((tid & 63) == 0) tot[q] = s;
-  }
-  __syncthreads();
-  int it = 0;
-  for (int q = 1; q <= T; ++q)
-    if (tot[q] < tot[it]) it = q;
-  if ((int)blockIdx.x == wg_lo && tid == 0) {
-    grp_iter[(long)si * (d_in / G)] = it;
-    grp_err[(long)si * (d_in / G)] = tot[it];
+    if (blk == wg_lo && tid == 0) {
+      grp_iter[(long)si * (d_in / G)] = kept;
+      grp_err[(long)si * (d_in / G)] = best;
+    }
+    if ((tid >> 8) >= h) it = kept;                      // 256 threads to a row block
+    si_done = si;
   }
 
-  const int row0 = blockIdx.x * kRowsPerWG;
+  const int row0 = blockIdx.x * kCommitRows;
   const int rloc = tid >> 4;
   const int row = row0 + rloc;
   const bool valid = row < d_out;
@@ -1261,27 +1288,37 @@ __global__ __launch_bounds__(256) void commit_group_kernel(
       if (valid && lane16 == 0) planes[((long)i * d_out + row) * n_word + s0 / 32 + w] = word;
     }
   }
-  if (valid) {
-    if (W_hat) {
+  if (W_hat) {
 #pragma unroll
-      for (int m = 0; m < CPL; ++m) {
-        float v = lv[0];
+    for (int m = 0; m < CPL; ++m) sCode[rloc][16 * m + lane16] = (unsigned char)code[m];
+    float v = lv[0];
 #pragma unroll
-        for (int q = 1; q < (1 << K); ++q) v = (code[m] == q) ? lv[q] : v;
-        W_hat[(long)row * d_in + s0 + 16 * m + lane16] = v;
-      }
-    }
-    if (lane16 <= K) {
-      float v = c[0];
+    for (int q = 1; q < (1 << K); ++q) v = (lane16 == q) ? lv[q] : v;
+    if (lane16 < (1 << K)) sLevel[rloc][lane16] = v;
+  }
+  if (valid && lane16 <= K) {
+    float v = c[0];
 #pragma unroll
-      for (int i = 1; i <= K; ++i) v = (lane16 == i) ? c[i] : v;
-      coefs[((long)lane16 * d_out + row) * n_grp + gi] = v;
-    }
+    for (int i = 1; i <= K; ++i) v = (lane16 == i) ? c[i] : v;
+    coefs[((long)lane16 * d_out + row) * n_grp + gi] = v;
   }
   __syncthreads();
-  for (int idx = tid; idx < G * kRowsPerWG; idx += 256) {
-    const int j = idx >> 4, r = idx & 15;
-    Eblk[(long)(s0 - b0 + j) * lde + row0 + r] = sE[j][r];
+  for (int idx = tid; idx < G * kCommitRows / 4; idx += kCommitThreads) {
+    const int j = idx / (kCommitRows / 4), r = 4 * (idx % (kCommitRows / 4));
+    *reinterpret_cast<float4*>(Eblk + (long)(s0 - b0 + j) * lde + row0 + r) =
+        make_float4(sE[j][r], sE[j][r + 1], sE[j][r + 2], sE[j][r + 3]);
+  }
+  if (W_hat) {
+    typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));      // (W_hat need not be aligned to 16 bytes)
+    for (int idx = tid; idx < G * kCommitRows / 4; idx += kCommitThreads) {
+      const int r = idx / (G / 4), x = 4 * (idx % (G / 4));
+      if (row0 + r >= d_out) break;                      // (later ones are further rows)
+      const uint32_t four = *reinterpret_cast<const uint32_t*>(&sCode[r][x]);
+      f4_any v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = sLevel[r][(four >> (8 * e)) & 15u];
+      *reinterpret_cast<f4_any*>(W_hat + (long)(row0 + r) * d_in + s0 + x) = v;
+    }
   }
 }
 
@@ -1397,7 +1434,7 @@ static inline int launch_group(hipStream_t stream, const float* Wp, int d_out, i
                        L.n_wg, Eall, L.lde, kp0, ta);
   }
   BPDQ_LAUNCH_CHECK();
-  hipLaunchKernelGGL((commit_group_kernel<K, G>), dim3(L.lde / kRowsPerWG), dim3(256), 0, stream,
+  hipLaunchKernelGGL((commit_group_kernel<K, G>), dim3(L.lde / kCommitRows), dim3(kCommitThreads), 0, stream,
                      c_codes, c_coef, c_E, c_score, L.n_wg, T, seg, grp_err + gi, grp_iter + gi, d_out,
                      d_in, s0, 0, planes, coefs, W_hat, Eall, L.lde);
   BPDQ_LAUNCH_CHECK();

@@ -881,6 +881,46 @@ def test_stacked_layers_equal_separate_calls(dev):
             bq.bpdq_quantize_layers(Wd, bad, U, None, p)
 
 
+@pytest.mark.parametrize("rows,bits,group,iters", [
+    ([16, 16, 16, 1], 2, 64, 9),             # a boundary inside every 32 rows that are committed together; more iterates than wavefronts
+    ([80, 49], 4, 32, 0),                    # one iterate, 16 levels, a ragged end
+    ([48, 544], 1, 128, 7),                  # more row blocks than a lane takes scores
+    ([33], 3, 256, 8),                       # one row past a work-group
+])
+def test_commit_of_stacked_and_unaligned_layers(dev, rows, bits, group, iters):
+    """Two row blocks are committed together: they may belong to two layers, and W_hat may lie anywhere.  Every output
+    equals that of the layers by themselves bit for bit, and W_hat the matrix that the stored format gives."""
+    print(f"commit rows={rows} k={bits} g={group} T={iters}", flush=True)
+    d_in = 512
+    wl, W, X = _problem("cfg2_qwen7b_attn", sum(rows), d_in, 2 * d_in)
+    W[rows[0]:] *= 7.0
+    H = np.zeros((d_in, d_in))
+    orc.hessian_accumulate(X.numpy(), H)
+    U = torch.from_numpy(orc.prepare(H, wl.damp)[0].astype(np.float32)).to(dev)
+    p = bq.make_params(bits, group, max(128, group), iters, wl.alpha)
+    Wd, n_grp = W.to(dev), d_in // group
+    both = bq.bpdq_quantize_layers(Wd, np.cumsum(rows).tolist(), U, None, p)
+    r0 = 0
+    for s, n in enumerate(rows):
+        r1 = r0 + n
+        for shift in (0, 1, 2, 3):
+            flat = torch.full((n * d_in + shift + 4,), 3.0, device=dev)
+            out = dict(planes=torch.empty((bits, n, d_in // 32), dtype=torch.int32, device=dev),
+                       coefs=torch.empty((bits + 1, n, n_grp), device=dev),
+                       W_hat=flat[shift:shift + n * d_in],
+                       grp_err=torch.empty(n_grp, dtype=torch.float64, device=dev),
+                       grp_iter=torch.empty(n_grp, dtype=torch.int32, device=dev))
+            bq.bpdq_quantize_layer(Wd[r0:r1].contiguous(), U, None, p, out=out)
+            assert torch.equal(both["planes"][:, r0:r1], out["planes"])
+            assert torch.equal(both["coefs"][:, r0:r1], out["coefs"])
+            assert torch.equal(both["W_hat"][r0:r1].reshape(-1), out["W_hat"])
+            assert bool((flat[:shift] == 3.0).all()) and bool((flat[shift + n * d_in:] == 3.0).all())
+            assert torch.equal(both["grp_iter"][s], out["grp_iter"])
+            assert torch.equal(both["grp_err"][s], out["grp_err"])
+        r0 = r1
+    assert torch.equal(both["W_hat"], bq.bpdq_dequant(both["planes"], both["coefs"], group))
+
+
 # ------------------------------------------------------------------ serving side
 @pytest.mark.parametrize("bits,group,d_out,d_in", [
     (2, 128, 200, 384), (3, 64, 37, 320), (4, 32, 64, 2080), (1, 256, 19, 512), (2, 128, 515, 3584),
