@@ -104,8 +104,7 @@ struct RowState {
 // launch that copies W (pack_factor), together with 1 / U_ll and P_0 = 1 U_loc^-1, which are the
 // same for all rows: a group launch streams the image into LDS with LDS-DMA while it gathers its
 // target.  Fetching and rearranging U_loc in every work-group had cost 12 k of a launch's 186 k cycles
-// (k = 2, g = 128, 5 iterations) and the P_0 recurrence a quarter of the initial pass; a launch takes
-// 154 k now, 128 k of them in the five iterations.
+// (k = 2, g = 128, 5 iterations; 154 k without them) and the P_0 recurrence a quarter of the initial pass.
 template <int G>
 struct SuLayout {
   static constexpr int CPL = G / 16;
