@@ -274,15 +274,13 @@ __global__ __launch_bounds__(SplitSyrk::kThreads) void hess_syrk_bf16x3_kernel(
 
 // ---- pre-pass of the fp16 path ---------------------------------------------------------------
 // (1) per-channel largest magnitude, as partial maxima over token ranges; of a large call, of every kSampleStep-th token;
-// (2) per channel the power of two that brings that maximum into [2^13, 2^14), that of a sample into [2^7, 2^8) (so every
-//     half is far from the ends of the fp16 range whatever the activations' units), and its inverse;
+// (2) per channel the power of two that brings that maximum into [2^13, 2^14) (so every half is
+//     far from the ends of the fp16 range whatever the activations' units), and its inverse;
 // (3) the split itself: X -> planes[piece][token / 8][channel] (see mfma_split_f16.h), zeros for
 //     the tokens up to the next multiple of 32 and the channels up to the next multiple of 256.
-// A power of two changes nothing in the halves of a value, their products and sums: a sample has to be right only to
-// a factor of 256, which it is unless the channel has an outlier that it missed.  (A low half is denormal, and
-// keeps 2^-32 of the sample's largest, where the value is 2^10 times smaller than that.)  The split looks for values beyond the
-// range, and (1) to (3) then follow with all tokens for the blocks of 256 channels that have one; for the others these
-// launches end at once.
+// A sample's largest is at most the channel's, so its factor is at least that of all tokens: no half is coarser for it.
+// It leaves a factor of 4 to 8 to the end of the range.  The split looks for values beyond that, and (1) to (3) then follow
+// with all tokens for the blocks of 256 channels that have one; for the others these launches end at once.
 // Bound by HBM: X is read once and the planes are written, 262144 x 3584 in 1.5 ms against 2.07 with a pass for the maxima
 // of all tokens in front.
 // How a block is marked: its first channel's mul becomes NaN (by the split; nothing reads the planes before
@@ -380,7 +378,7 @@ __global__ __launch_bounds__(256) void hess_scale_kernel(const float* __restrict
 #pragma unroll
       for (int w = 1; w < 16; ++w) m = fmaxf(m, red[w][threadIdx.x]);
       // a sample of zeros says nothing: the largest factor, under which anything that counts is out of range
-      const int e = TURN != kSampled ? channel_exponent(m) : m == 0.f ? 100 : max(channel_exponent(m) - 6, -100);
+      const int e = TURN != kSampled ? channel_exponent(m) : m == 0.f ? 100 : channel_exponent(m);
       mul[c] = ldexpf(1.0f, e);
       inv[c] = (kSecond && u == 0 && threadIdx.x == 0) ? -ldexpf(1.0f, -e) : ldexpf(1.0f, -e);
     }

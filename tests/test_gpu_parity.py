@@ -414,6 +414,23 @@ def test_hessian_scales_from_a_sample(dev, n_tok, d_in, kind):
     assert torch.equal(torch.nan_to_num(H), torch.nan_to_num(again))
 
 
+def test_hessian_scales_from_a_sample_with_loud_tokens_in_it(dev):
+    """A value's halves are no coarser where its channel's scale comes from a sample: tokens 2^15 to 2^16 times the rest, at places
+    that the sample holds (the first of every 2048).  An entry of H is a single product of such a value and 1, so nothing but
+    the halves is rounded: the value scaled is at least 2^-3 and keeps an absolute error of 2^-25."""
+    n_tok, d_in = 131072, 1024
+    print(f"sampled scales, loud tokens, {n_tok}x{d_in}", flush=True)
+    g = torch.Generator(device=dev)
+    g.manual_seed(3)
+    c = 1.0 + torch.rand(d_in // 2, generator=g, device=dev)
+    X = torch.zeros((n_tok, d_in), device=dev)
+    X[::2048, 0::2], X[64::2048, 1::2] = 2.0 ** 16, 1.0
+    X[777, 0::2], X[777, 1::2] = c, 1.0
+    H = torch.zeros((d_in, d_in), device=dev)
+    bq.bpdq_hessian_accumulate(X, H, 2.0, True)
+    assert float((H[0::2, 1::2].double() / (2.0 * c.double())[:, None] - 1.0).abs().max()) <= 2.0 ** -22
+
+
 @pytest.mark.parametrize("d_in,sigma", [(96, 1.0), (200, 1.0), (640, 1.5), (1288, 1.0)])
 def test_prepare_matches_oracle(dev, d_in, sigma):
     print(f"prepare d_in={d_in}", flush=True)
