@@ -278,68 +278,69 @@ __global__ __launch_bounds__(SplitSyrk::kThreads) void hess_syrk_bf16x3_kernel(
 //     far from the ends of the fp16 range whatever the activations' units), and its inverse;
 // (3) the split itself: X -> planes[piece][token / 8][channel] (see mfma_split_f16.h), zeros for
 //     the tokens up to the next multiple of 32 and the channels up to the next multiple of 256.
+// Bound by HBM: with a sample X is read nine eighths times and the planes are written, 262144 x 3584 in 1.5 ms against 2.07
+// with a pass for the maxima of all tokens in front.
 // A sample's largest is at most the channel's, so its factor is at least that of all tokens: no half is coarser for it.
-// It leaves a factor of 4 to 8 to the end of the range.  The split looks for values beyond that, and (1) to (3) then follow
-// with all tokens for the blocks of 256 channels that have one; for the others these launches end at once.
-// Bound by HBM: X is read once and the planes are written, 262144 x 3584 in 1.5 ms against 2.07 with a pass for the maxima
-// of all tokens in front.
-// How a block is marked: its first channel's mul becomes NaN (by the split; nothing reads the planes before
-// the block is done again), then its first channel's inv negative (by the scale of the second turn, which
-// sets mul); the tile product takes magnitudes of inv.
-constexpr int kSampleStep = 64;
-// Values (tokens times channels) from which on the scales come from a sample.  us, all tokens / a sample / a sample that missed
-// an outlier in three blocks of 256 channels / in all of them, at their last tokens: 262144 x 3584 9415 / 8894 / 9280 / 11335;
-// 131072 x 1024 (four blocks) 607 / 532 / 719 / 863; 8192 x 256, below the line, 48 / 43 / 73 (one block): there the three
-// launches that follow up cost more than the pass they may spare.
+// What it may miss is values of more than 4 to 8 times its largest, which leave the half range.  The split looks for them and
+// takes the maximum of a channel that has one; a second split then does the runs of 16 channels that hold such a
+// channel again, with the factor of all tokens for that channel, and ends at once for the others.  Where a run is known
+// to hold one, the first split reads on for the maxima and no longer writes: the two together are then the pass over all
+// tokens and the split behind it.  They write planes twice where the values come late.
+// Runs of 16 channels are whole lines of the planes and half lines of X.  262144 x 3584, Student-t(4) tokens / one late value
+// in every 64 channels, us: runs of 64 channels 9763 / 10473, 32 9558 / 9638, 16 9485 / 9493, single channels 9791 / 9461 (all
+// with every 16th token; the pass over all tokens 9488).  Every 8th token in place of every 16th, 32nd, 64th: 9246, 9485, 9628,
+// 9832 on Student-t(4) tokens, 8867, 8848, 8812, 8805 on normal ones.
+constexpr int kSampleStep = 8;
+// Values (tokens times channels) from which on the scales come from a sample.  us on activations not read before, scales of all
+// tokens / of a sample on normal tokens / on Student-t(4) tokens / one late value in every 64 channels / in every channel:
+//   262144 x 3584 9424 / 8841 / 9258 / 9526 / 10371;  65536 x 3584 2364 / 2243 / 2358 / 2410 / 2596;
+//   131072 x 1024 606 / 549 / 617 / 642 / 746;  16384 x 8192 2722 / 2626 / 2740 / 2734 / 2827;  8192 x 18944 6524 / 6438 / 6567 / 6558 / 6600;
+// and below the line
+//   32768 x 3584 1191 / 1129 / 1195 / 1217 / 1306;  65536 x 1024 317 / 290 / 315 / 340 / 387;  8192 x 8192 1577 / 1531 / 1608 / 1608 / 1659;
+//   65536 x 256 105 / 88 / 102 / 105 / 110;  8192 x 256 52 / 40 / 50 / 50 / 49.
+// So the gain on tokens without outliers does not end at the line; below it a call's time follows from its size alone.
 constexpr long kSampleValues = 1L << 27;
 constexpr int kColmaxRows = 1024;      // tokens per partial maximum
 constexpr int kSplitKgPerWG = 16;      // k-groups (8 tokens each) per work-group of the split
 constexpr float kHalfMax = 65504.0f;
-enum : int { kAllTokens = 0, kSampled = 1, kMarked = 2 };       // all blocks; the same by a sample; marked blocks
+constexpr int kBeyondWGs = 8192;       // work-groups of the second split
+enum : int { kAllTokens = 0, kSampled = 1, kBeyond = 2 };       // maxima of all tokens; of a sample; the second split
 
-template <int TURN>
+template <bool SAMPLED>
 __global__ __launch_bounds__(256) void hess_colmax_kernel(const float* __restrict__ X, int n_tok, int d,
-                                                          long ldx, const float* __restrict__ mul, float* __restrict__ pmax,
-                                                          int n_split, int d_pad) {
-  constexpr int kStep = TURN == kSampled ? kSampleStep : 1, kFlight = TURN == kSampled ? 4 : 8;
+                                                          long ldx, float* __restrict__ pmax, int d_pad) {
+  constexpr int kStep = SAMPLED ? kSampleStep : 1, kFlight = 8;
   __shared__ float4 red[4][64];
-  if constexpr (TURN == kMarked) {
-    const float first = mul[blockIdx.x * 256];
-    if (first == first) return;
-  }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int c = blockIdx.x * 256 + lane * 4;
-  for (int sp = blockIdx.y; sp < n_split; sp += gridDim.y) {
-    const int t0 = sp * kColmaxRows;
-    const int t1 = min(n_tok, t0 + kColmaxRows);
-    float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (c < d) {                                    // d % 4 == 0: the float4 is inside the row
-      const float* p = X + c;
-      for (int t = t0 + wave * kStep; t < t1; t += 4 * kFlight * kStep) {    // kFlight rows of this wavefront in flight
-        float4 v[kFlight];
+  const int t0 = blockIdx.y * kColmaxRows;
+  const int t1 = min(n_tok, t0 + kColmaxRows);
+  float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (c < d) {                                    // d % 4 == 0: the float4 is inside the row
+    const float* p = X + c;
+    for (int t = t0 + wave * kStep; t < t1; t += 4 * kFlight * kStep) {    // kFlight rows of this wavefront in flight
+      float4 v[kFlight];
 #pragma unroll
-        for (int u = 0; u < kFlight; ++u) {
-          const int tt = min(t + 4 * u * kStep, t1 - 1);    // past the end: the last row again
-          v[u] = *reinterpret_cast<const float4*>(p + (long)tt * ldx);
-        }
+      for (int u = 0; u < kFlight; ++u) {
+        const int tt = min(t + 4 * u * kStep, t1 - 1);    // past the end: the last row again
+        v[u] = *reinterpret_cast<const float4*>(p + (long)tt * ldx);
+      }
 #pragma unroll
-        for (int u = 0; u < kFlight; ++u) {
-          m.x = fmaxf(m.x, fabsf(v[u].x)); m.y = fmaxf(m.y, fabsf(v[u].y));
-          m.z = fmaxf(m.z, fabsf(v[u].z)); m.w = fmaxf(m.w, fabsf(v[u].w));
-        }
+      for (int u = 0; u < kFlight; ++u) {
+        m.x = fmaxf(m.x, fabsf(v[u].x)); m.y = fmaxf(m.y, fabsf(v[u].y));
+        m.z = fmaxf(m.z, fabsf(v[u].z)); m.w = fmaxf(m.w, fabsf(v[u].w));
       }
     }
-    red[wave][lane] = m;
-    __syncthreads();
-    if (wave == 0) {
+  }
+  red[wave][lane] = m;
+  __syncthreads();
+  if (wave == 0) {
 #pragma unroll
-      for (int w = 1; w < 4; ++w) {
-        const float4 o = red[w][lane];
-        m.x = fmaxf(m.x, o.x); m.y = fmaxf(m.y, o.y); m.z = fmaxf(m.z, o.z); m.w = fmaxf(m.w, o.w);
-      }
-      *reinterpret_cast<float4*>(pmax + (long)sp * d_pad + c) = m;     // c < d_pad always
+    for (int w = 1; w < 4; ++w) {
+      const float4 o = red[w][lane];
+      m.x = fmaxf(m.x, o.x); m.y = fmaxf(m.y, o.y); m.z = fmaxf(m.z, o.z); m.w = fmaxf(m.w, o.w);
     }
-    __syncthreads();                                // (the next range writes red again)
+    *reinterpret_cast<float4*>(pmax + (long)blockIdx.y * d_pad + c) = m;     // c < d_pad always
   }
 }
 
@@ -355,35 +356,26 @@ __device__ __forceinline__ int channel_exponent(float m) {
   return e;
 }
 
-template <int TURN>
-__global__ __launch_bounds__(256) void hess_scale_kernel(const float* __restrict__ pmax, int n_split,
+// A sample also clears row 0 of the partial maxima, which then takes the maxima of channels with values beyond the range.
+template <bool SAMPLED>
+__global__ __launch_bounds__(256) void hess_scale_kernel(float* pmax, int n_split,
                                                          int d_pad, float* __restrict__ mul,
                                                          float* __restrict__ inv) {
-  // 16 channels per work-group, the partial maxima of a channel dealt to 16 threads; marked blocks, a work-group
-  // per block of 256: all of it has seen the mark before it is taken away
-  constexpr bool kSecond = TURN == kMarked;
+  // 16 channels per work-group, the partial maxima of a channel dealt to 16 threads
   __shared__ float red[16][16];
-  if constexpr (kSecond) {
-    const float first = mul[blockIdx.x * 256];
-    __syncthreads();
-    if (first == first) return;
-  }
-  for (int u = 0; u < (kSecond ? 16 : 1); ++u) {
-    const int c = (kSecond ? blockIdx.x * 256 + 16 * u : blockIdx.x * 16) + (threadIdx.x & 15), q = threadIdx.x >> 4;
-    float m = 0.f;
-    for (int s = q; s < n_split; s += 16) m = fmaxf(m, pmax[(long)s * d_pad + c]);
-    red[q][threadIdx.x & 15] = m;
-    __syncthreads();
-    if (q == 0) {
+  const int c = blockIdx.x * 16 + (threadIdx.x & 15), q = threadIdx.x >> 4;
+  float m = 0.f;
+  for (int s = q; s < n_split; s += 16) m = fmaxf(m, pmax[(long)s * d_pad + c]);
+  red[q][threadIdx.x & 15] = m;
+  __syncthreads();
+  if (q) return;
 #pragma unroll
-      for (int w = 1; w < 16; ++w) m = fmaxf(m, red[w][threadIdx.x]);
-      // a sample of zeros says nothing: the largest factor, under which anything that counts is out of range
-      const int e = TURN != kSampled ? channel_exponent(m) : m == 0.f ? 100 : channel_exponent(m);
-      mul[c] = ldexpf(1.0f, e);
-      inv[c] = (kSecond && u == 0 && threadIdx.x == 0) ? -ldexpf(1.0f, -e) : ldexpf(1.0f, -e);
-    }
-    __syncthreads();
-  }
+  for (int w = 1; w < 16; ++w) m = fmaxf(m, red[w][threadIdx.x]);
+  // a sample of zeros says nothing: the largest factor, under which anything that counts is out of range
+  const int e = SAMPLED && m == 0.f ? 100 : channel_exponent(m);
+  mul[c] = ldexpf(1.0f, e);
+  inv[c] = ldexpf(1.0f, -e);
+  if (SAMPLED) pmax[c] = 0.f;
 }
 
 __device__ __forceinline__ unsigned pack_halves(_Float16 a, _Float16 b) {
@@ -409,24 +401,35 @@ __device__ __forceinline__ void split_halves(const float (&x)[8], float s, int c
   lv = make_uint4(lw[0], lw[1], lw[2], lw[3]);
 }
 
+// any of the run of 16 lanes
+__device__ __forceinline__ bool any_of_run(bool b) { return ((__ballot(b) >> (threadIdx.x & 48)) & 0xffffu) != 0; }
+
+// top (kSampled: written, kBeyond: read): per channel 0, or the largest magnitude of all tokens where that, scaled, is beyond the
+// half range.  (Non-negative floats order like their bits; a NaN, which the maximum passes over, needs no other factor.)
 template <int TURN>
 __global__ __launch_bounds__(256) void hess_split_f16_kernel(const float* __restrict__ X, int n_tok, int d,
-                                                             long ldx, float* mul, const float* __restrict__ inv,
-                                                             uint4* __restrict__ planes, long n_kg,
+                                                             long ldx, const float* __restrict__ mul, float* __restrict__ inv,
+                                                             unsigned* top, uint4* __restrict__ planes, long n_kg,
                                                              int d_pad) {
-  if constexpr (TURN == kMarked)
-    if (inv[blockIdx.x * 256] > 0.f) return;
-  if constexpr (TURN == kSampled) {       // marked already: the block is done again anyway
-    const float first = __hip_atomic_load(mul + blockIdx.x * 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (first != first) return;
-  }
   const int ch = blockIdx.x * 256 + threadIdx.x;
   const bool live = ch < d;
   const int chc = live ? ch : d - 1;
-  const float s = mul[chc];
+  float s = mul[chc];
+  bool write = true;
+  if constexpr (TURN == kSampled)                 // known already: the second split writes the channel
+    write = !any_of_run(__hip_atomic_load(top + ch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u);
+  if constexpr (TURN == kBeyond) {
+    const float m = __builtin_bit_cast(float, top[ch]);
+    if (!any_of_run(m != 0.f)) return;
+    if (m != 0.f) {
+      const int e = channel_exponent(m);
+      s = ldexpf(1.0f, e);
+      if (blockIdx.y == 0) inv[ch] = ldexpf(1.0f, -e);
+    }
+  }
   const float* p = X + chc;
   const int t_last = n_tok - 1;
-  bool beyond = false;
+  float m = 0.f;
   for (long kg0 = (long)blockIdx.y * kSplitKgPerWG; kg0 < n_kg; kg0 += (long)gridDim.y * kSplitKgPerWG) {
     for (int g = 0; g < kSplitKgPerWG; g += 2) {
       const long kg = kg0 + g;
@@ -437,6 +440,11 @@ __global__ __launch_bounds__(256) void hess_split_f16_kernel(const float* __rest
         const long t = 8 * kg + i;
         x[i] = p[(t < t_last ? t : (long)t_last) * ldx];
       }
+      if constexpr (TURN == kSampled) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(x[i]));      // (tokens past the end repeat the last)
+        if (!write) continue;
+      }
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
         if (kg + half >= n_kg) break;
@@ -445,15 +453,10 @@ __global__ __launch_bounds__(256) void hess_split_f16_kernel(const float* __rest
         planes[(kg + half) * d_pad + ch] = hv;
         planes[(n_kg + kg + half) * d_pad + ch] = lv;
       }
-      if constexpr (TURN == kSampled) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) beyond |= !(fabsf(x[i] * s) <= kHalfMax);    // NaN too (tokens past the end repeat the last)
-      }
     }
   }
   if constexpr (TURN == kSampled)
-    if (__any(beyond) && (threadIdx.x & 63) == 0)
-      __hip_atomic_store(mul + blockIdx.x * 256, NAN, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (live && m * s > kHalfMax) atomicMax(top + ch, __builtin_bit_cast(unsigned, m));
 }
 
 // The whole pre-pass in one launch for calls of at most 4096 tokens: a work-group holds all tokens of 16
@@ -657,8 +660,8 @@ __global__ __launch_bounds__(SplitF16::kThreads, 1) void hess_syrk_f16x2_kernel(
   // the LDS ring is free now: the channel factors of this tile's rows and columns
   extern __shared__ uint4 smem_f16[];
   float* sInv = reinterpret_cast<float*>(smem_f16);
-  sInv[threadIdx.x] = fabsf(inv[r0 + threadIdx.x]);          // (the sign marks a block that was split twice)
-  sInv[256 + threadIdx.x] = fabsf(inv[c0 + threadIdx.x]);
+  sInv[threadIdx.x] = inv[r0 + threadIdx.x];
+  sInv[256 + threadIdx.x] = inv[c0 + threadIdx.x];
   __syncthreads();
   if constexpr (DIRECT) {
     // H += tile, in batches of 64 results per lane: all loads of a batch first, then its stores.  One load,
@@ -968,34 +971,27 @@ static int hessian_accumulate(int kind, const float* Xc, int n_tok, int d_in, in
       } else {
         const int cb = L.d_pad / SplitF16::kTile;
         const int kgs = bpdq_ceil_div((int)L.n_kg, kSplitKgPerWG);
-        auto colmax = [&](auto kern, int grid_y) {
-          hipLaunchKernelGGL(kern, dim3(cb, grid_y), dim3(256), 0, stream, Xpart, n_part, d_in, (long)ldx, mul, pmax,
-                             L.n_split, L.d_pad);
-        };
-        auto scale_of = [&](auto kern, int grid) {
-          hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, stream, pmax, L.n_split, L.d_pad, mul, inv);
-        };
-        auto split = [&](auto kern, int grid_y) {
-          hipLaunchKernelGGL(kern, dim3(cb, grid_y), dim3(256), 0, stream, Xpart, n_part, d_in, (long)ldx, mul, inv, planes,
-                             L.n_kg, L.d_pad);
-        };
-        auto turn = [&](auto which, int colmax_y, int scale_wgs, int split_y) -> int {
-          constexpr int kTurn = decltype(which)::value;
-          colmax(hess_colmax_kernel<kTurn>, colmax_y);
+        auto scales = [&](auto colmax, auto scale_of) -> int {
+          hipLaunchKernelGGL(colmax, dim3(cb, L.n_split), dim3(256), 0, stream, Xpart, n_part, d_in, (long)ldx, pmax, L.d_pad);
           BPDQ_LAUNCH_CHECK();
-          scale_of(hess_scale_kernel<kTurn>, scale_wgs);
+          hipLaunchKernelGGL(scale_of, dim3(L.d_pad / 16), dim3(256), 0, stream, pmax, L.n_split, L.d_pad, mul, inv);
           BPDQ_LAUNCH_CHECK();
-          split(hess_split_f16_kernel<kTurn>, split_y);
+          return 0;
+        };
+        auto split = [&](auto kern, int grid_y) -> int {
+          hipLaunchKernelGGL(kern, dim3(cb, grid_y), dim3(256), 0, stream, Xpart, n_part, d_in, (long)ldx, mul, inv,
+                             reinterpret_cast<unsigned*>(pmax), planes, L.n_kg, L.d_pad);
           BPDQ_LAUNCH_CHECK();
           return 0;
         };
         if ((long)n_part * d_in < kSampleValues) {
-          if (turn(std::integral_constant<int, kAllTokens>{}, L.n_split, L.d_pad / 16, kgs)) return BPDQ_ERR_LAUNCH;
+          if (scales(hess_colmax_kernel<false>, hess_scale_kernel<false>)) return BPDQ_ERR_LAUNCH;
+          if (split(hess_split_f16_kernel<kAllTokens>, kgs)) return BPDQ_ERR_LAUNCH;
         } else {
-          if (turn(std::integral_constant<int, kSampled>{}, L.n_split, L.d_pad / 16, kgs)) return BPDQ_ERR_LAUNCH;
-          const int rounds = cb < 512 ? 2048 / cb + 1 : 4;          // small grids where they end at once
-          if (turn(std::integral_constant<int, kMarked>{}, L.n_split < rounds ? L.n_split : rounds, cb, kgs < rounds ? kgs : rounds))
-            return BPDQ_ERR_LAUNCH;
+          if (scales(hess_colmax_kernel<true>, hess_scale_kernel<true>)) return BPDQ_ERR_LAUNCH;
+          if (split(hess_split_f16_kernel<kSampled>, kgs)) return BPDQ_ERR_LAUNCH;
+          const int rounds = cb < 2048 ? kBeyondWGs / cb + 1 : 4;          // a small grid where it ends at once
+          if (split(hess_split_f16_kernel<kBeyond>, kgs < rounds ? kgs : rounds)) return BPDQ_ERR_LAUNCH;
         }
       }
       if (mark_begin()) return BPDQ_ERR_LAUNCH;

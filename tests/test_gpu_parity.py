@@ -371,7 +371,7 @@ def test_hessian_f16_path_channel_scaling(dev):
 @pytest.mark.parametrize("n_tok,d_in", [(131077, 1024), (44740, 3000)])
 @pytest.mark.parametrize("kind", ["plain", "missed", "not_finite"])
 def test_hessian_scales_from_a_sample(dev, n_tok, d_in, kind):
-    """Calls of 2^27 values and more take a channel's scale from every 64th token.  A channel whose sample is all zeros, or
+    """Calls of 2^27 values and more take a channel's scale from every 8th token.  A channel whose sample is all zeros, or
     small against an outlier that it missed (first, middle, last token), is split again with all tokens; so is one
     with an infinity or a NaN, whose row and column of H alone are not finite."""
     print(f"sampled scales {n_tok}x{d_in} {kind}", flush=True)
@@ -384,9 +384,9 @@ def test_hessian_scales_from_a_sample(dev, n_tok, d_in, kind):
     X[:, 33] *= 1e-30
     X[:, 34] *= 1e15 / X[:, 34].abs().max()                   # (its H entry, below 2 n_tok 1e30, is in fp32's range)
     if kind != "plain":
-        X[::64, 300] = 0.0                                   # the whole sample
+        X[::8, 300] = 0.0                                    # the whole sample
         X[1, 301], X[n_tok // 2 | 1, 302] = 3e4 * X[1, 301], 1e6
-        X[n_tok - 1 if (n_tok - 1) % 64 else n_tok - 2, 999] = -1e5
+        X[n_tok - 1 if (n_tok - 1) % 8 else n_tok - 2, 999] = -1e5
     bad = [] if kind != "not_finite" else [40, 600]
     if bad:
         X[5, 40], X[70001 % n_tok | 1, 600] = float("inf"), float("nan")
@@ -429,6 +429,36 @@ def test_hessian_scales_from_a_sample_with_loud_tokens_in_it(dev):
     H = torch.zeros((d_in, d_in), device=dev)
     bq.bpdq_hessian_accumulate(X, H, 2.0, True)
     assert float((H[0::2, 1::2].double() / (2.0 * c.double())[:, None] - 1.0).abs().max()) <= 2.0 ** -22
+
+
+@pytest.mark.parametrize("n_tok,d_in,first", [(10000, 16640, 8192), (600000, 256, 524288)])
+def test_hessian_scales_from_a_sample_in_the_first_of_two_launches(dev, n_tok, d_in, first):
+    """A launch of 2^27 values or more, whose scales come from a sample, and one of fewer behind it in the same workspace;
+    16640 channels add their tiles straight into H.  Values that the sample misses in one block of 256 channels, in both
+    launches' tokens."""
+    print(f"sampled scales in the first launch {n_tok}x{d_in}", flush=True)
+    assert first * d_in >= 1 << 27 > (n_tok - first) * d_in
+    g = torch.Generator(device=dev)
+    g.manual_seed(d_in)
+    X = torch.randn((n_tok, d_in), generator=g, device=dev)
+    X *= torch.exp(torch.randn(d_in, generator=g, device=dev))
+    loud = d_in - 200
+    X[first - 1, loud], X[n_tok - 1, loud], X[1, loud + 70] = 3e3, -2e4, 1e5
+    H = torch.zeros((d_in, d_in), device=dev)
+    bq.bpdq_hessian_accumulate(X, H, 2.0, False)
+    c = torch.arange(1, d_in, max(1, d_in // 300), device=dev)
+    c = torch.unique(torch.cat([c, torch.tensor([loud, loud + 1, loud + 70], device=dev)]))
+    ref = torch.zeros((len(c), len(c)), dtype=torch.float64, device=dev)
+    for a in range(0, n_tok, 16384):
+        x = X[a:a + 16384, c].double()
+        ref.addmm_(x.t().contiguous(), x, alpha=2.0)
+    root = ref.diagonal().sqrt()
+    off = ((H[c][:, c].double() - ref) / root[:, None] / root[None, :]).triu()
+    assert float(off.abs().max()) < 2e-5
+    assert float(off.norm() / (ref / root[:, None] / root[None, :]).triu().norm()) < H_TOL
+    again = torch.zeros_like(H)
+    bq.bpdq_hessian_accumulate(X, again, 2.0, False)
+    assert torch.equal(H, again)
 
 
 @pytest.mark.parametrize("d_in,sigma", [(96, 1.0), (200, 1.0), (640, 1.5), (1288, 1.0)])
