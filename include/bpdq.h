@@ -89,10 +89,16 @@ int bpdq_version(void);
  * bpdq_hessian_accumulate (the fastest) runs on the fp16 matrix cores: a streaming pre-pass finds
  *   every channel's largest magnitude in the call, scales the channel by the power of two that
  *   brings it into [2^13, 2^14) and cuts every scaled value into two halves h + l (22 significant
- *   bits); a product is the sum of the three half products of weight >= 2^-11, accumulated in fp32,
- *   and the result is scaled back exactly.  The error of a product is below 2^-21 of it -- above
- *   the 2^-24 of an fp32 product, far below the rounding of the fp32 accumulation over thousands of
- *   tokens.  Small calls (up to 64 tokens on 3072 channels, 256 on 2048, 512 on 704, 1024 on 512, 2048
+ *   bits, fewer where the value is below 2^-16 of the channel's largest, of which the error is 2^-38 at most); a product is
+ *   the sum of the three half products of weight >= 2^-11, accumulated in fp32, and the result is scaled back exactly.  The
+ *   error of a product of values above 2^-15 of their channels' largest is below 2^-21 of it -- above the 2^-24 of an fp32
+ *   product, far below the rounding of the fp32 accumulation over thousands of tokens.
+ *   Launches of n_tok * d_in >= 2^27 (a call of up to 524288 tokens, of up to 8192 on a layer of 1024 tiles or more, is one
+ *   launch) scale a channel by the largest of every 8th token instead: that factor is the same or larger, so the halves are
+ *   as fine or finer, and no value is lost, because channels with a value that leaves the half range under it are scaled
+ *   again by the largest of all tokens.  The time of such a call depends on the activations: at 262144 x 3584 9.4 ms with the
+ *   scales of all tokens, 8.8 to 9.0 without outliers that the sample missed, up to 10.4 where every channel has one.
+ *   Small calls (up to 64 tokens on 3072 channels, 256 on 2048, 512 on 704, 1024 on 512, 2048
  *   on 320, less some that the above does sooner) are one launch on the fp32 matrix cores instead: fp32
  *   products (2^-24) of the channels scaled in the same way, in chains of at most 32 tokens.  Which of
  *   the two follows from n_tok and d_in alone.

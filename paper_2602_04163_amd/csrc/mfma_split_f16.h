@@ -1,9 +1,9 @@
 // Symmetric tile product on the fp16 matrix cores from pre-split operands (split-precision SYRK):
 //   C[m][n] = sum_k X[k][m0 + m] * X[k][n0 + n]
 // where every value, scaled per channel by a power of two so that the channel's largest magnitude
-// lies in [2^13, 2^14), has been cut into two halves  x s = h + l,  h = fp16(x s),
-// l = fp16(x s - h)  (the difference is exact in fp32; 22 significant bits survive, and a value
-// far below its channel's maximum keeps an absolute error of 2^-25 in the scaled units).  A product
+// lies in [2^13, 2^14) (that of a sample of the tokens in large calls: then the channel's is below 2^16), has been cut into
+// two halves  x s = h + l,  h = fp16(x s), l = fp16(x s - h)  (the difference is exact in fp32; 22 significant bits survive,
+// and a value far below its channel's maximum keeps an absolute error of 2^-25 in the scaled units).  A product
 // keeps the three terms of weight >= 2^-11,
 //   x y = h h' + (h l' + l h')  +  O(2^-22 |x y|),
 // each an exact fp16 x fp16 product accumulated in fp32 by v_mfma_f32_32x32x16_f16: three 8-pass
