@@ -54,11 +54,12 @@ static double hess_makespan(int n_full, double c_full, int n_short, double c_sho
 }
 
 // Measured: a sum of squares (the diagonal of H) accumulated by chained MFMAs comes out low, the
-// more so the longer the chain, as if the products of an instruction were truncated when aligned
-// to the running sum: about -1.3e-6 relative after 11 k tokens on the fp32 path, -4.5e-6 after
-// 52 k tokens and -2.5e-6 after 8 k tokens on the split path.  Both paths therefore end every
-// chain after kChainTokens[kind] tokens; the partial sums are added by ordinary round-to-nearest
-// fp32 additions, which do not drift.
+// more so the longer the chain: about -9e-7 relative after 16 k tokens on the fp32 path, -4.5e-6 after
+// 52 k tokens and -2.5e-6 after 8 k tokens on the bf16 path, -2.8e-7 after 8 k tokens on the fp16 path.  On the fp32 path
+// that is what fp32 sums do: the instruction is an ascending chain of fused multiply-adds rounded to nearest, bit
+// for bit (256 x 256 entries after 511, 4096 and 16384 tokens of widely spread sizes).  How the 16-bit instructions round
+// inside was not established.  All paths end every
+// chain after kChainTokens[kind] tokens; the partial sums are added by ordinary fp32 additions, few enough not to drift.
 constexpr int kChainTokens[3] = {16384, 8192, 8192};
 constexpr int kMaxSlices = 64;
 

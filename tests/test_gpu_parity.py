@@ -1202,6 +1202,69 @@ def test_sweep_is_its_definition_where_squares_leave_fp32(dev, bits, group, expo
     assert np.array_equal(orc.unpack_planes(out["planes"].cpu().numpy().view(np.uint32), group), want)
 
 
+def _fma32(a, b, c):
+    """Fused multiply-add of fp32 arrays, rounded once: the product is exact in 64 bits, the sum is rounded to odd there
+    and then to fp32."""
+    p, c = a.astype(np.float64) * b.astype(np.float64), c.astype(np.float64)
+    s = p + c
+    back = s - p
+    lost = (p - (s - back)) + (c - back)
+    odd = np.nextafter(s, np.where(lost > 0, np.inf, -np.inf))
+    return np.where((lost != 0) & (s.view(np.int64) & 1 == 0), odd, s).astype(np.float32)
+
+
+def _solve_chain(v, b, U, fused=True):
+    """z U = v + b by the ascending recurrence in fp32: z_l = (b_l + v_l) (1 / U_ll), v_j = v_j - z_l U_lj."""
+    f, inv = np.float32, np.float32(1) / U.diagonal()
+    v, z = v.copy(), np.empty_like(v)
+    for l in range(U.shape[0]):
+        z[:, l] = (v[:, l] if b is None else b[:, l] + v[:, l]) * inv[l]
+        if fused:
+            v[:, l + 1:] = _fma32(z[:, l:l + 1], -U[l:l + 1, l + 1:], v[:, l + 1:])
+        else:
+            v[:, l + 1:] = (z[:, l:l + 1] * -U[l:l + 1, l + 1:]).astype(f) + v[:, l + 1:]
+    return z
+
+
+@pytest.mark.parametrize("bits,group", [(k, g) for k in (1, 2, 3, 4) for g in (32, 64, 128, 256) if (k, g) != (4, 256)])
+@pytest.mark.parametrize("iters", [0, 3])
+def test_solves_are_an_ascending_chain_of_fused_multiply_adds(dev, bits, group, iters):
+    """tau and the planes' solves, whose products to later blocks go through the matrix cores, are the ascending recurrence in
+    fp32 with one rounding per multiply-add, bit for bit.  Seen through a group's error, the sum of E'^2 in 64 bits over one
+    row block: E' from the recurrence emulated with the returned planes and coefficients.  Off-diagonals of the factor over
+    12 binary orders of magnitude, so that products meet larger and smaller sums.  iters = 0: tau beside the planes (alone
+    first where there are four); 3: a kept iterate's planes by themselves."""
+    print(f"solves k={bits} g={group} T={iters}", flush=True)
+    rng = np.random.default_rng(1000 * bits + group + iters)
+    f, d_out = np.float32, 16
+    W = rng.standard_normal((d_out, group)).astype(f)
+    W *= np.exp2(rng.integers(-3, 4, size=(d_out, 1))).astype(f)
+    off = rng.standard_normal((group, group)) * np.exp2(rng.uniform(-10, 2, (group, group)))
+    U = (np.diag(1 + 0.3 * rng.random(group)) + 0.3 / group ** 0.5 * np.triu(off, 1)).astype(f)
+    out = bq.bpdq_quantize_layer(torch.from_numpy(W).to(dev), torch.from_numpy(U).to(dev), None,
+                                 bq.make_params(bits, group, group, iters, 1e-4))
+    assert (int(out["grp_iter"][0]) > 0) == (iters > 0)
+    code = orc.unpack_planes(out["planes"].cpu().numpy().view(np.uint32), group)
+    coef = out["coefs"].cpu().numpy()[:, :, 0]
+
+    def group_error(fused):
+        e = _fma32(-coef[0][:, None], _solve_chain(np.ones((1, group), f), None, U), _solve_chain(W, None, U, fused))
+        for i in range(bits):
+            e = _fma32(-coef[i + 1][:, None], _solve_chain(np.zeros_like(W), (code >> i & 1).astype(f), U, fused), e)
+        lanes = np.zeros((d_out, 16))
+        for m in range(group // 16):                       # a lane's columns in order, then the butterfly, then the rows
+            lanes += e[:, 16 * m:16 * m + 16].astype(np.float64) ** 2
+        for x in (1, 2, 4, 8):
+            lanes = lanes + lanes[:, np.arange(16) ^ x]
+        total = 0.0
+        for r in range(d_out):
+            total += lanes[r, 0]
+        return total
+
+    assert float(out["grp_err"][0]) == group_error(True)
+    assert float(out["grp_err"][0]) != group_error(False)
+
+
 @pytest.mark.parametrize("bits,group", [(1, 64), (2, 32), (2, 128), (3, 256), (4, 64)])
 def test_levels_that_are_not_finite_never_win(dev, bits, group):
     """The nearest level is the one that a scan from code 0 with a strict `<` keeps: an infinite or NaN distance never
