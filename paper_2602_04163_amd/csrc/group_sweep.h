@@ -175,15 +175,11 @@ constexpr int kMaxIters = 63;             // largest refine_iters
 template <int G>
 constexpr int kStageFloats = (SuLayout<G>::floats() + 255) / 256 * 256;
 
-// x of lane O of this 16-lane row as the DPP operand of the arithmetic it feeds (bound_ctrl set and no
+// x of another lane of this 16-lane row as the DPP operand of the arithmetic it feeds (bound_ctrl set and no
 // "old" value: the compiler folds the move into a VOP2 instruction that uses it once).
 template <int CTRL>
 __device__ __forceinline__ int dpp_operand(int x) {
   return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, true);
-}
-template <int O>
-__device__ __forceinline__ float from_lane(float x) {
-  return __builtin_bit_cast(float, dpp_operand<0x150 + O>(__builtin_bit_cast(int, x)));
 }
 // unsigned minimum with the partner of butterfly stage R (xor 1, xor 2, half mirror, mirror)
 template <int R>
