@@ -14,7 +14,7 @@
 // The same forward recurrence as the error propagation of Eq. 3-4 gives them
 // (x_l = v_l / U_ll;  v_{l+1:} -= x_l U_{l,l+1:}).  The sweep is that recurrence on the working weights alone, one
 // column per step (column_step); the plane solves need the finished codes and no decision needs them, so they
-// follow it by blocks of 16 columns (solve_planes).  Then
+// follow it by blocks of 16 columns (solve_planes; a single plane of a large group advances with it).  Then
 //   * the fit of Eq. 6 is the (k+1) x (k+1) system G c = r with G_ab = P_a.P_b, r_a = P_a.tau
 //     (since U_loc^-T B_r = [P_0 .. P_k]^T), accumulated and solved in fp64;
 //   * the corrected propagation coordinates of Eq. 9 are E' = tau - sum_a c_a P_a
@@ -181,6 +181,10 @@ template <int CTRL>
 __device__ __forceinline__ int dpp_operand(int x) {
   return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, true);
 }
+template <int O>
+__device__ __forceinline__ float from_lane(float x) {
+  return __builtin_bit_cast(float, dpp_operand<0x150 + O>(__builtin_bit_cast(int, x)));
+}
 // unsigned minimum with the partner of butterfly stage R (xor 1, xor 2, half mirror, mirror)
 template <int R>
 __device__ __forceinline__ unsigned min_stage(unsigned x) {
@@ -207,6 +211,7 @@ constexpr int kAhead = G > 128 ? 1 : 3;
 template <int G>
 struct RowRing {
   float e;                              // broadcast error coordinate of the column before
+  float x;                              // its coordinate of the plane's solve, where that advances with the sweep
   float u[kAhead<G> + 2][G / 16];
 };
 template <int G, int L>
@@ -220,12 +225,17 @@ constexpr int reads_behind(int L) {
   for (int r = L + 1; r <= L + kAhead<G> && r + 1 < G; ++r) n += SuLayout<G>::chunks(r / 16);
   return n;
 }
-template <int K, int G, int L, int FIRST, int F0, int F1>
+template <bool SOLVE, int K, int G, int L, int FIRST, int F0, int F1>
 __device__ __forceinline__ void far_updates(RowState<K, G>& st, const RowRing<G>& ring) {
   if constexpr (F0 < F1) {
-    st.wg[FIRST + F0] = fmaf(ring.e, ring.u[L % (kAhead<G> + 2)][FIRST + F0], st.wg[FIRST + F0]);
+    const float u = ring.u[L % (kAhead<G> + 2)][FIRST + F0];
+    st.wg[FIRST + F0] = fmaf(ring.e, u, st.wg[FIRST + F0]);
     BPDQ_PIN(st.wg[FIRST + F0]);
-    far_updates<K, G, L, FIRST, F0 + 1, F1>(st, ring);
+    if constexpr (SOLVE) {
+      st.P[FIRST + F0][0] = fmaf(ring.x, u, st.P[FIRST + F0][0]);
+      BPDQ_PIN(st.P[FIRST + F0][0]);
+    }
+    far_updates<SOLVE, K, G, L, FIRST, F0 + 1, F1>(st, ring);
   }
 }
 
@@ -250,7 +260,14 @@ __device__ __forceinline__ void far_updates(RowState<K, G>& st, const RowRing<G>
 // Sweep and solves together, a group of 128 columns, 2 planes: 22.5 k -> 18.6 k cycles; whole layers, the same bits:
 // 3584 x 3584, 2 planes, 5 iterations 2531 -> 2212 us; 18944 x 3584, 3 planes 10.4 -> 8.96 ms; 256 x 256 (groups of 64, 3
 // iterations) 113.5 -> 90.3 us.
-template <int K, int G, int L>
+// One plane in groups of 128 and 256 (kSolveInSweep): the plane's solve advances with the sweep, 4 instructions and a
+// multiply-add per slot, with the row that is there.  Behind the sweep it reads the factor again and fills a quarter of the
+// matrix products' rows.  Whole layers, 5 iterations, solve behind / in the sweep, us: groups of 256, 3584 x 2048 1372 / 1170,
+// 18944 x 1024 2940 / 2428, 70 x 2048 1282 / 1076; groups of 128, 986 / 954, 1514 / 1405, 802 / 764; on the other side, groups of 64,
+// 1006 / 1061, 1428 / 1460, 808 / 860, of 32 1309 / 1392, 1707 / 1817, 1117 / 1180 (chains that the few slots do not fill).
+template <int K, int G>
+constexpr bool kSolveInSweep = K == 1 && G >= 128;
+template <bool SOLVE, int K, int G, int L>
 __device__ __forceinline__ void column_step(RowState<K, G>& st, const float* __restrict__ sU, float lv, int lane16,
                                             RowRing<G>& ring) {
   constexpr int CPL = G / 16, M = L / 16, O = L % 16, MN = (L + 1) / 16;
@@ -268,24 +285,25 @@ __device__ __forceinline__ void column_step(RowState<K, G>& st, const float* __r
   __builtin_amdgcn_sched_barrier(0);
   asm volatile("v_sub_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf\n\t"
                "v_alignbit_b32 %0, %0, %0, 31" : "=&v"(key) : "v"(st.wg[M]), "v"(lv), "n"(O));      // distance_key
-  far_updates<K, G, L - 1, M + 1, 0, at(2)>(st, ring);
+  far_updates<SOLVE, K, G, L - 1, M + 1, 0, at(2)>(st, ring);
+  const unsigned own = key;
   key = min_stage<0>(key);
   if constexpr (K > 1) {
     BPDQ_PIN(key);
-    far_updates<K, G, L - 1, M + 1, at(2), at(4)>(st, ring);
+    far_updates<SOLVE, K, G, L - 1, M + 1, at(2), at(4)>(st, ring);
     key = min_stage<1>(key);
   }
   if constexpr (K > 2) {
     BPDQ_PIN(key);
-    far_updates<K, G, L - 1, M + 1, at(4), at(6)>(st, ring);
+    far_updates<SOLVE, K, G, L - 1, M + 1, at(4), at(6)>(st, ring);
     key = min_stage<2>(key);
   }
   if constexpr (K > 3) {
     BPDQ_PIN(key);
-    far_updates<K, G, L - 1, M + 1, at(6), at(8)>(st, ring);
+    far_updates<SOLVE, K, G, L - 1, M + 1, at(6), at(8)>(st, ring);
     key = min_stage<3>(key);
   }
-  far_updates<K, G, L - 1, M + 1, at(2 * K), NF>(st, ring);
+  far_updates<SOLVE, K, G, L - 1, M + 1, at(2 * K), NF>(st, ring);
   // back to the distance, its error coordinate, and the slot of column L + 1 at once; the others in the next step
   float e;
   asm volatile("v_alignbit_b32 %0, %2, %2, 1\n\t"
@@ -293,9 +311,14 @@ __device__ __forceinline__ void column_step(RowState<K, G>& st, const float* __r
                "v_fmac_f32 %1, %0, %4"
                : "=&v"(e), "+v"(st.wg[MN]) : "v"(key), "v"(st.inv[M]), "v"(ring.u[L % (kAhead<G> + 2)][MN]), "n"(O));
   ring.e = e;
+  if constexpr (SOLVE) {
+    const float b = (unsigned)dpp_operand<0x150>((int)own) != key ? 1.f : 0.f;     // level 0 is not the nearest
+    ring.x = (from_lane<O>(st.P[M][0]) + b) * from_lane<O>(st.inv[M]);
+    st.P[MN][0] = fmaf(ring.x, ring.u[L % (kAhead<G> + 2)][MN], st.P[MN][0]);
+  }
   __builtin_amdgcn_sched_barrier(0);     // later steps' reads stay behind this step
 }
-template <int K, int G, int... Ls>
+template <bool SOLVE, int K, int G, int... Ls>
 __device__ __forceinline__ void run_columns(RowState<K, G>& st, const float* sU, float lv, int lane16,
                                             std::integer_sequence<int, Ls...>) {
   RowRing<G> ring;
@@ -305,7 +328,7 @@ __device__ __forceinline__ void run_columns(RowState<K, G>& st, const float* sU,
     request_row<G, 2>(ring, sU, lane16);
   }
   __builtin_amdgcn_sched_barrier(0);
-  (column_step<K, G, Ls>(st, sU, lv, lane16, ring), ...);
+  (column_step<SOLVE, K, G, Ls>(st, sU, lv, lane16, ring), ...);
 }
 
 // v(code) = ((c0 + b1 c1) + b2 c2) + ...  in fp32 (Eq. 7)
@@ -366,17 +389,21 @@ __device__ __forceinline__ void sweep_by_scan(RowState<K, G>& st, const float* _
   if constexpr (M + 1 < CPL) sweep_by_scan<K, G, M + 1>(st, sU, lv, lane16);
 }
 
-// One sweep over the group's columns with coefficients c: leaves the codes, and in wg the weights they were decided on.
-template <int K, int G>
-__device__ __forceinline__ void sweep(RowState<K, G>& st, const float* __restrict__ sU, const float (&c)[K + 1], int lane16) {
+// One sweep over the group's columns with coefficients c: leaves the codes, and in wg the weights they were decided on.  With
+// SOLVE also the plane's solve, true then; false if it has to follow.
+template <bool SOLVE, int K, int G>
+__device__ __forceinline__ bool sweep(RowState<K, G>& st, const float* __restrict__ sU, const float (&c)[K + 1], int lane16) {
   constexpr int CPL = G / 16;
   float lv = c[0];
 #pragma unroll
   for (int i = 0; i < K; ++i) lv = ((lane16 >> i) & 1) ? lv + c[i + 1] : lv;
   lv = __builtin_isfinite(lv) ? lv : c[0];
 #pragma unroll
-  for (int m = 0; m < CPL; ++m) st.wg[m] = st.t[m];
-  run_columns<K, G>(st, sU, lv, lane16, std::make_integer_sequence<int, G - 1>{});     // the last column has none behind it
+  for (int m = 0; m < CPL; ++m) {
+    st.wg[m] = st.t[m];
+    if constexpr (SOLVE) st.P[m][0] = 0.f;
+  }
+  run_columns<SOLVE, K, G>(st, sU, lv, lane16, std::make_integer_sequence<int, G - 1>{});     // the last column has none behind it
 
   // The codes, by the smallest magnitude; its order is that of the squares unless those leave the range of fp32.  Where levels
   // descend somewhere (ties, see column_step), lie so close that squares of distances between them underflow, or so
@@ -407,7 +434,7 @@ __device__ __forceinline__ void sweep(RowState<K, G>& st, const float* __restric
       }
       st.code[m] = code;
     }
-    return;
+    return SOLVE;
   }
   bool other = false;
 #pragma unroll
@@ -425,7 +452,9 @@ __device__ __forceinline__ void sweep(RowState<K, G>& st, const float* __restric
 #pragma unroll
     for (int m = 0; m < CPL; ++m) st.wg[m] = st.t[m];
     sweep_by_scan<K, G>(st, sU, lvl, lane16);
+    return false;
   }
+  return SOLVE;
 }
 
 // Right-solves with U_loc of rows that are known: slots [0, NP) of st.P run from the plane bits, and, where NT, slot NP from
@@ -1084,8 +1113,12 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void bpdq_gro
 
   // ---- refinement iterations (Sec. 3.3)
   for (int it = 1; it <= T; ++it) {
-    sweep<K, G>(st, sU, c32, lane16);
-    solve_planes<K, 0, K, G>(st, sU, sX);
+    if (sweep<kSolveInSweep<K, G>, K, G>(st, sU, c32, lane16)) {
+#pragma unroll
+      for (int m = 0; m < CPL; ++m) st.P[m][0] = ((float)(st.code[m] & 1) + st.P[m][0]) * st.inv[m];
+    } else {
+      solve_planes<K, 0, K, G>(st, sU, sX);
+    }
     rs = fit_and_score<K, G>(st, (double)alpha, coef_fp16, c32, Ep);
     store_candidate<K, G>(st, c32, Ep, rs, it, row, valid, d_out, cand_codes, cand_coef, cand_E, sScore, lane16);
   }
@@ -1143,7 +1176,7 @@ __global__ __launch_bounds__(kSweepThreads, kSweepWavesPerSimd<G>) void uniform_
 #pragma unroll
   for (int i = 0; i < K; ++i) grid[i + 1] = step * (float)(1 << i);
   store_precision(grid, coef_fp16, c32);
-  sweep<K, G>(st, sU, c32, lane16);
+  sweep<false, K, G>(st, sU, c32, lane16);
   float lvl[1 << K];
   sweep_levels<K>(c32, lvl);
   double sc = 0.0;

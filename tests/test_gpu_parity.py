@@ -1227,18 +1227,19 @@ def _solve_chain(v, b, U, fused=True):
 
 
 @pytest.mark.parametrize("bits,group", [(k, g) for k in (1, 2, 3, 4) for g in (32, 64, 128, 256) if (k, g) != (4, 256)])
-@pytest.mark.parametrize("iters", [0, 3])
-def test_solves_are_an_ascending_chain_of_fused_multiply_adds(dev, bits, group, iters):
+@pytest.mark.parametrize("iters,exponent", [(0, 0), (3, 0), (3, -66)])
+def test_solves_are_an_ascending_chain_of_fused_multiply_adds(dev, bits, group, iters, exponent):
     """tau and the planes' solves, whose products to later blocks go through the matrix cores, are the ascending recurrence in
     fp32 with one rounding per multiply-add, bit for bit.  Seen through a group's error, the sum of E'^2 in 64 bits over one
     row block: E' from the recurrence emulated with the returned planes and coefficients.  Off-diagonals of the factor over
     12 binary orders of magnitude, so that products meet larger and smaller sums.  iters = 0: tau beside the planes (alone
-    first where there are four); 3: a kept iterate's planes by themselves."""
-    print(f"solves k={bits} g={group} T={iters}", flush=True)
+    first where there are four); 3: a kept iterate's planes by themselves, one plane of a large group with the sweep unless
+    its decisions were taken again, as they are at 2^-66, where squared distances underflow and tie."""
+    print(f"solves k={bits} g={group} T={iters} 2^{exponent}", flush=True)
     rng = np.random.default_rng(1000 * bits + group + iters)
     f, d_out = np.float32, 16
     W = rng.standard_normal((d_out, group)).astype(f)
-    W *= np.exp2(rng.integers(-3, 4, size=(d_out, 1))).astype(f)
+    W *= np.exp2(exponent + rng.integers(-3, 4, size=(d_out, 1))).astype(f)
     off = rng.standard_normal((group, group)) * np.exp2(rng.uniform(-10, 2, (group, group)))
     U = (np.diag(1 + 0.3 * rng.random(group)) + 0.3 / group ** 0.5 * np.triu(off, 1)).astype(f)
     out = bq.bpdq_quantize_layer(torch.from_numpy(W).to(dev), torch.from_numpy(U).to(dev), None,
