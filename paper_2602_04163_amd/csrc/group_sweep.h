@@ -622,16 +622,52 @@ __device__ __forceinline__ void solve_planes(RowState<K, G>& st, const float* __
   for (int i = 0; i < NP + NT; ++i) v[i] = st.P[0][i];
   solve_block<NP, NT, K, G, 0>(st, sU, sX, lane, v, own, next);
 }
+// One column of the recurrence on the target alone, in wg.
+// (Four planes fill the rows of the matrix products; a pass of those for the target alone fills a quarter of them, and without
+// refinement made 18944 x 1024 in groups of 128 slower than column steps that hold target and planes: 671 us, 715 with the pass,
+// 675 with these steps; with one iteration 1152, 1082, 1046.)
+template <int K, int G, int L>
+__device__ __forceinline__ void target_step(RowState<K, G>& st, const float* __restrict__ sU, int lane16, RowRing<G>& ring) {
+  constexpr int CPL = G / 16, M = L / 16, O = L % 16, MN = (L + 1) / 16;
+  request_row<G, L + kAhead<G>>(ring, sU, lane16);
+  __builtin_amdgcn_s_waitcnt(0xc07f | (reads_behind<G>(L) << 8));        // lgkmcnt: this column's row is here
+  __builtin_amdgcn_sched_barrier(0);
+  float z = st.wg[M] * st.inv[M];
+  BPDQ_PIN(z);
+  far_updates<false, K, G, L - 1, M + 1, 0, (L == 0) ? 0 : CPL - M - 1>(st, ring);
+  ring.e = from_lane<O>(z);
+  st.wg[MN] = fmaf(ring.e, ring.u[L % (kAhead<G> + 2)][MN], st.wg[MN]);
+  __builtin_amdgcn_sched_barrier(0);
+}
+template <int K, int G, int... Ls>
+__device__ __forceinline__ void run_target(RowState<K, G>& st, const float* sU, int lane16, std::integer_sequence<int, Ls...>) {
+  RowRing<G> ring;
+  request_row<G, 0>(ring, sU, lane16);
+  if constexpr (kAhead<G> > 1) {
+    request_row<G, 1>(ring, sU, lane16);
+    request_row<G, 2>(ring, sU, lane16);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  (target_step<K, G, Ls>(st, sU, lane16, ring), ...);
+}
+
 // tau = t U_loc^-1 and the planes of the first codes: in one pass where a slot is left for tau
 template <int K, int G>
 __device__ __forceinline__ void solve_target(RowState<K, G>& st, const float* __restrict__ sU, float* sX) {
-  constexpr int kSlot = K < 4 ? K : 0;
+  if constexpr (K < 4) {
 #pragma unroll
-  for (int m = 0; m < G / 16; ++m) st.P[m][kSlot] = st.t[m];
-  solve_planes<kSlot, 1, K, G>(st, sU, sX);
+    for (int m = 0; m < G / 16; ++m) st.P[m][K] = st.t[m];
+    solve_planes<K, 1, K, G>(st, sU, sX);
 #pragma unroll
-  for (int m = 0; m < G / 16; ++m) st.tau[m] = st.P[m][kSlot];
-  if constexpr (K == 4) solve_planes<K, 0, K, G>(st, sU, sX);
+    for (int m = 0; m < G / 16; ++m) st.tau[m] = st.P[m][K];
+  } else {
+#pragma unroll
+    for (int m = 0; m < G / 16; ++m) st.wg[m] = st.t[m];
+    run_target<K, G>(st, sU, threadIdx.x & 15, std::make_integer_sequence<int, G - 1>{});
+#pragma unroll
+    for (int m = 0; m < G / 16; ++m) st.tau[m] = st.wg[m] * st.inv[m];
+    solve_planes<K, 0, K, G>(st, sU, sX);
+  }
 }
 
 // Group records of a layer (SuLayout), by work-groups of 256 threads, kPackWGs<G> to a group: one per 16 rows of the
