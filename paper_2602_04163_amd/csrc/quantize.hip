@@ -80,8 +80,8 @@ __device__ __forceinline__ float coef_value(_Float16 c) { return (float)c; }
 // threads wide and blockDim.y row blocks high, so that narrow matrices fill it too (131072 x 32, 2 planes: 23.8 us
 // with one row block per work-group, 15.5 with a thread per element, now 6.7).  Rows come from a grid-stride loop: no
 // division per element (one 64-bit division and a modulo per element had cost most of the kernel).
-// 8192 x 8192, 2 planes, half coefficients: 303 -> 66 us a call
-// (4.3 TB/s; one thread per element with its own division: 0.95 TB/s).
+// 4096 x 4096, 2 planes, half coefficients: 14.8 us on a matrix and a buffer that are in the cache, 19.7 (3.7 TB/s) on others
+// in turn.  (8192 x 8192, before it went by tiles: 303 us with one thread per element and its own division, 66 with this.)
 template <typename CT, int K, int COLS, int ROWS, bool WIDE>
 __global__ __launch_bounds__(256) void dequant_kernel(const uint32_t* __restrict__ planes,
                                                       const CT* __restrict__ coefs, int d_out,
@@ -125,8 +125,9 @@ __global__ __launch_bounds__(256) void dequant_kernel(const uint32_t* __restrict
 // (8192 x 8192: 38.5 us), the loads alone took 19 us and the two together 57: a thread that forms four columns of a row loads
 // K words and K + 1 coefficients that its seven neighbours load too, 20 small requests for every 16 values, and they
 // queue with the stores.  Staged, a row's words come as 256 consecutive bytes per plane, 4 K loads per thread and tile.
-// 8192 x 8192, 2 planes, half coefficients: 62 -> 46 us (16 x 1024 tiles 49, 8 x 4096 46, 32 x 1024 50; a second
-// tile's loads ahead of the stores gains nothing).
+// 8192 x 8192, 2 planes, half coefficients, the same matrix into the same buffer: 62 -> 46 us (16 x 1024 tiles 49, 8 x 4096 46,
+// 32 x 1024 50; a second tile's loads ahead of the stores gains nothing); matrices and buffers in turn, on another day, 66 -> 57
+// (5.0 TB/s; the former then 64 -> 48).
 constexpr int kTileRows = 16, kTileCols = 2048;
 template <int K>
 constexpr int kTileCoefs = K < 4 ? 4 : 8;           // floats a (row, group) takes in LDS
@@ -450,14 +451,26 @@ static int launch_dequant(const uint32_t* planes, const CT* coefs, int d_out, in
     return 0;
   };
   // Tiles through LDS where there are four for every compute unit and their columns are in use: one tile of 1024 or more, or
-  // seven eighths of several.  us, a thread's own loads / tiles, half coefficients: 8192 x 8192 61.3 / 48.2 at 2 planes and groups
-  // of 128, 82.5 / 64.5 at 4 and 64; 8192 x 3584 24.6 / 21.1 and 34.1 / 27.6; 16384 x 1280 22.7 / 17.4; 70000 x 1024 68.6 / 57.8.
-  // On the other side of the line: 4096 x 4096, 512 tiles, 14.9 / 13.8, but 3000 x 6016, 564, 18.6 / 20.4 at 3 planes and groups of 32
-  // (staging is a round trip to memory that only other work-groups hide, and units with three tiles wait for those with two);
-  // 9300 x 3072, the second of two tiles half full, 22.1 / 22.8; 8192 x 2304, an eighth full, 16.8 / 19.1.
+  // seven eighths of several.  us, a thread's own loads / tiles, half coefficients; first the same matrix into the same buffer
+  // again and again, then matrices and buffers in turn that nothing has touched for a gigabyte:
+  //   8192 x 8192 63.6 / 48.2 and 66.4 / 57.4 at 2 planes and groups of 128, 78.5 / 60.2 and 82.3 / 65.5 at 4 and 64; 8192 x 3584
+  //   25.5 / 20.9 and 34.2 / 24.5; 16384 x 1280 22.2 / 17.4 and 28.2 / 19.6; 16384 x 2048 24.0 / 23.7 and 34.2 / 28.1; 70000 x 1024,
+  //   groups of 64, 69.2 / 57.5 and 69.4 / 60.2.
+  // On the other side of the line: 4096 x 4096, 512 tiles, 14.8 / 13.8 and 19.7 / 14.7, but 3000 x 6016, 564, 18.1 / 20.2 and
+  //   24.4 / 22.6 at 3 planes and groups of 32 (staging is a round trip to memory that only other work-groups hide, and
+  //   units with three tiles wait for those with two); 9300 x 3072, the second of two tiles half full, 21.4 / 22.6 and 30.6 / 25.6;
+  //   8192 x 2304, an eighth full, 16.6 / 19.2 and 22.5 / 19.6.  (The line follows the first kind.)
+  // Four planes in groups of 32 fill so much LDS that a unit holds three tiles, which hides less; with 32-bit coefficients, twice
+  // the bytes to stage, that costs more than the tiles save until there are 2048, unless the other kernel's blocks of 1024 columns
+  // are not full: 16384 x 2048 31.0 / 35.1 and 40.5 / 43.3, 24576 x 2048 43.5 / 44.1 and 57.9 / 60.1, 32768 x 2048 85.9 / 84.1 and
+  // 85.5 / 84.3; 16384 x 1280 29.4 / 23.3 and 34.1 / 26.7.  With half coefficients 16384 x 2048 31.8 / 34.5 and 41.5 / 42.4, 8192 x 4096
+  // 31.2 / 33.7 and 42.6 / 41.3, 16384 x 1024 19.4 / 19.6 and 23.5 / 19.9, 20000 x 2048 37.0 / 35.8 and 50.6 / 46.7: tiles, as a program
+  // that reads its layers once a pass has the second kind.
   const int col_tiles = bpdq_ceil_div(d_in, kTileCols);
+  const long n_tiles = (long)bpdq_ceil_div(d_out, kTileRows) * col_tiles;
+  const bool many_coefs = sizeof(CT) == 4 && bits == 4 && group == 32;
   const bool tiles = vec && group % 32 == 0 && d_in >= 1024 && (col_tiles == 1 || 8L * d_in >= 7L * col_tiles * kTileCols) &&
-                     (long)bpdq_ceil_div(d_out, kTileRows) * col_tiles >= 1024;
+                     n_tiles >= (many_coefs && d_in % 1024 == 0 ? 2048 : 1024);
   auto pick = [&](auto planes_of) -> int {
     constexpr int K = decltype(planes_of)::value;
     if (tiles) {

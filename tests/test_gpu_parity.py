@@ -1384,9 +1384,21 @@ def test_pack_and_dequant_bit_exact(dev, bits):
 ])
 def test_dequant_tile_edges(dev, half, d_out, d_in, group, shift):
     """Both store widths of the dequant kernel at the edges of its tiles, bit for bit."""
-    print(f"dequant d_out={d_out} d_in={d_in} g={group} shift={shift} half={half}", flush=True)
+    _check_dequant(dev, half, 3, d_out, d_in, group, shift)
+
+
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("bits,d_out,d_in,group", [
+    (1, 16369, 1024, 128), (2, 16369, 1024, 32), (4, 16369, 1024, 64), (4, 8177, 3616, 32),      # tiles through LDS
+    (4, 32753, 1024, 32), (4, 32737, 1024, 32),            # where 32-bit coefficients begin to go by them, and one tile fewer
+])
+def test_dequant_tiles_of_every_plane_count(dev, half, bits, d_out, d_in, group):
+    _check_dequant(dev, half, bits, d_out, d_in, group, 0)
+
+
+def _check_dequant(dev, half, bits, d_out, d_in, group, shift):
+    print(f"dequant k={bits} d_out={d_out} d_in={d_in} g={group} shift={shift} half={half}", flush=True)
     rng = np.random.default_rng(d_in + group)
-    bits = 3
     code = rng.integers(0, 1 << bits, size=(d_out, d_in)).astype(np.uint8)
     planes = torch.from_numpy(orc.pack_planes(code, bits).view(np.int32)).to(dev)
     coef = rng.standard_normal((bits + 1, d_out, d_in // group)).astype(np.float16 if half else np.float32)
