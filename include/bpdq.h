@@ -94,10 +94,10 @@ int bpdq_version(void);
  *   error of a product of values above 2^-15 of their channels' largest is below 2^-21 of it -- above the 2^-24 of an fp32
  *   product, far below the rounding of the fp32 accumulation over thousands of tokens.
  *   Launches of n_tok * d_in >= 2^27 (a call of up to 524288 tokens, of up to 8192 on a layer of 1024 tiles or more, is one
- *   launch) scale a channel by the largest of every 8th token instead: that factor is the same or larger, so the halves are
+ *   launch) scale a channel by the largest of every 16th token instead: that factor is the same or larger, so the halves are
  *   as fine or finer, and no value is lost, because channels with a value that leaves the half range under it are scaled
- *   again by the largest of all tokens.  The time of such a call depends on the activations: at 262144 x 3584 9.4 ms with the
- *   scales of all tokens, 8.8 to 9.0 without outliers that the sample missed, up to 10.4 where every channel has one.
+ *   again by the largest of all tokens.  The time of such a call depends on the activations: at 262144 x 3584 9.5 ms with the
+ *   scales of all tokens, 9.0 without outliers that the sample missed, up to 10.5 where every channel has one.
  *   Small calls (up to 64 tokens on 3072 channels, 256 on 2048, 512 on 704, 1024 on 512, 2048
  *   on 320, less some that the above does sooner) are one launch on the fp32 matrix cores instead: fp32
  *   products (2^-24) of the channels scaled in the same way, in chains of at most 32 tokens.  Which of

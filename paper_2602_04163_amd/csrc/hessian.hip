@@ -279,8 +279,8 @@ __global__ __launch_bounds__(SplitSyrk::kThreads) void hess_syrk_bf16x3_kernel(
 //     far from the ends of the fp16 range whatever the activations' units), and its inverse;
 // (3) the split itself: X -> planes[piece][token / 8][channel] (see mfma_split_f16.h), zeros for
 //     the tokens up to the next multiple of 32 and the channels up to the next multiple of 256.
-// Bound by HBM: with a sample X is read nine eighths times and the planes are written, 262144 x 3584 in 1.5 ms against 2.07
-// with a pass for the maxima of all tokens in front.
+// Bound by HBM: with a sample X is read 17/16 times and the planes are written, 262144 x 3584 in 1.5 ms against 2.07 with a
+// pass for the maxima of all tokens in front.
 // A sample's largest is at most the channel's, so its factor is at least that of all tokens: no half is coarser for it.
 // What it may miss is values of more than 4 to 8 times its largest, which leave the half range.  The split looks for them and
 // takes the maximum of a channel that has one; a second split then does the runs of 16 channels that hold such a
@@ -288,17 +288,17 @@ __global__ __launch_bounds__(SplitSyrk::kThreads) void hess_syrk_bf16x3_kernel(
 // to hold one, the first split reads on for the maxima and no longer writes: the two together are then the pass over all
 // tokens and the split behind it.  They write planes twice where the values come late.
 // Runs of 16 channels are whole lines of the planes and half lines of X.  262144 x 3584, Student-t(4) tokens / one late value
-// in every 64 channels, us: runs of 64 channels 9763 / 10473, 32 9558 / 9638, 16 9485 / 9493, single channels 9791 / 9461 (all
-// with every 16th token; the pass over all tokens 9488).  Every 8th token in place of every 16th, 32nd, 64th: 9246, 9485, 9628,
-// 9832 on Student-t(4) tokens, 8867, 8848, 8812, 8805 on normal ones.
-constexpr int kSampleStep = 8;
+// in every 64 channels, us: runs of 64 channels 9763 / 10473, 32 9558 / 9638, 16 9485 / 9493, single channels 9791 / 9461; the pass
+// over all tokens 9488.  Every 8th token in place of every 16th, 32nd, 64th: 9246, 9485, 9628, 9832 on Student-t(4) tokens, and 113 us
+// for the sample itself, 57 with every 16th.
+constexpr int kSampleStep = 16;
 // Values (tokens times channels) from which on the scales come from a sample.  us on activations not read before, scales of all
 // tokens / of a sample on normal tokens / on Student-t(4) tokens / one late value in every 64 channels / in every channel:
-//   262144 x 3584 9424 / 8841 / 9258 / 9526 / 10371;  65536 x 3584 2364 / 2243 / 2358 / 2410 / 2596;
-//   131072 x 1024 606 / 549 / 617 / 642 / 746;  16384 x 8192 2722 / 2626 / 2740 / 2734 / 2827;  8192 x 18944 6524 / 6438 / 6567 / 6558 / 6600;
+//   262144 x 3584 9544 / 9007 / 9540 / 9503 / 10451;  65536 x 3584 2410 / 2263 / 2405 / 2432 / 2612;
+//   131072 x 1024 618 / 548 / 647 / 642 / 748;  16384 x 8192 2762 / 2655 / 2802 / 2750 / 2848;  8192 x 18944 6635 / 6508 / 6670 / 6630 / 6691;
 // and below the line
-//   32768 x 3584 1191 / 1129 / 1195 / 1217 / 1306;  65536 x 1024 317 / 290 / 315 / 340 / 387;  8192 x 8192 1577 / 1531 / 1608 / 1608 / 1659;
-//   65536 x 256 105 / 88 / 102 / 105 / 110;  8192 x 256 52 / 40 / 50 / 50 / 49.
+//   32768 x 3584 1216 / 1139 / 1227 / 1228 / 1320;  65536 x 1024 332 / 299 / 333 / 340 / 388;  8192 x 8192 1597 / 1552 / 1607 / 1603 / 1652;
+//   16384 x 3584 639 / 606 / 639 / 636 / 684;  65536 x 256 106 / 88 / 101 / 104 / 109.
 // So the gain on tokens without outliers does not end at the line; below it a call's time follows from its size alone.
 constexpr long kSampleValues = 1L << 27;
 constexpr int kColmaxRows = 1024;      // tokens per partial maximum
@@ -310,7 +310,7 @@ enum : int { kAllTokens = 0, kSampled = 1, kBeyond = 2 };       // maxima of all
 template <bool SAMPLED>
 __global__ __launch_bounds__(256) void hess_colmax_kernel(const float* __restrict__ X, int n_tok, int d,
                                                           long ldx, float* __restrict__ pmax, int d_pad) {
-  constexpr int kStep = SAMPLED ? kSampleStep : 1, kFlight = 8;
+  constexpr int kStep = SAMPLED ? kSampleStep : 1, kFlight = SAMPLED ? 16 : 8;
   __shared__ float4 red[4][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int c = blockIdx.x * 256 + lane * 4;

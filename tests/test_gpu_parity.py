@@ -371,7 +371,7 @@ def test_hessian_f16_path_channel_scaling(dev):
 @pytest.mark.parametrize("n_tok,d_in", [(131077, 1024), (44740, 3000)])
 @pytest.mark.parametrize("kind", ["plain", "missed", "not_finite"])
 def test_hessian_scales_from_a_sample(dev, n_tok, d_in, kind):
-    """Calls of 2^27 values and more take a channel's scale from every 8th token.  A channel whose sample is all zeros, or
+    """Calls of 2^27 values and more take a channel's scale from every 16th token.  A channel whose sample is all zeros, or
     small against an outlier that it missed (first, middle, last token), is split again with all tokens; so is one
     with an infinity or a NaN, whose row and column of H alone are not finite."""
     print(f"sampled scales {n_tok}x{d_in} {kind}", flush=True)
