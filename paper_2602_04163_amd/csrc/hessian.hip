@@ -289,8 +289,8 @@ __global__ __launch_bounds__(SplitSyrk::kThreads) void hess_syrk_bf16x3_kernel(
 // tokens and the split behind it.  They write planes twice where the values come late.
 // Runs of 16 channels are whole lines of the planes and half lines of X.  262144 x 3584, Student-t(4) tokens / one late value
 // in every 64 channels, us: runs of 64 channels 9763 / 10473, 32 9558 / 9638, 16 9485 / 9493, single channels 9791 / 9461; the pass
-// over all tokens 9488.  Every 8th token in place of every 16th, 32nd, 64th: 9246, 9485, 9628, 9832 on Student-t(4) tokens, and 113 us
-// for the sample itself, 64 with every 16th.
+// over all tokens 9488.  Every 8th, 16th, 32nd token: 9246, 9485, 9628 on Student-t(4) tokens; the sample itself takes 113 us with
+// every 8th, 64 with every 16th.
 constexpr int kSampleStep = 16;
 // Values (tokens times channels) from which on the scales come from a sample.  us on activations not read before, scales of all
 // tokens / of a sample on normal tokens / on Student-t(4) tokens / one late value in every 64 channels / in every channel:
